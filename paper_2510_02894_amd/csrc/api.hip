@@ -72,6 +72,9 @@ enum WsId {
   W_NUM
 };
 
+// Buffers of the block-pair pass, beside the layout buffers and the staging list.
+enum BlockId { B_PBOX, B_LPHYS, B_LBOX, B_SBROI, B_SBOX, B_LIST, B_NUM };
+
 struct Ptrs {
   void* p[W_NUM] = {};
   template <typename T>
@@ -95,6 +98,7 @@ struct Workspace {
   int cu_count = 0;
   long long generation = 0;  // bumped whenever a buffer is reallocated (graphs hold pointers)
   Buf buf[W_NUM];
+  Buf blk[B_NUM];
   Buf soft_rois, soft_edges, soft_field, soft_ctr, soft_blk;  // soft backward
   void* host = nullptr;  // pinned staging: ROI table, read-backs, results
   size_t host_cap = 0;
@@ -138,6 +142,10 @@ Tuning g_tune = {8, 1024, 0, 1, 1, 1};
 
 // Vertex count from which a ROI's 3D pairs are pruned: kPruneMinV for prune = 1,
 // every ROI with pairs for prune = 2.
+// Whether calls take the block-pair pass (every pair is visited with prune = 0
+// or the FP32 pair kernel).
+bool block_path() { return g_tune.kernel == 1 && g_tune.prune != 0; }
+
 int prune_min_v() { return g_tune.prune == 2 ? 2 : kPruneMinV; }
 
 bool valid_tuning(const Tuning& t) {
@@ -575,12 +583,18 @@ PairBufs pair_bufs(const Ptrs& P, const Batch& Bt, int dtype, const Sizes& S, in
 
 // The mesh pass (with the staging list's capacity in rows) and per-ROI
 // totals (launches only).
-int launch_head(const Ptrs& P, const Batch& Bt, int dtype, long long tmp_cap, hipStream_t st) {
+int launch_mesh(const Ptrs& P, const Batch& Bt, int dtype, long long tmp_cap, float4* pbox, hipStream_t st) {
   HIPCK(launch_mesh_pass(dtype, P.as<const Roi>(W_ROIS), Bt.n(), Bt.nbricks, Bt.max_G, P.as<double>(W_CASE_AREA),
                          P.as<BrickPart>(W_PART), P.as<unsigned int>(W_COUNTERS), kCounterWords,
                          P.as<unsigned long long>(W_TMPKEY), dtype == SHAPE3D_F32 ? P.as<double>(W_TMPT) : nullptr,
-                         tmp_cap, P.as<long long>(W_TOTALS), Bt.moments ? 1 : 0, P.as<int>(W_BRICK_ROI), st));
-  HIPCK(launch_mesh_totals(P.as<const Roi>(W_ROIS), Bt.n(), Bt.nbricks, dtype, P.as<const double>(W_CASE_AREA),
+                         tmp_cap, P.as<long long>(W_TOTALS), Bt.moments ? 1 : 0, P.as<int>(W_BRICK_ROI), pbox, st));
+  return SHAPE3D_OK;
+}
+
+int launch_head(const Ptrs& P, const Batch& Bt, int dtype, long long tmp_cap, hipStream_t st) {
+  const int rc = launch_mesh(P, Bt, dtype, tmp_cap, nullptr, st);
+  if (rc) return rc;
+  HIPCK(launch_mesh_totals(P.as<const Roi>(W_ROIS), Bt.n(), dtype, P.as<const double>(W_CASE_AREA),
                            P.as<const BrickPart>(W_PART),
                            P.as<long long>(W_BRICK_VOFF), P.as<RoiMeta>(W_META), P.as<long long>(W_TOTALS),
                            Bt.moments ? 1 : 0, prune_min_v(), st));
@@ -624,7 +638,7 @@ int launch_tail(const Ptrs& P, const Batch& Bt, int dtype, const Sizes& S, long 
   if (ev) HIPCK(hipEventRecord(ev[3], st));
   HIPCK(launch_refine(B, st));
   if (ev) HIPCK(hipEventRecord(ev[4], st));
-  HIPCK(launch_finalize(B, st));
+  HIPCK(launch_finalize(B, kMaxRows, st));
   return SHAPE3D_OK;
 }
 
@@ -691,6 +705,179 @@ int run_eager(Workspace& w, const Batch& Bt, int dtype, hipStream_t st, RoiResul
   return SHAPE3D_OK;
 }
 
+// ---------------------------------------------------------------------------
+// The block-pair pass: mesh pass into the staging list with the blocks' boxes,
+// per-ROI totals, block pairs (blocks.hip), results.  No vertex rows are laid
+// out, so the host needs no vertex count before the end.
+
+// Sizes of its buffers for a staging list of `rows` rows (a multiple of 32).
+struct BlockSizes {
+  long long rows, lblk, list;
+  size_t bytes[B_NUM];
+};
+
+// Room in the block pair list: 16 per block and 2^18 more (unions of ellipsoids
+// list about 4 per block; a sphere, whose blocks all have far partners, about a
+// hundred).  Block pairs beyond it are evaluated where they are found.
+BlockSizes block_sizes(long long rows, int n_rois) {
+  BlockSizes Z;
+  Z.rows = rows / kSegAlign * kSegAlign;
+  const long long nblk = Z.rows / kSegAlign;
+  Z.lblk = nblk + (long long)kSuper * n_rois;
+  Z.lblk = (Z.lblk + kSuper - 1) / kSuper * kSuper;
+  Z.list = 16 * nblk + (1ll << 18);
+  Z.bytes[B_PBOX] = sizeof(float4) * 2 * (size_t)nblk;
+  Z.bytes[B_LPHYS] = sizeof(int) * (size_t)Z.lblk;
+  Z.bytes[B_LBOX] = sizeof(float4) * 2 * (size_t)Z.lblk;
+  Z.bytes[B_SBROI] = sizeof(int) * (size_t)(Z.lblk / kSuper);
+  Z.bytes[B_SBOX] = sizeof(float4) * 2 * (size_t)(Z.lblk / kSuper);
+  Z.bytes[B_LIST] = sizeof(int4) * (size_t)Z.list;
+  return Z;
+}
+
+// Staged rows that hold any mesh of `v` vertices: each brick's are padded to whole blocks.
+long long staged_rows(const Batch& Bt, long long v) { return v + (long long)(kSegAlign - 1) * Bt.nbricks; }
+
+// The library's staging list and block buffers for at least `rows` staged rows.
+int ensure_block_bufs(Workspace& w, const Batch& Bt, int dtype, long long rows, BlockSizes& Z) {
+  long long cap = 0;
+  int rc = ensure_staging(w, dtype, rows, &cap);
+  if (rc) return rc;
+  if (cap > kMaxRows) cap = kMaxRows;
+  Z = block_sizes(cap, Bt.n());
+  for (int i = 0; i < B_NUM; ++i)
+    if ((rc = ensure(w, w.blk[i], Z.bytes[i]))) return rc;
+  return SHAPE3D_OK;
+}
+
+struct BlockPtrs {
+  void* p[B_NUM];
+  template <typename T>
+  T* as(int i) const {
+    return (T*)p[i];
+  }
+};
+
+BlockPtrs block_ptrs(const Workspace& w) {
+  BlockPtrs Q;
+  for (int i = 0; i < B_NUM; ++i) Q.p[i] = w.blk[i].p;
+  return Q;
+}
+
+// Everything after the mesh pass (launches only): per-ROI results in res, which
+// may be pinned host memory.  rows0_cap: vertex rows (each ROI's padded to 32)
+// the call accepts; more end with status SHAPE3D_ECAPACITY, as does a staging
+// list that was too short.  counts: also the in-plane pair counts.
+int launch_block_tail(const Ptrs& P, const BlockPtrs& Q, const BlockSizes& Z, const Batch& Bt, int dtype,
+                      long long rows0_cap, bool counts, int cu_count, RoiResult* res, hipStream_t st, hipEvent_t* ev) {
+  BlockIndex X;
+  X.lphys = Q.as<int>(B_LPHYS);
+  X.sbroi = Q.as<int>(B_SBROI);
+  X.gres = P.as<GroupRes>(W_GRES);
+  X.overflow = P.as<unsigned int>(W_COUNTERS) + 2;
+  X.rows_cap = Z.rows;
+  HIPCK(launch_block_totals(P.as<const Roi>(W_ROIS), Bt.n(), dtype, P.as<const double>(W_CASE_AREA),
+                            P.as<const BrickPart>(W_PART), P.as<RoiMeta>(W_META), P.as<long long>(W_TOTALS),
+                            Bt.moments ? 1 : 0, X, st));
+  PairBufs C = pair_bufs(P, Bt, dtype, Sizes{}, cu_count);
+  C.res = res;
+  C.key = P.as<const unsigned long long>(W_TMPKEY);
+  C.tsoft = nullptr;
+  if (counts)
+    HIPCK(launch_plane_counts(C, st));
+  else
+    C.pairs2d = nullptr;
+  BlockBufs B;
+  B.rois = P.as<const Roi>(W_ROIS);
+  B.n_rois = Bt.n();
+  B.meta = P.as<const RoiMeta>(W_META);
+  B.totals = P.as<const long long>(W_TOTALS);
+  B.key = P.as<const unsigned long long>(W_TMPKEY);
+  B.t = dtype == SHAPE3D_F32 ? P.as<const double>(W_TMPT) : nullptr;
+  B.rows_cap = Z.rows;
+  B.pbox = Q.as<const float4>(B_PBOX);
+  B.lphys = Q.as<const int>(B_LPHYS);
+  B.lblk_cap = Z.lblk;
+  B.lbox = Q.as<float4>(B_LBOX);
+  B.sbroi = Q.as<const int>(B_SBROI);
+  B.sbox = Q.as<float4>(B_SBOX);
+  B.list = Q.as<int4>(B_LIST);
+  B.list_n = (unsigned long long*)P.as<long long>(W_TOTALS) + 10;
+  B.list_cap = Z.list;
+  B.gres = P.as<GroupRes>(W_GRES);
+  B.cu_count = cu_count;
+  B.ids32 = C.ids32;
+  HIPCK(launch_blocks(B, st, ev));
+  if (ev) HIPCK(hipEventRecord(ev[3], st));
+  HIPCK(launch_finalize(C, rows0_cap, st));
+  return SHAPE3D_OK;
+}
+
+// A first guess of a batch's staged rows.
+long long block_guess(const Batch& Bt) { return staged_rows(Bt, staging_guess(Bt)); }
+
+// One run of a batch on the library workspace.  host_res (pinned) receives the
+// results; with host_res null they are left in W_RES (the staged row count is
+// then read back once, so that the list is known to have held every row).
+int run_blocks(Workspace& w, const Batch& Bt, int dtype, hipStream_t st, RoiResult* host_res, bool counts, int timing,
+               float* phase_ms, const DevTable* dt = nullptr) {
+  BlockSizes Z;
+  int rc = ensure_block_bufs(w, Bt, dtype, block_guess(Bt), Z);
+  if (rc) return rc;
+  long long* th = (long long*)w.host;
+  // a few results go to the host as they are written, many in one copy
+  const bool direct = host_res && Bt.n() <= 16;
+  for (int pass = 0;; ++pass) {
+    const Ptrs P = w.ptrs();
+    if ((rc = upload_rois(w, P, Bt, dtype, dt, st))) return rc;
+    if (timing) HIPCK(hipEventRecord(w.ev[0], st));
+    if ((rc = launch_mesh(P, Bt, dtype, Z.rows, w.blk[B_PBOX].p ? (float4*)w.blk[B_PBOX].p : nullptr, st))) return rc;
+    if (!host_res) {
+      HIPCK(hipMemcpyAsync(th, P.p[W_TOTALS], sizeof(long long) * 9, hipMemcpyDeviceToHost, st));
+      HIPCK(hipStreamSynchronize(st));
+      if (th[8] > Z.rows) {
+        if (pass > 0) return fail(SHAPE3D_EINTERNAL, "the mesh pass's staging list overflowed twice");
+        if ((rc = ensure_block_bufs(w, Bt, dtype, th[8], Z))) return rc;
+        continue;
+      }
+    }
+    if (timing) HIPCK(hipEventRecord(w.ev[1], st));
+    if ((rc = launch_block_tail(P, block_ptrs(w), Z, Bt, dtype, kMaxRows, counts, w.cu_count,
+                                direct ? host_res : P.as<RoiResult>(W_RES), st, timing ? &w.ev[2] : nullptr)))
+      return rc;
+    if (!host_res) return SHAPE3D_OK;
+    if (!direct)
+      HIPCK(hipMemcpyAsync(host_res, P.p[W_RES], sizeof(RoiResult) * Bt.n(), hipMemcpyDeviceToHost, st));
+    if (timing) HIPCK(hipEventRecord(w.ev[7], st));
+    HIPCK(hipStreamSynchronize(st));
+    bool short_list = false;
+    for (int r = 0; r < Bt.n(); ++r) short_list |= host_res[r].status == SHAPE3D_ECAPACITY;
+    if (!short_list) break;
+    HIPCK(hipMemcpyAsync(th, P.p[W_TOTALS], sizeof(long long) * 9, hipMemcpyDeviceToHost, st));
+    HIPCK(hipStreamSynchronize(st));
+    if (th[8] <= Z.rows || pass > 0) break;
+    if ((rc = ensure_block_bufs(w, Bt, dtype, th[8], Z))) return rc;
+  }
+  // the limit of the general pipeline's row indices holds for either path
+  long long rows0 = 0, vmax = 0;
+  for (int r = 0; r < Bt.n(); ++r) {
+    rows0 += (host_res[r].V + kSegAlign - 1) / kSegAlign * kSegAlign;
+    vmax = std::max(vmax, host_res[r].V);
+  }
+  Layout L;
+  if ((rc = ws_layout(Bt, dtype, g_tune, rows0, L))) return rc;
+  w.last_rows0 = rows0;
+  w.last_vmax = vmax;
+  if (timing && phase_ms) {
+    // 0 mesh pass, 1 totals and block boxes, 2 lower bounds and block pairs, 3 their exact maxima,
+    // 4 tie-break, 5 results, 6 whole call
+    const int a[7] = {0, 1, 2, 3, 4, 5, 0};
+    const int b[7] = {1, 2, 3, 4, 5, 7, 7};
+    for (int k = 0; k < 7; ++k) HIPCK(hipEventElapsedTime(&phase_ms[k], w.ev[a[k]], w.ev[b[k]]));
+  }
+  return SHAPE3D_OK;
+}
+
 // The whole pipeline on fixed buffers (a caller's workspace), without any
 // host synchronisation: the ROI table is set on the device, the vertex
 // capacity comes from the workspace size, and a mesh beyond it ends with
@@ -702,7 +889,39 @@ int run_fixed(const Batch& Bt, int dtype, const Roi* one_roi, const DevTable* dt
   Layout L;
   int rc = ws_layout(Bt, dtype, g_tune, cap, L);
   Ptrs P;
-  if (!rc) rc = carve(L, ws, ws_bytes, P);
+  BlockPtrs Q;
+  BlockSizes Z = block_sizes(0, 0);
+  bool blocks = false;
+  if (!rc && block_path()) {
+    // the vertex rows' buffers make room for the staging list and the block buffers
+    const long long rows = (staged_rows(Bt, cap) + kSegAlign - 1) / kSegAlign * kSegAlign;
+    Layout LB = L;
+    for (int i = W_FIRST_VERTEX_BUF; i < W_NUM; ++i) LB.bytes[i] = 0;
+    LB.bytes[W_TMPKEY] = sizeof(unsigned long long) * (size_t)rows;
+    LB.bytes[W_TMPT] = dtype == SHAPE3D_F32 ? sizeof(double) * (size_t)rows : 0;
+    Z = block_sizes(rows, Bt.n());
+    size_t need = ws_total(LB);
+    for (int i = 0; i < B_NUM; ++i) need += aligned(std::max<size_t>(Z.bytes[i], 1));
+    if (rows <= kMaxRows && need > ws_bytes) {
+      // a short list only: block pairs beyond it are evaluated where they are found
+      const size_t fixed = need - aligned(Z.bytes[B_LIST]);
+      if (fixed + 4096 * sizeof(int4) <= ws_bytes) {
+        Z.list = (long long)((ws_bytes - fixed - 256) / sizeof(int4));
+        Z.bytes[B_LIST] = sizeof(int4) * (size_t)Z.list;
+        need = fixed + aligned(Z.bytes[B_LIST]);
+      }
+    }
+    blocks = rows <= kMaxRows && need <= ws_bytes;
+    if (blocks) {
+      if ((rc = carve(LB, ws, ws_bytes, P))) return rc;
+      size_t off = ws_total(LB);
+      for (int i = 0; i < B_NUM; ++i) {
+        Q.p[i] = (char*)ws + off;
+        off += aligned(std::max<size_t>(Z.bytes[i], 1));
+      }
+    }
+  }
+  if (!rc && !blocks) rc = carve(L, ws, ws_bytes, P);
   if (rc) return rc;
   if (dt) {
     HIPCK(launch_plan_rois(dt->rois, Bt.n(), dtype, dt->max_dims, dt->base, dt->alloc_elems, P.as<Roi>(W_ROIS),
@@ -710,8 +929,14 @@ int run_fixed(const Batch& Bt, int dtype, const Roi* one_roi, const DevTable* dt
   } else {
     HIPCK(launch_set_roi(*one_roi, P.as<Roi>(W_ROIS), st));
   }
-  if ((rc = launch_head(P, Bt, dtype, cap, st))) return rc;
-  if ((rc = launch_tail(P, Bt, dtype, L.S, cap, cu_count, st, nullptr, cap))) return rc;
+  if (blocks) {
+    if ((rc = launch_mesh(P, Bt, dtype, Z.rows, Q.as<float4>(B_PBOX), st))) return rc;
+    if ((rc = launch_block_tail(P, Q, Z, Bt, dtype, cap, false, cu_count, P.as<RoiResult>(W_RES), st, nullptr)))
+      return rc;
+  } else {
+    if ((rc = launch_head(P, Bt, dtype, cap, st))) return rc;
+    if ((rc = launch_tail(P, Bt, dtype, L.S, cap, cu_count, st, nullptr, cap))) return rc;
+  }
   HIPCK(launch_results_out(P.as<const RoiResult>(W_RES), Bt.n(), out, status, Bt.nf(), st));
   return SHAPE3D_OK;
 }
@@ -800,7 +1025,11 @@ int shape3d_impl(const void* vol, int dtype, const int64_t dims[3], const double
     if ((rc = run_small(w, vol, dtype, dims, spacing, st, hres))) return rc;
     done = hres->status != kSmallOverflow;
   }
-  if (!done && (rc = run_eager(w, Bt, dtype, st, hres, timing, ms))) return rc;
+  if (!done && block_path())
+    rc = run_blocks(w, Bt, dtype, st, hres, stats != nullptr, timing, ms);
+  else if (!done)
+    rc = run_eager(w, Bt, dtype, st, hres, timing, ms);
+  if (rc) return rc;
   if (hres->status < 0) return fail(hres->status, "an internal capacity was exceeded");
   for (int f = 0; f < 6; ++f) out[f] = hres->out[f];
   if (moments)
@@ -826,7 +1055,7 @@ std::string layout_signature(const void* base, int dtype, const void* table, siz
 // replay and the results are copied to rec.host_res.  Device tables
 // (dt set): the graph plans the ROI table itself and ends with the results
 // in out/status on the device.
-int capture_graph(Workspace& w, const Batch& Bt, int dtype, hipStream_t st, GraphRec& rec,
+int capture_graph(Workspace& w, const Batch& Bt, int dtype, hipStream_t st, GraphRec& rec, bool counts,
                   const DevTable* dt = nullptr, double* out = nullptr, int* status = nullptr) {
   rec.n_rois = Bt.n();
   if (!dt) {
@@ -839,8 +1068,11 @@ int capture_graph(Workspace& w, const Batch& Bt, int dtype, hipStream_t st, Grap
   const Sizes S = sizes_for(Bt, w.last_rows0);
   // a staging list that holds the recorded row capacity, so that a replay
   // within that capacity stages every vertex
+  const bool blocks = block_path();
   long long tcap = 0;
-  int rc0 = ensure_staging(w, dtype, w.last_rows0, &tcap);
+  BlockSizes Z;
+  int rc0 = blocks ? ensure_block_bufs(w, Bt, dtype, staged_rows(Bt, w.last_rows0), Z)
+                   : ensure_staging(w, dtype, w.last_rows0, &tcap);
   if (rc0) return rc0;
   const Ptrs P = w.ptrs();
   hipGraph_t graph = nullptr;
@@ -851,8 +1083,15 @@ int capture_graph(Workspace& w, const Batch& Bt, int dtype, hipStream_t st, Grap
                                           P.as<Roi>(W_ROIS), P.as<long long>(W_PLAN), st);
     if (e != hipSuccess) rc = fail(SHAPE3D_EHIP, std::string("plan: ") + hipGetErrorString(e));
   }
-  if (!rc) rc = launch_head(P, Bt, dtype, tcap, st);
-  if (!rc) rc = launch_tail(P, Bt, dtype, S, tcap, w.cu_count, st, nullptr, w.last_vmax);
+  if (!rc && blocks) {
+    rc = launch_mesh(P, Bt, dtype, Z.rows, (float4*)w.blk[B_PBOX].p, st);
+    if (!rc)
+      rc = launch_block_tail(P, block_ptrs(w), Z, Bt, dtype, w.last_rows0, counts, w.cu_count, P.as<RoiResult>(W_RES),
+                             st, nullptr);
+  } else if (!rc) {
+    rc = launch_head(P, Bt, dtype, tcap, st);
+    if (!rc) rc = launch_tail(P, Bt, dtype, S, tcap, w.cu_count, st, nullptr, w.last_vmax);
+  }
   if (!rc) {
     const hipError_t e = dt ? launch_results_out(P.as<const RoiResult>(W_RES), Bt.n(), out, status, Bt.nf(), st)
                             : hipMemcpyAsync(rec.host_res, P.p[W_RES], sizeof(RoiResult) * Bt.n(),
@@ -917,8 +1156,9 @@ int make_batch(const void* base, int dtype, const shape3d_roi* rois, int64_t n_r
 
 // The batched forward pass; on success *hres_out points at the per-ROI results
 // (pinned host memory owned by the workspace, valid until the next call).
-int batched_impl(const void* base, int dtype, const shape3d_roi* rois, int64_t n_rois, int flags, hipStream_t st,
-                 const RoiResult** hres_out) {
+// counts: the in-plane pair counts are wanted.
+int batched_impl(const void* base, int dtype, const shape3d_roi* rois, int64_t n_rois, int flags, bool counts,
+                 hipStream_t st, const RoiResult** hres_out) {
   Batch Bt;
   Bt.moments = (flags & SHAPE3D_SHAPE_CLASS) != 0;
   int rc = make_batch(base, dtype, rois, n_rois, Bt);
@@ -928,7 +1168,7 @@ int batched_impl(const void* base, int dtype, const shape3d_roi* rois, int64_t n
   Workspace& w = *wp;
   if ((rc = ensure_layout_bufs(w, Bt, dtype))) return rc;
   const bool use_graph = (flags & SHAPE3D_BATCH_GRAPH) != 0;
-  const int sig_flags = flags & SHAPE3D_SHAPE_CLASS;
+  const int sig_flags = (flags & SHAPE3D_SHAPE_CLASS) | (counts ? 1 << 16 : 0);
   const std::string sig = use_graph ? layout_signature(base, dtype, rois, sizeof(shape3d_roi) * (size_t)n_rois,
                                                        &sig_flags, sizeof(sig_flags))
                                     : std::string();
@@ -955,13 +1195,15 @@ int batched_impl(const void* base, int dtype, const shape3d_roi* rois, int64_t n
   if (done) w.graphs[sig].stamp = ++w.stamp;
   if (!done) {
     RoiResult* eager = host_results(w, Bt);
-    if ((rc = run_eager(w, Bt, dtype, st, eager, 0, nullptr))) return rc;
+    rc = block_path() ? run_blocks(w, Bt, dtype, st, eager, counts, 0, nullptr)
+                      : run_eager(w, Bt, dtype, st, eager, 0, nullptr);
+    if (rc) return rc;
     hres = eager;
     if (use_graph) {
       graph_slot(w, sig);
       GraphRec rec;
       HIPCK(hipStreamSynchronize(st));
-      rc = capture_graph(w, Bt, dtype, w.graph_stream, rec);
+      rc = capture_graph(w, Bt, dtype, w.graph_stream, rec, counts);
       if (rc) {
         if (rec.exec) (void)hipGraphExecDestroy(rec.exec);
         if (rec.host_res) (void)hipHostFree(rec.host_res);
@@ -1036,13 +1278,15 @@ int batched_dev_impl(const void* base, int dtype, const shape3d_roi_ex* rois, in
       return SHAPE3D_OK;
     }
   }
-  if ((rc = run_eager(w, Bt, dtype, st, nullptr, 0, nullptr, &dt))) return rc;
+  rc = block_path() ? run_blocks(w, Bt, dtype, st, nullptr, false, 0, nullptr, &dt)
+                    : run_eager(w, Bt, dtype, st, nullptr, 0, nullptr, &dt);
+  if (rc) return rc;
   HIPCK(launch_results_out(w.ptrs().as<const RoiResult>(W_RES), Bt.n(), out, status, Bt.nf(), st));
   if (use_graph) {
     graph_slot(w, sig);
     GraphRec rec;
     HIPCK(hipStreamSynchronize(st));
-    rc = capture_graph(w, Bt, dtype, w.graph_stream, rec, &dt, out, status);
+    rc = capture_graph(w, Bt, dtype, w.graph_stream, rec, false, &dt, out, status);
     if (rc) {
       if (rec.exec) (void)hipGraphExecDestroy(rec.exec);
       return rc;
@@ -1490,7 +1734,7 @@ int shape3d_batched_ex(const void* base, int dtype, const shape3d_roi* rois, int
   if (!out || !status) return fail(SHAPE3D_EINVAL, "null output");
   if (flags & ~(SHAPE3D_BATCH_GRAPH | SHAPE3D_SHAPE_CLASS)) return fail(SHAPE3D_EINVAL, "unknown flags");
   const RoiResult* hres = nullptr;
-  const int rc = batched_impl(base, dtype, rois, n_rois, flags, (hipStream_t)stream, &hres);
+  const int rc = batched_impl(base, dtype, rois, n_rois, flags, stats != nullptr, (hipStream_t)stream, &hres);
   if (rc < 0 && !hres) return rc;
   const bool cls = (flags & SHAPE3D_SHAPE_CLASS) != 0;
   const int nf = cls ? SHAPE3D_N_CLASS : 6;
@@ -1590,7 +1834,7 @@ int shape3d_batched_soft_forward(const float* base, const shape3d_roi* rois, int
   std::lock_guard<std::mutex> lk(g_mu);
   if (!out || !saved) return fail(SHAPE3D_EINVAL, "null output");
   const RoiResult* hres = nullptr;
-  const int rc = batched_impl(base, SHAPE3D_F32, rois, n_rois, flags, (hipStream_t)stream, &hres);
+  const int rc = batched_impl(base, SHAPE3D_F32, rois, n_rois, flags, false, (hipStream_t)stream, &hres);
   if (rc < 0) return rc;
   for (int64_t r = 0; r < n_rois; ++r) {
     for (int f = 0; f < 6; ++f) out[6 * r + f] = hres[r].out[f];
@@ -1754,6 +1998,8 @@ int shape3d_release(void) {
     drop_graphs(*w);
     if (w->graph_stream) (void)hipStreamDestroy(w->graph_stream);
     for (Buf& b : w->buf)
+      if (b.p) (void)hipFree(b.p);
+    for (Buf& b : w->blk)
       if (b.p) (void)hipFree(b.p);
     for (Buf* b : w->soft_bufs())
       if (b->p) (void)hipFree(b->p);

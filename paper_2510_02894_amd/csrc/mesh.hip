@@ -468,7 +468,8 @@ __global__ __launch_bounds__(kBrickThreads, DT == 0 ? 6 : 4) void k_mesh_pass(co
                                                              unsigned long long* __restrict__ tmpkey,
                                                              double* __restrict__ tmpt, long long tmp_cap,
                                                              long long* __restrict__ totals, int moments,
-                                                             const int* __restrict__ bmap) {
+                                                             const int* __restrict__ bmap,
+                                                             float4* __restrict__ pbox) {
   extern __shared__ uint32_t s_bits[];
   __shared__ unsigned int s_hist[256];  // binary masks: active cubes per case
   __shared__ int s_tk[256];
@@ -586,12 +587,15 @@ __global__ __launch_bounds__(kBrickThreads, DT == 0 ? 6 : 4) void k_mesh_pass(co
       }
     }
   }
-  // the brick's staged rows: one reservation
+  // the brick's staged rows: one reservation (of whole 32-row blocks when the
+  // blocks' boxes are asked for)
   int total_e;
   const int off_e = block_excl_scan256(cnt_e, s_scan, total_e);
   nv = cnt_e;
-  if (tid == 0)
-    s_base = total_e ? (long long)atomicAdd((unsigned long long*)&totals[8], (unsigned long long)total_e) : 0;
+  if (tid == 0) {
+    const int rows = pbox ? (total_e + kSegAlign - 1) & ~(kSegAlign - 1) : total_e;
+    s_base = rows ? (long long)atomicAdd((unsigned long long*)&totals[8], (unsigned long long)rows) : 0;
+  }
   int total;
   const int off = block_excl_scan256(cnt, s_scan, total);
   for (int c0 = 0; c0 < total; c0 += kMeshItems) {
@@ -663,8 +667,11 @@ __global__ __launch_bounds__(kBrickThreads, DT == 0 ? 6 : 4) void k_mesh_pass(co
   for (int c0 = 0; c0 < total_e; c0 += kMeshItems) {
     const int n = min(kMeshItems, total_e - c0);
     mark_words<3 * kTZ>(edc, off_e, c0, n, s_items, s_mx);
-    for (int i = tid; i < n; i += kBrickThreads) {
-      const uint32_t mk = s_items[i];
+    // with boxes, the rows that fill up the last block repeat the last vertex
+    const int n_fill = pbox ? (n + kSegAlign - 1) & ~(kSegAlign - 1) : n;
+    for (int i = tid; i < n_fill; i += kBrickThreads) {
+      const int iv = min(i, n - 1);
+      const uint32_t mk = s_items[iv];
       const int j = (int)(mk & 255u), t = (int)((mk >> 8) & 255u);
       const int p = j / 3, a = j - 3 * p;
       const uint32_t ly = s_ly[t];
@@ -675,15 +682,45 @@ __global__ __launch_bounds__(kBrickThreads, DT == 0 ? 6 : 4) void k_mesh_pass(co
       const uint32_t r0 = s_bits[w0], rq = s_bits[wq];
       const uint32_t x0 = l > 0 ? (s_bits[w0 - 1] >> 31) : 0u, xq = l > 0 ? (s_bits[wq - 1] >> 31) : 0u;
       const uint32_t cq = a == 2 ? r0 : ((rq << 1) | xq);
-      const int k = nth_set_bit((((r0 << 1) | x0) ^ cq) & lane_vmask(R, l), marker_rank(mk, i));
+      const int k = nth_set_bit((((r0 << 1) | x0) ^ cq) & lane_vmask(R, l), marker_rank(mk, iv));
       const int u0 = T.pz0 - 1 + p, u1 = (int)(ly & 0xfffffu) - 1, u2 = 32 * l - 1 + k;
       const long long row = base + c0 + i;
+      double tt = 0.5;
+      if (DT == 1) {
+        const double pa = soft_value(R, u0, u1, u2);
+        const double pb = soft_value(R, u0 + (a == 0), u1 + (a == 1), u2 + (a == 2));
+        tt = (0.5 - pa) / (pb - pa);
+      }
       if (row < tmp_cap) {
         tmpkey[row] = pack_key(u0, u1, u2, a);
-        if (DT == 1) {
-          const double pa = soft_value(R, u0, u1, u2);
-          const double pb = soft_value(R, u0 + (a == 0), u1 + (a == 1), u2 + (a == 2));
-          tmpt[row] = (0.5 - pa) / (pb - pa);
+        if (DT == 1) tmpt[row] = tt;
+      }
+      if (pbox) {
+        // the block's box over its half wave, in half voxels: exact for binary
+        // masks, widened by the rounding of the soft coordinate
+        float lo[3], hi[3];
+        const int u[3] = {u0, u1, u2};
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+          if (DT == 0) {
+            lo[q] = hi[q] = (float)(2 * u[q] + (a == q));
+          } else {
+            const float c = (float)(2.0 * ((double)u[q] + (a == q ? tt : 0.0))), w = fabsf(c) * 1.1920928955078125e-07f;
+            lo[q] = c - w;
+            hi[q] = c + w;
+          }
+        }
+#pragma unroll
+        for (int m = 1; m < kSegAlign; m <<= 1)
+#pragma unroll
+          for (int q = 0; q < 3; ++q) {
+            lo[q] = fminf(lo[q], __shfl_xor(lo[q], m, 64));
+            hi[q] = fmaxf(hi[q], __shfl_xor(hi[q], m, 64));
+          }
+        if ((i & (kSegAlign - 1)) == 0 && row < tmp_cap) {
+          float4* bx = pbox + 2 * (row / kSegAlign);
+          bx[0] = make_float4(lo[0], lo[1], lo[2], hi[0]);
+          bx[1] = make_float4(hi[1], hi[2], 0.0f, 0.0f);
         }
       }
     }
@@ -801,92 +838,189 @@ __device__ inline double cov_entry(const __int128* S, const double* sp, int k) {
   return (double)c / ((double)n * (double)n) * (sp[i] * sp[j]);
 }
 
-__global__ __launch_bounds__(1024) void k_mesh_totals(const Roi* __restrict__ rois, int n_rois, long long nbricks,
-                                                      int dtype, const double* __restrict__ case_area,
-                                                      const BrickPart* __restrict__ part,
-                                                      long long* __restrict__ brick_voff,
-                                                      RoiMeta* __restrict__ meta, int moments) {
-  __shared__ long long s_l[2][1024];
-  __shared__ long long s_l2[1024];
-  __shared__ double s_d[2][1024];
-  __shared__ int s_b[6][1024];
-  __shared__ __int128 s_m[10][16];
+// Exclusive prefix sum over the workgroup's NT threads; s_w: NT / 64 words of
+// LDS.  Contains barriers.
+template <int NT>
+__device__ inline long long block_excl_scan_i64(long long v, long long* s_w, long long& total) {
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  long long inc = v;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const long long t = __shfl_up(inc, d, 64);
+    if (lane >= d) inc += t;
+  }
+  __syncthreads();  // s_w of an earlier scan has been read
+  if (lane == 63) s_w[wid] = inc;
+  __syncthreads();
+  long long base = 0;
+  total = 0;
+#pragma unroll
+  for (int w = 0; w < NT / 64; ++w) {
+    if (w < wid) base += s_w[w];
+    total += s_w[w];
+  }
+  return base + inc - v;
+}
+
+// Per-ROI totals, one workgroup of NT threads per ROI: a few large ROIs take
+// 1,024, a batch 256 (its ROIs have tens of bricks).  The FP64 partials of soft
+// masks are summed in one order whatever NT: 1,024 slots of consecutive
+// bricks, then a halving tree.  The bricks' first rows within the ROI go to
+// brick_voff (the general pipeline), or, with X.lphys set, the ROI's staged
+// blocks to the block list at a range that starts on a superblock.
+// totals: [0] rows of all ROIs, [1] largest V, [9] blocks (block list only;
+// the general pipeline's k_roi_rows writes the first two).
+template <int NT>
+__global__ __launch_bounds__(NT) void k_mesh_totals(const Roi* __restrict__ rois, int n_rois, int dtype,
+                                                    const double* __restrict__ case_area,
+                                                    const BrickPart* __restrict__ part,
+                                                    long long* __restrict__ brick_voff, RoiMeta* __restrict__ meta,
+                                                    long long* __restrict__ totals, int moments, BlockIndex X) {
+  constexpr int Q = 1024 / NT, NW = NT / 64;
+  __shared__ long long s_w[NW];
+  __shared__ long long s_l[3][NW];
+  __shared__ int s_b[6][NW];
+  __shared__ double s_d[2][512];
   __shared__ __int128 s_S[10];
-  const int r = blockIdx.x, tid = threadIdx.x;
-  const Roi R = rois[r];
-  const long long b0 = R.brick_begin, b1 = R.brick_end;
+  __shared__ long long s_base;
+  const int r = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  const long long b0 = rois[r].brick_begin, b1 = rois[r].brick_end;
   const long long n = b1 - b0;
   const long long chunk = (n + 1023) / 1024;
-  const long long lo = b0 + min(n, chunk * tid), hi = b0 + min(n, chunk * (tid + 1));
-  long long nv = 0, nt = 0, vi = 0;
-  double area = 0.0, vd = 0.0;
+  long long nv = 0, nt = 0, vi = 0, q_n[Q];
+  double area[Q], vd[Q];
   int bb[6] = {INT_MAX, INT_MAX, INT_MAX, INT_MIN, INT_MIN, INT_MIN};
-  for (long long b = lo; b < hi; ++b) {
-    const BrickPart P = part[b];
-    nv += P.nv;
-    nt += P.nt;
-    vi += P.vol_i;
-    area += P.area;
-    vd += P.vol_d;
-    for (int k = 0; k < 3; ++k) {
-      bb[k] = min(bb[k], P.bb[k]);
-      bb[3 + k] = max(bb[3 + k], P.bb[3 + k]);
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const long long slot = tid + (long long)NT * q;
+    const long long lo = b0 + min(n, chunk * slot), hi = b0 + min(n, chunk * (slot + 1));
+    q_n[q] = 0;
+    area[q] = 0.0;
+    vd[q] = 0.0;
+    for (long long b = lo; b < hi; ++b) {
+      const BrickPart& P = part[b];
+      const int pv = P.nv;
+      nv += pv;
+      nt += P.nt;
+      vi += P.vol_i;
+      area[q] += P.area;
+      vd[q] += P.vol_d;
+      for (int k = 0; k < 3; ++k) {
+        bb[k] = min(bb[k], P.bb[k]);
+        bb[3 + k] = max(bb[3 + k], P.bb[3 + k]);
+      }
+      q_n[q] += X.lphys ? (pv + kSegAlign - 1) / kSegAlign : pv;
     }
   }
-  // exclusive scan of nv over threads (Hillis-Steele in shared memory)
-  s_l[0][tid] = nv;
-  __syncthreads();
-  int src = 0;
-  for (int d = 1; d < 1024; d <<= 1) {
-    long long v = s_l[src][tid];
-    if (tid >= d) v += s_l[src][tid - d];
-    s_l[1 - src][tid] = v;
+  // where each slot's rows (or blocks) start
+  long long off[Q], total = 0;
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    long long t;
+    off[q] = total + block_excl_scan_i64<NT>(q_n[q], s_w, t);
+    total += t;
+  }
+  const bool fits = X.lphys == nullptr || totals[8] <= X.rows_cap;
+  if (X.lphys) {
+    const long long nsb = (total + kSuper - 1) / kSuper;
+    if (tid == 0)
+      s_base = fits && total ? (long long)atomicAdd((unsigned long long*)&totals[9], (unsigned long long)(nsb * kSuper))
+                             : 0;
     __syncthreads();
-    src = 1 - src;
+    if (fits) {
+      const long long base = s_base;
+      for (long long j = total + tid; j < nsb * kSuper; j += NT) X.lphys[base + j] = -1;
+      for (long long j = tid; j < nsb; j += NT) X.sbroi[base / kSuper + j] = r;
+    }
   }
-  long long off = s_l[src][tid] - nv;
-  for (long long b = lo; b < hi; ++b) {
-    brick_voff[b] = off;
-    off += part[b].nv;
-  }
-  s_l2[tid] = s_l[src][1023];
-  __syncthreads();
-  // fixed-order tree reductions
-  s_l[0][tid] = nt;
-  s_l[1][tid] = vi;
-  s_d[0][tid] = area;
-  s_d[1][tid] = vd;
-  for (int k = 0; k < 6; ++k) s_b[k][tid] = bb[k];
-  __syncthreads();
-  for (int w = 512; w >= 1; w >>= 1) {
-    if (tid < w) {
-      s_l[0][tid] += s_l[0][tid + w];
-      s_l[1][tid] += s_l[1][tid + w];
-      s_d[0][tid] += s_d[0][tid + w];
-      s_d[1][tid] += s_d[1][tid + w];
-      for (int k = 0; k < 3; ++k) {
-        s_b[k][tid] = min(s_b[k][tid], s_b[k][tid + w]);
-        s_b[3 + k][tid] = max(s_b[3 + k][tid], s_b[3 + k][tid + w]);
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const long long slot = tid + (long long)NT * q;
+    const long long lo = b0 + min(n, chunk * slot), hi = b0 + min(n, chunk * (slot + 1));
+    long long o = off[q];
+    for (long long b = lo; b < hi; ++b) {
+      const int pv = part[b].nv;
+      if (X.lphys) {
+        const int nb = (pv + kSegAlign - 1) / kSegAlign;
+        const int ph = (int)(part[b].stage / kSegAlign);
+        if (fits)
+          for (int j = 0; j < nb; ++j) X.lphys[s_base + o + j] = ph + j;
+        o += nb;
+      } else {
+        brick_voff[b] = o;
+        o += pv;
       }
     }
-    __syncthreads();
   }
-  // binary masks: the area from the case counts (s_d[1] is free for them)
-  if (dtype == 0)
-    binary_area_tree(case_area + (size_t)r * 256, case_hist(case_area, n_rois) + (size_t)r * 256, s_d[1]);
+  // integer totals: any order
+  nv = wave_sum(nv);
+  nt = wave_sum(nt);
+  vi = wave_sum(vi);
+  for (int k = 0; k < 3; ++k) {
+    bb[k] = wave_min(bb[k]);
+    bb[3 + k] = wave_max(bb[3 + k]);
+  }
+  if (lane == 0) {
+    s_l[0][wid] = nv;
+    s_l[1][wid] = nt;
+    s_l[2][wid] = vi;
+    for (int k = 0; k < 6; ++k) s_b[k][wid] = bb[k];
+  }
+  double sum_area = 0.0, sum_vd = 0.0;
+  if (dtype == 0) {
+    // binary masks: the area from the case counts
+    __syncthreads();
+    binary_area_tree(case_area + (size_t)r * 256, case_hist(case_area, n_rois) + (size_t)r * 256, s_d[0]);
+    sum_area = s_d[0][0];
+  } else {
+    // the halving tree over 1,024 slots: slot v takes in slot v + w, w = 512, 256, ..., 1
+    if (Q == 4) {
+      area[0] += area[2 % Q];
+      area[1 % Q] += area[3 % Q];
+      vd[0] += vd[2 % Q];
+      vd[1 % Q] += vd[3 % Q];
+      area[0] += area[1 % Q];
+      vd[0] += vd[1 % Q];
+    }
+    for (int w = NT / 2; w >= 1; w >>= 1) {
+      __syncthreads();
+      if (tid >= w && tid < 2 * w) {
+        s_d[0][tid - w] = area[0];
+        s_d[1][tid - w] = vd[0];
+      }
+      __syncthreads();
+      if (tid < w) {
+        area[0] += s_d[0][tid];
+        vd[0] += s_d[1][tid];
+      }
+    }
+    sum_area = area[0];
+    sum_vd = vd[0];
+  }
   if (tid == 0) {
-    const long long V = s_l2[0];
+    const Roi& R = rois[r];
     RoiMeta M;
+    long long V = 0, T = 0, vol_i = 0;
+    for (int w = 0; w < NW; ++w) {
+      V += s_l[0][w];
+      T += s_l[1][w];
+      vol_i += s_l[2][w];
+    }
     M.V = V;
-    M.T = s_l[0][0];
+    M.T = T;
     M.row_off = 0;
+    M.prune_off = 0;
     M.V_pad = (V + kSegAlign - 1) / kSegAlign * kSegAlign;
-    M.area = dtype == 0 ? s_d[1][0] : s_d[0][0];
-    M.vol = dtype == 0 ? (double)s_l[1][0] * (R.s[0] * R.s[1] * R.s[2] / 48.0) : s_d[1][0];
-    double R2 = 0.0;
+    M.area = sum_area;
+    M.vol = dtype == 0 ? (double)vol_i * (R.s[0] * R.s[1] * R.s[2] / 48.0) : sum_vd;
+    double R2 = 0.0, reach = 0.0;
     for (int k = 0; k < 3; ++k) {
       M.bb[k] = s_b[k][0];
       M.bb[3 + k] = s_b[3 + k][0];
+      for (int w = 1; w < NW; ++w) {
+        M.bb[k] = min(M.bb[k], s_b[k][w]);
+        M.bb[3 + k] = max(M.bb[3 + k], s_b[3 + k][w]);
+      }
       if (V > 0) {
         M.center[k] = 0.5 * (double)(M.bb[k] + M.bb[3 + k] + 1) * R.s[k];
         const double h = 0.5 * (double)(M.bb[3 + k] - M.bb[k] + 1) * R.s[k];
@@ -894,35 +1028,40 @@ __global__ __launch_bounds__(1024) void k_mesh_totals(const Roi* __restrict__ ro
       } else {
         M.center[k] = 0.0;
       }
+      reach = fmax(reach, (double)(R.d[k] + 1) * R.s[k]);
     }
     M.R2 = R2;
     M.n_in = 0;
     for (int k = 0; k < 6; ++k) M.cov[k] = 0.0;
+    M.blk0 = X.lphys ? s_base : 0;
+    M.nblk = X.lphys && fits ? (int)total : 0;
+    M.ex = ilogb(reach);
+    for (int k = 0; k < 3; ++k) M.hs[k] = (float)ldexp(0.5 * R.s[k], -M.ex);
     meta[r] = M;
+    if (X.lphys) {
+      atomicAdd((unsigned long long*)&totals[0], (unsigned long long)M.V_pad);
+      atomicMax((unsigned long long*)&totals[1], (unsigned long long)V);
+      if (!fits) *X.overflow = 1u;
+    }
+  }
+  if (X.lphys && tid < 4) {
+    GroupRes G;
+    G.best_bits = 0ull;
+    G.id_lo = ~0ull;
+    G.id_hi = ~0ull;
+    G.row_i = -1;
+    G.row_j = -1;
+    G.gmax = 0.0f;
+    G.n_cand = 0;
+    X.gres[4ll * r + tid] = G;
   }
   if (!moments) return;
-  // exact moment sums, last (few registers are live): 128-bit per thread, per
-  // wave, then over the 16 waves
-  {
-    __int128 m[10];
-#pragma unroll
-    for (int k = 0; k < 10; ++k) m[k] = 0;
-    for (long long b = lo; b < hi; ++b)
-#pragma unroll
-      for (int k = 0; k < 10; ++k) m[k] += (__int128)part[b].mom[k];
-#pragma unroll
-    for (int k = 0; k < 10; ++k) m[k] = wave_sum_i128(m[k]);
-    if ((tid & 63) == 0)
-#pragma unroll
-      for (int k = 0; k < 10; ++k) s_m[k][tid >> 6] = m[k];
-  }
-  __syncthreads();
-  // thread k < 10 sums moment k over the waves, then thread k < 6 forms
-  // covariance entry k (one 128-bit product pair per thread)
-  if (tid < 10) {
-    __int128 v = 0;
-    for (int w = 0; w < 16; ++w) v += s_m[tid][w];
-    s_S[tid] = v;
+  // exact moment sums in 128 bits, a wave per moment
+  for (int k = wid; k < 10; k += NW) {
+    __int128 m = 0;
+    for (long long b = b0 + lane; b < b1; b += 64) m += (__int128)part[b].mom[k];
+    m = wave_sum_i128(m);
+    if (lane == 0) s_S[k] = m;
   }
   __syncthreads();
   if (tid < 6) meta[r].cov[tid] = cov_entry(s_S, rois[r].s, tid);
@@ -1131,10 +1270,10 @@ __global__ __launch_bounds__(256) void k_brick_map(const Roi* __restrict__ rois,
   for (long long b = b0; b < b1; b += step) bmap[b] = v;
 }
 
-// Clears the call's counters and the staged-row count (totals[8]).
+// Clears the call's counters and device totals (the staged-row count among them).
 __global__ void k_head_clear(unsigned int* __restrict__ counters, int n_counters, long long* __restrict__ totals) {
   for (int i = threadIdx.x; i < n_counters; i += blockDim.x) counters[i] = 0u;
-  if (threadIdx.x == 0) totals[8] = 0;
+  if (threadIdx.x < 16) totals[threadIdx.x] = 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -1231,7 +1370,7 @@ size_t mesh_lds_bytes(int max_G) { return sizeof(uint32_t) * (size_t)(kTZ + 1) *
 hipError_t launch_mesh_pass(int dtype, const Roi* rois, int n_rois, long long nbricks, int max_G,
                             double* case_area, BrickPart* part, unsigned int* counters, int n_counters,
                             unsigned long long* tmpkey, double* tmpt, long long tmp_cap, long long* totals,
-                            int moments, int* bmap, hipStream_t st) {
+                            int moments, int* bmap, float4* pbox, hipStream_t st) {
   hipLaunchKernelGGL(k_head_clear, dim3(1), dim3(1024), 0, st, counters, n_counters, totals);
   if (nbricks <= 0) return hipGetLastError();
   if (n_rois < 2) bmap = nullptr;  // one ROI: the search is free
@@ -1242,10 +1381,10 @@ hipError_t launch_mesh_pass(int dtype, const Roi* rois, int n_rois, long long nb
   if (dtype == 0) {
     hipLaunchKernelGGL(k_case_area, dim3((unsigned)n_rois), dim3(256), 0, st, rois, n_rois, case_area);
     hipLaunchKernelGGL(k_mesh_pass<0>, dim3((unsigned)nbricks), dim3(kBrickThreads), lds, st, rois, n_rois, nbricks,
-                       case_area, part, tmpkey, tmpt, tmp_cap, totals, moments, (const int*)bmap);
+                       case_area, part, tmpkey, tmpt, tmp_cap, totals, moments, (const int*)bmap, pbox);
   } else {
     hipLaunchKernelGGL(k_mesh_pass<1>, dim3((unsigned)nbricks), dim3(kBrickThreads), lds, st, rois, n_rois, nbricks,
-                       case_area, part, tmpkey, tmpt, tmp_cap, totals, moments, (const int*)bmap);
+                       case_area, part, tmpkey, tmpt, tmp_cap, totals, moments, (const int*)bmap, pbox);
   }
   return hipGetLastError();
 }
@@ -1264,20 +1403,35 @@ hipError_t launch_mesh_core(int dtype, const Roi* rois, int n_rois, long long nb
   const size_t lds = mesh_lds_bytes(max_G);
   if (dtype == 0)
     hipLaunchKernelGGL(k_mesh_pass<0>, dim3((unsigned)nbricks), dim3(kBrickThreads), lds, st, rois, n_rois, nbricks,
-                       case_area, part, tmpkey, tmpt, tmp_cap, totals, moments, (const int*)nullptr);
+                       case_area, part, tmpkey, tmpt, tmp_cap, totals, moments, (const int*)nullptr, (float4*)nullptr);
   else
     hipLaunchKernelGGL(k_mesh_pass<1>, dim3((unsigned)nbricks), dim3(kBrickThreads), lds, st, rois, n_rois, nbricks,
-                       case_area, part, tmpkey, tmpt, tmp_cap, totals, moments, (const int*)nullptr);
+                       case_area, part, tmpkey, tmpt, tmp_cap, totals, moments, (const int*)nullptr, (float4*)nullptr);
   return hipGetLastError();
 }
 
-hipError_t launch_mesh_totals(const Roi* rois, int n_rois, long long nbricks, int dtype, const double* case_area,
-                              const BrickPart* part, long long* brick_voff, RoiMeta* meta, long long* totals,
-                              int moments, int prune_min_v, hipStream_t st) {
-  hipLaunchKernelGGL(k_mesh_totals, dim3(n_rois), dim3(1024), 0, st, rois, n_rois, nbricks, dtype, case_area, part,
-                     brick_voff,
-                     meta, moments);
+static void totals_kernel(const Roi* rois, int n_rois, int dtype, const double* case_area, const BrickPart* part,
+                          long long* brick_voff, RoiMeta* meta, long long* totals, int moments, const BlockIndex& X,
+                          hipStream_t st) {
+  if (n_rois <= 64)
+    hipLaunchKernelGGL(k_mesh_totals<1024>, dim3(n_rois), dim3(1024), 0, st, rois, n_rois, dtype, case_area, part,
+                       brick_voff, meta, totals, moments, X);
+  else
+    hipLaunchKernelGGL(k_mesh_totals<256>, dim3(n_rois), dim3(256), 0, st, rois, n_rois, dtype, case_area, part,
+                       brick_voff, meta, totals, moments, X);
+}
+
+hipError_t launch_mesh_totals(const Roi* rois, int n_rois, int dtype, const double* case_area, const BrickPart* part,
+                              long long* brick_voff, RoiMeta* meta, long long* totals, int moments, int prune_min_v,
+                              hipStream_t st) {
+  totals_kernel(rois, n_rois, dtype, case_area, part, brick_voff, meta, totals, moments, BlockIndex{}, st);
   hipLaunchKernelGGL(k_roi_rows, dim3(1), dim3(1024), 0, st, n_rois, meta, totals, prune_min_v);
+  return hipGetLastError();
+}
+
+hipError_t launch_block_totals(const Roi* rois, int n_rois, int dtype, const double* case_area, const BrickPart* part,
+                               RoiMeta* meta, long long* totals, int moments, const BlockIndex& X, hipStream_t st) {
+  totals_kernel(rois, n_rois, dtype, case_area, part, nullptr, meta, totals, moments, X, st);
   return hipGetLastError();
 }
 

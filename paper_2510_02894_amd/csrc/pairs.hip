@@ -151,7 +151,14 @@ __device__ inline bool brick_rows(const BrickArgs& A, long long brick, BrickRows
   const int r = A.bmap ? A.bmap[brick] : find_roi(A.rois, A.n_rois, brick);
   if (r < 0 || brick >= A.rois[r].brick_end) return false;
   const RoiMeta& M = A.meta[r];
-  const long long cnt = A.part[brick].nv, first = A.brick_voff[brick];
+  const long long cnt = A.part[brick].nv;
+  out.n = cnt;
+  out.roi = r;
+  if (!A.brick_voff) {  // in the staging list (whole, when the ROI has its blocks)
+    out.row0 = A.part[brick].stage;
+    return cnt > 0 && M.nblk > 0;
+  }
+  const long long first = A.brick_voff[brick];
   if (cnt == 0 || M.V == 0 || first + cnt > M.V) return false;
   out.row0 = M.row_off + first;
   out.n = cnt;
@@ -1431,13 +1438,14 @@ __device__ inline void shape_class_members(const RoiMeta& M, const Roi& R, doubl
 __global__ void k_finalize(int n_rois, const RoiMeta* __restrict__ meta, const GroupRes* __restrict__ gres,
                            const unsigned int* __restrict__ ncand, const unsigned long long* __restrict__ key,
                            const Roi* __restrict__ rois, const long long* __restrict__ pairs2d,
-                           RoiResult* __restrict__ res, long long cand_cap, int moments, int ids32) {
+                           RoiResult* __restrict__ res, long long cand_cap, int moments, int ids32,
+                           const long long* __restrict__ totals, long long rows0_cap) {
   for (int r = blockIdx.x * blockDim.x + threadIdx.x; r < n_rois; r += gridDim.x * blockDim.x) {
     const RoiMeta M = meta[r];
     RoiResult Q;
     Q.V = M.V;
     Q.T = M.T;
-    Q.pairs2d = pairs2d[r];
+    Q.pairs2d = pairs2d ? pairs2d[r] : 0;
     Q.out[0] = fabs(M.vol);
     Q.vol_signed = M.vol;
     Q.out[1] = M.area;
@@ -1454,7 +1462,7 @@ __global__ void k_finalize(int n_rois, const RoiMeta* __restrict__ meta, const G
       Q.cand[f] = G.n_cand;
     }
     Q.status = M.V == 0 ? 1 : 0;
-    if ((long long)*ncand > cand_cap || ncand[1] != 0u) Q.status = -4;
+    if ((long long)*ncand > cand_cap || ncand[1] != 0u || totals[T_ROWS0] > rows0_cap) Q.status = -4;
     if (rois[r].status != 0) Q.status = rois[r].status;
     Q.pad_ = 0;
     Q.n_in = moments ? M.n_in : 0;
@@ -1665,9 +1673,23 @@ hipError_t launch_refine(const PairBufs& B, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_finalize(const PairBufs& B, hipStream_t st) {
+// The in-plane pair counts alone, from the staged keys (B.key, B.brick_voff unused).
+hipError_t launch_plane_counts(const PairBufs& B, hipStream_t st) {
+  hipLaunchKernelGGL(k_zero_buckets, dim3(grid_for(std::max<long long>(B.n_buckets, B.n_rois), 4096)), dim3(256), 0,
+                     st, B.bcnt, B.bcur, B.n_buckets, B.pairs2d, (long long)B.n_rois, (int4*)nullptr);
+  BrickArgs A = brick_args(B);
+  A.brick_voff = nullptr;
+  if (B.nbricks > 0)
+    hipLaunchKernelGGL(k_brick_hist, dim3((unsigned)B.nbricks), dim3(256), sizeof(int) * B.brick_win, st, A, B.key,
+                       B.bcnt, (int4*)nullptr, B.brick_win);
+  hipLaunchKernelGGL(k_bucket_groups, dim3((unsigned)B.n_rois), dim3(256), 0, st, B.rois, B.bgroup, B.bcnt,
+                     B.pairs2d);
+  return hipGetLastError();
+}
+
+hipError_t launch_finalize(const PairBufs& B, long long rows0_cap, hipStream_t st) {
   hipLaunchKernelGGL(k_finalize, dim3(grid_for(B.n_rois)), dim3(256), 0, st, B.n_rois, B.meta, B.gres,
-                     B.counters + 1, B.key, B.rois, B.pairs2d, B.res, B.cand_cap, B.moments ? 1 : 0, B.ids32 ? 1 : 0);
+                     B.counters + 1, B.key, B.rois, B.pairs2d, B.res, B.cand_cap, B.moments ? 1 : 0, B.ids32 ? 1 : 0, B.totals, rows0_cap);
   return hipGetLastError();
 }
 

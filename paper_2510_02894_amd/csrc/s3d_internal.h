@@ -36,6 +36,7 @@ constexpr int kWorkStride = 32;     // words between two work counters (one 128-
 // kWorkStride, then those of the pruned 3D pass.
 constexpr int kCounterWords = kWorkStride * (1 + 2 * kWorkParts);
 constexpr int kListCounters = kWorkStride * (1 + kWorkParts);  // first work counter of the pruned 3D pass
+constexpr int kSuper = 16;           // 32-row blocks per superblock of the block-pair pass
 constexpr int kPruneSB = 32;          // 32-row blocks per column of the 3D pruning pass (1024 rows)
 constexpr int kPruneMinV = 1024;      // ROIs with fewer vertices run their 3D pairs unpruned (prune = 1)
 constexpr int kPruneCallMinV = 16384; // a call prunes (prune = 1) when its largest ROI may have this many vertices
@@ -178,6 +179,10 @@ struct RoiMeta {
   double R2;          // bound on |centred FP32 position|^2
   int bb[6];
   long long prune_off;  // first (column, column) pair of the ROI in the pruning pass (pruned ROIs)
+  long long blk0;     // first block of the ROI in ROI order (a multiple of kSuper)
+  int nblk;           // its 32-row blocks of staged vertices
+  int ex;             // the block bounds are taken in units of 2^ex (about the ROI's extent)
+  float hs[3];        // half its spacing in those units
   long long n_in;     // inside voxels (when moments are asked for)
   double cov[6];      // covariance of their physical coordinates: zz, yy, xx, zy, zx, yx
 };

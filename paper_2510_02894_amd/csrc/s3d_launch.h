@@ -67,12 +67,12 @@ hipError_t launch_small_pairs(int dtype, const Roi* rois, const BrickPart* part,
 hipError_t launch_mesh_pass(int dtype, const Roi* rois, int n_rois, long long nbricks, int max_G,
                             double* case_area, BrickPart* part, unsigned int* counters, int n_counters,
                             unsigned long long* tmpkey, double* tmpt, long long tmp_cap, long long* totals,
-                            int moments, int* bmap, hipStream_t st);
+                            int moments, int* bmap, float4* pbox, hipStream_t st);
 // Per-ROI totals and each brick's first row within its ROI (brick_voff);
 // prune_min_v: ROIs with at least this many vertices get the pruning pass's column-pair offsets.
-hipError_t launch_mesh_totals(const Roi* rois, int n_rois, long long nbricks, int dtype, const double* case_area,
-                              const BrickPart* part, long long* brick_voff, RoiMeta* meta, long long* totals,
-                              int moments, int prune_min_v, hipStream_t st);
+hipError_t launch_mesh_totals(const Roi* rois, int n_rois, int dtype, const double* case_area, const BrickPart* part,
+                              long long* brick_voff, RoiMeta* meta, long long* totals, int moments, int prune_min_v,
+                              hipStream_t st);
 // The capacity check (rows0_cap rows; *overflow raised and every ROI emptied
 // beyond it), the 3D segments, and layout 0 from the staging list (tmp_cap
 // rows): keys, soft t, pair-pass operands (pos, or posh when set), orig and
@@ -82,6 +82,45 @@ hipError_t launch_mesh_rows(const Roi* rois, int n_rois, long long nbricks, cons
                             const unsigned long long* tmpkey, const double* tmpt, long long tmp_cap,
                             unsigned long long* key, double* tsoft, float* pos, uint4* posh, int* orig, int* blkseg,
                             Seg* segs, unsigned int* overflow, const int* bmap, hipStream_t st);
+
+// The mesh pass's vertices in blocks of 32 staged rows, and the block-pair
+// pass over them (blocks.hip).
+struct BlockBufs {
+  const Roi* rois;
+  int n_rois;
+  const RoiMeta* meta;
+  const long long* totals;  // [8] staged rows, [9] blocks in ROI order (each ROI's padded to a superblock)
+  const unsigned long long* key;  // [rows_cap] staged keys
+  const double* t;                // [rows_cap] soft masks' interpolation parameters, else null
+  long long rows_cap;
+  const float4* pbox;  // [2 * rows_cap / 32] box of each staged block: lo x 3, hi x 3 (half voxels)
+  const int* lphys;    // [lblk_cap] staged block of each block in ROI order, -1: padding
+  long long lblk_cap;
+  float4* lbox;        // [2 * lblk_cap] boxes in ROI order, then the staged block's index
+  const int* sbroi;    // [lblk_cap / kSuper] ROI of each superblock
+  float4* sbox;        // [2 * lblk_cap / kSuper] superblock boxes, then the ROI
+  int4* list;          // [list_cap] block pairs: staged blocks, ROI, bound and families
+  unsigned long long* list_n;
+  long long list_cap;
+  GroupRes* gres;      // [4 * n_rois]
+  int cu_count;
+  bool ids32;          // every canonical vertex id of the call is below 2^32
+};
+// ev: optional events after the boxes, the listing and the exact maxima
+hipError_t launch_blocks(const BlockBufs& B, hipStream_t st, hipEvent_t* ev);
+
+// What the totals pass writes for the block-pair pass (all null / 0 when the
+// general pipeline follows).
+struct BlockIndex {
+  int* lphys;
+  int* sbroi;
+  GroupRes* gres;
+  unsigned int* overflow;  // raised when more rows were staged than rows_cap
+  long long rows_cap;
+};
+
+hipError_t launch_block_totals(const Roi* rois, int n_rois, int dtype, const double* case_area, const BrickPart* part,
+                               RoiMeta* meta, long long* totals, int moments, const BlockIndex& X, hipStream_t st);
 
 // labels.hip: the ROI table of labels 1..max_label of a dense uint8 label map
 // (crop to each label's box, select the label), the voxel counts (counts,
@@ -243,7 +282,9 @@ hipError_t launch_prune(const PairBufs& B, hipStream_t st);
 hipError_t launch_pair_maxima(const PairBufs& B, hipStream_t st);   // MFMA pass over the work list
 hipError_t launch_init_groups(const PairBufs& B, hipStream_t st);   // reset group results, pair-pass counters, row maxima
 hipError_t launch_refine(const PairBufs& B, hipStream_t st);        // candidates + exact FP64 passes
-hipError_t launch_finalize(const PairBufs& B, hipStream_t st);      // per-ROI results
+hipError_t launch_plane_counts(const PairBufs& B, hipStream_t st);  // in-plane pair counts from the staged keys
+// per-ROI results; status SHAPE3D_ECAPACITY when the ROIs' rows (totals[0]) exceed rows0_cap
+hipError_t launch_finalize(const PairBufs& B, long long rows0_cap, hipStream_t st);
 // res -> out[nf * n_rois] (nf = 6, or 17 for the whole Shape class; not written for a negative
 // status) and status[n_rois] (may be null), on the device
 hipError_t launch_results_out(const RoiResult* res, int n_rois, double* out, int* status, int nf, hipStream_t st);

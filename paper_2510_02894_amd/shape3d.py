@@ -239,9 +239,9 @@ def features(vol, spacing: Sequence[float] = (1.0, 1.0, 1.0), stats: bool = Fals
     dt = _volume(vol)
     dims, sp = _dims_spacing(vol.shape, spacing)
     out = (ctypes.c_double * 6)()
-    st = Stats()
-    rc = lib.shape3d_ex(ctypes.c_void_p(vol.data_ptr()), dt, dims, sp, out, ctypes.byref(st), 1 if timing else 0,
-                        _stream())
+    st = Stats() if stats else None
+    rc = lib.shape3d_ex(ctypes.c_void_p(vol.data_ptr()), dt, dims, sp, out, ctypes.byref(st) if stats else None,
+                        1 if timing else 0, _stream())
     _check(rc)
     f = np.array(out[:], dtype=np.float64)
     if stats:
@@ -259,8 +259,9 @@ def shape_class(vol, spacing: Sequence[float] = (1.0, 1.0, 1.0), stats: bool = F
     dt = _volume(vol)
     dims, sp = _dims_spacing(vol.shape, spacing)
     out = (ctypes.c_double * N_CLASS)()
-    st = Stats()
-    rc = lib.shape3d_class(ctypes.c_void_p(vol.data_ptr()), dt, dims, sp, out, ctypes.byref(st), _stream())
+    st = Stats() if stats else None
+    rc = lib.shape3d_class(ctypes.c_void_p(vol.data_ptr()), dt, dims, sp, out, ctypes.byref(st) if stats else None,
+                           _stream())
     _check(rc)
     f = np.array(out[:], dtype=np.float64)
     if stats:
