@@ -288,6 +288,7 @@ int check_args(const void* vol, int dtype, const int64_t dims[3], const double s
 // shape (tables planned on the device, `planned`).
 struct Batch {
   std::vector<Roi> rois;
+  Roi one;  // batch_one: the only ROI (rois is then empty)
   int n_rois = 0;
   long long nbricks = 0;    // bricks (a bound when planned)
   long long n_buckets = 0;  // plane buckets (a bound when planned)
@@ -314,6 +315,33 @@ void batch_add(Batch& B, const void* vol, const int64_t dims[3], const double sp
   for (int k = 0; k < 3; ++k) B.max_d[k] = std::max(B.max_d[k], d[k]);
   B.rois.push_back(R);
   B.n_rois = (int)B.rois.size();
+}
+
+// A batch of one ROI without a heap allocation (calls that promise none).
+void batch_one(Batch& B, const void* vol, const int64_t dims[3], const double spacing[3], int tz) {
+  memset(&B.one, 0, sizeof(B.one));
+  const long long d[3] = {dims[0], dims[1], dims[2]};
+  B.nbricks = roi_fill(B.one, vol, d, spacing, 0, 0, 0, tz);
+  B.one.brick_begin = 0;
+  B.one.brick_end = B.nbricks;
+  roi_set_buckets(B.one, 0);
+  B.n_buckets = roi_buckets(B.one.d);
+  B.max_G = B.one.G;
+  for (int k = 0; k < 3; ++k) B.max_d[k] = d[k];
+  B.n_rois = 1;
+}
+
+// Cube planes per brick of a call with one ROI.  A binary mask's results do not
+// depend on its bricks, so a ROI of few bricks is cut into thinner ones, down to
+// one plane, until there are two per CU: the bricks of a brick-bound call then
+// run side by side (97 x 181 x 163: mesh pass 42 us in 65 bricks).  Soft masks'
+// FP64 partials are summed per brick and keep kTZ.
+int single_tz(int dtype, const int64_t dims[3]) {
+  int tz = kTZ;
+  if (dtype != SHAPE3D_U8) return tz;
+  const long long rg = (dims[1] + 1) * ((dims[2] + 1 + 31) / 32), per = (rg + kBrickThreads - 1) / kBrickThreads;
+  while (tz > 1 && per * ((dims[0] + tz) / tz) < 512) tz >>= 1;
+  return tz;
 }
 
 // Bounds of a batch of n ROIs planned on the device, each at most max_dims.
@@ -583,16 +611,18 @@ PairBufs pair_bufs(const Ptrs& P, const Batch& Bt, int dtype, const Sizes& S, in
 
 // The mesh pass (with the staging list's capacity in rows) and per-ROI
 // totals (launches only).
-int launch_mesh(const Ptrs& P, const Batch& Bt, int dtype, long long tmp_cap, float4* pbox, hipStream_t st) {
-  HIPCK(launch_mesh_pass(dtype, P.as<const Roi>(W_ROIS), Bt.n(), Bt.nbricks, Bt.max_G, P.as<double>(W_CASE_AREA),
+// one: the ROI record of a call with one ROI, if it is not in W_ROIS yet.
+int launch_mesh(const Ptrs& P, const Batch& Bt, int dtype, long long tmp_cap, float4* pbox, const Roi* one,
+                hipStream_t st) {
+  HIPCK(launch_mesh_pass(dtype, P.as<Roi>(W_ROIS), Bt.n(), Bt.nbricks, Bt.max_G, P.as<double>(W_CASE_AREA),
                          P.as<BrickPart>(W_PART), P.as<unsigned int>(W_COUNTERS), kCounterWords,
                          P.as<unsigned long long>(W_TMPKEY), dtype == SHAPE3D_F32 ? P.as<double>(W_TMPT) : nullptr,
-                         tmp_cap, P.as<long long>(W_TOTALS), Bt.moments ? 1 : 0, P.as<int>(W_BRICK_ROI), pbox, st));
+                         tmp_cap, P.as<long long>(W_TOTALS), Bt.moments ? 1 : 0, P.as<int>(W_BRICK_ROI), pbox, one, st));
   return SHAPE3D_OK;
 }
 
 int launch_head(const Ptrs& P, const Batch& Bt, int dtype, long long tmp_cap, hipStream_t st) {
-  const int rc = launch_mesh(P, Bt, dtype, tmp_cap, nullptr, st);
+  const int rc = launch_mesh(P, Bt, dtype, tmp_cap, nullptr, nullptr, st);
   if (rc) return rc;
   HIPCK(launch_mesh_totals(P.as<const Roi>(W_ROIS), Bt.n(), dtype, P.as<const double>(W_CASE_AREA),
                            P.as<const BrickPart>(W_PART),
@@ -638,7 +668,7 @@ int launch_tail(const Ptrs& P, const Batch& Bt, int dtype, const Sizes& S, long 
   if (ev) HIPCK(hipEventRecord(ev[3], st));
   HIPCK(launch_refine(B, st));
   if (ev) HIPCK(hipEventRecord(ev[4], st));
-  HIPCK(launch_finalize(B, kMaxRows, st));
+  HIPCK(launch_finalize(B, kMaxRows, 0, st));
   return SHAPE3D_OK;
 }
 
@@ -738,15 +768,21 @@ BlockSizes block_sizes(long long rows, int n_rois) {
 // Staged rows that hold any mesh of `v` vertices: each brick's are padded to whole blocks.
 long long staged_rows(const Batch& Bt, long long v) { return v + (long long)(kSegAlign - 1) * Bt.nbricks; }
 
-// The library's staging list and block buffers for at least `rows` staged rows.
-int ensure_block_bufs(Workspace& w, const Batch& Bt, int dtype, long long rows, BlockSizes& Z) {
+// Most block pairs the library's list grows to (1 GiB).
+constexpr long long kMaxList = 1ll << 26;
+
+// The library's staging list and block buffers for at least `rows` staged rows
+// and (up to kMaxList) `list` block pairs.
+int ensure_block_bufs(Workspace& w, const Batch& Bt, int dtype, long long rows, long long list, BlockSizes& Z) {
   long long cap = 0;
   int rc = ensure_staging(w, dtype, rows, &cap);
   if (rc) return rc;
   if (cap > kMaxRows) cap = kMaxRows;
   Z = block_sizes(cap, Bt.n());
+  Z.bytes[B_LIST] = std::max(Z.bytes[B_LIST], sizeof(int4) * (size_t)std::min(list, kMaxList));
   for (int i = 0; i < B_NUM; ++i)
     if ((rc = ensure(w, w.blk[i], Z.bytes[i]))) return rc;
+  Z.list = (long long)(w.blk[B_LIST].cap / sizeof(int4));
   return SHAPE3D_OK;
 }
 
@@ -764,12 +800,9 @@ BlockPtrs block_ptrs(const Workspace& w) {
   return Q;
 }
 
-// Everything after the mesh pass (launches only): per-ROI results in res, which
-// may be pinned host memory.  rows0_cap: vertex rows (each ROI's padded to 32)
-// the call accepts; more end with status SHAPE3D_ECAPACITY, as does a staging
-// list that was too short.  counts: also the in-plane pair counts.
-int launch_block_tail(const Ptrs& P, const BlockPtrs& Q, const BlockSizes& Z, const Batch& Bt, int dtype,
-                      long long rows0_cap, bool counts, int cu_count, RoiResult* res, hipStream_t st, hipEvent_t* ev) {
+// Per-ROI totals and the block list (launches only).
+int launch_block_list(const Ptrs& P, const BlockPtrs& Q, const BlockSizes& Z, const Batch& Bt, int dtype,
+                      hipStream_t st) {
   BlockIndex X;
   X.lphys = Q.as<int>(B_LPHYS);
   X.sbroi = Q.as<int>(B_SBROI);
@@ -779,6 +812,17 @@ int launch_block_tail(const Ptrs& P, const BlockPtrs& Q, const BlockSizes& Z, co
   HIPCK(launch_block_totals(P.as<const Roi>(W_ROIS), Bt.n(), dtype, P.as<const double>(W_CASE_AREA),
                             P.as<const BrickPart>(W_PART), P.as<RoiMeta>(W_META), P.as<long long>(W_TOTALS),
                             Bt.moments ? 1 : 0, X, st));
+  return SHAPE3D_OK;
+}
+
+// Everything after that (launches only): per-ROI results in res, which may be
+// pinned host memory.  rows0_cap: vertex rows (each ROI's padded to 32) the
+// call accepts; more end with status SHAPE3D_ECAPACITY, as does a staging list
+// that was too short.  counts: also the in-plane pair counts.  again: a block
+// pair list that is too short is made good on the device; else status kListShort.
+int launch_block_tail(const Ptrs& P, const BlockPtrs& Q, const BlockSizes& Z, const Batch& Bt, int dtype,
+                      long long rows0_cap, bool counts, bool again, int cu_count, RoiResult* res, hipStream_t st,
+                      hipEvent_t* ev) {
   PairBufs C = pair_bufs(P, Bt, dtype, Sizes{}, cu_count);
   C.res = res;
   C.key = P.as<const unsigned long long>(W_TMPKEY);
@@ -807,9 +851,9 @@ int launch_block_tail(const Ptrs& P, const BlockPtrs& Q, const BlockSizes& Z, co
   B.gres = P.as<GroupRes>(W_GRES);
   B.cu_count = cu_count;
   B.ids32 = C.ids32;
-  HIPCK(launch_blocks(B, st, ev));
+  HIPCK(launch_blocks(B, again, st, ev));
   if (ev) HIPCK(hipEventRecord(ev[3], st));
-  HIPCK(launch_finalize(C, rows0_cap, st));
+  HIPCK(launch_finalize(C, rows0_cap, again ? (1ll << 62) : Z.list, st));
   return SHAPE3D_OK;
 }
 
@@ -822,27 +866,33 @@ long long block_guess(const Batch& Bt) { return staged_rows(Bt, staging_guess(Bt
 int run_blocks(Workspace& w, const Batch& Bt, int dtype, hipStream_t st, RoiResult* host_res, bool counts, int timing,
                float* phase_ms, const DevTable* dt = nullptr) {
   BlockSizes Z;
-  int rc = ensure_block_bufs(w, Bt, dtype, block_guess(Bt), Z);
+  int rc = ensure_block_bufs(w, Bt, dtype, block_guess(Bt), 0, Z);
   if (rc) return rc;
   long long* th = (long long*)w.host;
   // a few results go to the host as they are written, many in one copy
   const bool direct = host_res && Bt.n() <= 16;
+  const Roi* one = !dt && Bt.n() == 1 ? &Bt.rois[0] : nullptr;
+  bool again = host_res == nullptr;
   for (int pass = 0;; ++pass) {
     const Ptrs P = w.ptrs();
-    if ((rc = upload_rois(w, P, Bt, dtype, dt, st))) return rc;
+    if (!one && (rc = upload_rois(w, P, Bt, dtype, dt, st))) return rc;
     if (timing) HIPCK(hipEventRecord(w.ev[0], st));
-    if ((rc = launch_mesh(P, Bt, dtype, Z.rows, w.blk[B_PBOX].p ? (float4*)w.blk[B_PBOX].p : nullptr, st))) return rc;
+    if ((rc = launch_mesh(P, Bt, dtype, Z.rows, (float4*)w.blk[B_PBOX].p, one, st))) return rc;
+    if (timing) HIPCK(hipEventRecord(w.ev[1], st));
+    if ((rc = launch_block_list(P, block_ptrs(w), Z, Bt, dtype, st))) return rc;
     if (!host_res) {
       HIPCK(hipMemcpyAsync(th, P.p[W_TOTALS], sizeof(long long) * 9, hipMemcpyDeviceToHost, st));
       HIPCK(hipStreamSynchronize(st));
       if (th[8] > Z.rows) {
         if (pass > 0) return fail(SHAPE3D_EINTERNAL, "the mesh pass's staging list overflowed twice");
-        if ((rc = ensure_block_bufs(w, Bt, dtype, th[8], Z))) return rc;
+        if ((rc = ensure_block_bufs(w, Bt, dtype, th[8], 0, Z))) return rc;
         continue;
       }
+      Layout L;  // the limit of the general pipeline's row indices holds for either path
+      if ((rc = ws_layout(Bt, dtype, g_tune, th[0], L))) return rc;
+      w.last_rows0 = th[0];
     }
-    if (timing) HIPCK(hipEventRecord(w.ev[1], st));
-    if ((rc = launch_block_tail(P, block_ptrs(w), Z, Bt, dtype, kMaxRows, counts, w.cu_count,
+    if ((rc = launch_block_tail(P, block_ptrs(w), Z, Bt, dtype, kMaxRows, counts, again, w.cu_count,
                                 direct ? host_res : P.as<RoiResult>(W_RES), st, timing ? &w.ev[2] : nullptr)))
       return rc;
     if (!host_res) return SHAPE3D_OK;
@@ -850,13 +900,19 @@ int run_blocks(Workspace& w, const Batch& Bt, int dtype, hipStream_t st, RoiResu
       HIPCK(hipMemcpyAsync(host_res, P.p[W_RES], sizeof(RoiResult) * Bt.n(), hipMemcpyDeviceToHost, st));
     if (timing) HIPCK(hipEventRecord(w.ev[7], st));
     HIPCK(hipStreamSynchronize(st));
-    bool short_list = false;
-    for (int r = 0; r < Bt.n(); ++r) short_list |= host_res[r].status == SHAPE3D_ECAPACITY;
-    if (!short_list) break;
-    HIPCK(hipMemcpyAsync(th, P.p[W_TOTALS], sizeof(long long) * 9, hipMemcpyDeviceToHost, st));
+    bool short_rows = false, short_list = false;
+    for (int r = 0; r < Bt.n(); ++r) {
+      short_rows |= host_res[r].status == SHAPE3D_ECAPACITY;
+      short_list |= host_res[r].status == kListShort;
+    }
+    if (!short_rows && !short_list) break;
+    // once more with lists that are long enough (or, past kMaxList, without one)
+    HIPCK(hipMemcpyAsync(th, P.p[W_TOTALS], sizeof(long long) * 11, hipMemcpyDeviceToHost, st));
     HIPCK(hipStreamSynchronize(st));
-    if (th[8] <= Z.rows || pass > 0) break;
-    if ((rc = ensure_block_bufs(w, Bt, dtype, th[8], Z))) return rc;
+    if (pass > 2 || (!short_list && th[8] <= Z.rows)) break;
+    const long long list = short_list ? th[10] + th[10] / 8 : 0;
+    again |= list > kMaxList;
+    if ((rc = ensure_block_bufs(w, Bt, dtype, th[8], list, Z))) return rc;
   }
   // the limit of the general pipeline's row indices holds for either path
   long long rows0 = 0, vmax = 0;
@@ -882,56 +938,60 @@ int run_blocks(Workspace& w, const Batch& Bt, int dtype, hipStream_t st, RoiResu
 // host synchronisation: the ROI table is set on the device, the vertex
 // capacity comes from the workspace size, and a mesh beyond it ends with
 // status SHAPE3D_ECAPACITY for every ROI.  Results go to out/status (device).
-int run_fixed(const Batch& Bt, int dtype, const Roi* one_roi, const DevTable* dt, void* ws, size_t ws_bytes,
+// thin: the same ROI in thinner bricks (single_tz), used if the workspace has
+// room for their records; the vertex capacity is Bt's either way.
+int run_fixed(const Batch& Bt0, const Batch* thin, int dtype, const DevTable* dt, void* ws, size_t ws_bytes,
               int cu_count, double* out, int* status, hipStream_t st) {
-  const long long cap = rows_cap_for(Bt, dtype, g_tune, ws_bytes);
+  const long long cap = rows_cap_for(Bt0, dtype, g_tune, ws_bytes);
   if (cap < 0) return fail(SHAPE3D_ECAPACITY, "workspace too small for this input's mesh-pass buffers");
   Layout L;
-  int rc = ws_layout(Bt, dtype, g_tune, cap, L);
+  int rc = ws_layout(Bt0, dtype, g_tune, cap, L);
   Ptrs P;
   BlockPtrs Q;
   BlockSizes Z = block_sizes(0, 0);
   bool blocks = false;
-  if (!rc && block_path()) {
+  const Batch* cut[2] = {thin, &Bt0};
+  const Batch* chosen = &Bt0;
+  for (int c = 0; c < 2 && !rc && !blocks && block_path(); ++c) {
+    if (!cut[c]) continue;
     // the vertex rows' buffers make room for the staging list and the block buffers
-    const long long rows = (staged_rows(Bt, cap) + kSegAlign - 1) / kSegAlign * kSegAlign;
-    Layout LB = L;
+    const long long rows = (staged_rows(*cut[c], cap) + kSegAlign - 1) / kSegAlign * kSegAlign;
+    Layout LB;
+    if ((rc = ws_layout(*cut[c], dtype, g_tune, 0, LB))) break;
     for (int i = W_FIRST_VERTEX_BUF; i < W_NUM; ++i) LB.bytes[i] = 0;
     LB.bytes[W_TMPKEY] = sizeof(unsigned long long) * (size_t)rows;
     LB.bytes[W_TMPT] = dtype == SHAPE3D_F32 ? sizeof(double) * (size_t)rows : 0;
-    Z = block_sizes(rows, Bt.n());
+    Z = block_sizes(rows, cut[c]->n());
     size_t need = ws_total(LB);
     for (int i = 0; i < B_NUM; ++i) need += aligned(std::max<size_t>(Z.bytes[i], 1));
-    if (rows <= kMaxRows && need > ws_bytes) {
-      // a short list only: block pairs beyond it are evaluated where they are found
-      const size_t fixed = need - aligned(Z.bytes[B_LIST]);
-      if (fixed + 4096 * sizeof(int4) <= ws_bytes) {
-        Z.list = (long long)((ws_bytes - fixed - 256) / sizeof(int4));
-        Z.bytes[B_LIST] = sizeof(int4) * (size_t)Z.list;
-        need = fixed + aligned(Z.bytes[B_LIST]);
-      }
-    }
-    blocks = rows <= kMaxRows && need <= ws_bytes;
-    if (blocks) {
-      if ((rc = carve(LB, ws, ws_bytes, P))) return rc;
-      size_t off = ws_total(LB);
-      for (int i = 0; i < B_NUM; ++i) {
-        Q.p[i] = (char*)ws + off;
-        off += aligned(std::max<size_t>(Z.bytes[i], 1));
-      }
+    // the rest of the workspace, at least 4,096 entries, is the block pair list
+    need -= aligned(Z.bytes[B_LIST]);
+    if (rows > kMaxRows || need + 4096 * sizeof(int4) + 256 > ws_bytes) continue;
+    Z.list = std::min<long long>((long long)((ws_bytes - need - 256) / sizeof(int4)), kMaxList);
+    Z.bytes[B_LIST] = sizeof(int4) * (size_t)Z.list;
+    blocks = true;
+    chosen = cut[c];
+    if ((rc = carve(LB, ws, ws_bytes, P))) return rc;
+    size_t off = ws_total(LB);
+    for (int i = 0; i < B_NUM; ++i) {
+      Q.p[i] = (char*)ws + off;
+      off += aligned(std::max<size_t>(Z.bytes[i], 1));
     }
   }
+  const Batch& Bt = *chosen;
+  const Roi* one_roi = dt ? nullptr : &Bt.one;
   if (!rc && !blocks) rc = carve(L, ws, ws_bytes, P);
   if (rc) return rc;
   if (dt) {
     HIPCK(launch_plan_rois(dt->rois, Bt.n(), dtype, dt->max_dims, dt->base, dt->alloc_elems, P.as<Roi>(W_ROIS),
                            P.as<long long>(W_PLAN), st));
-  } else {
+  } else if (!blocks) {
     HIPCK(launch_set_roi(*one_roi, P.as<Roi>(W_ROIS), st));
   }
   if (blocks) {
-    if ((rc = launch_mesh(P, Bt, dtype, Z.rows, Q.as<float4>(B_PBOX), st))) return rc;
-    if ((rc = launch_block_tail(P, Q, Z, Bt, dtype, cap, false, cu_count, P.as<RoiResult>(W_RES), st, nullptr)))
+    if ((rc = launch_mesh(P, Bt, dtype, Z.rows, Q.as<float4>(B_PBOX), one_roi, st))) return rc;
+    if ((rc = launch_block_list(P, Q, Z, Bt, dtype, st))) return rc;
+    if ((rc = launch_block_tail(P, Q, Z, Bt, dtype, cap, false, true, cu_count, P.as<RoiResult>(W_RES), st, nullptr)))
       return rc;
   } else {
     if ((rc = launch_head(P, Bt, dtype, cap, st))) return rc;
@@ -1016,7 +1076,7 @@ int shape3d_impl(const void* vol, int dtype, const int64_t dims[3], const double
   Workspace& w = *wp;
   Batch Bt;
   Bt.moments = moments;
-  batch_add(Bt, vol, dims, spacing);
+  batch_add(Bt, vol, dims, spacing, 0, 0, 0, block_path() ? single_tz(dtype, dims) : kTZ);
   if ((rc = ensure_layout_bufs(w, Bt, dtype))) return rc;
   RoiResult* hres = host_results(w, Bt);
   float ms[8] = {0};
@@ -1071,7 +1131,7 @@ int capture_graph(Workspace& w, const Batch& Bt, int dtype, hipStream_t st, Grap
   const bool blocks = block_path();
   long long tcap = 0;
   BlockSizes Z;
-  int rc0 = blocks ? ensure_block_bufs(w, Bt, dtype, staged_rows(Bt, w.last_rows0), Z)
+  int rc0 = blocks ? ensure_block_bufs(w, Bt, dtype, staged_rows(Bt, w.last_rows0), 0, Z)
                    : ensure_staging(w, dtype, w.last_rows0, &tcap);
   if (rc0) return rc0;
   const Ptrs P = w.ptrs();
@@ -1084,10 +1144,11 @@ int capture_graph(Workspace& w, const Batch& Bt, int dtype, hipStream_t st, Grap
     if (e != hipSuccess) rc = fail(SHAPE3D_EHIP, std::string("plan: ") + hipGetErrorString(e));
   }
   if (!rc && blocks) {
-    rc = launch_mesh(P, Bt, dtype, Z.rows, (float4*)w.blk[B_PBOX].p, st);
+    rc = launch_mesh(P, Bt, dtype, Z.rows, (float4*)w.blk[B_PBOX].p, nullptr, st);
+    if (!rc) rc = launch_block_list(P, block_ptrs(w), Z, Bt, dtype, st);
     if (!rc)
-      rc = launch_block_tail(P, block_ptrs(w), Z, Bt, dtype, w.last_rows0, counts, w.cu_count, P.as<RoiResult>(W_RES),
-                             st, nullptr);
+      rc = launch_block_tail(P, block_ptrs(w), Z, Bt, dtype, w.last_rows0, counts, true, w.cu_count,
+                             P.as<RoiResult>(W_RES), st, nullptr);
   } else if (!rc) {
     rc = launch_head(P, Bt, dtype, tcap, st);
     if (!rc) rc = launch_tail(P, Bt, dtype, S, tcap, w.cu_count, st, nullptr, w.last_vmax);
@@ -1251,7 +1312,7 @@ int batched_dev_impl(const void* base, int dtype, const shape3d_roi_ex* rois, in
     HIPCK(hipGetDevice(&dev));
     if ((rc = device_cu_count(dev, &cu))) return rc;
     if ((rc = check_device_span(ws, ws_bytes, "workspace"))) return rc;
-    return run_fixed(Bt, dtype, nullptr, &dt, ws, ws_bytes, cu, out, status, st);
+    return run_fixed(Bt, nullptr, dtype, &dt, ws, ws_bytes, cu, out, status, st);
   }
   Workspace* wp = nullptr;
   if ((rc = get_workspace(&wp))) return rc;
@@ -1903,9 +1964,10 @@ int shape3d_ex_async(const void* vol, int dtype, const int64_t dims[3], const do
   int dev = 0, cu = 0;
   HIPCK(hipGetDevice(&dev));
   if ((rc = device_cu_count(dev, &cu))) return rc;
-  Batch Bt;
-  batch_add(Bt, vol, dims, spacing);
-  rc = run_fixed(Bt, dtype, &Bt.rois[0], nullptr, workspace, ws_bytes, cu, out, status, (hipStream_t)stream);
+  Batch Bt, thin;
+  batch_one(Bt, vol, dims, spacing, kTZ);
+  batch_one(thin, vol, dims, spacing, single_tz(dtype, dims));
+  rc = run_fixed(Bt, &thin, dtype, nullptr, workspace, ws_bytes, cu, out, status, (hipStream_t)stream);
   if (!rc) g_err.clear();
   return rc;
 }
@@ -1929,20 +1991,10 @@ int shape3d_noalloc(const void* vol, int dtype, const int64_t dims[3], const dou
     g_scratch[dev] = ptr;
   }
   if ((rc = device_cu_count(dev, &cu))) return rc;
-  // a one-ROI batch built without heap allocation (no ROI vector)
-  Batch Bt;
-  Roi R;
-  memset(&R, 0, sizeof(R));
-  const long long d[3] = {dims[0], dims[1], dims[2]};
-  const long long nb = roi_fill(R, vol, d, spacing, 0, 0, 0);
-  R.brick_begin = 0;
-  R.brick_end = nb;
-  roi_set_buckets(R, 0);
-  Bt.n_rois = 1;
-  Bt.nbricks = nb;
-  Bt.n_buckets = roi_buckets(R.d);
-  Bt.max_G = R.G;
-  rc = run_fixed(Bt, dtype, &R, nullptr, g_scratch[dev], (size_t)SHAPE3D_NOALLOC_SCRATCH_BYTES, cu, out, status,
+  Batch Bt, thin;
+  batch_one(Bt, vol, dims, spacing, kTZ);
+  batch_one(thin, vol, dims, spacing, single_tz(dtype, dims));
+  rc = run_fixed(Bt, &thin, dtype, nullptr, g_scratch[dev], (size_t)SHAPE3D_NOALLOC_SCRATCH_BYTES, cu, out, status,
                  (hipStream_t)stream);
   if (!rc) g_err.clear();
   return rc;

@@ -76,6 +76,8 @@ __device__ inline Metric metric_of(const RoiMeta& M, bool soft) {
   return m;
 }
 
+constexpr float kBoundUp = 1.0f + 3.814697265625e-06f;
+
 // Upper bounds f[0..3] on the squared distance of a vertex in a and one in b:
 // over all pairs, and over the pairs on a common plane of axis 0, 1, 2 (-1
 // where there is none).  Raised by 2^-18, above the FP32 rounding of the
@@ -91,135 +93,212 @@ __device__ inline void far_bounds(const Box& a, const Box& b, const Metric& m, f
     q[k] = x * x;
     p[k] = y * y;
   }
-  constexpr float up = 1.0f + 3.814697265625e-06f;
-  f[0] = (q[0] + q[1] + q[2]) * up;
-  f[1] = meet[0] ? (p[0] + q[1] + q[2]) * up : -1.0f;
-  f[2] = meet[1] ? (q[0] + p[1] + q[2]) * up : -1.0f;
-  f[3] = meet[2] ? (q[0] + q[1] + p[2]) * up : -1.0f;
+  f[0] = (q[0] + q[1] + q[2]) * kBoundUp;
+  f[1] = meet[0] ? (p[0] + q[1] + q[2]) * kBoundUp : -1.0f;
+  f[2] = meet[1] ? (q[0] + p[1] + q[2]) * kBoundUp : -1.0f;
+  f[3] = meet[2] ? (q[0] + q[1] + p[2]) * kBoundUp : -1.0f;
+}
+
+// The bound of family g alone (g the same for the whole wave).
+__device__ inline float far_bound(const Box& a, const Box& b, const Metric& m, int g) {
+  float sum = 0.0f;
+  bool meet = true;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    float d = fmaxf(a.hi[k] - b.lo[k], b.hi[k] - a.lo[k]);
+    if (g == k + 1) {
+      meet = fmaxf(a.lo[k] - b.hi[k], b.lo[k] - a.hi[k]) <= m.slack;
+      d = fminf(d, m.slack);
+    }
+    const float x = d * m.hs[k];
+    sum += x * x;
+  }
+  return meet ? sum * kBoundUp : -1.0f;
 }
 
 // A group's exact maximum so far in units of 2^(2 ex), rounded down to FP32:
 // a bound below this cannot matter.  Less 2^-120, above the rounding of
 // squares that fall out of FP32's normal range (planes whose two axes are
 // 10^18 times finer than the third); 0 if the maximum left FP64's range.
-__device__ inline float seen_max(const GroupRes* g, int ex) {
-  const unsigned long long b = __hip_atomic_load(&g->best_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+__device__ inline unsigned long long seen_bits(const GroupRes* g) {
+  return __hip_atomic_load(&g->best_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ inline float bits_bound(unsigned long long b, int ex) {
   const double v = ldexp(__longlong_as_double((long long)b), -2 * ex);
   return v < 1.0e30 ? (float)(v * (1.0 - 1.1920928955078125e-07) - 7.52316384526264e-37) : 0.0f;
 }
 
-__device__ inline void raise_max(GroupRes* g, double v) {
+__device__ inline float seen_max(const GroupRes* g, int ex) { return bits_bound(seen_bits(g), ex); }
+
+// Raises a group's maximum to v unless it is known to be as large: `seen` was
+// read earlier, and it is read again before the atomic, since the waves of a
+// ROI meet on four addresses (7,000 unconditional atomics took 50 us).  Returns
+// whether v is not below the maximum.
+__device__ inline bool raise_max(GroupRes* g, double v, unsigned long long seen) {
   const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-  if (b > __hip_atomic_load(&g->best_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(&g->best_bits, b);
+  if (b < seen) return false;
+  const unsigned long long now = seen_bits(g);
+  return b > now ? b >= atomicMax(&g->best_bits, b) : b == now;
 }
 
-// A staged vertex: position, and its three plane keys in 21-bit fields.
-struct VRow {
+// A staged vertex: position and the plane keys of its three axes.
+struct alignas(16) VRow {
   double x[3];
-  unsigned long long code;
+  uint32_t pk[3];
+  uint32_t pad_[3];
 };
-
-constexpr unsigned long long kField = (1ull << 21) - 1ull;
 
 __device__ inline VRow vertex_row(unsigned long long k, double t, const double* s) {
   VRow v;
   key_position(k, t, s, v.x);
-  const unsigned long long a = k >> 60 & 3ull;
-  const unsigned long long p0 = 2ull * (k >> 40 & 0xFFFFF) + (a == 0), p1 = 2ull * (k >> 20 & 0xFFFFF) + (a == 1),
-                           p2 = 2ull * (k & 0xFFFFF) + (a == 2);
-  v.code = p0 | p1 << 21 | p2 << 42;
+  const uint32_t a = (uint32_t)(k >> 60) & 3u;
+  v.pk[0] = 2u * ((uint32_t)(k >> 40) & 0xFFFFFu) + (a == 0u);
+  v.pk[1] = 2u * ((uint32_t)(k >> 20) & 0xFFFFFu) + (a == 1u);
+  v.pk[2] = 2u * ((uint32_t)k & 0xFFFFFu) + (a == 2u);
   return v;
 }
 
-struct VertexList {
-  const unsigned long long* key;
-  const double* t;  // null for binary masks
-};
-
-// A wave's LDS of a block pair: block b's rows, read by all lanes of a half
-// wave at once (broadcast), and their keys.
+// A wave's LDS of a block pair: rows from 0 on are block b's, rows from 32 on
+// block a's; and their keys.
 struct PairStage {
-  VRow row[32];
-  unsigned long long key[32];
+  VRow row[64];
+  unsigned long long key[64];
 };
 
-// Lane l holds row l % 32 of block a; the half waves take 16 rows of b each.
-__device__ inline VRow stage_pair(const VertexList& L, int a, int b, const double* s, int lane, PairStage* S,
-                                  unsigned long long* key_a) {
-  const long long ra = 32ll * a + (lane & 31), rb = 32ll * b + (lane & 31);
-  const unsigned long long ka = L.key[ra], kb = L.key[rb];
-  const double ta = L.t ? L.t[ra] : 0.5, tb = L.t ? L.t[rb] : 0.5;
-  __builtin_amdgcn_wave_barrier();  // the previous pair's rows have been read
-  if (lane < 32) {
-    S->row[lane] = vertex_row(kb, tb, s);
-    S->key[lane] = kb;
-  }
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  *key_a = ka;
-  return vertex_row(ka, ta, s);
+// One vertex per lane, b's rows by lanes 0..31, a's by lanes 32..63, and the box
+// of the other block.
+struct PairLoad {
+  unsigned long long k;
+  double t;
+  float4 b0, b1;
+};
+
+__device__ inline PairLoad load_pair(const BlockBufs& B, int a, int b, int lane) {
+  const long long mine = lane < 32 ? b : a, other = lane < 32 ? a : b;
+  const long long r = 32ll * mine + (lane & 31);
+  PairLoad K;
+  K.k = B.key[r];
+  K.t = B.t ? B.t[r] : 0.5;
+  K.b0 = B.pbox[2 * other];
+  K.b1 = B.pbox[2 * other + 1];
+  return K;
 }
 
 __device__ inline double wave_max_f64(double v) {
+  // maxima of squared distances and -1: signed integers of the same order
+  const unsigned long long r = lanes_reduce<6>(
+      (unsigned long long)__double_as_longlong(v),
+      [](unsigned long long x, unsigned long long y) { return (long long)x > (long long)y ? x : y; });
+  return __longlong_as_double((long long)r);
+}
+
+// The largest squared distance between the staged rows, n_a of block a and n_b
+// of b, over all pairs (G = 0) or those on a common plane of axis G - 1 (-1 if
+// there is none).  2^sh >= n_a lanes hold a row each, the groups of lanes take
+// b's rows in turn.
+template <int G>
+__device__ inline double staged_max(const PairStage* S, int n_a, int n_b, int sh, int lane) {
+  const int i = lane & ((1 << sh) - 1);
+  const VRow A = S->row[32 + i];
+  double m = -1.0;
+  for (int c = lane >> sh; c < n_b; c += 64 >> sh) {
+    const double d = dist2_exact(A.x, S->row[c].x);
+    m = fmax(m, G == 0 || A.pk[G ? G - 1 : 0] == S->row[c].pk[G ? G - 1 : 0] ? d : -1.0);
+  }
+  return wave_max_f64(i < n_a ? m : -1.0);
+}
+
+// Stages the vertices of a block pair that can take part in a pair at or above
+// thr for a family in `mask`: those whose bound to the other block's box reaches
+// it (of the 1,024 pairs of a listed block pair a few dozen are left).  n_a, n_b:
+// their numbers; false if there is no pair.
+__device__ inline bool stage_rows(const PairLoad& K, const Roi& R, const Metric& met, unsigned int mask,
+                                  const float* thr, int lane, PairStage* S, bool keys, int& n_a, int& n_b) {
+  const VRow V = vertex_row(K.k, K.t, R.s);
+  bool take = false;
+  {
+    Box v;
 #pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) v = fmax(v, __shfl_xor(v, m, 64));
-  return v;
+    for (int k = 0; k < 3; ++k) {
+      // half voxels: the plane key less the key offset, moved by the soft
+      // parameter along the edge and widened by its rounding
+      float c = (float)((int)V.pk[k] - 2), w = 0.0f;
+      if (met.slack > 0.0f) {
+        const bool along = (int)((K.k >> 60) & 3ull) == k;
+        c = along ? c - 1.0f + 2.0f * (float)K.t : c;
+        w = fabsf(c) * 2.384185791015625e-07f + 2.384185791015625e-07f;
+      }
+      v.lo[k] = c - w;
+      v.hi[k] = c + w;
+    }
+    float f[4];
+    far_bounds(v, box_of(K.b0, K.b1), met, f);
+#pragma unroll
+    for (int g = 0; g < 4; ++g) take |= (mask >> g & 1u) && f[g] >= thr[g];
+  }
+  const unsigned long long em = __ballot(take);
+  const unsigned int mb = (unsigned int)em, ma = (unsigned int)(em >> 32);
+  if (!ma || !mb) return false;
+  n_a = __popc(ma);
+  n_b = __popc(mb);
+  __builtin_amdgcn_wave_barrier();  // the previous pair's rows have been read
+  if (take) {
+    const int slot = (lane & 32) + __popc((lane < 32 ? mb : ma) & ((1u << (lane & 31)) - 1u));
+    S->row[slot] = V;
+    if (keys) S->key[slot] = K.k;
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  return true;
 }
 
 // The exact maxima over the pairs of two blocks, for the families in `mask`
-// (bit 0: all pairs, bits 1..3: pairs on a common plane of axis 0, 1, 2);
-// -1 where there is no pair.  Every lane returns them.
-__device__ inline void pair_max(const VertexList& L, int a, int b, const Roi& R, unsigned int mask, int lane,
-                                PairStage* S, double* m) {
-  unsigned long long ka;
-  const VRow A = stage_pair(L, a, b, R.s, lane, S, &ka);
+// (bit 0: all pairs, bits 1..3: pairs on a common plane of axis 0, 1, 2) as far
+// as they reach thr (pairs below it may be left out); -1 where no pair was
+// visited.  Every lane returns them.
+__device__ inline void pair_max(const PairLoad& K, const Roi& R, const Metric& met, unsigned int mask,
+                                const float* thr, int lane, PairStage* S, double* m) {
 #pragma unroll
   for (int g = 0; g < 4; ++g) m[g] = -1.0;
-  const VRow* col = S->row + (lane & 32 ? 16 : 0);
-  if (mask == 1u) {
-#pragma unroll 4
-    for (int c = 0; c < 16; ++c) m[0] = fmax(m[0], dist2_exact(A.x, col[c].x));
-  } else {
-#pragma unroll 2
-    for (int c = 0; c < 16; ++c) {
-      const double d = dist2_exact(A.x, col[c].x);
-      const unsigned long long x = A.code ^ col[c].code;
-      m[0] = fmax(m[0], d);
-      m[1] = fmax(m[1], (x & kField) == 0ull ? d : -1.0);
-      m[2] = fmax(m[2], (x & kField << 21) == 0ull ? d : -1.0);
-      m[3] = fmax(m[3], (x & kField << 42) == 0ull ? d : -1.0);
-    }
-  }
-#pragma unroll
-  for (int g = 0; g < 4; ++g)
-    if (mask >> g & 1u) m[g] = wave_max_f64(m[g]);
+  int n_a, n_b;
+  if (!stage_rows(K, R, met, mask, thr, lane, S, false, n_a, n_b)) return;
+  const int sh = n_a > 1 ? 32 - __clz(n_a - 1) : 0;
+  if (mask & 1u) m[0] = staged_max<0>(S, n_a, n_b, sh, lane);
+  if (mask & 2u) m[1] = staged_max<1>(S, n_a, n_b, sh, lane);
+  if (mask & 4u) m[2] = staged_max<2>(S, n_a, n_b, sh, lane);
+  if (mask & 8u) m[3] = staged_max<3>(S, n_a, n_b, sh, lane);
 }
 
 // The smallest id pair among the block pairs' pairs at the families' maxima:
 // with ids32 id_lo * 2^32 + id_hi at once, else PASS 0 takes the smallest
 // id_lo and PASS 1 the smallest id_hi that goes with it.
-__device__ inline void pair_ties(const VertexList& L, int a, int b, const Roi& R, unsigned int mask, int lane,
-                                 PairStage* S, GroupRes* g4, int ids32, int pass) {
-  unsigned long long ka;
-  const VRow A = stage_pair(L, a, b, R.s, lane, S, &ka);
-  const unsigned long long ida = key_canonical_id(ka, R.d);
+__device__ inline void pair_ties(const BlockBufs& B, int a, int b, const Roi& R, const Metric& met, unsigned int mask,
+                                 int lane, PairStage* S, GroupRes* g4, int ids32, int pass) {
   double target[4];
+  float thr[4];
   unsigned long long red[4];
 #pragma unroll
   for (int g = 0; g < 4; ++g) {
-    target[g] = __longlong_as_double((long long)g4[g].best_bits);
+    const unsigned long long t = seen_bits(&g4[g]);
+    target[g] = __longlong_as_double((long long)t);
+    thr[g] = bits_bound(t, met.ex);
     red[g] = ~0ull;
   }
-  const int c0 = lane & 32 ? 16 : 0;
-  for (int c = c0; c < c0 + 16; ++c) {
-    const VRow& B = S->row[c];
-    const double d = dist2_exact(A.x, B.x);
-    const unsigned long long x = A.code ^ B.code;
+  int n_a, n_b;
+  if (!stage_rows(load_pair(B, a, b, lane), R, met, mask, thr, lane, S, true, n_a, n_b)) return;
+  const int sh = n_a > 1 ? 32 - __clz(n_a - 1) : 0;
+  const int i = lane & ((1 << sh) - 1);
+  const VRow A = S->row[32 + i];
+  const unsigned long long ida = key_canonical_id(S->key[32 + i], R.d);
+  for (int c = lane >> sh; c < n_b; c += 64 >> sh) {
+    const VRow& C = S->row[c];
+    const double d = dist2_exact(A.x, C.x);
     const bool t0 = (mask & 1u) && d == target[0];
-    const bool t1 = (mask & 2u) && d == target[1] && (x & kField) == 0ull;
-    const bool t2 = (mask & 4u) && d == target[2] && (x & kField << 21) == 0ull;
-    const bool t3 = (mask & 8u) && d == target[3] && (x & kField << 42) == 0ull;
-    if (t0 | t1 | t2 | t3) {
+    const bool t1 = (mask & 2u) && d == target[1] && A.pk[0] == C.pk[0];
+    const bool t2 = (mask & 4u) && d == target[2] && A.pk[1] == C.pk[1];
+    const bool t3 = (mask & 8u) && d == target[3] && A.pk[2] == C.pk[2];
+    if (i < n_a && (t0 | t1 | t2 | t3)) {
       const unsigned long long idb = key_canonical_id(S->key[c], R.d);
       const unsigned long long lo = min(ida, idb), hi = max(ida, idb);
       const bool hit[4] = {t0, t1, t2, t3};
@@ -238,23 +317,24 @@ __device__ inline void pair_ties(const VertexList& L, int a, int b, const Roi& R
 #pragma unroll
   for (int g = 0; g < 4; ++g) {
     if (!(mask >> g & 1u)) continue;
-    for (int k = 32; k >= 1; k >>= 1) red[g] = min(red[g], (unsigned long long)__shfl_xor(red[g], k, 64));
+    red[g] = lanes_reduce<6>(red[g], [](unsigned long long x, unsigned long long y) { return x < y ? x : y; });
     if (lane == 0 && red[g] != ~0ull) atomicMin(ids32 || pass == 0 ? &g4[g].id_lo : &g4[g].id_hi, red[g]);
   }
 }
 
 // The largest (value, index) key over a wave.
 __device__ inline unsigned long long wave_max_u64(unsigned long long v) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) {
-    const unsigned long long o = __shfl_xor(v, m, 64);
-    v = o > v ? o : v;
-  }
-  return v;
+  return lanes_reduce<6>(v, [](unsigned long long x, unsigned long long y) { return x > y ? x : y; });
 }
 
 __device__ inline unsigned long long bound_key(float f, int i) {
   return f > 0.0f ? (unsigned long long)__float_as_uint(f) << 32 | (unsigned int)i : 0ull;
+}
+
+// The listed block pairs; 0 when the list was too short.
+__device__ inline long long listed_pairs(const BlockBufs& B) {
+  const long long n = (long long)*B.list_n;
+  return n <= B.list_cap ? n : 0;
 }
 
 __device__ inline long long staged_superblocks(const BlockBufs& B) {
@@ -293,21 +373,24 @@ __global__ __launch_bounds__(256) void k_block_boxes(BlockBufs B) {
     if ((lane & (kSuper - 1)) == 0) {
       const long long s = i / kSuper;
       B.sbox[2 * s] = make_float4(lo[0], lo[1], lo[2], hi[0]);
-      B.sbox[2 * s + 1] = make_float4(hi[1], hi[2], __int_as_float(B.sbroi[s]), 0.0f);
+      const int r = B.sbroi[s];
+      const RoiMeta& M = B.meta[r];
+      const int left = (M.nblk + kSuper - 1) / kSuper - (int)(s - M.blk0 / kSuper);
+      B.sbox[2 * s + 1] = make_float4(hi[1], hi[2], __int_as_float(r), __int_as_float(left));
     }
   }
 }
 
-// A lower bound per family and ROI: a workgroup per superblock A.  Its waves
-// share the scan for the superblock with the largest bound per family; wave g
-// then takes family g: the pair of blocks with the largest bound, and its
-// exact maximum (unless the bound shows that it cannot raise the family's).
-__global__ __launch_bounds__(64 * kWaves) void k_block_seed(BlockBufs B) {
-  __shared__ unsigned long long s_best[4];
+// A lower bound per family and ROI: a workgroup per superblock A, a wave per
+// family: the superblock with the largest bound, there the pair of blocks with
+// the largest bound, and its exact maximum (unless a bound shows that it cannot
+// raise the family's).
+__global__ __launch_bounds__(64 * kWaves, 7) void k_block_seed(BlockBufs B) {
   __shared__ PairStage s_pair[kWaves];
+  __shared__ unsigned long long s_best[4][kWaves];
+  static_assert(kWaves == 4, "a wave per family");
   const long long nsb = staged_superblocks(B);
-  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  const VertexList L{B.key, B.t};
+  const int lane = threadIdx.x & 63, g = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   for (long long A = blockIdx.x; A < nsb; A += gridDim.x) {
     const float4 a0 = B.sbox[2 * A], a1 = B.sbox[2 * A + 1];
     const int r = __builtin_amdgcn_readfirstlane(__float_as_int(a1.z));
@@ -315,71 +398,97 @@ __global__ __launch_bounds__(64 * kWaves) void k_block_seed(BlockBufs B) {
     const RoiMeta& M = B.meta[r];
     const Metric m = metric_of(M, B.t != nullptr);
     const Box ba = box_of(a0, a1);
-    const long long s0 = M.blk0 / kSuper;
-    const int ns = (M.nblk + kSuper - 1) / kSuper;
-    unsigned long long key[4] = {0ull, 0ull, 0ull, 0ull};
-    for (int j = tid; j < ns; j += 64 * kWaves) {
-      const float4 b0 = B.sbox[2 * (s0 + j)], b1 = B.sbox[2 * (s0 + j) + 1];
-      float f[4];
-      far_bounds(ba, box_of(b0, b1), m, f);
-#pragma unroll
-      for (int g = 0; g < 4; ++g) key[g] = max(key[g], bound_key(f[g], j));
-    }
-    __syncthreads();
-    if (tid < 4) s_best[tid] = 0ull;
-    __syncthreads();
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const unsigned long long k = wave_max_u64(key[g]);
-      if (lane == 0 && k) atomicMax(&s_best[g], k);
-    }
-    __syncthreads();
-    const int g = wid;
+    const long long blk0 = M.blk0, s0 = blk0 / kSuper;
+    const int nblk = M.nblk, ns = (nblk + kSuper - 1) / kSuper;
+    // 16 x 16 block pairs later: lane holds block lane % 16 of A
+    const int ia = (int)(A - s0) * kSuper + (lane & 15), ic = min(ia, nblk - 1);
+    const float4 p0 = B.lbox[2 * (blk0 + ic)], p1 = B.lbox[2 * (blk0 + ic) + 1];
     GroupRes* G = B.gres + 4ll * r + g;
-    const unsigned long long sk = s_best[g];
-    if (sk == 0ull) continue;
-    if (__uint_as_float((unsigned int)(sk >> 32)) < seen_max(G, m.ex)) continue;
-    // 16 x 16 block pairs: lane holds block lane % 16 of A, and blocks lane / 16 + 4 q of B
-    const int ia = (int)(A - s0) * kSuper + (lane & 15);
-    const int jb = (int)(sk & 0xffffffffull) * kSuper + (lane >> 4);
-    unsigned long long bk = 0ull;
-    if (ia < M.nblk) {
-      const float4 p0 = B.lbox[2 * (M.blk0 + ia)], p1 = B.lbox[2 * (M.blk0 + ia) + 1];
-      const Box pa = box_of(p0, p1);
+    const unsigned long long seen = seen_bits(G);
+    unsigned long long key = 0ull;
+    if (ns <= 64) {
+      if (lane < ns) {
+        const float4 b0 = B.sbox[2 * (s0 + lane)], b1 = B.sbox[2 * (s0 + lane) + 1];
+        key = bound_key(far_bound(ba, box_of(b0, b1), m, g), lane);
+      }
+      key = wave_max_u64(key);
+    } else {
+      // the waves share the scan, each for all families (four times the reads
+      // of a large ROI's superblocks would be bound by the L2)
+      unsigned long long k4[4] = {0ull, 0ull, 0ull, 0ull};
+      for (int j = threadIdx.x; j < ns; j += 64 * kWaves) {
+        const float4 b0 = B.sbox[2 * (s0 + j)], b1 = B.sbox[2 * (s0 + j) + 1];
+        float f[4];
+        far_bounds(ba, box_of(b0, b1), m, f);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const unsigned long long k = bound_key(f[q], j);
+          k4[q] = k > k4[q] ? k : k4[q];
+        }
+      }
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const int j = min(jb + 4 * q, M.nblk - 1);
-        const float4 c0 = B.lbox[2 * (M.blk0 + j)], c1 = B.lbox[2 * (M.blk0 + j) + 1];
-        float f[4];
-        far_bounds(pa, box_of(c0, c1), m, f);
-        const float fg = g == 0 ? f[0] : (g == 1 ? f[1] : (g == 2 ? f[2] : f[3]));
-        bk = max(bk, bound_key(fg, (lane & 15) << 8 | (j & (kSuper - 1))));
+        k4[q] = wave_max_u64(k4[q]);
+        if (lane == 0) s_best[q][g] = k4[q];
       }
+      __syncthreads();
+#pragma unroll
+      for (int q = 0; q < kWaves; ++q) key = s_best[g][q] > key ? s_best[g][q] : key;
+      __syncthreads();
+    }
+    const float bar = bits_bound(seen, m.ex);
+    if (key == 0ull || __uint_as_float((unsigned int)(key >> 32)) < bar) continue;
+    // ... and blocks lane / 16 + 4 q of that superblock
+    const int jb = (int)(key & 0xffffffffull) * kSuper + (lane >> 4);
+    const Box pa = box_of(p0, p1);
+    unsigned long long bk = 0ull;
+    int phb[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int j = min(jb + 4 * q, nblk - 1);
+      const float4 c0 = B.lbox[2 * (blk0 + j)], c1 = B.lbox[2 * (blk0 + j) + 1];
+      phb[q] = __float_as_int(c1.z);
+      const unsigned long long k =
+          ia < nblk && jb + 4 * q < nblk
+              ? bound_key(far_bound(pa, box_of(c0, c1), m, g), (lane & 15) << 8 | q << 4 | lane >> 4)
+              : 0ull;
+      bk = k > bk ? k : bk;
     }
     bk = wave_max_u64(bk);
-    if (bk == 0ull || __uint_as_float((unsigned int)(bk >> 32)) < seen_max(G, m.ex)) continue;
-    const long long la = M.blk0 + (A - s0) * kSuper + (int)(bk >> 8 & 15ull);
-    const long long lb = M.blk0 + (long long)(sk & 0xffffffffull) * kSuper + (int)(bk & 15ull);
+    if (bk == 0ull || __uint_as_float((unsigned int)(bk >> 32)) < bar) continue;
+    const int wi = __builtin_amdgcn_readfirstlane((int)(bk >> 8 & 15ull));
+    const int wq = __builtin_amdgcn_readfirstlane((int)(bk >> 4 & 15ull));
+    const int wl = __builtin_amdgcn_readfirstlane((int)(bk & 15ull));
+    const int pha = __builtin_amdgcn_readlane(__float_as_int(p1.z), wi);
+    const int sel = wq == 0 ? phb[0] : (wq == 1 ? phb[1] : (wq == 2 ? phb[2] : phb[3]));
     double mx[4];
-    pair_max(L, __builtin_amdgcn_readfirstlane(B.lphys[la]), __builtin_amdgcn_readfirstlane(B.lphys[lb]), R, 1u << g,
-             lane, &s_pair[wid], mx);
+    const float thr[4] = {bar, bar, bar, bar};
+    pair_max(load_pair(B, pha, __builtin_amdgcn_readlane(sel, 16 * wl), lane), R, m, 1u << g, thr, lane, &s_pair[g],
+             mx);
     const double v = g == 0 ? mx[0] : (g == 1 ? mx[1] : (g == 2 ? mx[2] : mx[3]));
-    if (lane == 0 && v > 0.0) raise_max(G, v);
+    if (lane == 0 && v > 0.0) raise_max(G, v, seen);
   }
 }
 
 namespace {
 
-// What a wave does with the block pairs of k_block_pairs' enumeration: list
-// them (or, past the list's end, evaluate them at once), or, in the pass for
-// the ties of a call whose list was too short, take their ties.
-constexpr int kModeList = 0, kModeTies = 1;
+// The bound and the families of a list entry: the FP32 bound rounded up to make
+// room for the families' bits.
+__device__ inline int entry_word(float bound, unsigned int mask) {
+  return (int)(((__float_as_uint(bound) & ~15u) + 16u) | mask);
+}
+__device__ inline float entry_bound(int w) { return __uint_as_float((unsigned int)w & ~15u); }
+
+// What a wave does with the block pairs it finds: list them, or, when the list
+// was too short, evaluate them at once, and later take their ties.
+constexpr int kModeList = 0, kModeEval = 1, kModeTies = 2;
 
 constexpr int kStageItems = 320;  // block pairs a wave collects before it appends them with one atomic
 
-// Appends a wave's collected block pairs to the list; those past its end are
-// evaluated here.
-__device__ inline void append_pairs(const BlockBufs& B, int lane, const int4* buf, int n, PairStage* S) {
+// Appends a wave's collected block pairs to the list.  Those past its end are
+// dropped: a list that was too short (*list_n counts them all) is not used,
+// k_block_again then goes through the block pairs once more.
+__device__ inline void append_pairs(const BlockBufs& B, int lane, const int4* buf, int n) {
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
   unsigned long long got = 0ull;
@@ -387,108 +496,133 @@ __device__ inline void append_pairs(const BlockBufs& B, int lane, const int4* bu
   const long long first = (long long)__shfl(got, 0, 64);
   for (int e = lane; e < n; e += 64)
     if (first + e < B.list_cap) B.list[first + e] = buf[e];
-  const VertexList L{B.key, B.t};
-  for (int e = (int)max(0ll, min((long long)n, B.list_cap - first)); e < n; ++e) {
-    const int4 E = buf[e];
-    double mx[4];
-    const unsigned int mask = (unsigned int)E.w & 15u;
-    pair_max(L, E.x, E.y, B.rois[E.z], mask, lane, S, mx);
-    if (lane == 0)
-      for (int g = 0; g < 4; ++g)
-        if ((mask >> g & 1u) && mx[g] > 0.0) raise_max(&B.gres[4ll * E.z + g], mx[g]);
-  }
   __builtin_amdgcn_wave_barrier();
 }
 
-// Superblock A of ROI r against the superblocks A + 64 (split + nsplit i) + lane.
+// Partners of a superblock that a wave tests at once.
+constexpr int kPartners = 16;
+
+// Superblock A against every nsplit-th group of four of its ROI's superblocks
+// from A on (the far partners of a superblock are neighbours: dealt out in turn
+// they are shared by its waves).
 template <int MODE>
 __device__ inline void enumerate_pairs(const BlockBufs& B, long long A, int split, int nsplit, int lane, int4* buf,
                                        int& n_buf, PairStage* S, int ids32, int pass) {
   const float4 a0 = B.sbox[2 * A], a1 = B.sbox[2 * A + 1];
+  const int left = __builtin_amdgcn_readfirstlane(__float_as_int(a1.w));  // the ROI's superblocks from A on
+  if (4 * split >= left) return;
   const int r = __builtin_amdgcn_readfirstlane(__float_as_int(a1.z));
   const Roi& R = B.rois[r];
   const RoiMeta& M = B.meta[r];
   const Metric m = metric_of(M, B.t != nullptr);
-  const VertexList L{B.key, B.t};
   GroupRes* G = B.gres + 4ll * r;
   const long long blk0 = M.blk0;
   const int nblk = M.nblk;
-  const long long s0 = blk0 / kSuper;
-  const int ns = (nblk + kSuper - 1) / kSuper, ia = (int)(A - s0);
-  if (ia + 64 * split >= ns) return;
+  const int ia = (int)(A - blk0 / kSuper);
+  unsigned long long tb[4];
   float thr[4];
+  auto read_seen = [&]() {
 #pragma unroll
-  for (int g = 0; g < 4; ++g) thr[g] = seen_max(&G[g], m.ex);
+    for (int g = 0; g < 4; ++g) {
+      tb[g] = seen_bits(&G[g]);
+      thr[g] = bits_bound(tb[g], m.ex);
+    }
+  };
+  read_seen();
   const Box ba = box_of(a0, a1);
-  // lane holds block lane % 16 of A
-  const int i = ia * kSuper + (lane & 15);
-  const int ic = min(i, nblk - 1);
-  const float4 p0 = B.lbox[2 * (blk0 + ic)], p1 = B.lbox[2 * (blk0 + ic) + 1];
-  const Box pa = box_of(p0, p1);
-  const int pha = __float_as_int(p1.z);
-  for (int j0 = ia + 64 * split; j0 < ns; j0 += 64 * nsplit) {
-    const int j = j0 + lane;
+  // lane holds blocks lane / 16 + 4 q of A, and in turn block lane % 16 of each partner
+  Box pa[4];
+  int pha[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int i = min(ia * kSuper + (lane >> 4) + 4 * q, nblk - 1);
+    const float4 p0 = B.lbox[2 * (blk0 + i)], p1 = B.lbox[2 * (blk0 + i) + 1];
+    pa[q] = box_of(p0, p1);
+    pha[q] = __float_as_int(p1.z);
+  }
+  // partner l of the wave's group of kPartners that starts at superblock A + j0
+  auto partner = [&](int j0, int l) { return j0 + 4 * nsplit * (l >> 2) + (l & 3); };
+  for (int j0 = 4 * split; j0 < left; j0 += kPartners * nsplit) {
+    const int j = partner(j0, lane & (kPartners - 1));
     unsigned int um = 0u;
-    if (j < ns) {
-      const float4 b0 = B.sbox[2 * (s0 + j)], b1 = B.sbox[2 * (s0 + j) + 1];
+    if (j < left) {
+      const float4 b0 = B.sbox[2 * (A + j)], b1 = B.sbox[2 * (A + j) + 1];
       float f[4];
       far_bounds(ba, box_of(b0, b1), m, f);
 #pragma unroll
       for (int g = 0; g < 4; ++g) um |= (unsigned int)(f[g] >= thr[g]) << g;
     }
-    unsigned long long todo = __ballot(um != 0u);
+    unsigned int todo = (unsigned int)(__ballot(um != 0u) & ((1ull << kPartners) - 1ull));
+    int src = todo ? __ffs((int)todo) - 1 : 0;
+    float4 c0, c1;
+    {
+      const int jc = min((ia + partner(j0, src)) * kSuper + (lane & 15), nblk - 1);
+      c0 = B.lbox[2 * (blk0 + jc)];
+      c1 = B.lbox[2 * (blk0 + jc) + 1];
+    }
     while (todo) {
-      const int src = __ffsll((long long)todo) - 1;
-      todo &= todo - 1ull;
-      const int ju = j0 + src;
-      const unsigned int unit = (unsigned int)__shfl((int)um, src, 64);
+      todo &= todo - 1u;
+      const unsigned int unit = (unsigned int)__builtin_amdgcn_readlane((int)um, src);
+      if (MODE == kModeEval) read_seen();  // once per partner: it only rises
+      const Box pb = box_of(c0, c1);
+      const int phb = __float_as_int(c1.z);
+      const int jj = (ia + partner(j0, src)) * kSuper + (lane & 15);
+      if (todo) {  // the next partner's boxes, in flight while this one's are tested
+        src = __ffs((int)todo) - 1;
+        const int jc = min((ia + partner(j0, src)) * kSuper + (lane & 15), nblk - 1);
+        c0 = B.lbox[2 * (blk0 + jc)];
+        c1 = B.lbox[2 * (blk0 + jc) + 1];
+      }
       unsigned int pm[4];
       float ff[4];
-      int phb[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const int jj = ju * kSuper + (lane >> 4) + 4 * q;
-        const int jc = min(jj, nblk - 1);
-        const float4 c0 = B.lbox[2 * (blk0 + jc)], c1 = B.lbox[2 * (blk0 + jc) + 1];
+        const int i = ia * kSuper + (lane >> 4) + 4 * q;
         float f[4];
-        far_bounds(pa, box_of(c0, c1), m, f);
+        far_bounds(pa[q], pb, m, f);
         pm[q] = 0u;
         ff[q] = 0.0f;
-        phb[q] = __float_as_int(c1.z);
-        if (i < nblk && jj < nblk && jj >= i)
 #pragma unroll
-          for (int g = 0; g < 4; ++g)
-            if ((unit >> g & 1u) && f[g] >= thr[g]) {
-              pm[q] |= 1u << g;
-              ff[q] = fmaxf(ff[q], f[g]);
-            }
+        for (int g = 0; g < 4; ++g)
+          if ((unit >> g & 1u) && f[g] >= thr[g]) {
+            pm[q] |= 1u << g;
+            ff[q] = fmaxf(ff[q], f[g]);
+          }
+        if (i >= nblk || jj >= nblk || jj < i) pm[q] = 0u;
+      }
+      unsigned long long em[4];
+      int k = 0;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        em[q] = __ballot(pm[q] != 0u);
+        k += __popcll(em[q]);
+      }
+      if (k == 0) continue;
+      if (MODE == kModeList && n_buf + k > kStageItems) {
+        append_pairs(B, lane, buf, n_buf);
+        n_buf = 0;
       }
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const unsigned long long em = __ballot(pm[q] != 0u);
-        if (!em) continue;
-        const int k = __popcll(em);
         if (MODE == kModeList) {
-          if (n_buf + k > kStageItems) {
-            // append the collected pairs with one atomic
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            append_pairs(B, lane, buf, n_buf, S);
-            n_buf = 0;
-          }
-          if (pm[q]) {
-            // the largest bound of the listed families, rounded up to make room for their bits
-            const unsigned int fb = (__float_as_uint(ff[q]) & ~15u) + 16u;
-            buf[n_buf + __popcll(em & ((1ull << lane) - 1ull))] = make_int4(pha, phb[q], r, (int)(fb | pm[q]));
-          }
-          n_buf += k;
-        } else {
-          unsigned long long t = em;
-          while (t) {
-            const int s = __ffsll((long long)t) - 1;
-            t &= t - 1ull;
-            pair_ties(L, __shfl(pha, s, 64), __shfl(phb[q], s, 64), R, (unsigned int)__shfl((int)pm[q], s, 64), lane,
-                      S, G, ids32, pass);
+          if (pm[q])  // with the largest bound of its families
+            buf[n_buf + __popcll(em[q] & ((1ull << lane) - 1ull))] =
+                make_int4(pha[q], phb, r, entry_word(ff[q], pm[q]));
+          n_buf += __popcll(em[q]);
+          continue;
+        }
+        for (unsigned long long t = em[q]; t; t &= t - 1ull) {
+          const int s = __ffsll((long long)t) - 1;
+          const int a = __builtin_amdgcn_readlane(pha[q], s), b = __builtin_amdgcn_readlane(phb, s);
+          const unsigned int mask = (unsigned int)__builtin_amdgcn_readlane((int)pm[q], s);
+          if (MODE == kModeTies) {
+            pair_ties(B, a, b, R, m, mask, lane, S, G, ids32, pass);
+          } else {
+            double mx[4];
+            pair_max(load_pair(B, a, b, lane), R, m, mask, thr, lane, S, mx);
+            if (lane == 0)
+              for (int g = 0; g < 4; ++g)
+                if (mx[g] > 0.0) raise_max(&G[g], mx[g], tb[g]);
           }
         }
       }
@@ -500,111 +634,142 @@ __device__ inline void enumerate_pairs(const BlockBufs& B, long long A, int spli
 
 // Lists the block pairs whose bound reaches the lower bound of some family:
 // a wave per (superblock, 1 / nsplit of its partners).
-__global__ __launch_bounds__(64 * kWaves) void k_block_pairs(BlockBufs B, int nsplit) {
+__global__ __launch_bounds__(64 * kWaves, 4) void k_block_pairs(BlockBufs B, int nsplit) {
   __shared__ int4 s_buf[kWaves][kStageItems];
-  __shared__ PairStage s_pair[kWaves];
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   const long long n = staged_superblocks(B) * nsplit;
   int n_buf = 0;
   int4* buf = s_buf[wid];
   for (long long w = (long long)blockIdx.x * kWaves + wid; w < n; w += (long long)gridDim.x * kWaves)
-    enumerate_pairs<kModeList>(B, w / nsplit, (int)(w % nsplit), nsplit, lane, buf, n_buf, &s_pair[wid], 0, 0);
-  if (n_buf) append_pairs(B, lane, buf, n_buf, &s_pair[wid]);
+    enumerate_pairs<kModeList>(B, w / nsplit, (int)(w % nsplit), nsplit, lane, buf, n_buf, nullptr, 0, 0);
+  if (n_buf) append_pairs(B, lane, buf, n_buf);
 }
 
 // The exact maxima of the listed block pairs, a wave each.  An entry keeps the
-// families whose maximum it may hold (its own is not below the one seen).
-__global__ __launch_bounds__(64 * kWaves) void k_block_eval(BlockBufs B) {
+// families whose maximum it may hold (its own is not below the one seen), and
+// its own maximum as the new bound (none if it keeps several).
+// A wave takes up to 8 neighbouring entries at a time: it reads the maxima seen
+// so far once for those of one ROI (the waves of a large ROI all read the same
+// line), and loads the next pair's vertices while it evaluates one.
+__global__ __launch_bounds__(64 * kWaves, 7) void k_block_eval(BlockBufs B) {
   __shared__ PairStage s_pair[kWaves];
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  const VertexList L{B.key, B.t};
-  const long long n = min((long long)*B.list_n, B.list_cap);
-  for (long long e = (long long)blockIdx.x * kWaves + wid; e < n; e += (long long)gridDim.x * kWaves) {
-    const int4 E = B.list[e];
-    const int r = __builtin_amdgcn_readfirstlane(E.z);
-    GroupRes* G = B.gres + 4ll * r;
-    unsigned int mask = (unsigned int)E.w & 15u;
-    const float f = __uint_as_float((unsigned int)E.w & ~15u);
-    const int ex = B.meta[r].ex;
+  const long long n = listed_pairs(B);
+  const long long nwaves = (long long)gridDim.x * kWaves;
+  const int take = (int)max(1ll, min(8ll, n / nwaves));
+  for (long long e0 = ((long long)blockIdx.x * kWaves + wid) * take; e0 < n; e0 += nwaves * take) {
+    const int cnt = (int)min((long long)take, n - e0);
+    int4 E = make_int4(0, 0, 0, 0);
+    if (lane < cnt) E = B.list[e0 + lane];
+    PairLoad K = load_pair(B, __builtin_amdgcn_readlane(E.x, 0), __builtin_amdgcn_readlane(E.y, 0), lane);
+    int r = -1, word = 0;
+    unsigned long long sbits = 0ull;
+    float seen = 0.0f, thr[4];
+    Metric met;
+    for (int k = 0; k < cnt; ++k) {
+      const int rk = __builtin_amdgcn_readlane(E.z, k), w = __builtin_amdgcn_readlane(E.w, k);
+      const PairLoad K0 = K;
+      if (k + 1 < cnt)
+        K = load_pair(B, __builtin_amdgcn_readlane(E.x, k + 1), __builtin_amdgcn_readlane(E.y, k + 1), lane);
+      GroupRes* G = B.gres + 4ll * rk;
+      if (rk != r) {
+        r = rk;
+        met = metric_of(B.meta[r], B.t != nullptr);
+        sbits = seen_bits(&G[lane & 3]);  // lane g < 4 sees to family g
+        seen = bits_bound(sbits, met.ex);
 #pragma unroll
-    for (int g = 0; g < 4; ++g)
-      if (f < seen_max(&G[g], ex)) mask &= ~(1u << g);
-    mask = (unsigned int)__builtin_amdgcn_readfirstlane((int)mask);
-    unsigned int keep = 0u;
-    if (mask) {
-      double mx[4];
-      pair_max(L, __builtin_amdgcn_readfirstlane(E.x), __builtin_amdgcn_readfirstlane(E.y), B.rois[r], mask, lane,
-               &s_pair[wid], mx);
-      if (lane < 4) {
-        const double v = lane == 0 ? mx[0] : (lane == 1 ? mx[1] : (lane == 2 ? mx[2] : mx[3]));
-        if ((mask >> lane & 1u) && v > 0.0) {
-          const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-          unsigned long long seen = __hip_atomic_load(&G[lane].best_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          if (b > seen) seen = atomicMax(&G[lane].best_bits, b);
-          keep = b >= seen ? 1u << lane : 0u;
-        }
+        for (int g = 0; g < 4; ++g) thr[g] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(seen), g));
       }
-      keep |= __shfl_xor(keep, 1, 64);
-      keep |= __shfl_xor(keep, 2, 64);
+      const bool on = lane < 4 && ((unsigned int)w >> (lane & 3) & 1u) && !(entry_bound(w) < seen);
+      const unsigned int mask = (unsigned int)(__ballot(on) & 15ull);
+      if (!mask) continue;
+      double mx[4];
+      pair_max(K0, B.rois[r], met, mask, thr, lane, &s_pair[wid], mx);
+      const double v = (lane & 2) ? ((lane & 1) ? mx[3] : mx[2]) : ((lane & 1) ? mx[1] : mx[0]);
+      bool hold = false;
+      if (on && v > 0.0) hold = raise_max(&G[lane], v, sbits);
+      const unsigned int keep = (unsigned int)(__ballot(hold) & 15ull);
+      if (!keep) continue;
+      int wk = entry_word(3.0e38f, keep);
+      if (!(keep & (keep - 1u))) wk = entry_word((float)ldexp(__shfl(v, __ffs((int)keep) - 1, 64), -2 * met.ex), keep);
+      if (lane == k) word = wk;
     }
-    if (lane == 0) B.list[e].w = (int)keep;
+    if (lane < cnt) B.list[e0 + lane].w = word;
   }
 }
 
-// The smallest id pair at each family's maximum, over the entries that may
-// hold it; a call whose list was too short enumerates its block pairs again.
-__global__ __launch_bounds__(64 * kWaves) void k_block_ties(BlockBufs B, int nsplit, int ids32, int pass) {
+// The smallest id pair at each family's maximum, over the entries that may hold it.
+__global__ __launch_bounds__(64 * kWaves) void k_block_ties(BlockBufs B, int ids32, int pass) {
   __shared__ PairStage s_pair[kWaves];
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  const VertexList L{B.key, B.t};
-  const long long n = (long long)*B.list_n;
+  const long long n = listed_pairs(B);
   const long long wave = (long long)blockIdx.x * kWaves + wid, nwaves = (long long)gridDim.x * kWaves;
-  if (n > B.list_cap) {
-    int n_buf = 0;
-    const long long nu = staged_superblocks(B) * nsplit;
-    for (long long w = wave; w < nu; w += nwaves)
-      enumerate_pairs<kModeTies>(B, w / nsplit, (int)(w % nsplit), nsplit, lane, nullptr, n_buf, &s_pair[wid], ids32,
-                                 pass);
-    return;
-  }
-  // 64 entries at a time, a lane each; the few that are left are visited by the wave
-  for (long long e0 = wave * 64; e0 < n; e0 += nwaves * 64) {
-    const long long e = e0 + lane;
+  // 64 entries at a time, a lane each, 4 neighbours to a cache line and the
+  // lines dealt to the waves in turn (the entries of a shape with flat faces, all
+  // ties, are neighbours); those left are visited by the wave
+  for (long long it = 0; 4 * (16 * it * nwaves + wave) < n; ++it) {
+    const long long e = 4 * ((16 * it + (lane >> 2)) * nwaves + wave) + (lane & 3);
     int4 E = make_int4(0, 0, 0, 0);
     if (e < n) E = B.list[e];
     unsigned int mask = (unsigned int)E.w & 15u;
+    if (mask) {
+      const int ex = B.meta[E.z].ex;
+      for (int g = 0; g < 4; ++g)
+        if ((mask >> g & 1u) && entry_bound(E.w) < seen_max(&B.gres[4ll * E.z + g], ex)) mask &= ~(1u << g);
+    }
     unsigned long long todo = __ballot(mask != 0u);
     while (todo) {
       const int s = __ffsll((long long)todo) - 1;
       todo &= todo - 1ull;
       const int r = __builtin_amdgcn_readfirstlane(__shfl(E.z, s, 64));
-      pair_ties(L, __builtin_amdgcn_readfirstlane(__shfl(E.x, s, 64)),
+      pair_ties(B, __builtin_amdgcn_readfirstlane(__shfl(E.x, s, 64)),
                 __builtin_amdgcn_readfirstlane(__shfl(E.y, s, 64)), B.rois[r],
-                (unsigned int)__builtin_amdgcn_readfirstlane(__shfl((int)mask, s, 64)), lane, &s_pair[wid],
+                metric_of(B.meta[r], B.t != nullptr), (unsigned int)__builtin_amdgcn_readfirstlane(__shfl((int)mask, s, 64)), lane, &s_pair[wid],
                 B.gres + 4ll * r, ids32, pass);
     }
   }
 }
 
-hipError_t launch_blocks(const BlockBufs& B, hipStream_t st, hipEvent_t* ev) {
+// A list that was too short: the block pairs once more, evaluated where they are
+// found (kModeEval), and later their ties (kModeTies).
+template <int MODE>
+__global__ __launch_bounds__(64 * kWaves) void k_block_again(BlockBufs B, int nsplit, int ids32, int pass) {
+  __shared__ PairStage s_pair[kWaves];
+  if ((long long)*B.list_n <= B.list_cap) return;
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  const long long n = staged_superblocks(B) * nsplit;
+  int n_buf = 0;
+  for (long long w = (long long)blockIdx.x * kWaves + wid; w < n; w += (long long)gridDim.x * kWaves)
+    enumerate_pairs<MODE>(B, w / nsplit, (int)(w % nsplit), nsplit, lane, nullptr, n_buf, &s_pair[wid], ids32, pass);
+}
+
+hipError_t launch_blocks(const BlockBufs& B, bool again, hipStream_t st, hipEvent_t* ev) {
   // grids that fill the chip, or fewer workgroups where the capacity bounds the work
   auto grid = [&](long long work, long long cap) {
     return dim3((unsigned)std::max(1ll, std::min(work, cap * B.cu_count)));
   };
   hipError_t e;
   const long long nsb = B.lblk_cap / kSuper;
-  // one ROI: many partners per superblock, split over waves; a batch has superblocks enough
-  const int nsplit = B.n_rois == 1 ? 8 : 2;
+  // a few ROIs may have thousands of superblocks each, many have tens
+  const int nsplit = B.n_rois <= 16 ? 16 : 2, nsplit_again = B.n_rois <= 16 ? 128 : 16;
   hipLaunchKernelGGL(k_block_boxes, grid((B.lblk_cap + 255) / 256, 8), dim3(256), 0, st, B);
   if (ev && (e = hipEventRecord(ev[0], st))) return e;
   hipLaunchKernelGGL(k_block_seed, grid(nsb, 16), dim3(64 * kWaves), 0, st, B);
-  hipLaunchKernelGGL(k_block_pairs, grid((nsb * nsplit + kWaves - 1) / kWaves, 8), dim3(64 * kWaves), 0, st, B, nsplit);
+  hipLaunchKernelGGL(k_block_pairs, grid((nsb * nsplit + kWaves - 1) / kWaves, 16), dim3(64 * kWaves), 0, st, B,
+                     nsplit);
   if (ev && (e = hipEventRecord(ev[1], st))) return e;
   hipLaunchKernelGGL(k_block_eval, grid((B.list_cap + kWaves - 1) / kWaves, 8), dim3(64 * kWaves), 0, st, B);
+  if (again)
+    hipLaunchKernelGGL(k_block_again<kModeEval>, grid((nsb * nsplit_again + kWaves - 1) / kWaves, 16),
+                       dim3(64 * kWaves), 0, st, B, nsplit_again, 0, 0);
   if (ev && (e = hipEventRecord(ev[2], st))) return e;
-  for (int pass = 0; pass < (B.ids32 ? 1 : 2); ++pass)
-    hipLaunchKernelGGL(k_block_ties, grid((B.list_cap + 255) / 256, 4), dim3(64 * kWaves), 0, st, B, nsplit,
-                       B.ids32 ? 1 : 0, pass);
+  for (int pass = 0; pass < (B.ids32 ? 1 : 2); ++pass) {
+    hipLaunchKernelGGL(k_block_ties, grid((B.list_cap + 255) / 256, 4), dim3(64 * kWaves), 0, st, B, B.ids32 ? 1 : 0,
+                       pass);
+    if (again)
+      hipLaunchKernelGGL(k_block_again<kModeTies>, grid((nsb * nsplit_again + kWaves - 1) / kWaves, 16),
+                         dim3(64 * kWaves), 0, st, B, nsplit_again, B.ids32 ? 1 : 0, pass);
+  }
   return hipGetLastError();
 }
 

@@ -26,6 +26,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstring>
 
 #define MC_TABLE_QUAL __constant__ const
 #include "mc_table.h"
@@ -415,13 +416,6 @@ __device__ inline double case_area_of(const Roi& R, int c) {
   return a;
 }
 
-__global__ __launch_bounds__(256) void k_case_area(const Roi* __restrict__ rois, int n_rois,
-                                                   double* __restrict__ case_area) {
-  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-  case_area[i] = case_area_of(rois[blockIdx.x], (int)threadIdx.x);
-  case_hist(case_area, n_rois)[i] = 0ull;
-}
-
 // The small-mesh path's first launch (one workgroup): the ROI record, the
 // cleared staged-row count and pair-kernel accumulators, and (binary masks)
 // the per-case areas and cleared case counts.
@@ -697,26 +691,23 @@ __global__ __launch_bounds__(kBrickThreads, DT == 0 ? 6 : 4) void k_mesh_pass(co
       }
       if (pbox) {
         // the block's box over its half wave, in half voxels: exact for binary
-        // masks, widened by the rounding of the soft coordinate
+        // masks, widened by the rounding of the soft coordinate (a vertex that
+        // NaN voxels leave without a position is in no box)
         float lo[3], hi[3];
         const int u[3] = {u0, u1, u2};
 #pragma unroll
         for (int q = 0; q < 3; ++q) {
           if (DT == 0) {
-            lo[q] = hi[q] = (float)(2 * u[q] + (a == q));
+            const int c = 2 * u[q] + (a == q);
+            lo[q] = (float)lanes_min_i32<5>(c);
+            hi[q] = (float)lanes_max_i32<5>(c);
           } else {
             const float c = (float)(2.0 * ((double)u[q] + (a == q ? tt : 0.0))), w = fabsf(c) * 1.1920928955078125e-07f;
-            lo[q] = c - w;
-            hi[q] = c + w;
+            const bool ok = tt == tt;
+            lo[q] = order_float(lanes_min_i32<5>(float_order(ok ? c - w : 3.0e38f)));
+            hi[q] = order_float(lanes_max_i32<5>(float_order(ok ? c + w : -3.0e38f)));
           }
         }
-#pragma unroll
-        for (int m = 1; m < kSegAlign; m <<= 1)
-#pragma unroll
-          for (int q = 0; q < 3; ++q) {
-            lo[q] = fminf(lo[q], __shfl_xor(lo[q], m, 64));
-            hi[q] = fmaxf(hi[q], __shfl_xor(hi[q], m, 64));
-          }
         if ((i & (kSegAlign - 1)) == 0 && row < tmp_cap) {
           float4* bx = pbox + 2 * (row / kSegAlign);
           bx[0] = make_float4(lo[0], lo[1], lo[2], hi[0]);
@@ -868,14 +859,14 @@ __device__ inline long long block_excl_scan_i64(long long v, long long* s_w, lon
 // bricks, then a halving tree.  The bricks' first rows within the ROI go to
 // brick_voff (the general pipeline), or, with X.lphys set, the ROI's staged
 // blocks to the block list at a range that starts on a superblock.
-// totals: [0] rows of all ROIs, [1] largest V, [9] blocks (block list only;
-// the general pipeline's k_roi_rows writes the first two).
+// totals: [0] rows of all ROIs, [9] blocks (with the block list; else
+// k_roi_rows writes the rows).
 template <int NT>
 __global__ __launch_bounds__(NT) void k_mesh_totals(const Roi* __restrict__ rois, int n_rois, int dtype,
                                                     const double* __restrict__ case_area,
-                                                    const BrickPart* __restrict__ part,
-                                                    long long* __restrict__ brick_voff, RoiMeta* __restrict__ meta,
-                                                    long long* __restrict__ totals, int moments, BlockIndex X) {
+                                                    const BrickPart* __restrict__ part, long long* brick_voff,
+                                                    RoiMeta* __restrict__ meta, long long* __restrict__ totals,
+                                                    int moments, BlockIndex X) {
   constexpr int Q = 1024 / NT, NW = NT / 64;
   __shared__ long long s_w[NW];
   __shared__ long long s_l[3][NW];
@@ -883,6 +874,9 @@ __global__ __launch_bounds__(NT) void k_mesh_totals(const Roi* __restrict__ rois
   __shared__ double s_d[2][512];
   __shared__ __int128 s_S[10];
   __shared__ long long s_base;
+  // first block, staged block and end of the ROI's first kBricks bricks
+  constexpr int kBricks = 2 * NT;
+  __shared__ int s_first[kBricks + 1], s_ph[kBricks];
   const int r = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const long long b0 = rois[r].brick_begin, b1 = rois[r].brick_end;
   const long long n = b1 - b0;
@@ -923,9 +917,10 @@ __global__ __launch_bounds__(NT) void k_mesh_totals(const Roi* __restrict__ rois
   const bool fits = X.lphys == nullptr || totals[8] <= X.rows_cap;
   if (X.lphys) {
     const long long nsb = (total + kSuper - 1) / kSuper;
-    if (tid == 0)
-      s_base = fits && total ? (long long)atomicAdd((unsigned long long*)&totals[9], (unsigned long long)(nsb * kSuper))
-                             : 0;
+    if (tid == 0 && fits && total)
+      s_base = (long long)atomicAdd((unsigned long long*)&totals[9], (unsigned long long)(nsb * kSuper));
+    else if (tid == 0)
+      s_base = 0;
     __syncthreads();
     if (fits) {
       const long long base = s_base;
@@ -940,17 +935,31 @@ __global__ __launch_bounds__(NT) void k_mesh_totals(const Roi* __restrict__ rois
     long long o = off[q];
     for (long long b = lo; b < hi; ++b) {
       const int pv = part[b].nv;
-      if (X.lphys) {
-        const int nb = (pv + kSegAlign - 1) / kSegAlign;
-        const int ph = (int)(part[b].stage / kSegAlign);
-        if (fits)
-          for (int j = 0; j < nb; ++j) X.lphys[s_base + o + j] = ph + j;
-        o += nb;
-      } else {
+      if (!X.lphys) {
         brick_voff[b] = o;
         o += pv;
+        continue;
       }
+      const int nb = (pv + kSegAlign - 1) / kSegAlign;
+      const int ph = (int)(part[b].stage / kSegAlign);
+      if (b - b0 < kBricks) {
+        s_first[b - b0] = (int)o;
+        s_ph[b - b0] = ph;
+        if (b + 1 == b1 || b - b0 == kBricks - 1) s_first[b - b0 + 1] = (int)(o + nb);
+      } else if (fits) {
+        for (int j = 0; j < nb; ++j) X.lphys[s_base + o + j] = ph + j;
+      }
+      o += nb;
     }
+  }
+  if (X.lphys) {
+    // the bricks' blocks, a wave per brick
+    __syncthreads();
+    if (fits)
+      for (int b = wid; b < (int)min(n, (long long)kBricks); b += NW) {
+        const int f = s_first[b], nb = s_first[b + 1] - f, ph = s_ph[b];
+        for (int j = lane; j < nb; j += 64) X.lphys[s_base + f + j] = ph + j;
+      }
   }
   // integer totals: any order
   nv = wave_sum(nv);
@@ -1040,7 +1049,6 @@ __global__ __launch_bounds__(NT) void k_mesh_totals(const Roi* __restrict__ rois
     meta[r] = M;
     if (X.lphys) {
       atomicAdd((unsigned long long*)&totals[0], (unsigned long long)M.V_pad);
-      atomicMax((unsigned long long*)&totals[1], (unsigned long long)V);
       if (!fits) *X.overflow = 1u;
     }
   }
@@ -1247,33 +1255,39 @@ __global__ __launch_bounds__(256) void k_mesh_rows(const Roi* __restrict__ rois,
   }
 }
 
-// Brick -> ROI map of a batch, so that a brick's workgroup finds its ROI with
-// one load instead of a search of the ROI table.  Workgroup r < n_rois writes r
-// over its ROI's bricks; the others write -1 over the bricks past the last ROI
-// (the grid of a call planned on the device is sized by a bound).
+// Workgroups that write the brick -> ROI map (so that a brick's workgroup finds
+// its ROI with one load instead of a search of the ROI table) past the last ROI:
+// the grid of a call planned on the device is sized by a bound.
 constexpr int kBrickMapTailGroups = 64;
 
-__global__ __launch_bounds__(256) void k_brick_map(const Roi* __restrict__ rois, int n_rois, long long nbricks,
-                                                   int* __restrict__ bmap) {
-  long long b0, b1, step = blockDim.x;
-  int v;
-  if ((int)blockIdx.x < n_rois) {
-    v = (int)blockIdx.x;
-    b0 = rois[v].brick_begin + threadIdx.x;
-    b1 = min(rois[v].brick_end, nbricks);
-  } else {
-    v = -1;
-    b0 = rois[n_rois - 1].brick_end + (long long)(blockIdx.x - n_rois) * blockDim.x + threadIdx.x;
-    b1 = nbricks;
-    step = (long long)kBrickMapTailGroups * blockDim.x;
+// The call's head, one launch: clears its counters and device totals (the
+// staged-row count among them); per ROI the binary masks' case areas and
+// cleared case counts, and the brick -> ROI map.  Workgroup r < n_rois serves
+// ROI r, the others write -1 over the bricks past the last ROI.  one: the
+// ROI record of a call with one ROI, stored here instead of uploaded.
+__global__ __launch_bounds__(256) void k_head(Roi* __restrict__ rois, int n_rois, long long nbricks,
+                                              double* __restrict__ case_area, int* __restrict__ bmap,
+                                              unsigned int* __restrict__ counters, int n_counters,
+                                              long long* __restrict__ totals, Roi one, int use_one) {
+  const int tid = threadIdx.x;
+  if (blockIdx.x == 0) {
+    for (int i = tid; i < n_counters; i += 256) counters[i] = 0u;
+    if (tid < 16) totals[tid] = 0;
+    if (use_one && tid == 0) rois[0] = one;
   }
-  for (long long b = b0; b < b1; b += step) bmap[b] = v;
-}
-
-// Clears the call's counters and device totals (the staged-row count among them).
-__global__ void k_head_clear(unsigned int* __restrict__ counters, int n_counters, long long* __restrict__ totals) {
-  for (int i = threadIdx.x; i < n_counters; i += blockDim.x) counters[i] = 0u;
-  if (threadIdx.x < 16) totals[threadIdx.x] = 0;
+  if ((int)blockIdx.x < n_rois && case_area) {
+    const size_t i = (size_t)blockIdx.x * 256 + tid;
+    case_area[i] = use_one ? case_area_of(one, tid) : case_area_of(rois[blockIdx.x], tid);
+    case_hist(case_area, n_rois)[i] = 0ull;
+  }
+  if (!bmap) return;
+  if ((int)blockIdx.x < n_rois) {
+    const long long b1 = min(rois[blockIdx.x].brick_end, nbricks);
+    for (long long b = rois[blockIdx.x].brick_begin + tid; b < b1; b += 256) bmap[b] = (int)blockIdx.x;
+  } else {
+    const long long b0 = rois[n_rois - 1].brick_end + (long long)(blockIdx.x - n_rois) * 256 + tid;
+    for (long long b = b0; b < nbricks; b += (long long)kBrickMapTailGroups * 256) bmap[b] = -1;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1367,25 +1381,27 @@ __global__ void k_set_roi(Roi R, Roi* __restrict__ out) {
 
 size_t mesh_lds_bytes(int max_G) { return sizeof(uint32_t) * (size_t)(kTZ + 1) * (kBrickThreads + 1 + max_G); }
 
-hipError_t launch_mesh_pass(int dtype, const Roi* rois, int n_rois, long long nbricks, int max_G,
+hipError_t launch_mesh_pass(int dtype, Roi* rois, int n_rois, long long nbricks, int max_G,
                             double* case_area, BrickPart* part, unsigned int* counters, int n_counters,
                             unsigned long long* tmpkey, double* tmpt, long long tmp_cap, long long* totals,
-                            int moments, int* bmap, float4* pbox, hipStream_t st) {
-  hipLaunchKernelGGL(k_head_clear, dim3(1), dim3(1024), 0, st, counters, n_counters, totals);
-  if (nbricks <= 0) return hipGetLastError();
+                            int moments, int* bmap, float4* pbox, const Roi* one, hipStream_t st) {
   if (n_rois < 2) bmap = nullptr;  // one ROI: the search is free
-  if (bmap)
-    hipLaunchKernelGGL(k_brick_map, dim3((unsigned)(n_rois + kBrickMapTailGroups)), dim3(256), 0, st, rois, n_rois,
-                       nbricks, bmap);
+  Roi R;
+  if (one)
+    R = *one;
+  else
+    memset(&R, 0, sizeof(R));
+  hipLaunchKernelGGL(k_head, dim3((unsigned)(n_rois + (bmap ? kBrickMapTailGroups : 0))), dim3(256), 0, st, rois,
+                     n_rois, nbricks, dtype == 0 ? case_area : (double*)nullptr, bmap, counters, n_counters, totals, R,
+                     one ? 1 : 0);
+  if (nbricks <= 0) return hipGetLastError();
   const size_t lds = mesh_lds_bytes(max_G);
-  if (dtype == 0) {
-    hipLaunchKernelGGL(k_case_area, dim3((unsigned)n_rois), dim3(256), 0, st, rois, n_rois, case_area);
-    hipLaunchKernelGGL(k_mesh_pass<0>, dim3((unsigned)nbricks), dim3(kBrickThreads), lds, st, rois, n_rois, nbricks,
-                       case_area, part, tmpkey, tmpt, tmp_cap, totals, moments, (const int*)bmap, pbox);
-  } else {
-    hipLaunchKernelGGL(k_mesh_pass<1>, dim3((unsigned)nbricks), dim3(kBrickThreads), lds, st, rois, n_rois, nbricks,
-                       case_area, part, tmpkey, tmpt, tmp_cap, totals, moments, (const int*)bmap, pbox);
-  }
+  if (dtype == 0)
+    hipLaunchKernelGGL(k_mesh_pass<0>, dim3((unsigned)nbricks), dim3(kBrickThreads), lds, st, (const Roi*)rois, n_rois,
+                       nbricks, case_area, part, tmpkey, tmpt, tmp_cap, totals, moments, (const int*)bmap, pbox);
+  else
+    hipLaunchKernelGGL(k_mesh_pass<1>, dim3((unsigned)nbricks), dim3(kBrickThreads), lds, st, (const Roi*)rois, n_rois,
+                       nbricks, case_area, part, tmpkey, tmpt, tmp_cap, totals, moments, (const int*)bmap, pbox);
   return hipGetLastError();
 }
 

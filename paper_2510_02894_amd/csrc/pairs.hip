@@ -33,7 +33,7 @@ namespace s3d {
 
 typedef float v4f __attribute__((ext_vector_type(4)));
 
-enum { T_ROWS0 = 0, T_VMAX = 1, T_ROWS2D = 2, T_NSEG2D = 3, T_NCOL = 4, T_NITEM = 5, T_NEXACT = 6, T_NSB = 7 };
+enum { T_ROWS0 = 0, T_VMAX = 1, T_ROWS2D = 2, T_NSEG2D = 3, T_NCOL = 4, T_NITEM = 5, T_NEXACT = 6, T_NSB = 7, T_LIST = 10 };
 
 // ---------------------------------------------------------------------------
 // Plane buckets.
@@ -1439,7 +1439,7 @@ __global__ void k_finalize(int n_rois, const RoiMeta* __restrict__ meta, const G
                            const unsigned int* __restrict__ ncand, const unsigned long long* __restrict__ key,
                            const Roi* __restrict__ rois, const long long* __restrict__ pairs2d,
                            RoiResult* __restrict__ res, long long cand_cap, int moments, int ids32,
-                           const long long* __restrict__ totals, long long rows0_cap) {
+                           const long long* __restrict__ totals, long long rows0_cap, long long list_cap) {
   for (int r = blockIdx.x * blockDim.x + threadIdx.x; r < n_rois; r += gridDim.x * blockDim.x) {
     const RoiMeta M = meta[r];
     RoiResult Q;
@@ -1463,6 +1463,7 @@ __global__ void k_finalize(int n_rois, const RoiMeta* __restrict__ meta, const G
     }
     Q.status = M.V == 0 ? 1 : 0;
     if ((long long)*ncand > cand_cap || ncand[1] != 0u || totals[T_ROWS0] > rows0_cap) Q.status = -4;
+    if (Q.status >= 0 && totals[T_LIST] > list_cap) Q.status = kListShort;
     if (rois[r].status != 0) Q.status = rois[r].status;
     Q.pad_ = 0;
     Q.n_in = moments ? M.n_in : 0;
@@ -1687,9 +1688,9 @@ hipError_t launch_plane_counts(const PairBufs& B, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_finalize(const PairBufs& B, long long rows0_cap, hipStream_t st) {
+hipError_t launch_finalize(const PairBufs& B, long long rows0_cap, long long list_cap, hipStream_t st) {
   hipLaunchKernelGGL(k_finalize, dim3(grid_for(B.n_rois)), dim3(256), 0, st, B.n_rois, B.meta, B.gres,
-                     B.counters + 1, B.key, B.rois, B.pairs2d, B.res, B.cand_cap, B.moments ? 1 : 0, B.ids32 ? 1 : 0, B.totals, rows0_cap);
+                     B.counters + 1, B.key, B.rois, B.pairs2d, B.res, B.cand_cap, B.moments ? 1 : 0, B.ids32 ? 1 : 0, B.totals, rows0_cap, list_cap);
   return hipGetLastError();
 }
 

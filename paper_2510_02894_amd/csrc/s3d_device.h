@@ -55,6 +55,75 @@ __device__ inline int wave_max(int v) {
   return v;
 }
 
+// Reductions across lanes without LDS traffic (a __shfl_xor is an LDS permute):
+// step STEP combines a lane's value with that of another lane of its 2^(STEP+1)
+// group, after steps 0 .. STEP - 1 have made the smaller groups uniform: DPP
+// quad permutes and row mirrors within 16 lanes, then the row swaps of gfx950.
+template <int STEP, typename Op>
+__device__ inline uint32_t lane_step(uint32_t v, Op op) {
+  static_assert(STEP >= 0 && STEP < 6, "64 lanes");
+  if constexpr (STEP < 4) {
+    constexpr int ctrl[4] = {0xB1, 0x4E, 0x141, 0x140};  // lane ^ 1, lane ^ 2, half-row mirror, row mirror
+    return op(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, ctrl[STEP], 0xf, 0xf, true));
+  } else if constexpr (STEP == 4) {
+    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    return op((uint32_t)r[0], (uint32_t)r[1]);
+  } else {
+    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return op((uint32_t)r[0], (uint32_t)r[1]);
+  }
+}
+
+template <int STEP, typename Op>
+__device__ inline unsigned long long lane_step(unsigned long long v, Op op) {
+  const uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);
+  if constexpr (STEP < 4) {
+    constexpr int ctrl[4] = {0xB1, 0x4E, 0x141, 0x140};
+    const uint32_t ol = (uint32_t)__builtin_amdgcn_mov_dpp((int)lo, ctrl[STEP], 0xf, 0xf, true);
+    const uint32_t oh = (uint32_t)__builtin_amdgcn_mov_dpp((int)hi, ctrl[STEP], 0xf, 0xf, true);
+    return op(v, (unsigned long long)oh << 32 | ol);
+  } else if constexpr (STEP == 4) {
+    const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    return op((unsigned long long)(uint32_t)h[0] << 32 | (uint32_t)l[0],
+              (unsigned long long)(uint32_t)h[1] << 32 | (uint32_t)l[1]);
+  } else {
+    const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    return op((unsigned long long)(uint32_t)h[0] << 32 | (uint32_t)l[0],
+              (unsigned long long)(uint32_t)h[1] << 32 | (uint32_t)l[1]);
+  }
+}
+
+// Reduction over groups of 2^STEPS consecutive lanes (all lanes active); every
+// lane receives its group's value.
+template <int STEPS, typename T, typename Op>
+__device__ inline T lanes_reduce(T v, Op op) {
+  v = lane_step<0>(v, op);
+  if constexpr (STEPS > 1) v = lane_step<1>(v, op);
+  if constexpr (STEPS > 2) v = lane_step<2>(v, op);
+  if constexpr (STEPS > 3) v = lane_step<3>(v, op);
+  if constexpr (STEPS > 4) v = lane_step<4>(v, op);
+  if constexpr (STEPS > 5) v = lane_step<5>(v, op);
+  return v;
+}
+
+template <int STEPS>
+__device__ inline int lanes_min_i32(int v) {
+  return (int)lanes_reduce<STEPS>((uint32_t)v, [](uint32_t a, uint32_t b) { return (uint32_t)min((int)a, (int)b); });
+}
+template <int STEPS>
+__device__ inline int lanes_max_i32(int v) {
+  return (int)lanes_reduce<STEPS>((uint32_t)v, [](uint32_t a, uint32_t b) { return (uint32_t)max((int)a, (int)b); });
+}
+
+// A float as an integer of the same order (NaN apart), and back.
+__device__ inline int float_order(float f) {
+  const int b = __float_as_int(f);
+  return b ^ ((b >> 31) & 0x7fffffff);
+}
+__device__ inline float order_float(int b) { return __int_as_float(b ^ ((b >> 31) & 0x7fffffff)); }
+
 // Exclusive prefix sum over a 256-thread block; `total` receives the block sum.
 // `sh` must hold 4 ints of shared memory.  Contains barriers.
 __device__ inline int block_excl_scan256(int v, int* sh, int& total) {

@@ -64,10 +64,12 @@ hipError_t launch_small_pairs(int dtype, const Roi* rois, const BrickPart* part,
 // moments: also the inside-voxel moments;
 // bmap: [nbricks] scratch for the brick -> ROI map of a batch (unused, and may
 // be null, for one ROI).
-hipError_t launch_mesh_pass(int dtype, const Roi* rois, int n_rois, long long nbricks, int max_G,
+// one: host ROI record of a call with one ROI, which the launch then stores in
+// rois[0] (null: rois is already there).
+hipError_t launch_mesh_pass(int dtype, Roi* rois, int n_rois, long long nbricks, int max_G,
                             double* case_area, BrickPart* part, unsigned int* counters, int n_counters,
                             unsigned long long* tmpkey, double* tmpt, long long tmp_cap, long long* totals,
-                            int moments, int* bmap, float4* pbox, hipStream_t st);
+                            int moments, int* bmap, float4* pbox, const Roi* one, hipStream_t st);
 // Per-ROI totals and each brick's first row within its ROI (brick_voff);
 // prune_min_v: ROIs with at least this many vertices get the pruning pass's column-pair offsets.
 hipError_t launch_mesh_totals(const Roi* rois, int n_rois, int dtype, const double* case_area, const BrickPart* part,
@@ -106,8 +108,10 @@ struct BlockBufs {
   int cu_count;
   bool ids32;          // every canonical vertex id of the call is below 2^32
 };
-// ev: optional events after the boxes, the listing and the exact maxima
-hipError_t launch_blocks(const BlockBufs& B, hipStream_t st, hipEvent_t* ev);
+// again: also the kernels that serve a list that was too short (*list_n tells;
+// without them the results of such a call are not valid); ev: optional events
+// after the boxes, the listing and the exact maxima.
+hipError_t launch_blocks(const BlockBufs& B, bool again, hipStream_t st, hipEvent_t* ev);
 
 // What the totals pass writes for the block-pair pass (all null / 0 when the
 // general pipeline follows).
@@ -284,7 +288,9 @@ hipError_t launch_init_groups(const PairBufs& B, hipStream_t st);   // reset gro
 hipError_t launch_refine(const PairBufs& B, hipStream_t st);        // candidates + exact FP64 passes
 hipError_t launch_plane_counts(const PairBufs& B, hipStream_t st);  // in-plane pair counts from the staged keys
 // per-ROI results; status SHAPE3D_ECAPACITY when the ROIs' rows (totals[0]) exceed rows0_cap
-hipError_t launch_finalize(const PairBufs& B, long long rows0_cap, hipStream_t st);
+// and kListShort when more than list_cap block pairs were listed (totals[10])
+constexpr int kListShort = -101;
+hipError_t launch_finalize(const PairBufs& B, long long rows0_cap, long long list_cap, hipStream_t st);
 // res -> out[nf * n_rois] (nf = 6, or 17 for the whole Shape class; not written for a negative
 // status) and status[n_rois] (may be null), on the device
 hipError_t launch_results_out(const RoiResult* res, int n_rois, double* out, int* status, int nf, hipStream_t st);
