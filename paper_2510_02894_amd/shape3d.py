@@ -323,13 +323,27 @@ def roi_table(offsets, shapes, spacings):
     return tab
 
 
+_ROI_DTYPE = np.dtype([("offset", "<i8"), ("dims", "<i8", 3), ("spacing", "<f8", 3)])
+
+
+def _extents(table):
+    """Offsets, dims and voxel counts of a dense ROI table, read from its memory
+    at once (4,096 ROIs one ctypes field at a time took longer than their
+    features).  A count beyond int64 is -1."""
+    t = np.frombuffer(table, dtype=_ROI_DTYPE) if len(table) else np.zeros(0, dtype=_ROI_DTYPE)
+    off, dims = t["offset"], t["dims"]
+    fits = np.abs(dims.astype(np.float64)).prod(axis=1) < 2.0 ** 62
+    return off, dims, np.where(fits, np.where(fits[:, None], dims, 0).prod(axis=1), -1)
+
+
 def _check_extents(table, numel: int):
     """Every ROI of a dense table lies inside a base tensor of numel elements."""
-    for r in range(len(table)):
-        d = [int(table[r].dims[k]) for k in range(3)]
-        if min(d) < 1 or int(table[r].offset) < 0 or int(table[r].offset) + d[0] * d[1] * d[2] > numel:
-            raise ValueError("ROI %d (offset %d, dims %s) does not fit in a base of %d elements"
-                             % (r, int(table[r].offset), d, numel))
+    off, dims, n = _extents(table)
+    bad = (dims < 1).any(axis=1) | (off < 0) | (n < 0) | (n > numel) | (off > numel - n)
+    if bad.any():
+        r = int(np.argmax(bad))
+        raise ValueError("ROI %d (offset %d, dims %s) does not fit in a base of %d elements"
+                         % (r, int(off[r]), [int(d) for d in dims[r]], numel))
 
 
 def workspace_size(shape, dtype: int = U8, max_vertices: int = -1) -> int:
@@ -596,15 +610,14 @@ def soft_backward(p, saved: SoftSaved, grad_out):
 def _uncovered(table, numel: int):
     """The element ranges [a, b) of a packed buffer of numel elements that no
     ROI of the table covers."""
-    spans = sorted((int(r.offset), int(r.offset) + int(r.dims[0]) * int(r.dims[1]) * int(r.dims[2])) for r in table)
-    out, pos = [], 0
-    for a, b in spans:
-        if a > pos:
-            out.append((pos, min(a, numel)))
-        pos = max(pos, b)
-    if pos < numel:
-        out.append((pos, numel))
-    return [(a, b) for a, b in out if b > a]
+    first, _, n = _extents(table)
+    order = np.argsort(first, kind="stable")
+    first, last = first[order], (first + n)[order]
+    # where the elements covered so far end, before each ROI and after the last
+    pos = np.maximum.accumulate(np.concatenate([[0], last]))
+    nxt = np.minimum(np.concatenate([first, [numel]]), numel)
+    gap = nxt > pos
+    return list(zip(pos[gap].tolist(), nxt[gap].tolist()))
 
 
 def _soft_base(base):
