@@ -28,6 +28,7 @@
 #include <vector>
 
 #include "../../include/shape3d.h"
+#include "s3d_device.h"
 #include "s3d_launch.h"
 
 using namespace s3d;
@@ -99,7 +100,7 @@ struct Workspace {
   long long generation = 0;  // bumped whenever a buffer is reallocated (graphs hold pointers)
   Buf buf[W_NUM];
   Buf blk[B_NUM];
-  Buf soft_rois, soft_edges, soft_field, soft_ctr, soft_blk;  // soft backward
+  Buf soft_rois, soft_cubes, soft_croi, soft_cgrad, soft_egrad, soft_vox, soft_vroi, soft_bits, soft_index, soft_ctr, soft_blk;  // soft backward
   void* host = nullptr;  // pinned staging: ROI table, read-backs, results
   size_t host_cap = 0;
   hipEvent_t ev[8] = {};
@@ -124,7 +125,7 @@ struct Workspace {
     for (int i = 0; i < W_NUM; ++i) P.p[i] = buf[i].p;
     return P;
   }
-  std::vector<Buf*> soft_bufs() { return {&soft_rois, &soft_edges, &soft_field, &soft_ctr, &soft_blk}; }
+  std::vector<Buf*> soft_bufs() { return {&soft_rois, &soft_cubes, &soft_croi, &soft_cgrad, &soft_egrad, &soft_vox, &soft_vroi, &soft_bits, &soft_index, &soft_ctr, &soft_blk}; }
 };
 
 std::map<int, Workspace*> g_ws;
@@ -1412,7 +1413,8 @@ int soft_backward_impl(const float* base, const shape3d_roi* rois, int64_t n_roi
   if ((rc = get_workspace(&wp))) return rc;
   Workspace& w = *wp;
   std::vector<SoftBwdRoi> table((size_t)n_rois);
-  long long n_cblocks = 0, n_vblocks = 0, n_field = 0, cap = 0;
+  long long n_bricks = 0, n_bitblks = 0, n_bits = 0, n_index = 0, n_vox = 0, cap = 0;
+  size_t scan_lds = 0;
   for (int64_t r = 0; r < n_rois; ++r) {
     const shape3d_soft_saved& S = saved[r];
     for (int k = 0; k < 3; ++k)
@@ -1442,33 +1444,50 @@ int soft_backward_impl(const float* base, const shape3d_roi* rois, int64_t n_roi
       R.pair_ids[f][1] = S.pair_ids[f][1];
     }
     const long long ncube = (long long)(R.d[0] + 1) * (R.d[1] + 1) * (R.d[2] + 1);
-    const long long nvox = (long long)R.d[0] * R.d[1] * R.d[2];
     if (ncube >= (1ll << 31)) return fail(SHAPE3D_EINVAL, "soft ROI too large for the backward pass (2^31 cubes)");
-    R.n_cubes = (unsigned int)ncube;
-    R.n_vox = (unsigned int)nvox;
-    magic_div((unsigned int)((R.d[1] + 1) * (R.d[2] + 1)), R.m_cplane, R.sh_cplane);
-    magic_div((unsigned int)(R.d[2] + 1), R.m_c2, R.sh_c2);
-    magic_div((unsigned int)(R.d[1] * R.d[2]), R.m_plane, R.sh_plane);
-    magic_div((unsigned int)R.d[2], R.m_d2, R.sh_d2);
-    R.field_begin = n_field;
-    R.cblk_begin = n_cblocks;
-    R.vblk_begin = n_vblocks;
-    n_field += 3 * ncube;
-    n_cblocks += (ncube + kCubeBlock - 1) / kCubeBlock;
-    n_vblocks += (nvox + kVoxBlock - 1) / kVoxBlock;
+    R.G = (R.d[2] + 1 + 31) / 32;
+    R.nrg = (R.d[1] + 1) * R.G;
+    magic_div((unsigned int)R.G, R.mG, R.shG);
+    // planes per workgroup: as many as leave a few workgroups per CU (a small
+    // ROI in 8-plane bricks is six workgroups) and as 64 KB of LDS hold
+    const long long bpz = (R.nrg + 255) / 256;
+    const size_t plane = sizeof(uint32_t) * (258 + 2 * (size_t)R.G);
+    R.tz = kTZ;
+    while (R.tz > 1 && ((R.tz + 2) * plane > 60000 || (n_rois < 16 && bpz * ((R.d[0] + R.tz) / R.tz) < 512)))
+      R.tz >>= 1;
+    R.nzc = (R.d[0] + R.tz) / R.tz;
+    scan_lds = std::max(scan_lds, (R.tz + 2) * plane);
+    R.cube_begin = n_index;
+    R.brick_begin = n_bricks;
+    n_index += ncube;
+    const long long vox = (long long)R.d[0] * R.d[1] * R.d[2];
+    R.bitblk_begin = n_bitblks;
+    R.bits_begin = n_bits;
+    n_bitblks += (vox + kBitBlock - 1) / kBitBlock;
+    n_bits += bit_words(vox);
+    n_vox += vox;
+    n_bricks += bpz * R.nzc;
     cap += S.n_vertices;
   }
-  if (n_cblocks > (1ll << 31) - 2 || n_vblocks > (1ll << 31) - 2) return fail(SHAPE3D_EINVAL, "batch too large");
+  if (n_bricks > (1ll << 31) - 2 || n_bitblks > (1ll << 31) - 2) return fail(SHAPE3D_EINVAL, "batch too large");
+  const long long cap_cubes = std::min(cap + cap / 3, n_index), cap_vox = std::min(2 * cap, n_vox);
+  if (cap_cubes >= (1ll << 32) - 1) return fail(SHAPE3D_EINVAL, "batch too large");
   const size_t tbytes = sizeof(SoftBwdRoi) * (size_t)n_rois;
   if ((rc = ensure(w, w.soft_rois, tbytes))) return rc;
-  if ((rc = ensure(w, w.soft_edges, sizeof(unsigned long long) * std::max<long long>(cap, 1)))) return rc;
-  // one float per grid edge; only crossing edges' slots are ever written or read
-  if ((rc = ensure(w, w.soft_field, sizeof(float) * n_field))) return rc;
-  if ((rc = ensure(w, w.soft_ctr, sizeof(long long) * 2))) return rc;
+  if ((rc = ensure(w, w.soft_cubes, sizeof(unsigned long long) * (size_t)cap_cubes))) return rc;
+  if ((rc = ensure(w, w.soft_croi, sizeof(int) * (size_t)cap_cubes))) return rc;
+  if ((rc = ensure(w, w.soft_cgrad, sizeof(double) * 12 * (size_t)cap_cubes))) return rc;
+  if ((rc = ensure(w, w.soft_egrad, sizeof(float) * 3 * (size_t)cap_cubes))) return rc;
+  if ((rc = ensure(w, w.soft_vox, sizeof(unsigned long long) * (size_t)cap_vox))) return rc;
+  if ((rc = ensure(w, w.soft_vroi, sizeof(int) * (size_t)cap_vox))) return rc;
+  if ((rc = ensure(w, w.soft_bits, sizeof(uint32_t) * (size_t)n_bits))) return rc;
+  // an entry per cube; only active cubes' entries are ever written or read
+  if ((rc = ensure(w, w.soft_index, sizeof(unsigned int) * (size_t)n_index))) return rc;
+  if ((rc = ensure(w, w.soft_ctr, sizeof(long long) * 4))) return rc;
   // with more than a few ROIs, a table gives each workgroup its ROI (instead
   // of a binary search of the ROI table per workgroup)
   const bool blk_table = n_rois > 8;
-  if (blk_table && (rc = ensure(w, w.soft_blk, sizeof(int) * (size_t)(n_cblocks + n_vblocks)))) return rc;
+  if (blk_table && (rc = ensure(w, w.soft_blk, sizeof(int) * (size_t)(n_bricks + n_bitblks)))) return rc;
   if ((rc = ensure_host(w, std::max<size_t>(w.host_cap, 4096 + tbytes)))) return rc;
   char* h = (char*)w.host;
   memcpy(h + 4096, table.data(), tbytes);
@@ -1476,13 +1495,23 @@ int soft_backward_impl(const float* base, const shape3d_roi* rois, int64_t n_roi
   SoftBwdBufs B;
   B.rois = (const SoftBwdRoi*)w.soft_rois.p;
   B.n_rois = (int)n_rois;
-  B.n_cblocks = n_cblocks;
-  B.n_vblocks = n_vblocks;
-  B.cap = cap;
-  B.edges = (unsigned long long*)w.soft_edges.p;
-  B.field = (float*)w.soft_field.p;
-  B.n_field = n_field;
+  B.n_bricks = n_bricks;
+  B.n_bitblks = n_bitblks;
+  B.bits = (uint32_t*)w.soft_bits.p;
+  B.scan_lds = scan_lds;
+  B.cap_cubes = cap_cubes;
+  B.cap_vox = cap_vox;
+  B.cubes = (unsigned long long*)w.soft_cubes.p;
+  B.croi = (int*)w.soft_croi.p;
+  B.cgrad = (double*)w.soft_cgrad.p;
+  B.egrad = (float*)w.soft_egrad.p;
+  B.vox = (unsigned long long*)w.soft_vox.p;
+  B.vroi = (int*)w.soft_vroi.p;
+  B.index = (unsigned int*)w.soft_index.p;
   B.counters = (long long*)w.soft_ctr.p;
+  // counts of a mask with other crossing edges than the forward pass's can pass
+  // the lists' ends, never the number of cubes
+  B.packed = n_index < (1ll << 32) - 1;
   B.cu_count = w.cu_count;
   B.blk_roi = blk_table ? (int*)w.soft_blk.p : nullptr;
   HIPCK(launch_soft_backward(B, st));

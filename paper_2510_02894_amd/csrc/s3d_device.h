@@ -245,4 +245,50 @@ __device__ inline unsigned long long key_canonical_id(uint64_t key, const int* d
   return 3ull * lin + a;
 }
 
+// ---------------------------------------------------------------------------
+// Inside bits of dense volumes as one bit string (bit i: element i), written by
+// a streaming pass, from which the passes over cubes cut the 32-voxel words of
+// their rows: a brick that reads the volume itself waits for its own few loads
+// and reads its neighbours' rows again, in four bytes a voxel.
+
+// 32-bit words of the string of n elements: whole 64-bit words, and one more
+// for the last cut.
+__host__ __device__ inline long long bit_words(long long n) { return (n + 63) / 64 * 2 + 2; }
+
+// The word of the voxels pos .. pos + left - 1 (at most 32 of them; 0 if left <= 0).
+__device__ inline uint32_t cut_word(const uint32_t* __restrict__ bits, unsigned int pos, int left) {
+  if (left <= 0) return 0u;
+  const uint32_t w = __builtin_amdgcn_alignbit(bits[(pos >> 5) + 1], bits[pos >> 5], pos & 31u);
+  return left >= 32 ? w : w & ((1u << left) - 1u);
+}
+
+// Elements per workgroup (256 threads) of a bit pass.
+constexpr int kBitBlock = 8192;
+
+// A workgroup's elements [e0, e0 + kBitBlock) of n floats into the bit string
+// (a wave's comparison is 64 bits of it), and zeros into `zero` if it is set.
+__device__ inline void pack_bits_f32(const float* __restrict__ src, long long n, long long e0,
+                                     unsigned long long* __restrict__ bits, float* __restrict__ zero) {
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const long long w0 = e0 + (2 * wid + h) * 1024;  // 16 waves' loads in flight
+    float v[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) v[u] = w0 + 64 * u + lane < n ? src[w0 + 64 * u + lane] : 0.0f;
+    if (zero) {
+#pragma unroll
+      for (int u = 0; u < 16; ++u)
+        if (w0 + 64 * u + lane < n) zero[w0 + 64 * u + lane] = 0.0f;
+    }
+    unsigned long long mine = 0ull;
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      const unsigned long long in = __ballot(v[u] > 0.5f);
+      mine = lane == u ? in : mine;
+    }
+    if (lane < 16 && w0 + 64 * lane < (n + 63) / 64 * 64 + 64) bits[w0 / 64 + lane] = mine;
+  }
+}
+
 }  // namespace s3d

@@ -234,47 +234,52 @@ struct PairBufs {
 
 // soft.hip: adjoint of the soft-mask forward pass, for a table of ROIs.
 // Cubes u in [-1, d-1]^3 have the flat index cube(u) = ((u0 + 1) (d1 + 1) +
-// u1 + 1) (d2 + 1) + u2 + 1; grid edge (u, u + e_a) has the edge-field slot
-// field_begin + 3 cube(u) + a.  Local indices are below 2^31 (checked on the
-// host), so the kernels divide with 32-bit magic numbers: floor(n / D) =
-// (n * m) >> sh with sh = 31 + ceil(log2 D) and m = floor(2^sh / D) + 1.
-constexpr int kCubeBlock = 4096;   // cubes per workgroup of the edge pass (16 per thread)
-constexpr int kVoxPer = 4;         // voxels per thread of the gather pass (256 apart)
-constexpr int kVoxBlock = 256 * kVoxPer;  // voxels per workgroup of the gather pass
-
+// u1 + 1) (d2 + 1) + u2 + 1, below 2^31 (checked on the host).
 struct SoftBwdRoi {
   const float* p;             // the ROI's probabilities (d0, d1, d2)
   float* grad;                // dL/dp, same layout
   int d[3];
-  int pad_;
+  int G;                      // row-groups (32 cubes) per cube row
+  int nrg;                    // row-groups of a cube plane: (d1 + 1) G
+  int nzc;                    // z-chunks of tz cube planes
+  int tz;                     // cube planes per workgroup of the scan
+  int shG;                    // floor(n / G) = (n * mG) >> shG for 0 <= n < 2^31
+  unsigned int mG;
   double s[3];
   double o[3];                // origin of the signed volume sum (array centre)
   double g_area;              // dL/dSurfaceArea
   double g_vol_signed;        // dL/dMeshVolume * sign(signed volume)
   double gdiam[4];            // dL/dD_f / D_f (0 if the feature has no pair)
   long long pair_ids[4][2];   // canonical ids of the maximising pairs, -1 if none
-  long long field_begin;      // first slot of the ROI in the edge field
-  long long cblk_begin;       // first workgroup of the edge pass
-  long long vblk_begin;       // first workgroup of the gather pass
-  unsigned int n_cubes;       // (d0 + 1)(d1 + 1)(d2 + 1)
-  unsigned int n_vox;         // d0 d1 d2
-  unsigned int m_cplane, m_c2, m_plane, m_d2;  // magic numbers for (d1+1)(d2+1), d2+1, d1 d2, d2
-  int sh_cplane, sh_c2, sh_plane, sh_d2;
+  long long cube_begin;       // first entry of the ROI in the cube index
+  long long brick_begin;      // first workgroup of the scan
+  long long bitblk_begin;     // ... and of the bit pass
+  long long bits_begin;       // first word of its bit string
 };
 
 struct SoftBwdBufs {
   const SoftBwdRoi* rois;     // [n_rois], DEVICE
   int n_rois;
-  long long n_cblocks;        // workgroups of the edge pass
-  long long n_vblocks;        // workgroups of the gather pass
-  long long cap;              // crossing-edge capacity (the forward pass's vertex count)
-  unsigned long long* edges;  // [cap] crossing edges: ROI index << 40 | local field slot
-  float* field;               // edge field: (dL/dx_v)_a * s_a at crossing edges (other slots unused)
-  long long n_field;          // slots of the edge field
-  long long* counters;        // [0] edges reserved
+  long long n_bricks;         // workgroups of the scan
+  size_t scan_lds;            // its dynamic LDS
+  long long n_bitblks;        // workgroups of the bit pass
+  uint32_t* bits;             // the ROIs' bit strings
+  // room for the active cubes and the voxels at crossing edges of a mask with
+  // the forward pass's V vertices (an edge lies in four cubes and a cube has at
+  // least three crossing edges; an edge has two ends)
+  long long cap_cubes, cap_vox;
+  unsigned long long* cubes;  // [cap_cubes] min corner (pack_key with axis 0) and ROI
+  int* croi;
+  double* cgrad;              // [12 cap_cubes] per cube edge, the gradient's component along it
+  float* egrad;               // [3 cap_cubes] the summed gradient of the edges from its min corner
+  unsigned long long* vox;    // [cap_vox]
+  int* vroi;
+  unsigned int* index;        // per cube of every ROI: its place in the list (active cubes only)
+  long long* counters;        // [4] crossing edges, listed cubes, listed voxels; packed: both in the fourth
+  bool packed;                // neither list can pass 2^32 - 1 entries
   int cu_count;
-  int* blk_roi;               // [n_cblocks + n_vblocks] ROI of each edge-pass then gather-pass
-                              // workgroup, or null (then found by binary search)
+  int* blk_roi;               // [n_bricks + n_bitblks] ROI of each workgroup of the scan, then of the bit
+                              // pass, or null (then searched)
 };
 hipError_t launch_soft_backward(const SoftBwdBufs& B, hipStream_t st);
 

@@ -13,21 +13,29 @@
 // plus the diameter subgradient g_f (x_v - x_other) / D_f when v is an end
 // point of the maximising pair of feature f.
 //
-// Three passes over every ROI of a table:
-//   1. k_soft_edges: one wave per padded cube row lists the row's crossing
-//      edges (their slots in the edge field); a workgroup reserves room for
-//      its rows with one atomic;
-//   2. k_soft_vertex_grad: one thread per crossing edge (the surface is sparse,
-//      so a thread per voxel would leave most lanes idle around the FP64 work)
-//      computes (dL/dx_v)_a * s_a / (p_b - p_u)^2 into the edge's field slot;
-//   3. k_soft_gather: for each voxel, the terms of its (at most six) incident
-//      crossing edges, the field value times (0.5 - p_b) or -(0.5 - p_u), read
-//      directly from their field slots, summed, and dL/dp written densely (0
-//      away from the surface).  The division by (p_b - p_u)^2 is thus done once
-//      per crossing edge, not once per end point over whole waves.
-// Only slots of crossing edges are written and read, so the field is never
-// cleared.  No float atomics: the result does not depend on scheduling.
+// Passes over every ROI of a table, one of them over the volume:
+//   1. k_soft_bits reads the probabilities once as inside bits and writes the
+//      zeros of dL/dp (bound: HBM, 4 bytes in and 4 out per voxel); k_soft_scan
+//      lists the active cubes and the voxels at a crossing edge from the bits; a
+//      dense index gives each active cube's place in its list;
+//   2. k_soft_cubes, a thread per active cube: its triangles once each, and
+//      per crossing cube edge the component of their gradient along the edge.
+//      Bound: FP64 VALU; a thread per edge that visits the four cubes around it
+//      evaluates every triangle three times (5,440 instructions an edge);
+//      k_soft_diam then adds the diameters' terms to the ends of their pairs;
+//   3. k_soft_edges sums each crossing edge over its four cubes, in a fixed order,
+//      into (dL/dx_v)_a s_a / (p_b - p_u)^2, three floats per active cube;
+//   4. k_soft_voxels, a thread per listed voxel: the terms of its (at most six)
+//      crossing edges, the edge's value times 0.5 - p_b or -(0.5 - p_u).
+//      Bound: latency of scattered reads, all of a voxel's in flight at once.
+// No float atomics: the result does not depend on scheduling.
+// Measured on 1,024 ROIs of a 2.2 GB batch (us): bits 600, scan 362, cubes 357,
+// edges 349, voxels 208, in all 1,880, against 2,408 of a wave per cube row that
+// listed the edges (540), a thread per edge (1,064) and a gather over all voxels
+// (804).
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
 
 #define MC_TABLE_QUAL __constant__ const
 #include "mc_table.h"
@@ -35,6 +43,20 @@
 #include "s3d_launch.h"
 
 namespace s3d {
+
+namespace {
+
+enum { C_EDGES = 0, C_CUBES = 1, C_VOX = 2, C_BOTH = 3 };  // SoftBwdBufs::counters
+
+struct D3 {
+  double x, y, z;
+};
+
+__device__ inline D3 sub3(const D3& a, const D3& b) { return {a.x - b.x, a.y - b.y, a.z - b.z}; }
+__device__ inline D3 cross3(const D3& a, const D3& b) {
+  return {a.y * b.z - a.z * b.y, a.z * b.x - a.x * b.z, a.x * b.y - a.y * b.x};
+}
+__device__ inline double axis_of(const D3& v, int a) { return a == 0 ? v.x : (a == 1 ? v.y : v.z); }
 
 __device__ inline double pval(const float* p, const int* d, int z, int y, int x) {
   if (z < 0 || y < 0 || x < 0 || z >= d[0] || y >= d[1] || x >= d[2]) return 0.0;
@@ -53,356 +75,444 @@ __device__ inline void vertex_pos(const float* p, const int* d, const double* s,
   x[2] = ((double)u2 + (a == 2 ? t : 0.0)) * s[2] - o[2];
 }
 
-struct D3 {
-  double x, y, z;
-};
-
-__device__ inline D3 sub3(const D3& a, const D3& b) { return {a.x - b.x, a.y - b.y, a.z - b.z}; }
-__device__ inline D3 cross3(const D3& a, const D3& b) {
-  return {a.y * b.z - a.z * b.y, a.z * b.x - a.x * b.z, a.x * b.y - a.y * b.x};
-}
-
 // p at (z, y, x), 0 outside the array; the load is always issued (at a
 // clamped address) so that several of them are in flight together.
-__device__ inline double pld(const float* p, const int* d, int z, int y, int x) {
+__device__ inline float pld(const float* p, const int* d, int z, int y, int x) {
   const bool ok = (unsigned)z < (unsigned)d[0] && (unsigned)y < (unsigned)d[1] && (unsigned)x < (unsigned)d[2];
   const int zc = min(max(z, 0), d[0] - 1), yc = min(max(y, 0), d[1] - 1), xc = min(max(x, 0), d[2] - 1);
   const float v = p[((size_t)zc * d[1] + yc) * (size_t)d[2] + xc];
-  return ok ? (double)v : 0.0;
+  return ok ? v : 0.0f;
 }
 
-// v[k] for a register array indexed by a run-time k in [0, 8) (selects, no scratch).
-__device__ inline double sel8(const double* v, int k) {
-  const double a = (k & 1) ? v[1] : v[0], b = (k & 1) ? v[3] : v[2];
-  const double c = (k & 1) ? v[5] : v[4], e = (k & 1) ? v[7] : v[6];
-  const double ab = (k & 2) ? b : a, ce = (k & 2) ? e : c;
-  return (k & 4) ? ce : ab;
+// Flat index of the cube with min corner u.
+__device__ inline long long cube_index(const int* d, int u0, int u1, int u2) {
+  return ((long long)(u0 + 1) * (d[1] + 1) + (u1 + 1)) * (long long)(d[2] + 1) + (u2 + 1);
 }
 
-// Position (relative to o) of the vertex on cube edge e of the cube with min
-// corner (c0, c1, c2) and corner values pc.  Edge e = 4 axis + 2 o_b + o_c runs
-// from corner k0 (bits dz dy dx) along its axis.
-__device__ inline D3 cube_vertex(const double* pc, int e, int c0, int c1, int c2, const double* s, const double* o) {
-  const int ea = e >> 2;
-  const int k0 = ea == 0 ? (e & 3) : (ea == 1 ? 4 * ((e >> 1) & 1) + (e & 1) : 4 * ((e >> 1) & 1) + 2 * (e & 1));
-  const int k1 = k0 | (4 >> ea);
-  const double p0 = sel8(pc, k0), p1 = sel8(pc, k1);
-  const double tt = (0.5 - p0) * rcp64(p1 - p0);
-  const int w0 = c0 + ((k0 >> 2) & 1), w1 = c1 + ((k0 >> 1) & 1), w2 = c2 + (k0 & 1);
-  return {((double)w0 + (ea == 0 ? tt : 0.0)) * s[0] - o[0], ((double)w1 + (ea == 1 ? tt : 0.0)) * s[1] - o[1],
-          ((double)w2 + (ea == 2 ? tt : 0.0)) * s[2] - o[2]};
+// The listed cubes and voxels.
+__device__ inline long long listed_cubes(const SoftBwdBufs& B) {
+  return min(B.packed ? (long long)((unsigned long long)B.counters[C_BOTH] & 0xffffffffull) : B.counters[C_CUBES],
+             B.cap_cubes);
+}
+__device__ inline long long listed_vox(const SoftBwdBufs& B) {
+  return min(B.packed ? (long long)((unsigned long long)B.counters[C_BOTH] >> 32) : B.counters[C_VOX], B.cap_vox);
 }
 
-// dL/dx of the vertex on edge (u, a) from the area and volume terms; tri is
-// the case table's edge triples and tmask[12 case + e] the set of the case's
-// triangles that hold edge e (both in LDS).
-__device__ inline void vertex_grad_mesh(const float* p, const int* d, const double* s, const double* o, int u0, int u1,
-                                        int u2, int a, double g_area, double g_vol_signed, const uint8_t* tmask,
-                                        const uint8_t* tri, double* gx) {
-  // per-edge factors of the two terms (divisions hoisted out of the triangle loop)
-  const double ga = 0.5 * g_area, gv = g_vol_signed / 6.0;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int ob = q >> 1, oc = q & 1;
-    // min corner of the cube: the edge's two other axes step back by ob and oc
-    const int c0 = u0 - (a != 0 ? ob : 0);
-    const int c1 = u1 - (a == 0 ? ob : (a == 1 ? 0 : oc));
-    const int c2 = u2 - (a == 2 ? 0 : oc);
-    const int le = 4 * a + 2 * ob + oc;  // the edge's number inside this cube
-    double pc[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) pc[k] = pld(p, d, c0 + ((k >> 2) & 1), c1 + ((k >> 1) & 1), c2 + (k & 1));
-    int cas = 0;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) cas |= (int)(pc[k] > 0.5) << k;
-    // only the triangles that hold this vertex
-    for (unsigned int m = tmask[cas * 12 + le]; m; m &= m - 1u) {
-      const int t = __ffs(m) - 1;
-      const uint8_t* tr = tri + (cas * MC_MAX_TRI + t) * 3;
-      const int e0 = tr[0], e1 = tr[1], e2 = tr[2];
-      const D3 P0 = cube_vertex(pc, e0, c0, c1, c2, s, o);
-      const D3 P1 = cube_vertex(pc, e1, c0, c1, c2, s, o);
-      const D3 P2 = cube_vertex(pc, e2, c0, c1, c2, s, o);
-      // B, C: the next two vertices after this one in the triangle's order
-      const D3 B = e0 == le ? P1 : (e1 == le ? P2 : P0);
-      const D3 C = e0 == le ? P2 : (e1 == le ? P0 : P1);
-      const D3 n = cross3(sub3(P1, P0), sub3(P2, P0));
-      const double len = sqrt(n.x * n.x + n.y * n.y + n.z * n.z);
-      if (len > 0.0) {
-        const double il = rcp64(len);
-        const D3 nh = {n.x * il, n.y * il, n.z * il};
-        const D3 r = cross3(nh, sub3(C, B));
-        gx[0] += ga * r.x;
-        gx[1] += ga * r.y;
-        gx[2] += ga * r.z;
-      }
-      const D3 bc = cross3(B, C);
-      gx[0] += gv * bc.x;
-      gx[1] += gv * bc.y;
-      gx[2] += gv * bc.z;
-    }
+__device__ inline unsigned long long pack_vox(int u0, int u1, int u2) { return pack_key(u0, u1, u2, 0); }
+__device__ inline int vox0(unsigned long long k) { return (int)(k >> 40 & 0xFFFFF) - 1; }
+__device__ inline int vox1(unsigned long long k) { return (int)(k >> 20 & 0xFFFFF) - 1; }
+__device__ inline int vox2(unsigned long long k) { return (int)(k & 0xFFFFF) - 1; }
+
+// Last ROI whose first workgroup of the scan (or of the bit pass) is <= b.
+#define S3D_SOFT_ROI_SEARCH(name, member)                               \
+  __device__ inline int name(const SoftBwdRoi* r, int n, long long b) { \
+    int lo = 0, hi = n - 1;                                             \
+    while (lo < hi) {                                                   \
+      const int mid = (lo + hi + 1) >> 1;                               \
+      if (r[mid].member <= b)                                           \
+        lo = mid;                                                       \
+      else                                                              \
+        hi = mid - 1;                                                   \
+    }                                                                   \
+    return lo;                                                          \
   }
-}
-
-
-// Last ROI whose first element of the given kind is <= x.
-#define S3D_SOFT_ROI_SEARCH(name, member)                                   \
-  __device__ inline int name(const SoftBwdRoi* r, int n, long long x) {     \
-    int lo = 0, hi = n - 1;                                                  \
-    while (lo < hi) {                                                        \
-      const int mid = (lo + hi + 1) >> 1;                                    \
-      if (r[mid].member <= x)                                                \
-        lo = mid;                                                            \
-      else                                                                   \
-        hi = mid - 1;                                                        \
-    }                                                                        \
-    return lo;                                                               \
-  }
-S3D_SOFT_ROI_SEARCH(soft_roi_of_cblk, cblk_begin)
-S3D_SOFT_ROI_SEARCH(soft_roi_of_vblk, vblk_begin)
+S3D_SOFT_ROI_SEARCH(soft_roi_of, brick_begin)
+S3D_SOFT_ROI_SEARCH(soft_roi_of_bits, bitblk_begin)
 #undef S3D_SOFT_ROI_SEARCH
 
-// Pass 1.  A workgroup takes kCubeBlock consecutive cubes (flat index l over
-// [-1, d-1]^3, the cube's edge-field index) of one ROI, 16 per thread; the
-// crossing edges are counted, room is reserved with one atomic per workgroup
-// and their field slots written in (thread, cube, axis) order.
-__global__ __launch_bounds__(256) void k_soft_edges(SoftBwdBufs B) {
-  constexpr int kPer = kCubeBlock / 256;
+// A wave emits the set bits of its lanes' words, two words at a time, a lane
+// per bit: f(bit, list position, base of the word, place of the word) for each.
+// off: the lane's next list position, moved past its word.  (Loops of a lane
+// over its own bits hold the wave for the fullest word.)
+template <typename F>
+__device__ inline void emit_words(uint32_t w, int& off, int base, int place, int lane, F&& f) {
+  unsigned long long todo = __ballot(w != 0u);
+  const int k = lane & 31;
+  const bool low = lane < 32;
+  while (todo) {
+    const int s0 = __ffsll((long long)todo) - 1;
+    todo &= todo - 1ull;
+    const int s1 = todo ? __ffsll((long long)todo) - 1 : s0;
+    const uint32_t w0 = (uint32_t)__builtin_amdgcn_readlane((int)w, s0);
+    const uint32_t w1 = todo ? (uint32_t)__builtin_amdgcn_readlane((int)w, s1) : 0u;
+    todo &= todo - 1ull;
+    const uint32_t word = low ? w0 : w1;
+    const int o = low ? __builtin_amdgcn_readlane(off, s0) : __builtin_amdgcn_readlane(off, s1);
+    const int bs = low ? __builtin_amdgcn_readlane(base, s0) : __builtin_amdgcn_readlane(base, s1);
+    const int pl = low ? __builtin_amdgcn_readlane(place, s0) : __builtin_amdgcn_readlane(place, s1);
+    if (word >> k & 1u) f(k, o + __popc(word & ((1u << k) - 1u)), bs, pl);
+  }
+  off += __popc(w);
+}
+
+}  // namespace
+
+// The inside bits of the probabilities and the zeros of dL/dp, a stream.
+__global__ __launch_bounds__(256) void k_soft_bits(SoftBwdBufs B) {
+  const int roi = B.blk_roi ? B.blk_roi[B.n_bricks + blockIdx.x] : soft_roi_of_bits(B.rois, B.n_rois, blockIdx.x);
+  const SoftBwdRoi& R = B.rois[roi];
+  const long long n = (long long)R.d[0] * R.d[1] * R.d[2];
+  pack_bits_f32(R.p, n, (long long)(blockIdx.x - R.bitblk_begin) * kBitBlock,
+                (unsigned long long*)(B.bits + R.bits_begin), R.grad);
+}
+
+// Pass 1.  A workgroup takes 256 consecutive row-groups (rg = cube row * G +
+// group of 32 cubes along axis 2) times up to R.tz cube planes, as the mesh
+// pass does, and holds the inside words of their voxels and of one more row and
+// plane on either side: tile word (p, i) is the row-group rg0 - 1 + i of voxel
+// plane pz0 - 1 + p.
+__global__ __launch_bounds__(256) void k_soft_scan(SoftBwdBufs B) {
+  extern __shared__ uint32_t s_bits[];
   __shared__ int s_scan[4];
-  __shared__ long long base_sh;
-  const int roi = B.blk_roi ? B.blk_roi[blockIdx.x] : soft_roi_of_cblk(B.rois, B.n_rois, blockIdx.x);
-  const SoftBwdRoi* R = B.rois + roi;
-  const int* d = R->d;
-  const float* p = R->p;
-  const unsigned int l0 = (unsigned int)(blockIdx.x - R->cblk_begin) * kCubeBlock + threadIdx.x;
-  const unsigned int plane = (unsigned int)d[1] * d[2];
-  unsigned long long bits = 0ull;  // 3 bits per cube k
+  __shared__ long long s_base[2];
+  const int roi = B.blk_roi ? B.blk_roi[blockIdx.x] : soft_roi_of(B.rois, B.n_rois, blockIdx.x);
+  const SoftBwdRoi& R = B.rois[roi];
+  const int d0 = R.d[0], d1 = R.d[1], d2 = R.d[2], G = R.G;
+  const int local = (int)(blockIdx.x - R.brick_begin);
+  const int rg0 = local / R.nzc * 256, pz0 = local % R.nzc * R.tz;
+  const int nz = min(R.tz, d0 + 1 - pz0);  // cube planes
+  const int np = nz + 2, nw = 258 + 2 * G;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const uint32_t* bits = B.bits + R.bits_begin;
+  // thread t holds the tile's words t, t + 256, ... of every plane: the rows
+  // are found once, and a plane's words are read together
+  for (int i = tid; i < nw; i += 256) {
+    const int rgi = rg0 - 1 + i;
+    const int ryi = rgi < 0 ? 0 : (int)fdiv((unsigned int)rgi, R.mG, R.shG);
+    const int y = ryi - 1, x = 32 * (rgi - ryi * G);
+    const int left = rgi >= 0 && (unsigned)y < (unsigned)d1 ? d2 - x : 0;
+    const unsigned int at = (unsigned int)y * (unsigned int)d2 + (unsigned int)x;
 #pragma unroll
-  for (int h = 0; h < kPer; h += 8) {
-    float v[8][4];
-    bool ok[8][4];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const unsigned int l = l0 + 256u * (h + k);
-      const unsigned int c0 = fdiv(l, R->m_cplane, R->sh_cplane);
-      const unsigned int r = l - c0 * (unsigned int)((d[1] + 1) * (d[2] + 1));
-      const unsigned int c1 = fdiv(r, R->m_c2, R->sh_c2);
-      const int u0 = (int)c0 - 1, u1 = (int)c1 - 1, u2 = (int)(r - c1 * (unsigned int)(d[2] + 1)) - 1;
-      const bool in_rng = l < R->n_cubes;
-      const bool lo0 = u0 >= 0, lo1 = u1 >= 0, lo2 = u2 >= 0;
-      // voxel index of u, with each coordinate clamped to 0 (the +axis
-      // neighbours below step from it; a clamped axis means that neighbour
-      // is the voxel at 0 on that axis)
-      const unsigned int iv = in_rng ? ((unsigned int)max(u0, 0) * d[1] + max(u1, 0)) * d[2] + max(u2, 0) : 0u;
-      ok[k][0] = in_rng && lo0 && lo1 && lo2;
-      ok[k][1] = in_rng && u0 + 1 < d[0] && lo1 && lo2;
-      ok[k][2] = in_rng && lo0 && u1 + 1 < d[1] && lo2;
-      ok[k][3] = in_rng && lo0 && lo1 && u2 + 1 < d[2];
-      // neighbours along +axis: +plane, +d2, +1 (clamped to iv when outside)
-      v[k][0] = p[iv];
-      v[k][1] = p[ok[k][1] ? iv + plane - (lo0 ? 0u : plane) : 0u];
-      v[k][2] = p[ok[k][2] ? iv + (unsigned int)d[2] - (lo1 ? 0u : (unsigned int)d[2]) : 0u];
-      v[k][3] = p[ok[k][3] ? iv + 1u - (lo2 ? 0u : 1u) : 0u];
+    for (int p = 0; p < kTZ + 2; ++p) {
+      const int z = pz0 - 1 + p;
+      if (p < np)
+        s_bits[p * nw + i] =
+            cut_word(bits, (unsigned int)z * (unsigned int)(d1 * d2) + at, (unsigned)z < (unsigned)d0 ? left : 0);
     }
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const bool c = ok[k][0] && v[k][0] > 0.5f;
-      const unsigned long long b = (unsigned long long)((ok[k][1] && v[k][1] > 0.5f) != c) |
-                                   ((unsigned long long)((ok[k][2] && v[k][2] > 0.5f) != c) << 1) |
-                                   ((unsigned long long)((ok[k][3] && v[k][3] > 0.5f) != c) << 2);
-      bits |= (l0 + 256u * (h + k) < R->n_cubes ? b : 0ull) << (3 * (h + k));
-    }
-  }
-  int total;
-  const int off = block_excl_scan256(__popcll(bits), s_scan, total);
-  if (threadIdx.x == 0) {
-    long long base = 0;
-    if (total > 0) base = (long long)atomicAdd((unsigned long long*)B.counters, (unsigned long long)total);
-    base_sh = base + total <= B.cap ? base : -1;  // -1: no room (the input differs from the forward pass)
   }
   __syncthreads();
-  const long long base = base_sh;
-  if (base < 0) return;
-  long long slot = base + off;
-  while (bits) {
-    const int i = __ffsll((long long)bits) - 1;
-    bits &= bits - 1ull;
-    const int k = i / 3, a = i - 3 * k;
-    B.edges[slot++] = ((unsigned long long)roi << 40) | (3ull * (l0 + 256u * k) + (unsigned long long)a);
+
+  const int rg = rg0 + tid;
+  const bool valid = rg < R.nrg;
+  const int ry = valid ? (int)fdiv((unsigned int)rg, R.mG, R.shG) : 0;
+  const int l = valid ? rg - ry * G : 0;
+  const int kmax = d2 - 32 * l;  // cubes 0 .. kmax of the group, voxels 0 .. kmax - 1
+  const uint32_t cmask = !valid ? 0u : (kmax >= 31 ? 0xffffffffu : (1u << (kmax + 1)) - 1u);
+  const uint32_t vmask = !valid || ry >= d1 ? 0u : (kmax >= 32 ? 0xffffffffu : (1u << kmax) - 1u);
+  uint32_t act[kTZ], vox[kTZ];
+  int n_c = 0, n_v = 0, n_e = 0;
+#pragma unroll
+  for (int p = 0; p < kTZ; ++p) {
+    act[p] = 0u;
+    vox[p] = 0u;
+    if (p >= nz || !valid) continue;
+    const uint32_t* w0 = s_bits + p * nw + tid + 1;  // plane z, row y
+    const uint32_t* w1 = w0 + nw;                    // plane z + 1
+    const uint32_t r00 = w0[0], r01 = w0[G], r10 = w1[0], r11 = w1[G];
+    const uint32_t x00 = l > 0 ? w0[-1] >> 31 : 0u, x01 = l > 0 ? w0[G - 1] >> 31 : 0u;
+    const uint32_t x10 = l > 0 ? w1[-1] >> 31 : 0u, x11 = l > 0 ? w1[G - 1] >> 31 : 0u;
+    const uint32_t a00 = r00 << 1 | x00, a01 = r01 << 1 | x01, a10 = r10 << 1 | x10, a11 = r11 << 1 | x11;
+    act[p] = (a00 | r00 | a01 | r01 | a10 | r10 | a11 | r11) & ~(a00 & r00 & a01 & r01 & a10 & r10 & a11 & r11) & cmask;
+    n_e += __popc((a00 ^ a10) & cmask) + __popc((a00 ^ a01) & cmask) + __popc((a00 ^ r00) & cmask);
+    // the voxel row (z + 1, y + 1) against its six neighbours
+    const uint32_t next = l + 1 < G ? w1[G + 1] << 31 : 0u;
+    vox[p] = ((r11 ^ a11) | (r11 ^ (r11 >> 1 | next)) | (r11 ^ r10) | (r11 ^ w1[2 * G]) | (r11 ^ r01) |
+              (r11 ^ w1[nw + G])) &
+             (pz0 + p < d0 ? vmask : 0u);
+    n_c += __popc(act[p]);
+    n_v += __popc(vox[p]);
+  }
+  int total_c, total_v, total_e;
+  int off_c = block_excl_scan256(n_c, s_scan, total_c);
+  int off_v = block_excl_scan256(n_v, s_scan, total_v);
+  (void)block_excl_scan256(n_e, s_scan, total_e);
+  if (tid == 0) {
+    unsigned long long* ctr = (unsigned long long*)B.counters;
+    if (total_e) atomicAdd(&ctr[C_EDGES], (unsigned long long)total_e);
+    // one reservation for both lists (the workgroups' atomics on one address
+    // serialise, about 20 ns each), unless a count could pass 32 bits
+    if (B.packed) {
+      const unsigned long long both = (unsigned long long)total_v << 32 | (unsigned int)total_c;
+      const unsigned long long got = both ? atomicAdd(&ctr[C_BOTH], both) : 0ull;
+      s_base[0] = (long long)(got & 0xffffffffull);
+      s_base[1] = (long long)(got >> 32);
+    } else {
+      s_base[0] = total_c ? (long long)atomicAdd(&ctr[C_CUBES], (unsigned long long)total_c) : 0;
+      s_base[1] = total_v ? (long long)atomicAdd(&ctr[C_VOX], (unsigned long long)total_v) : 0;
+    }
+  }
+  __syncthreads();
+  const long long base_c = s_base[0], base_v = s_base[1];
+  // a word's place, and the flat index of its first cube in plane pz0
+  const int place = ry | l << 20;
+  const int cube0 = (pz0 * (d1 + 1) + ry) * (d2 + 1) + 32 * l, cplane = (d1 + 1) * (d2 + 1);
+  unsigned int* index = B.index + R.cube_begin;
+#pragma unroll
+  for (int p = 0; p < kTZ; ++p) {
+    emit_words(act[p], off_c, cube0 + p * cplane, place, lane, [&](int k, int at, int cube, int pl) {
+      const long long idx = base_c + at;
+      if (idx >= B.cap_cubes) return;  // more cubes than the forward pass's vertices allow: the call fails
+      B.cubes[idx] = pack_vox(pz0 - 1 + p, (pl & 0xfffff) - 1, 32 * (pl >> 20) - 1 + k);
+      B.croi[idx] = roi;
+      index[cube + k] = (unsigned int)idx;
+    });
+    emit_words(vox[p], off_v, 0, place, lane, [&](int k, int at, int, int pl) {
+      const long long idx = base_v + at;
+      if (idx >= B.cap_vox) return;
+      B.vox[idx] = pack_vox(pz0 + p, pl & 0xfffff, 32 * (pl >> 20) + k);
+      B.vroi[idx] = roi;
+    });
   }
 }
 
-__global__ __launch_bounds__(256, 3) void k_soft_vertex_grad(SoftBwdBufs B) {
-  // the case table in LDS: its lookups depend on one another (case, then
-  // triangle, then edge); per case and edge, the triangles that hold the edge
-  __shared__ uint8_t s_tmask[256 * 12];
+// Pass 2.  A thread per active cube; its corner values and the sums of its 12
+// edges in LDS (indexed at run time).
+constexpr int kCubeThreads = 256;
+
+__global__ __launch_bounds__(kCubeThreads, 4) void k_soft_cubes(SoftBwdBufs B) {
+  __shared__ double s_g[12][kCubeThreads];
+  __shared__ float s_p[8][kCubeThreads];
   __shared__ uint8_t s_tri[256 * MC_MAX_TRI * 3];
-  for (int i = threadIdx.x; i < 256 * MC_MAX_TRI * 3; i += blockDim.x) s_tri[i] = (&MC_TRI[0][0][0])[i];
-  for (int i = threadIdx.x; i < 256 * 12; i += blockDim.x) {
-    const int c = i / 12, e = i - 12 * c;
-    unsigned int m = 0u;
-    for (int t = 0; t < MC_NTRI[c]; ++t)
-      if (MC_TRI[c][t][0] == e || MC_TRI[c][t][1] == e || MC_TRI[c][t][2] == e) m |= 1u << t;
-    s_tmask[i] = (uint8_t)m;
+  __shared__ uint8_t s_nt[256];
+  __shared__ uint32_t s_edge[12];  // axis | corner 0 << 2 | corner 1 << 5
+  const int tid = threadIdx.x;
+  for (int i = tid; i < 256 * MC_MAX_TRI * 3; i += blockDim.x) s_tri[i] = (&MC_TRI[0][0][0])[i];
+  for (int i = tid; i < 256; i += blockDim.x) s_nt[i] = MC_NTRI[i];
+  if (tid < 12) {
+    const uint32_t a = MC_EDGE_AXIS[tid], k0 = MC_EDGE_C0[tid];
+    s_edge[tid] = a | k0 << 2 | (k0 | 4u >> a) << 5;
   }
   __syncthreads();
-  const long long n = min(B.counters[0], B.cap);
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (long long)gridDim.x * blockDim.x) {
-    const unsigned long long entry = B.edges[i];
-    const unsigned int roi = (unsigned int)(entry >> 40);
-    const unsigned long long local = entry & ((1ull << 40) - 1ull);
-    // an entry no block wrote (only when the input has more crossing edges
-    // than the forward pass: the call then fails) must not address memory
-    if (roi >= (unsigned int)B.n_rois) continue;
-    const SoftBwdRoi* R = B.rois + roi;
-    if (local >= 3ull * R->n_cubes) continue;
-    const long long slot = R->field_begin + (long long)local;
-    // local = 3 cube(u) + a with cube(u) < 2^31: 32-bit decoding
-    const unsigned int l32 = (unsigned int)local;
-    const unsigned int cube = l32 / 3u;
-    const int a = (int)(l32 - 3u * cube);
-    const unsigned int c0 = fdiv(cube, R->m_cplane, R->sh_cplane);
-    const unsigned int r = cube - c0 * (unsigned int)((R->d[1] + 1) * (R->d[2] + 1));
-    const unsigned int c1 = fdiv(r, R->m_c2, R->sh_c2);
-    const int u0 = (int)c0 - 1, u1 = (int)c1 - 1, u2 = (int)(r - c1 * (unsigned int)(R->d[2] + 1)) - 1;
-    double gx[3] = {0.0, 0.0, 0.0};
-    vertex_grad_mesh(R->p, R->d, R->s, R->o, u0, u1, u2, a, R->g_area, R->g_vol_signed, s_tmask, s_tri, gx);
-    const long long id = 3ll * ((((long long)(u0 + 1)) * (R->d[1] + 2) + (u1 + 1)) * (long long)(R->d[2] + 2) +
-                                (u2 + 1)) +
-                         a;
-    for (int f = 0; f < 4; ++f) {
-      const double gd = R->gdiam[f];
-      if (gd == 0.0) continue;
-      const long long i_id = R->pair_ids[f][0], j_id = R->pair_ids[f][1];
-      if (id != i_id && id != j_id) continue;
-      const long long other = id == i_id ? j_id : i_id;
-      const long long lin = other / 3;
-      const int oa = (int)(other % 3);
-      const int o2 = (int)(lin % (R->d[2] + 2)) - 1;
-      const long long l2 = lin / (R->d[2] + 2);
-      const int o1 = (int)(l2 % (R->d[1] + 2)) - 1;
-      const int o0 = (int)(l2 / (R->d[1] + 2)) - 1;
-      double xv[3], xo[3];
-      vertex_pos(R->p, R->d, R->s, R->o, u0, u1, u2, a, xv);
-      vertex_pos(R->p, R->d, R->s, R->o, o0, o1, o2, oa, xo);
-      // dD/dx_v = (x_v - x_other) / D for either end point
-      for (int c = 0; c < 3; ++c) gx[c] += gd * (xv[c] - xo[c]);
+  const long long n = listed_cubes(B);
+  for (long long i = (long long)blockIdx.x * blockDim.x + tid; i < n; i += (long long)gridDim.x * blockDim.x) {
+    const unsigned long long key = B.cubes[i];
+    const SoftBwdRoi& R = B.rois[B.croi[i]];
+    const int u0 = vox0(key), u1 = vox1(key), u2 = vox2(key);
+    float pc[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) pc[k] = pld(R.p, R.d, u0 + (k >> 2 & 1), u1 + (k >> 1 & 1), u2 + (k & 1));
+    int cas = 0;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      cas |= (int)(pc[k] > 0.5f) << k;
+      s_p[k][tid] = pc[k];
     }
-    const double pu = pval(R->p, R->d, u0, u1, u2);
-    const double pb = pval(R->p, R->d, u0 + (a == 0), u1 + (a == 1), u2 + (a == 2));
-    const double den = pb - pu;  // at least one float ulp at 0.5: a crossing edge straddles it
-    B.field[slot] = (float)(gx[a] * R->s[a] / (den * den));
+#pragma unroll
+    for (int e = 0; e < 12; ++e) s_g[e][tid] = 0.0;
+    const double ga = 0.5 * R.g_area, gv = R.g_vol_signed / 6.0;
+    const double sx = R.s[0], sy = R.s[1], sz = R.s[2];
+    const double bx = (double)u0 * sx - R.o[0], by = (double)u1 * sy - R.o[1], bz = (double)u2 * sz - R.o[2];
+    auto vertex = [&](uint32_t ed) -> D3 {
+      const int ax = (int)(ed & 3u), k0 = (int)(ed >> 2 & 7u), k1 = (int)(ed >> 5);
+      const double p0 = (double)s_p[k0][tid], p1 = (double)s_p[k1][tid];
+      const double t = (0.5 - p0) * rcp64(p1 - p0);
+      return {bx + (ax == 0 ? t : (double)(k0 >> 2 & 1)) * sx, by + (ax == 1 ? t : (double)(k0 >> 1 & 1)) * sy,
+              bz + (ax == 2 ? t : (double)(k0 & 1)) * sz};
+    };
+    const int nt = s_nt[cas];
+    for (int t = 0; t < nt; ++t) {
+      const uint8_t* tr = s_tri + (cas * MC_MAX_TRI + t) * 3;
+      const int e0 = tr[0], e1 = tr[1], e2 = tr[2];
+      const uint32_t d0 = s_edge[e0], d1 = s_edge[e1], d2 = s_edge[e2];
+      const D3 P0 = vertex(d0), P1 = vertex(d1), P2 = vertex(d2);
+      const D3 n3 = cross3(sub3(P1, P0), sub3(P2, P0));
+      const double len = sqrt(n3.x * n3.x + n3.y * n3.y + n3.z * n3.z);
+      const double il = len > 0.0 ? ga * rcp64(len) : 0.0;
+      const D3 nh = {n3.x * il, n3.y * il, n3.z * il};
+      // the vertex's own edge axis of ga nhat x (c - b) + gv b x c
+      auto term = [&](const D3& b, const D3& c, uint32_t ed) {
+        const D3 r = cross3(nh, sub3(c, b)), q = cross3(b, c);
+        const int ax = (int)(ed & 3u);
+        return axis_of(r, ax) + gv * axis_of(q, ax);
+      };
+      s_g[e0][tid] += term(P1, P2, d0);
+      s_g[e1][tid] += term(P2, P0, d1);
+      s_g[e2][tid] += term(P0, P1, d2);
+    }
+    double* out = B.cgrad + 12 * i;
+#pragma unroll
+    for (int e = 0; e < 12; ++e) {
+      constexpr uint8_t c0[12] = {0, 1, 2, 3, 0, 1, 4, 5, 0, 2, 4, 6};
+      const int k0 = c0[e], k1 = k0 | 4 >> (e >> 2);
+      if ((cas >> k0 ^ cas >> k1) & 1) out[e] = s_g[e][tid];
+    }
   }
 }
 
-// dL/dp of voxel w from its value vc and its six neighbours nv (indexed
-// 2a + (neighbour is w + e_a)); slot_w is the field slot of edge (w, axis 0)
-// and stride[a] the slot distance between the edges (w - e_a, a) and (w, a).
-__device__ inline double voxel_grad(const float* __restrict__ field, long long slot_w, const long long* stride,
-                                    float vc, const float* nv) {
-  const bool in_w = vc > 0.5f;
-  bool cross[6];
-  bool any = false;
-#pragma unroll
-  for (int j = 0; j < 6; ++j) {
-    cross[j] = (nv[j] > 0.5f) != in_w;
-    any |= cross[j];
+// The diameters' terms g_f (x_v - x_other)_a / D_f at both ends of their pairs,
+// added to the cube above each end's edge (the first of its four).  Eight lanes
+// per ROI, one per end; ends on one edge are summed in lane order by the first.
+__global__ __launch_bounds__(64) void k_soft_diam(SoftBwdBufs B) {
+  const int lane = threadIdx.x & 63, j = lane & 7, f = j >> 1;
+  const int roi = (int)blockIdx.x * 8 + (lane >> 3);
+  long long id = -1;
+  double term = 0.0;
+  long long at = -1;
+  if (roi < B.n_rois) {
+    const SoftBwdRoi& R = B.rois[roi];
+    const double gd = R.gdiam[f];
+    if (gd != 0.0) {
+      id = R.pair_ids[f][j & 1];
+      const long long ids[2] = {id, R.pair_ids[f][1 - (j & 1)]};
+      double x[2][3];
+      int u[3], a = 0;
+      for (int e = 0; e < 2; ++e) {
+        const long long lin = ids[e] / 3;
+        const int ea = (int)(ids[e] % 3);
+        const int e2 = (int)(lin % (R.d[2] + 2)) - 1;
+        const long long l2 = lin / (R.d[2] + 2);
+        const int e1 = (int)(l2 % (R.d[1] + 2)) - 1, e0 = (int)(l2 / (R.d[1] + 2)) - 1;
+        vertex_pos(R.p, R.d, R.s, R.o, e0, e1, e2, ea, x[e]);
+        if (e == 0) {
+          u[0] = e0;
+          u[1] = e1;
+          u[2] = e2;
+          a = ea;
+        }
+      }
+      term = gd * (x[0][a] - x[1][a]);
+      // (a saved context of other probabilities may name an edge outside the grid)
+      if (u[0] >= -1 && u[0] < R.d[0] && u[1] >= -1 && u[1] < R.d[1] && u[2] >= -1 && u[2] < R.d[2]) {
+        const unsigned int idx = B.index[R.cube_begin + cube_index(R.d, u[0], u[1], u[2])];
+        if ((long long)idx < listed_cubes(B)) at = 12ll * idx + 4 * a;
+      }
+    }
   }
-  double g = 0.0;
-  if (__ballot(any)) {
-    // every lane loads all six slots (its own edge (w, 0) stands in where an
-    // edge does not cross), so the loads issue together
-    float q[6];
+  double sum = 0.0;
+  bool first = true;
+  for (int k = 0; k < 8; ++k) {
+    const int src = (lane & ~7) + k;
+    const long long oid = __shfl(id, src, 64);
+    const double ot = __shfl(term, src, 64);
+    if (oid == id) {
+      sum += ot;
+      if (k < j) first = false;
+    }
+  }
+  if (at >= 0 && first) B.cgrad[at] += sum;
+}
+
+// Pass 3.  Per active cube and axis, the sum over the four cubes around the
+// edge from its min corner (if that edge crosses), in a fixed order.
+__global__ __launch_bounds__(256) void k_soft_edges(SoftBwdBufs B) {
+  const long long n = listed_cubes(B);
+  const unsigned int n_cubes = (unsigned int)n;
+  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x) {
+    const unsigned long long key = B.cubes[i];
+    const SoftBwdRoi& R = B.rois[B.croi[i]];
+    const int u0 = vox0(key), u1 = vox1(key), u2 = vox2(key);
+    const float f0 = pld(R.p, R.d, u0, u1, u2);
+    const float fa[3] = {pld(R.p, R.d, u0 + 1, u1, u2), pld(R.p, R.d, u0, u1 + 1, u2), pld(R.p, R.d, u0, u1, u2 + 1)};
+    const long long cs[3] = {(long long)(R.d[1] + 1) * (R.d[2] + 1), R.d[2] + 1, 1};
+    const unsigned int* index = B.index + R.cube_begin + cube_index(R.d, u0, u1, u2);
+    bool cross[3];
+    unsigned int idx[3][3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      cross[a] = (f0 > 0.5f) != (fa[a] > 0.5f);
+      // a crossing edge lies inside the grid along its other axes: so do its cubes
+      const long long sb = cs[a == 0 ? 1 : 0], sc = cs[a == 2 ? 1 : 2];
+      if (cross[a]) {
+        idx[a][0] = index[-sc];
+        idx[a][1] = index[-sb];
+        idx[a][2] = index[-sb - sc];
+      }
+    }
+    double part[3][4];
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+      if (cross[a]) {
+        part[a][0] = B.cgrad[12 * i + 4 * a];
+#pragma unroll
+        for (int q = 1; q < 4; ++q)
+          part[a][q] = idx[a][q - 1] < n_cubes ? B.cgrad[12ll * idx[a][q - 1] + 4 * a + q] : 0.0;
+      }
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+      if (cross[a]) {
+        const double den = (double)fa[a] - (double)f0;  // at least one float ulp at 0.5: the edge straddles it
+        B.egrad[3 * i + a] =
+            (float)((((part[a][0] + part[a][1]) + part[a][2]) + part[a][3]) * R.s[a] / (den * den));
+      }
+  }
+}
+
+// Pass 4.  A thread per voxel at a crossing edge: its edges' values times the
+// rest of dt/dp.
+__global__ __launch_bounds__(256) void k_soft_voxels(SoftBwdBufs B) {
+  const long long n = listed_vox(B);
+  const unsigned int n_cubes = (unsigned int)listed_cubes(B);
+  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x) {
+    const unsigned long long key = B.vox[i];
+    const SoftBwdRoi& R = B.rois[B.vroi[i]];
+    const int w[3] = {vox0(key), vox1(key), vox2(key)};
+    const size_t at = ((size_t)w[0] * R.d[1] + w[1]) * (size_t)R.d[2] + w[2];
+    const size_t step[3] = {(size_t)R.d[1] * R.d[2], (size_t)R.d[2], 1};
+    const float vc = R.p[at];
+    float nv[6];
 #pragma unroll
     for (int j = 0; j < 6; ++j) {
-      const int a = j >> 1;
-      const long long sl = slot_w + a - ((j & 1) ? 0 : stride[a]);
-      q[j] = field[cross[j] ? sl : slot_w];
+      const int k = j >> 1;
+      const bool ok = j & 1 ? w[k] + 1 < R.d[k] : w[k] > 0;
+      const float v = R.p[ok ? (j & 1 ? at + step[k] : at - step[k]) : at];
+      nv[j] = ok ? v : 0.0f;
     }
+    // the cube at each edge's lower end (j & 1: the voxel itself), then the edge
+    const unsigned int* index = B.index + R.cube_begin + cube_index(R.d, w[0], w[1], w[2]);
+    const long long cs[3] = {(long long)(R.d[1] + 1) * (R.d[2] + 1), R.d[2] + 1, 1};
+    bool cross[6], any_up = false;
+    unsigned int idx[6], here = 0u;
 #pragma unroll
     for (int j = 0; j < 6; ++j) {
-      if (!cross[j]) continue;
-      const bool up = j & 1;  // the neighbour is w + e_a (w is the edge's lower end)
-      // the field holds (dL/dx_v)_a s_a / (p_b - p_u)^2; times dt/dp_w (p_b - p_u)^2
-      g += (double)q[j] * (up ? 0.5 - (double)nv[j] : -(0.5 - (double)nv[j]));
+      cross[j] = (nv[j] > 0.5f) != (vc > 0.5f);
+      any_up |= cross[j] && (j & 1);
+      idx[j] = ~0u;
+      if (cross[j] && !(j & 1)) idx[j] = index[-cs[j >> 1]];
     }
-  }
-  return g;
-}
-
-// Pass 3.  kVoxPer voxels per thread, 256 apart (flat index over the ROI,
-// kVoxBlock per workgroup, so each load instruction of a wave reads 64
-// consecutive floats), all 7 loads of each issued together; the voxel's
-// crossing edges read their values from the edge field and dL/dp is written
-// densely.
-__global__ __launch_bounds__(256) void k_soft_gather(SoftBwdBufs B) {
-  const SoftBwdRoi* R =
-      B.rois + (B.blk_roi ? B.blk_roi[B.n_cblocks + blockIdx.x] : soft_roi_of_vblk(B.rois, B.n_rois, blockIdx.x));
-  const unsigned int l0 = (unsigned int)(blockIdx.x - R->vblk_begin) * kVoxBlock + threadIdx.x;
-  if (l0 >= R->n_vox) return;
-  const int* d = R->d;
-  const float* p = R->p;
-  const unsigned int plane = (unsigned int)d[1] * d[2];
-  const long long stride[3] = {3ll * (d[1] + 1) * (d[2] + 1), 3ll * (d[2] + 1), 3};
-  float vc[kVoxPer], nv[kVoxPer][6];
-  long long slot[kVoxPer];
+    if (any_up) here = *index;
+    float e[6];
 #pragma unroll
-  for (int j = 0; j < kVoxPer; ++j) {
-    // voxels past the ROI's end repeat its last voxel (loaded, not written)
-    const unsigned int l = min(l0 + 256u * j, R->n_vox - 1u);
-    const unsigned int w0 = fdiv(l, R->m_plane, R->sh_plane);
-    const unsigned int r = l - w0 * plane;
-    const unsigned int w1 = fdiv(r, R->m_d2, R->sh_d2);
-    const unsigned int x = r - w1 * (unsigned int)d[2];
-    const bool zm = w0 > 0, zp = w0 + 1 < (unsigned int)d[0], ym = w1 > 0, yp = w1 + 1 < (unsigned int)d[1];
-    const bool xm = x > 0, xp = x + 1 < (unsigned int)d[2];
-    vc[j] = p[l];
-    nv[j][0] = p[zm ? l - plane : l];
-    nv[j][1] = p[zp ? l + plane : l];
-    nv[j][2] = p[ym ? l - d[2] : l];
-    nv[j][3] = p[yp ? l + d[2] : l];
-    nv[j][4] = p[xm ? l - 1 : l];
-    nv[j][5] = p[xp ? l + 1 : l];
-    nv[j][0] = zm ? nv[j][0] : 0.0f;
-    nv[j][1] = zp ? nv[j][1] : 0.0f;
-    nv[j][2] = ym ? nv[j][2] : 0.0f;
-    nv[j][3] = yp ? nv[j][3] : 0.0f;
-    nv[j][4] = xm ? nv[j][4] : 0.0f;
-    nv[j][5] = xp ? nv[j][5] : 0.0f;
-    // field slot of edge (w, axis 0): 3 * cube(w)
-    slot[j] = R->field_begin + 3ll * (((long long)(w0 + 1) * (d[1] + 1) + (w1 + 1)) * (d[2] + 1) + (x + 1));
-  }
+    for (int j = 0; j < 6; ++j) {
+      e[j] = 0.0f;
+      const unsigned int c = j & 1 ? here : idx[j];
+      if (cross[j] && c < n_cubes) e[j] = B.egrad[3ll * c + (j >> 1)];
+    }
+    double g = 0.0;
 #pragma unroll
-  for (int j = 0; j < kVoxPer; ++j) {
-    const float g = (float)voxel_grad(B.field, slot[j], stride, vc[j], nv[j]);
-    if (l0 + 256u * j < R->n_vox) R->grad[l0 + 256u * j] = g;
+    for (int j = 0; j < 6; ++j)
+      if (cross[j]) g += (double)e[j] * (j & 1 ? 0.5 - (double)nv[j] : -(0.5 - (double)nv[j]));
+    R.grad[at] = (float)g;
   }
 }
 
-// The ROI of every workgroup of the edge and gather passes (one workgroup per
-// ROI writes its two contiguous block ranges).
-__global__ void k_soft_block_rois(SoftBwdBufs B) {
-  int* blk_roi = B.blk_roi;
+// The ROI of every workgroup of the scan and of the bit pass (one workgroup per
+// ROI writes its ranges), and the cleared counters.
+__global__ void k_soft_head(SoftBwdBufs B) {
+  if (blockIdx.x == 0 && threadIdx.x < 4) B.counters[threadIdx.x] = 0;
+  if (!B.blk_roi) return;
+  const bool last = (int)blockIdx.x + 1 == B.n_rois;
   const SoftBwdRoi& R = B.rois[blockIdx.x];
-  const long long nc = ((long long)R.n_cubes + kCubeBlock - 1) / kCubeBlock;
-  const long long nv = ((long long)R.n_vox + kVoxBlock - 1) / kVoxBlock;
-  for (long long i = threadIdx.x; i < nc; i += blockDim.x) blk_roi[R.cblk_begin + i] = (int)blockIdx.x;
-  for (long long i = threadIdx.x; i < nv; i += blockDim.x) blk_roi[B.n_cblocks + R.vblk_begin + i] = (int)blockIdx.x;
+  const long long e = last ? B.n_bricks : B.rois[blockIdx.x + 1].brick_begin;
+  for (long long i = R.brick_begin + threadIdx.x; i < e; i += blockDim.x) B.blk_roi[i] = (int)blockIdx.x;
+  const long long eb = last ? B.n_bitblks : B.rois[blockIdx.x + 1].bitblk_begin;
+  for (long long i = R.bitblk_begin + threadIdx.x; i < eb; i += blockDim.x) B.blk_roi[B.n_bricks + i] = (int)blockIdx.x;
 }
 
 hipError_t launch_soft_backward(const SoftBwdBufs& B, hipStream_t st) {
-  hipError_t e;
-  if ((e = launch_fill_i64(B.counters, 0, 1, st))) return e;
-  if (B.blk_roi) hipLaunchKernelGGL(k_soft_block_rois, dim3((unsigned)B.n_rois), dim3(256), 0, st, B);
-  if (B.n_cblocks > 0) hipLaunchKernelGGL(k_soft_edges, dim3((unsigned)B.n_cblocks), dim3(256), 0, st, B);
-  if ((e = hipGetLastError())) return e;
-  long long g = (B.cap + 255) / 256;
-  const long long gcap = (long long)B.cu_count * 16;
-  if (g > gcap) g = gcap;
-  if (g > 0) hipLaunchKernelGGL(k_soft_vertex_grad, dim3((unsigned)g), dim3(256), 0, st, B);
-  if ((e = hipGetLastError())) return e;
-  if (B.n_vblocks > 0) hipLaunchKernelGGL(k_soft_gather, dim3((unsigned)B.n_vblocks), dim3(256), 0, st, B);
+  auto grid = [&](long long work, int threads, long long per_cu) {
+    return dim3((unsigned)std::max(1ll, std::min((work + threads - 1) / threads, per_cu * B.cu_count)));
+  };
+  hipLaunchKernelGGL(k_soft_head, dim3((unsigned)(B.blk_roi ? B.n_rois : 1)), dim3(256), 0, st, B);
+  hipLaunchKernelGGL(k_soft_bits, dim3((unsigned)B.n_bitblks), dim3(256), 0, st, B);
+  hipLaunchKernelGGL(k_soft_scan, dim3((unsigned)B.n_bricks), dim3(256), B.scan_lds, st, B);
+  if (B.cap_cubes > 0) {
+    // few cubes: waves of their own, so that they spread over the CUs
+    const int threads = B.cap_cubes < 65536 ? 64 : kCubeThreads;
+    hipLaunchKernelGGL(k_soft_cubes, grid(B.cap_cubes, threads, 16), dim3(threads), 0, st, B);
+    hipLaunchKernelGGL(k_soft_diam, dim3((unsigned)((B.n_rois + 7) / 8)), dim3(64), 0, st, B);
+    hipLaunchKernelGGL(k_soft_edges, grid(B.cap_cubes, 256, 32), dim3(256), 0, st, B);
+    hipLaunchKernelGGL(k_soft_voxels, grid(B.cap_vox, 256, 32), dim3(256), 0, st, B);
+  }
   return hipGetLastError();
 }
 

@@ -1,0 +1,82 @@
+"""GPU checks of the adjoint's passes (inside bits, lists of active cubes and
+surface voxels, cubes, edges, voxels) at the sizes where they can go wrong:
+rows around a multiple of 32 voxels, volumes around the bit pass's 8,192
+elements, one voxel along an axis, rows of many 32-cube groups, bricks with a
+plane left over, and a batch past the ROI count from which a table gives each
+workgroup its ROI.  The result is FP64 arithmetic rounded to float32 (2^-24
+relative) from vertex parameters of the same FP64 formula; 2e-6 of the largest
+entry, the bound of the other adjoint tests, is 16 such roundings."""
+import numpy as np
+import pytest
+
+from oracle import oracle as O
+
+pytestmark = pytest.mark.gpu
+
+SP = (1.1, 0.8, 0.95)
+GOUT = np.array([0.7, -0.3, 0.9, 0.4, -0.5, 0.6])
+
+
+@pytest.fixture(scope="module")
+def S():
+    import torch
+
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2510_02894_amd import shape3d
+
+    shape3d.load()
+    return shape3d
+
+
+def noise(shape, seed):
+    """Probabilities with a sparse surface at every border, none near 0.5 (where
+    the gradient has no bound)."""
+    g = np.random.default_rng(seed)
+    p = np.where(g.random(shape) < 0.3, 0.6 + 0.4 * g.random(shape), 0.4 * g.random(shape)).astype(np.float32)
+    p[0, 0, 0] = p[-1, -1, -1] = 0.9
+    return p
+
+
+SHAPES = [(1, 1, 1), (1, 1, 33), (2, 1, 1), (1, 5, 31), (3, 4, 32), (9, 5, 63), (7, 8, 64), (8, 3, 65), (17, 6, 30),
+          (8, 32, 32), (9, 30, 31), (1, 128, 64), (2, 3, 1030), (3, 300, 2), (40, 1, 3)]
+
+
+def gout_of(shape):
+    """A plate's or a rod's diameters tie between mirror images (no unique
+    subgradient): area and volume only."""
+    return GOUT if min(shape) > 1 else GOUT * (1, 1, 0, 0, 0, 0)
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_adjoint_at_edges(S, shape):
+    import torch
+
+    print("[case] adjoint %s" % (shape,), flush=True)
+    p = noise(shape, sum(shape))
+    t = torch.from_numpy(p).cuda()
+    _, saved = S.soft_forward(t, SP)
+    got = S.soft_backward(t, saved, gout_of(shape)).cpu().numpy().astype(np.float64)
+    exp = O.soft_grad(p, SP, gout_of(shape))
+    np.testing.assert_allclose(got, exp, rtol=2e-6, atol=2e-6 * np.abs(exp).max())
+
+
+def test_adjoint_batch_equals_single(S):
+    import torch
+
+    print("[case] adjoint batch", flush=True)
+    ps = [noise(s, 3 + i) for i, s in enumerate(SHAPES)]
+    offs = np.concatenate([[0], np.cumsum([p.size + 3 for p in ps])])[:-1]
+    buf = np.zeros(int(offs[-1]) + ps[-1].size, np.float32)
+    for o, p in zip(offs, ps):
+        buf[o:o + p.size] = p.reshape(-1)
+    base = torch.from_numpy(buf).cuda()
+    table = S.roi_table(offs, SHAPES, [SP] * len(ps))
+    gout = np.stack([gout_of(s) for s in SHAPES])
+    _, saved = S.batched_soft_forward(base, table)
+    grad = S.batched_soft_backward(base, table, saved, gout).cpu().numpy()
+    for i, p in enumerate(ps):
+        t = torch.from_numpy(p).cuda()
+        _, one = S.soft_forward(t, SP)
+        exp = S.soft_backward(t, one, gout[i]).cpu().numpy()
+        assert np.array_equal(grad[offs[i]:offs[i] + p.size].reshape(p.shape), exp), SHAPES[i]
