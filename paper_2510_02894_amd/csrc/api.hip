@@ -100,6 +100,7 @@ struct Workspace {
   long long generation = 0;  // bumped whenever a buffer is reallocated (graphs hold pointers)
   Buf buf[W_NUM];
   Buf blk[B_NUM];
+  Buf vol_bits, bit_map;  // the forward pass's bit strings
   Buf soft_rois, soft_cubes, soft_croi, soft_cgrad, soft_egrad, soft_vox, soft_vroi, soft_bits, soft_index, soft_ctr, soft_blk;  // soft backward
   void* host = nullptr;  // pinned staging: ROI table, read-backs, results
   size_t host_cap = 0;
@@ -285,6 +286,10 @@ int check_args(const void* vol, int dtype, const int64_t dims[3], const double s
   return check_device_span(vol, need, "volume");
 }
 
+// Voxels from which one ROI's bit pass takes kBitRounds rounds per workgroup (a
+// small one in such workgroups leaves CUs idle).
+constexpr long long kBitManyVoxels = 1ll << 24;
+
 // Host description of a batch: its ROIs (host tables), or only bounds on its
 // shape (tables planned on the device, `planned`).
 struct Batch {
@@ -296,6 +301,11 @@ struct Batch {
   int max_G = 1;
   bool planned = false;
   long long max_d[3] = {0, 0, 0};  // every ROI's dims are at most these
+  // the bit pass over dense ROIs without labels (host tables): elements per workgroup / kBitRound, its
+  // workgroups and 32-bit words; bits = false: a ROI is not of that kind
+  int bit_rounds = kBitRounds;
+  long long bit_blks = 0, bit_words = 0;
+  bool bits = true;
   bool moments = false;  // also the inside-voxel moments and the whole Shape class
   int n() const { return n_rois; }
   int nf() const { return moments ? SHAPE3D_N_CLASS : 6; }  // features per ROI in out
@@ -310,6 +320,12 @@ void batch_add(Batch& B, const void* vol, const int64_t dims[3], const double sp
   R.brick_begin = B.nbricks;
   R.brick_end = B.nbricks + nb;
   roi_set_buckets(R, B.n_buckets);
+  const long long vox = d[0] * d[1] * d[2];
+  B.bits = B.bits && vox < (1ll << 31) && label == 0 && R.stride1 == d[2] && R.stride0 == d[1] * d[2];
+  R.bits_begin = B.bit_words;
+  R.bitblk_begin = B.bit_blks;
+  B.bit_words += bit_words(vox);
+  B.bit_blks += bit_blocks(vox, B.bit_rounds * kBitRound);
   B.nbricks += nb;
   B.n_buckets += roi_buckets(R.d);
   B.max_G = std::max(B.max_G, R.G);
@@ -613,17 +629,17 @@ PairBufs pair_bufs(const Ptrs& P, const Batch& Bt, int dtype, const Sizes& S, in
 // The mesh pass (with the staging list's capacity in rows) and per-ROI
 // totals (launches only).
 // one: the ROI record of a call with one ROI, if it is not in W_ROIS yet.
-int launch_mesh(const Ptrs& P, const Batch& Bt, int dtype, long long tmp_cap, float4* pbox, const Roi* one,
-                hipStream_t st) {
+int launch_mesh(const Ptrs& P, const Batch& Bt, int dtype, long long tmp_cap, float4* pbox, const VolumeBits* vb,
+                const Roi* one, hipStream_t st) {
   HIPCK(launch_mesh_pass(dtype, P.as<Roi>(W_ROIS), Bt.n(), Bt.nbricks, Bt.max_G, P.as<double>(W_CASE_AREA),
                          P.as<BrickPart>(W_PART), P.as<unsigned int>(W_COUNTERS), kCounterWords,
                          P.as<unsigned long long>(W_TMPKEY), dtype == SHAPE3D_F32 ? P.as<double>(W_TMPT) : nullptr,
-                         tmp_cap, P.as<long long>(W_TOTALS), Bt.moments ? 1 : 0, P.as<int>(W_BRICK_ROI), pbox, one, st));
+                         tmp_cap, P.as<long long>(W_TOTALS), Bt.moments ? 1 : 0, P.as<int>(W_BRICK_ROI), pbox, vb, one, st));
   return SHAPE3D_OK;
 }
 
 int launch_head(const Ptrs& P, const Batch& Bt, int dtype, long long tmp_cap, hipStream_t st) {
-  const int rc = launch_mesh(P, Bt, dtype, tmp_cap, nullptr, nullptr, st);
+  const int rc = launch_mesh(P, Bt, dtype, tmp_cap, nullptr, nullptr, nullptr, st);
   if (rc) return rc;
   HIPCK(launch_mesh_totals(P.as<const Roi>(W_ROIS), Bt.n(), dtype, P.as<const double>(W_CASE_AREA),
                            P.as<const BrickPart>(W_PART),
@@ -787,6 +803,25 @@ int ensure_block_bufs(Workspace& w, const Batch& Bt, int dtype, long long rows, 
   return SHAPE3D_OK;
 }
 
+// The bit pass of a host table of soft masks, if its ROIs can have one: a brick
+// that reads the volume itself waits for its own few loads, unaligned where
+// rows are, and reads its neighbours' rows again (mesh pass of 256 ROIs of edges
+// 48 to 160: 787 us, after a bit pass of 218 us 460; 256^3: 101 against 13 + 92;
+// 96^3: 46 against 3 + 38).  A uint8 brick reads a quarter of the bytes and is
+// bound by its instructions (300 x 512 x 512: 55 us, after a bit pass of 15 us 51).
+bool wants_bits(const Batch& Bt, int dtype) { return dtype == SHAPE3D_F32 && Bt.bits && !Bt.planned; }
+
+int ensure_bits(Workspace& w, const Batch& Bt, int dtype) {
+  if (!wants_bits(Bt, dtype)) return SHAPE3D_OK;
+  const int rc = ensure(w, w.vol_bits, sizeof(uint32_t) * (size_t)Bt.bit_words);
+  return rc ? rc : ensure(w, w.bit_map, sizeof(int) * (size_t)Bt.bit_blks);
+}
+
+const VolumeBits* volume_bits(const Workspace& w, const Batch& Bt, int dtype, VolumeBits& vb) {
+  vb = VolumeBits{(uint32_t*)w.vol_bits.p, (int*)w.bit_map.p, Bt.bit_blks, Bt.bit_rounds};
+  return wants_bits(Bt, dtype) ? &vb : nullptr;
+}
+
 struct BlockPtrs {
   void* p[B_NUM];
   template <typename T>
@@ -868,7 +903,8 @@ int run_blocks(Workspace& w, const Batch& Bt, int dtype, hipStream_t st, RoiResu
                float* phase_ms, const DevTable* dt = nullptr) {
   BlockSizes Z;
   int rc = ensure_block_bufs(w, Bt, dtype, block_guess(Bt), 0, Z);
-  if (rc) return rc;
+  if (rc || (!dt && (rc = ensure_bits(w, Bt, dtype)))) return rc;
+  VolumeBits vb;
   long long* th = (long long*)w.host;
   // a few results go to the host as they are written, many in one copy
   const bool direct = host_res && Bt.n() <= 16;
@@ -878,7 +914,8 @@ int run_blocks(Workspace& w, const Batch& Bt, int dtype, hipStream_t st, RoiResu
     const Ptrs P = w.ptrs();
     if (!one && (rc = upload_rois(w, P, Bt, dtype, dt, st))) return rc;
     if (timing) HIPCK(hipEventRecord(w.ev[0], st));
-    if ((rc = launch_mesh(P, Bt, dtype, Z.rows, (float4*)w.blk[B_PBOX].p, one, st))) return rc;
+    if ((rc = launch_mesh(P, Bt, dtype, Z.rows, (float4*)w.blk[B_PBOX].p, dt ? nullptr : volume_bits(w, Bt, dtype, vb), one, st)))
+      return rc;
     if (timing) HIPCK(hipEventRecord(w.ev[1], st));
     if ((rc = launch_block_list(P, block_ptrs(w), Z, Bt, dtype, st))) return rc;
     if (!host_res) {
@@ -990,7 +1027,7 @@ int run_fixed(const Batch& Bt0, const Batch* thin, int dtype, const DevTable* dt
     HIPCK(launch_set_roi(*one_roi, P.as<Roi>(W_ROIS), st));
   }
   if (blocks) {
-    if ((rc = launch_mesh(P, Bt, dtype, Z.rows, Q.as<float4>(B_PBOX), one_roi, st))) return rc;
+    if ((rc = launch_mesh(P, Bt, dtype, Z.rows, Q.as<float4>(B_PBOX), nullptr, one_roi, st))) return rc;
     if ((rc = launch_block_list(P, Q, Z, Bt, dtype, st))) return rc;
     if ((rc = launch_block_tail(P, Q, Z, Bt, dtype, cap, false, true, cu_count, P.as<RoiResult>(W_RES), st, nullptr)))
       return rc;
@@ -1077,6 +1114,7 @@ int shape3d_impl(const void* vol, int dtype, const int64_t dims[3], const double
   Workspace& w = *wp;
   Batch Bt;
   Bt.moments = moments;
+  if (dims[0] * dims[1] * dims[2] < kBitManyVoxels) Bt.bit_rounds = 1;
   batch_add(Bt, vol, dims, spacing, 0, 0, 0, block_path() ? single_tz(dtype, dims) : kTZ);
   if ((rc = ensure_layout_bufs(w, Bt, dtype))) return rc;
   RoiResult* hres = host_results(w, Bt);
@@ -1134,6 +1172,8 @@ int capture_graph(Workspace& w, const Batch& Bt, int dtype, hipStream_t st, Grap
   BlockSizes Z;
   int rc0 = blocks ? ensure_block_bufs(w, Bt, dtype, staged_rows(Bt, w.last_rows0), 0, Z)
                    : ensure_staging(w, dtype, w.last_rows0, &tcap);
+  VolumeBits vb;
+  if (!rc0 && blocks && !dt) rc0 = ensure_bits(w, Bt, dtype);
   if (rc0) return rc0;
   const Ptrs P = w.ptrs();
   hipGraph_t graph = nullptr;
@@ -1145,7 +1185,7 @@ int capture_graph(Workspace& w, const Batch& Bt, int dtype, hipStream_t st, Grap
     if (e != hipSuccess) rc = fail(SHAPE3D_EHIP, std::string("plan: ") + hipGetErrorString(e));
   }
   if (!rc && blocks) {
-    rc = launch_mesh(P, Bt, dtype, Z.rows, (float4*)w.blk[B_PBOX].p, nullptr, st);
+    rc = launch_mesh(P, Bt, dtype, Z.rows, (float4*)w.blk[B_PBOX].p, dt ? nullptr : volume_bits(w, Bt, dtype, vb), nullptr, st);
     if (!rc) rc = launch_block_list(P, block_ptrs(w), Z, Bt, dtype, st);
     if (!rc)
       rc = launch_block_tail(P, block_ptrs(w), Z, Bt, dtype, w.last_rows0, counts, true, w.cu_count,
@@ -1413,6 +1453,7 @@ int soft_backward_impl(const float* base, const shape3d_roi* rois, int64_t n_roi
   if ((rc = get_workspace(&wp))) return rc;
   Workspace& w = *wp;
   std::vector<SoftBwdRoi> table((size_t)n_rois);
+  const int bit_rounds = n_rois == 1 && rois[0].dims[0] * rois[0].dims[1] * rois[0].dims[2] < kBitManyVoxels ? 1 : kBitRounds;
   long long n_bricks = 0, n_bitblks = 0, n_bits = 0, n_index = 0, n_vox = 0, cap = 0;
   size_t scan_lds = 0;
   for (int64_t r = 0; r < n_rois; ++r) {
@@ -1463,7 +1504,7 @@ int soft_backward_impl(const float* base, const shape3d_roi* rois, int64_t n_roi
     const long long vox = (long long)R.d[0] * R.d[1] * R.d[2];
     R.bitblk_begin = n_bitblks;
     R.bits_begin = n_bits;
-    n_bitblks += (vox + kBitBlock - 1) / kBitBlock;
+    n_bitblks += bit_blocks(vox, bit_rounds * kBitRound);
     n_bits += bit_words(vox);
     n_vox += vox;
     n_bricks += bpz * R.nzc;
@@ -1497,6 +1538,7 @@ int soft_backward_impl(const float* base, const shape3d_roi* rois, int64_t n_roi
   B.n_rois = (int)n_rois;
   B.n_bricks = n_bricks;
   B.n_bitblks = n_bitblks;
+  B.bit_rounds = bit_rounds;
   B.bits = (uint32_t*)w.soft_bits.p;
   B.scan_lds = scan_lds;
   B.cap_cubes = cap_cubes;
@@ -2083,6 +2125,8 @@ int shape3d_release(void) {
     for (Buf& b : w->blk)
       if (b.p) (void)hipFree(b.p);
     for (Buf* b : w->soft_bufs())
+      if (b->p) (void)hipFree(b->p);
+    for (Buf* b : {&w->vol_bits, &w->bit_map})
       if (b->p) (void)hipFree(b->p);
     if (w->host) (void)hipHostFree(w->host);
     if (w->small_slots.p) (void)hipFree(w->small_slots.p);

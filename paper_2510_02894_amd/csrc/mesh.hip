@@ -38,12 +38,6 @@ namespace s3d {
 // ---------------------------------------------------------------------------
 // Voxel bytes to inside bits, four at a time.
 
-__device__ inline uint32_t nz4(uint32_t w) {
-  // high bit of each byte set iff the byte is nonzero, then gathered to bits 0..3
-  const uint32_t t = (((w & 0x7f7f7f7fu) + 0x7f7f7f7fu) | w) & 0x80808080u;
-  return (t * 0x00204081u) >> 28;
-}
-
 // Bits 0..3 set for the bytes of w equal to the ROI's label (label != 0), or
 // for its nonzero bytes (label == 0).
 __device__ inline uint32_t in4(uint32_t w, uint32_t label4) {
@@ -138,17 +132,13 @@ __device__ inline void mark_words(const uint32_t* counts, int off, int c0, int n
 
 __device__ inline int marker_rank(uint32_t mk, int i) { return i - (int)(mk >> 21) + (int)((mk >> 16) & 31u); }
 
-// v[k] of an 8-entry register array for a run-time k (selects, no scratch).
-__device__ inline double sel8d(const double* v, int k) {
-  const double a = (k & 1) ? v[1] : v[0], b = (k & 1) ? v[3] : v[2];
-  const double c = (k & 1) ? v[5] : v[4], e = (k & 1) ? v[7] : v[6];
-  const double ab = (k & 2) ? b : a, ce = (k & 2) ? e : c;
-  return (k & 4) ? ce : ab;
-}
-
-__device__ inline double soft_value(const Roi& R, int z, int y, int x) {
-  if (z < 0 || y < 0 || x < 0 || z >= R.d[0] || y >= R.d[1] || x >= R.d[2]) return 0.0;
-  return (double)((const float*)R.vol)[(size_t)z * (size_t)R.stride0 + (size_t)y * (size_t)R.stride1 + (size_t)x];
+// The probability at (z, y, x), 0 outside the array; the load is always issued
+// (at a clamped address), so that several of them are in flight together.
+__device__ inline float soft_load(const Roi& R, int z, int y, int x) {
+  const bool ok = (unsigned)z < (unsigned)R.d[0] && (unsigned)y < (unsigned)R.d[1] && (unsigned)x < (unsigned)R.d[2];
+  const int zc = min(max(z, 0), R.d[0] - 1), yc = min(max(y, 0), R.d[1] - 1), xc = min(max(x, 0), R.d[2] - 1);
+  const float v = ((const float*)R.vol)[(size_t)zc * (size_t)R.stride0 + (size_t)yc * (size_t)R.stride1 + (size_t)xc];
+  return ok ? v : 0.0f;
 }
 
 // A brick is kBrickThreads consecutive row-groups (rg = cube row * G + group)
@@ -455,7 +445,9 @@ __global__ __launch_bounds__(256) void k_small_head(Roi R, Roi* __restrict__ roi
 // registers spill; measured faster than 96 VGPRs and five bricks per CU).
 // Soft masks: at most 128 VGPRs (four bricks per CU instead of three; a few
 // registers spill, measured slightly faster).
-template <int DT>
+// BITS: the volumes' bit strings are there (k_volume_bits), and the tiles are
+// cut from them.
+template <int DT, bool BITS>
 __global__ __launch_bounds__(kBrickThreads, DT == 0 ? 6 : 4) void k_mesh_pass(const Roi* __restrict__ rois, int n_rois,
                                                              long long nbricks, double* __restrict__ case_area,
                                                              BrickPart* __restrict__ part,
@@ -463,11 +455,18 @@ __global__ __launch_bounds__(kBrickThreads, DT == 0 ? 6 : 4) void k_mesh_pass(co
                                                              double* __restrict__ tmpt, long long tmp_cap,
                                                              long long* __restrict__ totals, int moments,
                                                              const int* __restrict__ bmap,
-                                                             float4* __restrict__ pbox) {
+                                                             float4* __restrict__ pbox,
+                                                             const uint32_t* __restrict__ bits) {
   extern __shared__ uint32_t s_bits[];
   __shared__ unsigned int s_hist[256];  // binary masks: active cubes per case
   __shared__ int s_tk[256];
   __shared__ int s_tm[256];
+  // soft masks: the corner values of the threads' cubes and the triangle table
+  // (indexed at run time: from LDS 40 cycles a triangle vertex, from constant
+  // memory or by selects over registers several times that)
+  __shared__ float s_p[DT == 1 ? 8 : 1][DT == 1 ? kBrickThreads : 1];
+  __shared__ uint8_t s_tri[DT == 1 ? 256 * MC_MAX_TRI * 3 : 1];
+  __shared__ uint32_t s_edge[DT == 1 ? 12 : 1];  // axis | corner 0 << 2 | corner 1 << 5
   __shared__ __align__(16) uint32_t s_items[kMeshItems];
   __shared__ uint32_t s_ly[kBrickThreads];  // (y + 1) | l << 20 of each thread's row-group
   __shared__ int s_scan[4];
@@ -491,11 +490,22 @@ __global__ __launch_bounds__(kBrickThreads, DT == 0 ? 6 : 4) void k_mesh_pass(co
     s_hist[c] = 0u;
     s_tk[c] = nt | ((MC_CASE_KAPPA[c] + 128) << 8);
     s_tm[c] = (MC_CASE_M[c][0] + 128) | ((MC_CASE_M[c][1] + 128) << 8) | ((MC_CASE_M[c][2] + 128) << 16);
+    if (DT == 1) {
+      for (int i = tid; i < 256 * MC_MAX_TRI * 3; i += kBrickThreads) s_tri[i] = (uint8_t)(&MC_TRI[0][0][0])[i];
+      if (tid < 12) {
+        const uint32_t a = MC_EDGE_AXIS[tid], k0 = MC_EDGE_C0[tid];
+        s_edge[tid] = a | k0 << 2 | (k0 | 4u >> a) << 5;
+      }
+    }
   }
   __syncthreads();
 
   const Tile T = tile_of(R, brick - R.brick_begin);
-  load_tile<DT>(R, T, s_bits);
+  if (BITS)
+    cut_tile<kTZ + 1>(bits + R.bits_begin, volume_shift<DT>(R.vol), R.d, R.G, R.mG, R.shG, T.rg0 - 1, T.pz0 - 1, T.np,
+                      T.nw, s_bits);
+  else
+    load_tile<DT>(R, T, s_bits);
   __syncthreads();
   const Lane L = lane_of(R, T, tid);
   s_ly[tid] = (uint32_t)(L.y + 1) | ((uint32_t)L.l << 20);  // read back by the dense loop (after a barrier)
@@ -622,21 +632,20 @@ __global__ __launch_bounds__(kBrickThreads, DT == 0 ? 6 : 4) void k_mesh_pass(co
                  2ll * ((long long)z * ((tm & 0xff) - 128) + (long long)y * (((tm >> 8) & 0xff) - 128) +
                         (long long)x * (((tm >> 16) & 0xff) - 128));
       } else {
-        double pc[8];
 #pragma unroll
-        for (int c = 0; c < 8; ++c) pc[c] = soft_value(R, z + ((c >> 2) & 1), y + ((c >> 1) & 1), x + (c & 1));
+        for (int c = 0; c < 8; ++c) s_p[c][tid] = soft_load(R, z + ((c >> 2) & 1), y + ((c >> 1) & 1), x + (c & 1));
         const int ntri = tk & 0xff;
         for (int tr = 0; tr < ntri; ++tr) {
           double P[3][3];
 #pragma unroll
           for (int v = 0; v < 3; ++v) {
-            const int e = MC_TRI[cas][tr][v];
-            const int ax = MC_EDGE_AXIS[e], k0 = MC_EDGE_C0[e];
-            const int k1 = k0 | (4 >> ax);
+            const uint32_t ed = s_edge[s_tri[(cas * MC_MAX_TRI + tr) * 3 + v]];
+            const int ax = (int)(ed & 3u), k0 = (int)(ed >> 2 & 7u), k1 = (int)(ed >> 5);
+            const double p0 = (double)s_p[k0][tid], p1 = (double)s_p[k1][tid];
             // the area and volume terms only (the vertex rows take the edge
             // pass's correctly rounded quotient): a reciprocal estimate refined
             // by Newton steps is within a unit in the last place
-            const double tt = (0.5 - sel8d(pc, k0)) * rcp64(sel8d(pc, k1) - sel8d(pc, k0));
+            const double tt = (0.5 - p0) * rcp64(p1 - p0);
             const int u0 = z + ((k0 >> 2) & 1), u1 = y + ((k0 >> 1) & 1), u2 = x + (k0 & 1);
             P[v][0] = ((double)u0 + (ax == 0 ? tt : 0.0)) * R.s[0] - o0;
             P[v][1] = ((double)u1 + (ax == 1 ? tt : 0.0)) * R.s[1] - o1;
@@ -681,8 +690,8 @@ __global__ __launch_bounds__(kBrickThreads, DT == 0 ? 6 : 4) void k_mesh_pass(co
       const long long row = base + c0 + i;
       double tt = 0.5;
       if (DT == 1) {
-        const double pa = soft_value(R, u0, u1, u2);
-        const double pb = soft_value(R, u0 + (a == 0), u1 + (a == 1), u2 + (a == 2));
+        const double pa = (double)soft_load(R, u0, u1, u2);
+        const double pb = (double)soft_load(R, u0 + (a == 0), u1 + (a == 1), u2 + (a == 2));
         tt = (0.5 - pa) / (pb - pa);
       }
       if (row < tmp_cap) {
@@ -1268,7 +1277,8 @@ constexpr int kBrickMapTailGroups = 64;
 __global__ __launch_bounds__(256) void k_head(Roi* __restrict__ rois, int n_rois, long long nbricks,
                                               double* __restrict__ case_area, int* __restrict__ bmap,
                                               unsigned int* __restrict__ counters, int n_counters,
-                                              long long* __restrict__ totals, Roi one, int use_one) {
+                                              long long* __restrict__ totals, int* __restrict__ bitmap,
+                                              long long n_bitblks, Roi one, int use_one) {
   const int tid = threadIdx.x;
   if (blockIdx.x == 0) {
     for (int i = tid; i < n_counters; i += 256) counters[i] = 0u;
@@ -1281,6 +1291,10 @@ __global__ __launch_bounds__(256) void k_head(Roi* __restrict__ rois, int n_rois
     case_hist(case_area, n_rois)[i] = 0ull;
   }
   if (!bmap) return;
+  if (bitmap && (int)blockIdx.x < n_rois) {
+    const long long e = (int)blockIdx.x + 1 < n_rois ? rois[blockIdx.x + 1].bitblk_begin : n_bitblks;
+    for (long long b = rois[blockIdx.x].bitblk_begin + tid; b < e; b += 256) bitmap[b] = (int)blockIdx.x;
+  }
   if ((int)blockIdx.x < n_rois) {
     const long long b1 = min(rois[blockIdx.x].brick_end, nbricks);
     for (long long b = rois[blockIdx.x].brick_begin + tid; b < b1; b += 256) bmap[b] = (int)blockIdx.x;
@@ -1288,6 +1302,17 @@ __global__ __launch_bounds__(256) void k_head(Roi* __restrict__ rois, int n_rois
     const long long b0 = rois[n_rois - 1].brick_end + (long long)(blockIdx.x - n_rois) * 256 + tid;
     for (long long b = b0; b < nbricks; b += (long long)kBrickMapTailGroups * 256) bmap[b] = -1;
   }
+}
+
+// ---------------------------------------------------------------------------
+// The bit strings of a table of dense volumes, a stream: 16-byte loads, 16 in
+// flight a thread (256 soft ROIs of edges 48 to 160, 1.09 GB: 218 us, 5.0 TB/s).
+template <int DT, int ROUNDS>
+__global__ __launch_bounds__(256) void k_volume_bits(const Roi* __restrict__ rois, const int* __restrict__ map,
+                                                     uint32_t* __restrict__ bits) {
+  const Roi& R = rois[map ? map[blockIdx.x] : 0];
+  pack_bits<DT, ROUNDS>(R.vol, (long long)R.d[0] * R.d[1] * R.d[2],
+                        (blockIdx.x - R.bitblk_begin) * (ROUNDS * 4096ll), bits + R.bits_begin);
 }
 
 // ---------------------------------------------------------------------------
@@ -1384,24 +1409,30 @@ size_t mesh_lds_bytes(int max_G) { return sizeof(uint32_t) * (size_t)(kTZ + 1) *
 hipError_t launch_mesh_pass(int dtype, Roi* rois, int n_rois, long long nbricks, int max_G,
                             double* case_area, BrickPart* part, unsigned int* counters, int n_counters,
                             unsigned long long* tmpkey, double* tmpt, long long tmp_cap, long long* totals,
-                            int moments, int* bmap, float4* pbox, const Roi* one, hipStream_t st) {
+                            int moments, int* bmap, float4* pbox, const VolumeBits* vb, const Roi* one,
+                            hipStream_t st) {
   if (n_rois < 2) bmap = nullptr;  // one ROI: the search is free
+  int* const bitmap = vb && n_rois > 1 ? vb->map : nullptr;
   Roi R;
   if (one)
     R = *one;
   else
     memset(&R, 0, sizeof(R));
   hipLaunchKernelGGL(k_head, dim3((unsigned)(n_rois + (bmap ? kBrickMapTailGroups : 0))), dim3(256), 0, st, rois,
-                     n_rois, nbricks, dtype == 0 ? case_area : (double*)nullptr, bmap, counters, n_counters, totals, R,
-                     one ? 1 : 0);
+                     n_rois, nbricks, dtype == 0 ? case_area : (double*)nullptr, bmap, counters, n_counters, totals,
+                     bitmap, vb ? vb->n_blocks : 0ll, R, one ? 1 : 0);
   if (nbricks <= 0) return hipGetLastError();
   const size_t lds = mesh_lds_bytes(max_G);
-  if (dtype == 0)
-    hipLaunchKernelGGL(k_mesh_pass<0>, dim3((unsigned)nbricks), dim3(kBrickThreads), lds, st, (const Roi*)rois, n_rois,
-                       nbricks, case_area, part, tmpkey, tmpt, tmp_cap, totals, moments, (const int*)bmap, pbox);
-  else
-    hipLaunchKernelGGL(k_mesh_pass<1>, dim3((unsigned)nbricks), dim3(kBrickThreads), lds, st, (const Roi*)rois, n_rois,
-                       nbricks, case_area, part, tmpkey, tmpt, tmp_cap, totals, moments, (const int*)bmap, pbox);
+  const uint32_t* bits = nullptr;
+  if (vb) {
+    const auto pack = vb->rounds == 1 ? k_volume_bits<1, 1> : k_volume_bits<1, kBitRounds>;
+    hipLaunchKernelGGL(pack, dim3((unsigned)vb->n_blocks), dim3(256), 0, st, (const Roi*)rois, (const int*)bitmap,
+                       vb->bits);
+    bits = vb->bits;
+  }
+  const auto pass = dtype == 0 ? k_mesh_pass<0, false> : vb ? k_mesh_pass<1, true> : k_mesh_pass<1, false>;
+  hipLaunchKernelGGL(pass, dim3((unsigned)nbricks), dim3(kBrickThreads), lds, st, (const Roi*)rois, n_rois, nbricks,
+                     case_area, part, tmpkey, tmpt, tmp_cap, totals, moments, (const int*)bmap, pbox, bits);
   return hipGetLastError();
 }
 
@@ -1417,12 +1448,10 @@ hipError_t launch_mesh_core(int dtype, const Roi* rois, int n_rois, long long nb
                             long long tmp_cap, long long* totals, int moments, hipStream_t st) {
   if (nbricks <= 0) return hipGetLastError();
   const size_t lds = mesh_lds_bytes(max_G);
-  if (dtype == 0)
-    hipLaunchKernelGGL(k_mesh_pass<0>, dim3((unsigned)nbricks), dim3(kBrickThreads), lds, st, rois, n_rois, nbricks,
-                       case_area, part, tmpkey, tmpt, tmp_cap, totals, moments, (const int*)nullptr, (float4*)nullptr);
-  else
-    hipLaunchKernelGGL(k_mesh_pass<1>, dim3((unsigned)nbricks), dim3(kBrickThreads), lds, st, rois, n_rois, nbricks,
-                       case_area, part, tmpkey, tmpt, tmp_cap, totals, moments, (const int*)nullptr, (float4*)nullptr);
+  const auto pass = dtype == 0 ? k_mesh_pass<0, false> : k_mesh_pass<1, false>;
+  hipLaunchKernelGGL(pass, dim3((unsigned)nbricks), dim3(kBrickThreads), lds, st, rois, n_rois, nbricks, case_area, part,
+                     tmpkey, tmpt, tmp_cap, totals, moments, (const int*)nullptr, (float4*)nullptr,
+                     (const uint32_t*)nullptr);
   return hipGetLastError();
 }
 

@@ -251,43 +251,103 @@ __device__ inline unsigned long long key_canonical_id(uint64_t key, const int* d
 // their rows: a brick that reads the volume itself waits for its own few loads
 // and reads its neighbours' rows again, in four bytes a voxel.
 
-// 32-bit words of the string of n elements: whole 64-bit words, and one more
-// for the last cut.
-__host__ __device__ inline long long bit_words(long long n) { return (n + 63) / 64 * 2 + 2; }
+// The string starts at the 16-byte boundary at or before the volume: bit
+// shift + i is element i, shift = volume_shift(), so that every load is a whole
+// aligned 16 bytes (one that holds a byte of the volume lies on its pages).
 
-// The word of the voxels pos .. pos + left - 1 (at most 32 of them; 0 if left <= 0).
+template <int DT>
+__host__ __device__ inline int volume_shift(const void* vol) {
+  return (int)((uintptr_t)vol & 15u) / (DT == 0 ? 1 : 4);
+}
+
+// 32-bit words of the string of n elements (whatever its shift), one more for
+// the last cut and even, and its workgroups of `block` elements.
+__host__ __device__ inline long long bit_words(long long n) { return (n + 15 + 63) / 64 * 2 + 2; }
+__host__ __device__ inline long long bit_blocks(long long n, int block) { return (n + 15 + block - 1) / block; }
+
+// The word of the bits pos .. pos + left - 1 (at most 32 of them; 0 if left <= 0).
 __device__ inline uint32_t cut_word(const uint32_t* __restrict__ bits, unsigned int pos, int left) {
   if (left <= 0) return 0u;
   const uint32_t w = __builtin_amdgcn_alignbit(bits[(pos >> 5) + 1], bits[pos >> 5], pos & 31u);
   return left >= 32 ? w : w & ((1u << left) - 1u);
 }
 
-// Elements per workgroup (256 threads) of a bit pass.
-constexpr int kBitBlock = 8192;
+// The words of voxel planes z0 .. z0 + np - 1 (at most MAXP), row-groups rg0 ..
+// rg0 + nw - 1 (row-group = cube row * G + group; 0 outside the array) of a
+// dense volume of dims d into tile[plane * nw + word].  Thread t (of 256) takes
+// words t, t + 256, ... of every plane: the rows are found once, and the planes'
+// words are read together.
+template <int MAXP>
+__device__ inline void cut_tile(const uint32_t* __restrict__ bits, int shift, const int* d, int G, unsigned int mG,
+                                int shG, int rg0, int z0, int np, int nw, uint32_t* tile) {
+  const int d0 = d[0], d1 = d[1], d2 = d[2];
+  for (int i = threadIdx.x; i < nw; i += 256) {
+    const int rg = rg0 + i;
+    const int ry = rg < 0 ? 0 : (int)fdiv((unsigned int)rg, mG, shG);
+    const int y = ry - 1, x = 32 * (rg - ry * G);
+    const int left = rg >= 0 && (unsigned)y < (unsigned)d1 ? d2 - x : 0;
+    const unsigned int at = (unsigned int)shift + (unsigned int)y * (unsigned int)d2 + (unsigned int)x;
+    const unsigned int plane = (unsigned int)d1 * (unsigned int)d2;
+#pragma unroll
+    for (int p = 0; p < MAXP; ++p) {
+      const int z = z0 + p;
+      if (p < np)
+        tile[p * nw + i] = cut_word(bits, (unsigned int)z * plane + at, (unsigned)z < (unsigned)d0 ? left : 0);
+    }
+  }
+}
 
-// A workgroup's elements [e0, e0 + kBitBlock) of n floats into the bit string
-// (a wave's comparison is 64 bits of it), and zeros into `zero` if it is set.
-__device__ inline void pack_bits_f32(const float* __restrict__ src, long long n, long long e0,
-                                     unsigned long long* __restrict__ bits, float* __restrict__ zero) {
+// Bits 0..3 set for the nonzero bytes of w.
+__device__ inline uint32_t nz4(uint32_t w) {
+  // high bit of each byte set iff the byte is nonzero, then gathered to bits 0..3
+  const uint32_t t = (((w & 0x7f7f7f7fu) + 0x7f7f7f7fu) | w) & 0x80808080u;
+  return (t * 0x00204081u) >> 28;
+}
+
+// A workgroup's (256 threads) bits [e0, e0 + ROUNDS * 4096) of the string of n
+// elements, a wave's ROUNDS * 1024 together.
+template <int DT, int ROUNDS>
+__device__ inline void pack_bits(const void* __restrict__ vol, long long n, long long e0,
+                                 uint32_t* __restrict__ bits) {
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  const long long end = n + volume_shift<DT>(vol);
+  const long long w0 = e0 + (long long)wid * (ROUNDS * 1024);
+  const uint4* src = (const uint4*)((uintptr_t)vol & ~(uintptr_t)15);
+  if (DT == 0) {
+    uint4 v[ROUNDS];
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const long long w0 = e0 + (2 * wid + h) * 1024;  // 16 waves' loads in flight
-    float v[16];
-#pragma unroll
-    for (int u = 0; u < 16; ++u) v[u] = w0 + 64 * u + lane < n ? src[w0 + 64 * u + lane] : 0.0f;
-    if (zero) {
-#pragma unroll
-      for (int u = 0; u < 16; ++u)
-        if (w0 + 64 * u + lane < n) zero[w0 + 64 * u + lane] = 0.0f;
+    for (int u = 0; u < ROUNDS; ++u) {
+      const long long e = w0 + 1024 * u + 16 * lane;
+      v[u] = e < end ? src[e >> 4] : make_uint4(0u, 0u, 0u, 0u);
     }
-    unsigned long long mine = 0ull;
 #pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      const unsigned long long in = __ballot(v[u] > 0.5f);
-      mine = lane == u ? in : mine;
+    for (int u = 0; u < ROUNDS; ++u) {
+      const uint32_t h = nz4(v[u].x) | nz4(v[u].y) << 4 | nz4(v[u].z) << 8 | nz4(v[u].w) << 12;
+      const uint32_t w = lane_step<0>(h << (16 * (lane & 1)), [](uint32_t a, uint32_t b) { return a | b; });
+      const long long e = w0 + 1024 * u + 16 * lane;
+      if (!(lane & 1) && e < end) bits[e >> 5] = w;
     }
-    if (lane < 16 && w0 + 64 * lane < (n + 63) / 64 * 64 + 64) bits[w0 / 64 + lane] = mine;
+  } else {
+    constexpr int J = ROUNDS > 1 ? 8 : 4;  // 16-byte loads in flight per thread
+#pragma unroll
+    for (int g = 0; g < ROUNDS * 4; g += J) {
+      uint4 v[J];
+#pragma unroll
+      for (int j = 0; j < J; ++j) {
+        const long long e = w0 + 256 * (g + j) + 4 * lane;
+        v[j] = e < end ? src[e >> 2] : make_uint4(0u, 0u, 0u, 0u);
+      }
+      uint32_t mine = 0u;
+#pragma unroll
+      for (int j = 0; j < J; ++j) {
+        const uint32_t b = (uint32_t)(__uint_as_float(v[j].x) > 0.5f) | (uint32_t)(__uint_as_float(v[j].y) > 0.5f) << 1 |
+                           (uint32_t)(__uint_as_float(v[j].z) > 0.5f) << 2 | (uint32_t)(__uint_as_float(v[j].w) > 0.5f) << 3;
+        const uint32_t w = lanes_reduce<3>(b << (4 * (lane & 7)), [](uint32_t a, uint32_t c) { return a | c; });
+        mine = (lane & 7) == j ? w : mine;
+      }
+      const long long e = w0 + 256 * (g + (lane & 7)) + 32 * (lane >> 3);
+      if ((lane & 7) < J && e < end) bits[e >> 5] = mine;
+    }
   }
 }
 

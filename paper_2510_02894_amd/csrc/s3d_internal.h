@@ -67,6 +67,8 @@ struct Roi {
   int status;             // 0, or a negative status for a rejected table entry (then it has no bricks)
   int tz;                 // cube planes per brick (kTZ, or fewer for a small ROI on its own)
   long long bucket_base[3];  // first global plane bucket of each axis
+  long long bits_begin;   // volumes read by the bit pass: first word of the ROI's bit string,
+  long long bitblk_begin; // ... and the pass's first workgroup for it
 };
 
 // A ROI as a caller describes it (the layout of shape3d_roi_ex in shape3d.h).

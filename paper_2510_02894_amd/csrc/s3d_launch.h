@@ -56,6 +56,17 @@ hipError_t launch_small_pairs(int dtype, const Roi* rois, const BrickPart* part,
                               const long long* totals, long long vmax, SmallAcc* acc, int n_groups,
                               RoiResult* res, hipStream_t st);
 
+// The bit pass over the volumes of a table of dense ROIs without labels
+// (Roi::bits_begin, bitblk_begin): workgroups of rounds (1 or kBitRounds) times
+// kBitRound elements; map: [n_blocks] scratch for the ROI of each.
+constexpr int kBitRound = 4096, kBitRounds = 4;
+struct VolumeBits {
+  uint32_t* bits;
+  int* map;
+  long long n_blocks;
+  int rounds;
+};
+
 // The mesh pass (one read of the volume): clears counters[0, n_counters),
 // then per brick its BrickPart and its vertices' keys (and soft t) in the
 // staging list (rows below tmp_cap are written; totals[8] counts all).
@@ -64,12 +75,14 @@ hipError_t launch_small_pairs(int dtype, const Roi* rois, const BrickPart* part,
 // moments: also the inside-voxel moments;
 // bmap: [nbricks] scratch for the brick -> ROI map of a batch (unused, and may
 // be null, for one ROI).
+// vb: the bit pass to run first, from whose strings the mesh pass then cuts its
+// tiles, or null (the bricks read the volumes themselves).
 // one: host ROI record of a call with one ROI, which the launch then stores in
 // rois[0] (null: rois is already there).
 hipError_t launch_mesh_pass(int dtype, Roi* rois, int n_rois, long long nbricks, int max_G,
                             double* case_area, BrickPart* part, unsigned int* counters, int n_counters,
                             unsigned long long* tmpkey, double* tmpt, long long tmp_cap, long long* totals,
-                            int moments, int* bmap, float4* pbox, const Roi* one, hipStream_t st);
+                            int moments, int* bmap, float4* pbox, const VolumeBits* vb, const Roi* one, hipStream_t st);
 // Per-ROI totals and each brick's first row within its ROI (brick_voff);
 // prune_min_v: ROIs with at least this many vertices get the pruning pass's column-pair offsets.
 hipError_t launch_mesh_totals(const Roi* rois, int n_rois, int dtype, const double* case_area, const BrickPart* part,
@@ -263,6 +276,7 @@ struct SoftBwdBufs {
   long long n_bricks;         // workgroups of the scan
   size_t scan_lds;            // its dynamic LDS
   long long n_bitblks;        // workgroups of the bit pass
+  int bit_rounds;             // their size, 4,096 elements times 1 or kBitRounds
   uint32_t* bits;             // the ROIs' bit strings
   // room for the active cubes and the voxels at crossing edges of a mask with
   // the forward pass's V vertices (an edge lies in four cubes and a cube has at

@@ -15,7 +15,7 @@
 //
 // Passes over every ROI of a table, one of them over the volume:
 //   1. k_soft_bits reads the probabilities once as inside bits and writes the
-//      zeros of dL/dp (bound: HBM, 4 bytes in and 4 out per voxel); k_soft_scan
+//      zeros of dL/dp (bound: HBM, 4 bytes in and 4 out per voxel, 5.1 TB/s); k_soft_scan
 //      lists the active cubes and the voxels at a crossing edge from the bits; a
 //      dense index gives each active cube's place in its list;
 //   2. k_soft_cubes, a thread per active cube: its triangles once each, and
@@ -29,8 +29,8 @@
 //      crossing edges, the edge's value times 0.5 - p_b or -(0.5 - p_u).
 //      Bound: latency of scattered reads, all of a voxel's in flight at once.
 // No float atomics: the result does not depend on scheduling.
-// Measured on 1,024 ROIs of a 2.2 GB batch (us): bits 600, scan 362, cubes 357,
-// edges 349, voxels 208, in all 1,880, against 2,408 of a wave per cube row that
+// Measured on a batch of 256 soft ROIs of edges 48 to 160 (us): bits 424, scan 367, cubes 367,
+// edges 348, voxels 210, in all 1,716, against 2,408 of a wave per cube row that
 // listed the edges (540), a thread per edge (1,064) and a gather over all voxels
 // (804).
 #include <hip/hip_runtime.h>
@@ -148,12 +148,26 @@ __device__ inline void emit_words(uint32_t w, int& off, int base, int place, int
 }  // namespace
 
 // The inside bits of the probabilities and the zeros of dL/dp, a stream.
+template <int ROUNDS>
 __global__ __launch_bounds__(256) void k_soft_bits(SoftBwdBufs B) {
   const int roi = B.blk_roi ? B.blk_roi[B.n_bricks + blockIdx.x] : soft_roi_of_bits(B.rois, B.n_rois, blockIdx.x);
   const SoftBwdRoi& R = B.rois[roi];
   const long long n = (long long)R.d[0] * R.d[1] * R.d[2];
-  pack_bits_f32(R.p, n, (long long)(blockIdx.x - R.bitblk_begin) * kBitBlock,
-                (unsigned long long*)(B.bits + R.bits_begin), R.grad);
+  const long long e0 = (blockIdx.x - R.bitblk_begin) * (long long)(ROUNDS * kBitRound);
+  pack_bits<1, ROUNDS>(R.p, n, e0, B.bits + R.bits_begin);
+  // the gradient's elements have their own 16-byte boundary
+  const int shift = volume_shift<1>(R.grad);
+  float4* out = (float4*)((uintptr_t)R.grad & ~(uintptr_t)15);
+#pragma unroll
+  for (int u = 0; u < ROUNDS * kBitRound / 1024; ++u) {
+    const long long e = e0 + 1024 * u + 4 * threadIdx.x;
+    if (e >= shift && e + 4 <= n + shift) {
+      out[e >> 2] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    } else {
+      for (int k = 0; k < 4; ++k)
+        if (e + k >= shift && e + k < n + shift) ((float*)out)[e + k] = 0.0f;
+    }
+  }
 }
 
 // Pass 1.  A workgroup takes 256 consecutive row-groups (rg = cube row * G +
@@ -173,23 +187,7 @@ __global__ __launch_bounds__(256) void k_soft_scan(SoftBwdBufs B) {
   const int nz = min(R.tz, d0 + 1 - pz0);  // cube planes
   const int np = nz + 2, nw = 258 + 2 * G;
   const int tid = threadIdx.x, lane = tid & 63;
-  const uint32_t* bits = B.bits + R.bits_begin;
-  // thread t holds the tile's words t, t + 256, ... of every plane: the rows
-  // are found once, and a plane's words are read together
-  for (int i = tid; i < nw; i += 256) {
-    const int rgi = rg0 - 1 + i;
-    const int ryi = rgi < 0 ? 0 : (int)fdiv((unsigned int)rgi, R.mG, R.shG);
-    const int y = ryi - 1, x = 32 * (rgi - ryi * G);
-    const int left = rgi >= 0 && (unsigned)y < (unsigned)d1 ? d2 - x : 0;
-    const unsigned int at = (unsigned int)y * (unsigned int)d2 + (unsigned int)x;
-#pragma unroll
-    for (int p = 0; p < kTZ + 2; ++p) {
-      const int z = pz0 - 1 + p;
-      if (p < np)
-        s_bits[p * nw + i] =
-            cut_word(bits, (unsigned int)z * (unsigned int)(d1 * d2) + at, (unsigned)z < (unsigned)d0 ? left : 0);
-    }
-  }
+  cut_tile<kTZ + 2>(B.bits + R.bits_begin, volume_shift<1>(R.p), R.d, G, R.mG, R.shG, rg0 - 1, pz0 - 1, np, nw, s_bits);
   __syncthreads();
 
   const int rg = rg0 + tid;
@@ -503,7 +501,8 @@ hipError_t launch_soft_backward(const SoftBwdBufs& B, hipStream_t st) {
     return dim3((unsigned)std::max(1ll, std::min((work + threads - 1) / threads, per_cu * B.cu_count)));
   };
   hipLaunchKernelGGL(k_soft_head, dim3((unsigned)(B.blk_roi ? B.n_rois : 1)), dim3(256), 0, st, B);
-  hipLaunchKernelGGL(k_soft_bits, dim3((unsigned)B.n_bitblks), dim3(256), 0, st, B);
+  hipLaunchKernelGGL(B.bit_rounds == 1 ? k_soft_bits<1> : k_soft_bits<kBitRounds>, dim3((unsigned)B.n_bitblks), dim3(256),
+                     0, st, B);
   hipLaunchKernelGGL(k_soft_scan, dim3((unsigned)B.n_bricks), dim3(256), B.scan_lds, st, B);
   if (B.cap_cubes > 0) {
     // few cubes: waves of their own, so that they spread over the CUs

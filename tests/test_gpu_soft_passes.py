@@ -1,4 +1,5 @@
-"""GPU checks of the adjoint's passes (inside bits, lists of active cubes and
+"""GPU checks of the soft forward pass over bit strings (volumes at every offset
+from a 16-byte boundary) and of the adjoint's passes (inside bits, lists of active cubes and
 surface voxels, cubes, edges, voxels) at the sizes where they can go wrong:
 rows around a multiple of 32 voxels, volumes around the bit pass's 8,192
 elements, one voxel along an axis, rows of many 32-cube groups, bricks with a
@@ -55,7 +56,8 @@ def test_adjoint_at_edges(S, shape):
     print("[case] adjoint %s" % (shape,), flush=True)
     p = noise(shape, sum(shape))
     t = torch.from_numpy(p).cuda()
-    _, saved = S.soft_forward(t, SP)
+    feats, saved = S.soft_forward(t, SP)
+    np.testing.assert_allclose(feats, O.shape3d(p, SP)["features"], rtol=1e-9)
     got = S.soft_backward(t, saved, gout_of(shape)).cpu().numpy().astype(np.float64)
     exp = O.soft_grad(p, SP, gout_of(shape))
     np.testing.assert_allclose(got, exp, rtol=2e-6, atol=2e-6 * np.abs(exp).max())
@@ -73,10 +75,11 @@ def test_adjoint_batch_equals_single(S):
     base = torch.from_numpy(buf).cuda()
     table = S.roi_table(offs, SHAPES, [SP] * len(ps))
     gout = np.stack([gout_of(s) for s in SHAPES])
-    _, saved = S.batched_soft_forward(base, table)
+    feats, saved = S.batched_soft_forward(base, table)
     grad = S.batched_soft_backward(base, table, saved, gout).cpu().numpy()
     for i, p in enumerate(ps):
         t = torch.from_numpy(p).cuda()
-        _, one = S.soft_forward(t, SP)
+        f1, one = S.soft_forward(t, SP)
+        assert np.array_equal(feats[i], f1), SHAPES[i]
         exp = S.soft_backward(t, one, gout[i]).cpu().numpy()
         assert np.array_equal(grad[offs[i]:offs[i] + p.size].reshape(p.shape), exp), SHAPES[i]
