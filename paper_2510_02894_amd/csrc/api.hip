@@ -808,7 +808,7 @@ int ensure_block_bufs(Workspace& w, const Batch& Bt, int dtype, long long rows, 
 // rows are, and reads its neighbours' rows again (mesh pass of 256 ROIs of edges
 // 48 to 160: 787 us, after a bit pass of 218 us 460; 256^3: 101 against 13 + 92;
 // 96^3: 46 against 3 + 38).  A uint8 brick reads a quarter of the bytes and is
-// bound by its instructions (300 x 512 x 512: 55 us, after a bit pass of 15 us 51).
+// bound by its instructions (300 x 512 x 512: 46 us, after a bit pass of 15 us 41).
 bool wants_bits(const Batch& Bt, int dtype) { return dtype == SHAPE3D_F32 && Bt.bits && !Bt.planned; }
 
 int ensure_bits(Workspace& w, const Batch& Bt, int dtype) {

@@ -28,7 +28,13 @@ small integer coordinates):
   2*offset(start corner) + e_axis;
 * per triangle (a, b, c): the integer normal m = (l_b - l_a) x (l_c - l_a);
 * per case: M = sum of m over its triangles and kappa = sum of
-  l_a . (l_b x l_c).
+  l_a . (l_b x l_c);
+* per case: the inside volume V of its cube, 48 for a whole one.  Six times
+  the volume of a closed region is the sum of l_a . (l_b x l_c) over its
+  boundary: the case's triangles, and the inside parts of the cube's faces
+  (about the cube's min corner only the three far faces count, each 6 / 3 * 8
+  = 16 times its inside area).  The near and far parts of a shared face
+  cancel, so the sum of V over all cubes is that of the closed surface.
 
 Usage: ``python gen_mc_table.py [output]`` (default: ``mc_table.h`` beside
 this script).
@@ -175,6 +181,14 @@ def dot(a, b):
     return sum(x * y for x, y in zip(a, b))
 
 
+def face_area8(case, axis):
+    """Eight times the inside area of the cube's far face along axis."""
+    on = [bool(case >> c & 1) for c in range(8) if corner_offset(c)[axis] == 1]
+    n = sum(on)
+    diagonal = n == 2 and on[0] == on[3]
+    return [0, 1, 2 if diagonal else 4, 7, 8][n]
+
+
 def build():
     table = []
     for case in range(256):
@@ -187,7 +201,8 @@ def build():
             normals.append(m)
             M = [M[k] + m[k] for k in range(3)]
             kappa += dot(la, cross(lb, lc))
-        table.append(dict(tris=tris, normals=normals, M=M, kappa=kappa))
+        volume = kappa + 2 * sum(face_area8(case, k) for k in range(3))
+        table.append(dict(tris=tris, normals=normals, M=M, kappa=kappa, volume=volume))
     return table
 
 
@@ -234,14 +249,10 @@ def render(table):
         w("    {%s}," % ", ".join("{%d, %d, %d}" % x for x in n))
     w("};")
     w("")
-    w("// per-case sum of triangle normals M and of l_a . (l_b x l_c) (kappa)")
-    w("static MC_TABLE_QUAL int8_t MC_CASE_M[256][3] = {")
-    for r in range(0, 256, 8):
-        w("    " + ", ".join("{%d, %d, %d}" % tuple(table[c]["M"]) for c in range(r, r + 8)) + ",")
-    w("};")
-    w("static MC_TABLE_QUAL int16_t MC_CASE_KAPPA[256] = {")
+    w("// per-case inside volume of the cube in 1/48 of it")
+    w("static MC_TABLE_QUAL int8_t MC_CASE_VOLUME[256] = {")
     for r in range(0, 256, 16):
-        w("    " + ", ".join("%d" % table[c]["kappa"] for c in range(r, r + 16)) + ",")
+        w("    " + ", ".join("%d" % table[c]["volume"] for c in range(r, r + 16)) + ",")
     w("};")
     w("")
     return "\n".join(lines)

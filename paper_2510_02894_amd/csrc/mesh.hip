@@ -38,45 +38,38 @@ namespace s3d {
 // ---------------------------------------------------------------------------
 // Voxel bytes to inside bits, four at a time.
 
-// Bits 0..3 set for the bytes of w equal to the ROI's label (label != 0), or
-// for its nonzero bytes (label == 0).
-__device__ inline uint32_t in4(uint32_t w, uint32_t label4) {
-  return label4 ? (~nz4(w ^ label4) & 0xfu) : nz4(w);
+// Bits 7..14 set for the nonzero bytes of x (low four) and y.
+__device__ inline uint32_t nz8(uint32_t x, uint32_t y) {
+  // high bit of each byte set iff the byte is nonzero, then gathered by dot products
+  const uint32_t s = (((x & 0x7f7f7f7fu) + 0x7f7f7f7fu) | x) & 0x80808080u;
+  const uint32_t t = (((y & 0x7f7f7f7fu) + 0x7f7f7f7fu) | y) & 0x80808080u;
+  return __builtin_amdgcn_udot4(s, 0x08040201u, __builtin_amdgcn_udot4(t, 0x80402010u, 0u, false), false);
 }
 
-// Slots per chunk of a brick's dense enumeration of active cubes or crossing
-// edges (8 per thread).
-constexpr int kMeshItems = 2048;
-static_assert(kMeshItems == 8 * kBrickThreads, "the slot scan gives each thread 8 slots");
+// Active cubes per chunk of a brick's dense enumeration (4 per thread).
+constexpr int kMeshItems = 1024;
+static_assert(kMeshItems == 4 * kBrickThreads, "the slot scan gives each thread 4 slots");
 
 // Position of the r-th set bit (r = 0 for the lowest) of w; r < popc(w).
 __device__ inline int nth_set_bit(uint32_t w, int r) {
   int pos = 0;
 #pragma unroll
   for (int h = 16; h >= 1; h >>= 1) {
-    const int c = __popc(w & ((1u << h) - 1u));
-    const bool up = r >= c;
-    r = up ? r - c : r;
-    w = up ? w >> h : w;
-    pos = up ? pos + h : pos;
+    const int up = pos | h;
+    pos = __popc(w & ((1u << up) - 1u)) <= r ? up : pos;
   }
   return pos;
 }
 
-// Inclusive max-scan of s[0, n) by the workgroup, 8 consecutive slots per
+// Inclusive max-scan of s[0, n) by the workgroup, 4 consecutive slots per
 // thread (slots >= n read as 0).  s_mx holds 4 words.  Contains barriers.
 __device__ inline void block_max_scan(uint32_t* s, int n, uint32_t* s_mx) {
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  const int b = 8 * tid;
-  const uint4 q0 = *(const uint4*)(s + b), q1 = *(const uint4*)(s + b + 4);
-  const uint32_t in[8] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w};
-  uint32_t v[8], m = 0u;
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    m = max(m, b + j < n ? in[j] : 0u);
-    v[j] = m;
-  }
-  uint32_t x = m;
+  const int b = 4 * tid;
+  const uint4 q = *(const uint4*)(s + b);
+  const uint32_t v0 = b < n ? q.x : 0u, v1 = max(v0, b + 1 < n ? q.y : 0u), v2 = max(v1, b + 2 < n ? q.z : 0u),
+                 v3 = max(v2, b + 3 < n ? q.w : 0u);
+  uint32_t x = v3;
 #pragma unroll
   for (int d = 1; d < 64; d <<= 1) {
     const uint32_t y = __shfl_up(x, d, 64);
@@ -87,8 +80,7 @@ __device__ inline void block_max_scan(uint32_t* s, int n, uint32_t* s_mx) {
   __syncthreads();
   uint32_t pre = lane > 0 ? prev : 0u;
   for (int w = 0; w < wid; ++w) pre = max(pre, s_mx[w]);
-  *(uint4*)(s + b) = make_uint4(max(pre, v[0]), max(pre, v[1]), max(pre, v[2]), max(pre, v[3]));
-  *(uint4*)(s + b + 4) = make_uint4(max(pre, v[4]), max(pre, v[5]), max(pre, v[6]), max(pre, v[7]));
+  *(uint4*)(s + b) = make_uint4(max(pre, v0), max(pre, v1), max(pre, v2), max(pre, v3));
   __syncthreads();
 }
 
@@ -183,62 +175,90 @@ __device__ inline const char* row_span(const Roi& R, const Tile& T, int p, int v
 
 // Stages the tile's voxel row-groups in LDS.  Each thread issues the loads of
 // several row-groups before converting any of them, so a workgroup keeps its
-// whole tile in flight instead of one row-group per thread at a time.  A full
-// row-group at a 16-byte aligned address is read with 16-byte loads; any other
-// (rows of packed ROIs start anywhere, row ends) with loads of the aligned
-// dwords (uint8) or floats that hold its voxels inside the array, and never
+// whole tile in flight instead of one row-group per thread at a time.  A
+// row-group's voxels are read as the aligned dwords (uint8; four to a load) or
+// floats (four to a load at a 16-byte aligned address) that hold them, and never
 // past them, since an aligned dword holding a valid byte lies on a mapped page.
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4), aligned(4)));
+
+// The inside word of up to 32 uint8 voxels: the loads, and then the bits.
+struct MaskWord {
+  uint32_t d[9];
+  int nvox, sh;
+
+  __device__ inline void load(const char* ptr, int n) {
+    nvox = n;
+    sh = (int)((uintptr_t)ptr & 3u);
+#pragma unroll
+    for (int j = 0; j < 9; ++j) d[j] = 0u;
+    if (n > 0) {
+      const uint32_t* q = (const uint32_t*)((uintptr_t)ptr & ~(uintptr_t)3);
+      const int last = (sh + n - 1) >> 2;  // last dword holding one of the voxels
+#pragma unroll
+      for (int h = 0; h < 8; h += 4) {
+        if (last >= h + 3) {
+          const u32x4 v = *(const u32x4*)(q + h);
+          d[h] = v.x;
+          d[h + 1] = v.y;
+          d[h + 2] = v.z;
+          d[h + 3] = v.w;
+        } else {
+#pragma unroll
+          for (int j = h; j < h + 3; ++j)
+            if (j <= last) d[j] = q[j];
+        }
+      }
+      if (last == 8) d[8] = q[8];
+    }
+  }
+
+  // inside: nonzero, or (with a label) no difference from it
+  __device__ inline uint32_t bits(int label) const {
+    uint32_t x[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) x[j] = __builtin_amdgcn_alignbyte(d[j + 1], d[j], (uint32_t)sh);
+    if (label) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) x[j] ^= (uint32_t)(label & 0xff) * 0x01010101u;
+    }
+    uint32_t b = nz8(x[0], x[1]) >> 7 | nz8(x[2], x[3]) << 1 | nz8(x[4], x[5]) << 9 | nz8(x[6], x[7]) << 17;
+    if (label) b = ~b;
+    return nvox >= 32 ? b : b & ((1u << nvox) - 1u);
+  }
+};
+
 template <int DT>
 __device__ inline void load_tile(const Roi& R, const Tile& T, uint32_t* s_bits) {
   const int n = T.np * T.nw;
   if (DT == 0) {
+    // thread t takes the word t of every plane (its row is found once), five
+    // planes in flight, and then a share of the words past the 256th
+    const int rg = T.rg0 - 1 + (int)threadIdx.x;
+    const int ry = rg < 0 ? 0 : (int)fdiv((unsigned int)rg, R.mG, R.shG);
+    const int y = ry - 1, x0 = 32 * (rg - ry * R.G);
+    const int nvox = rg >= 0 && (unsigned)y < (unsigned)R.d[1] ? min(32, R.d[2] - x0) : 0;
+    const char* row = (const char*)R.vol + (T.pz0 - 1) * R.stride0 + y * R.stride1 + x0;
     constexpr int kLoadBatch = 5;
-    const uint32_t label4 = (uint32_t)(R.label & 0xff) * 0x01010101u;
-    for (int base = threadIdx.x; base < n; base += kBrickThreads * kLoadBatch) {
-      uint32_t d[kLoadBatch][9];
-      int nv[kLoadBatch], sh[kLoadBatch];
+#pragma unroll
+    for (int p0 = 0; p0 <= kTZ; p0 += kLoadBatch) {
+      MaskWord m[kLoadBatch];
 #pragma unroll
       for (int u = 0; u < kLoadBatch; ++u) {
-        const int idx = base + u * kBrickThreads;
-        const char* ptr = nullptr;
-        nv[u] = 0;
-        sh[u] = 0;
-#pragma unroll
-        for (int j = 0; j < 9; ++j) d[u][j] = 0u;
-        if (idx < n) {
-          const int p = (int)fdiv((unsigned int)idx, R.mNW, R.shNW);
-          ptr = row_span<DT>(R, T, p, T.rg0 - 1 + idx - p * T.nw, nv[u]);
-        }
-        if (nv[u] == 32 && (((uintptr_t)ptr) & 15u) == 0) {
-          const uint4 a = *(const uint4*)ptr, b = *((const uint4*)ptr + 1);
-          d[u][0] = a.x;
-          d[u][1] = a.y;
-          d[u][2] = a.z;
-          d[u][3] = a.w;
-          d[u][4] = b.x;
-          d[u][5] = b.y;
-          d[u][6] = b.z;
-          d[u][7] = b.w;
-        } else if (nv[u] > 0) {
-          const uintptr_t a = (uintptr_t)ptr;
-          const uint32_t* q = (const uint32_t*)(a & ~(uintptr_t)3);
-          sh[u] = (int)(a & 3u);
-          const int last = (sh[u] + nv[u] - 1) >> 2;  // last dword holding a voxel of the row-group
-#pragma unroll
-          for (int j = 0; j < 9; ++j)
-            if (j <= last) d[u][j] = q[j];
-        }
+        const int p = p0 + u, z = T.pz0 - 1 + p;
+        if (p <= kTZ) m[u].load(row + p * R.stride0, p < T.np && (unsigned)z < (unsigned)R.d[0] ? nvox : 0);
       }
 #pragma unroll
-      for (int u = 0; u < kLoadBatch; ++u) {
-        const int idx = base + u * kBrickThreads;
-        if (idx >= n) continue;
-        uint32_t bits = 0u;
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-          bits |= in4(__builtin_amdgcn_alignbyte(d[u][j + 1], d[u][j], (uint32_t)sh[u]), label4) << (4 * j);
-        s_bits[idx] = nv[u] >= 32 ? bits : bits & ((1u << nv[u]) - 1u);
-      }
+      for (int u = 0; u < kLoadBatch; ++u)
+        if (p0 + u <= kTZ && p0 + u < T.np) s_bits[(p0 + u) * T.nw + threadIdx.x] = m[u].bits(R.label);
+    }
+    for (int i = threadIdx.x; i < (kTZ + 1) * (T.nw - kBrickThreads); i += kBrickThreads) {
+      const int w = kBrickThreads + i / (kTZ + 1), p = i % (kTZ + 1);
+      if (p >= T.np) continue;
+      int n;
+      const char* ptr = row_span<DT>(R, T, p, T.rg0 - 1 + w, n);
+      MaskWord m;
+      m.load(ptr, n);
+      s_bits[p * T.nw + w] = m.bits(R.label);
     }
   } else {
     // float32: a row-group is 128 B; two of them are in flight per thread
@@ -312,38 +332,13 @@ __device__ inline Lane lane_of(const Roi& R, const Tile& T, int tid) {
   return L;
 }
 
-// Corner masks of the 32 cubes between voxel planes z (rows r0*) and z + 1
-// (rows r1*); corner c = 4*dz + 2*dy + dx.
-struct Corners {
-  uint32_t c[8];
-};
+// The bits one voxel before those of row word r (prev: the word before it;
+// bit 31 of a row's last word lies past the array, so it is 0 before a row).
+__device__ inline uint32_t shifted(uint32_t r, uint32_t prev) { return __builtin_amdgcn_alignbit(r, prev, 31u); }
 
-__device__ inline Corners make_corners(uint32_t r00, uint32_t x00, uint32_t r01, uint32_t x01, uint32_t r10,
-                                       uint32_t x10, uint32_t r11, uint32_t x11) {
-  Corners C;
-  C.c[0] = (r00 << 1) | x00;
-  C.c[1] = r00;
-  C.c[2] = (r01 << 1) | x01;
-  C.c[3] = r01;
-  C.c[4] = (r10 << 1) | x10;
-  C.c[5] = r10;
-  C.c[6] = (r11 << 1) | x11;
-  C.c[7] = r11;
-  return C;
-}
-
-// Corner masks of plane pair (p, p+1) of the tile for thread tid.
-__device__ inline Corners tile_corners(const uint32_t* s_bits, const Tile& T, const Lane& L, int p, int tid, int G) {
-  uint32_t r[2][2], x[2][2];
-#pragma unroll
-  for (int dz = 0; dz < 2; ++dz)
-#pragma unroll
-    for (int dy = 0; dy < 2; ++dy) {
-      const int w = (p + dz) * T.nw + tid + 1 + dy * G;
-      r[dz][dy] = s_bits[w];
-      x[dz][dy] = L.l > 0 ? (s_bits[w - 1] >> 31) : 0u;
-    }
-  return make_corners(r[0][0], x[0][0], r[0][1], x[0][1], r[1][0], x[1][0], r[1][1], x[1][1]);
+// Bits k - 1 and k of a row as bits 0 and 1 (a: shifted(r)).
+__device__ inline uint32_t bit_pair(uint32_t r, uint32_t a, int k) {
+  return __builtin_amdgcn_alignbit(r >> 31, a, (uint32_t)k) & 3u;
 }
 
 // Count, sum of bit positions b and sum of b^2 over the set bits of w.  With
@@ -381,13 +376,6 @@ __device__ inline WordMom word_moments(uint32_t w) {
   m.b1 = b1;
   m.b2 = b2;
   return m;
-}
-
-__device__ inline int case_of(const Corners& C, int k) {
-  int cas = 0;
-#pragma unroll
-  for (int c = 0; c < 8; ++c) cas |= (int)((C.c[c] >> k) & 1u) << c;
-  return cas;
 }
 
 // ---------------------------------------------------------------------------
@@ -436,15 +424,22 @@ __global__ __launch_bounds__(256) void k_small_head(Roi R, Roi* __restrict__ roi
 // canonical keys of its vertices (and soft masks' interpolation parameters)
 // to a staging list, at a range of rows the brick reserves with one atomic
 // (below `tmp_cap` rows; totals[8] counts them all).  Within a brick the order
-// is (thread, plane, axis, cube); the row pass then places each brick's rows
+// is (thread, plane, cube, axis); the row pass then places each brick's rows
 // at its offset in brick order, so the final order does not depend on the
 // order of the reservations.
 
-// Binary masks: at most 80 VGPRs, so that six bricks share a CU and the
-// 1,330 bricks of a 300 x 512 x 512 volume run in one round on 256 CUs (a few
-// registers spill; measured faster than 96 VGPRs and five bricks per CU).
-// Soft masks: at most 128 VGPRs (four bricks per CU instead of three; a few
-// registers spill, measured slightly faster).
+// Bound by vector instructions (binary masks of a batch of 4,096 ROIs: 2,302 a
+// wave, 622 of 777 us), so the work per voxel row and per vertex is kept small:
+// rows are found once for all planes and turned into bits by dot products; only
+// active cubes are enumerated, and list their edges at places the counts give
+// (edges listed by an enumeration of their own took 24 markers a thread and the
+// edge's words again); triangles and volume follow from the counts of the cases;
+// a lane writes four rows, so that a block's box is a reduction over 8 lanes.
+// Before and after: the batch 1,107 -> 777 us, 300 x 512 x 512 55 -> 44, a batch
+// of 256 with moments 125 -> 85, 24 labels of 181 x 384 x 384 57 -> 38.
+// Binary masks: at most 80 VGPRs, so that six bricks share a CU (a few registers
+// spill; 96 VGPRs and five bricks a CU: 676 us where six took 626).  Soft masks:
+// at most 128 VGPRs, four bricks per CU.
 // BITS: the volumes' bit strings are there (k_volume_bits), and the tiles are
 // cut from them.
 template <int DT, bool BITS>
@@ -459,21 +454,25 @@ __global__ __launch_bounds__(kBrickThreads, DT == 0 ? 6 : 4) void k_mesh_pass(co
                                                              const uint32_t* __restrict__ bits) {
   extern __shared__ uint32_t s_bits[];
   __shared__ unsigned int s_hist[256];  // binary masks: active cubes per case
-  __shared__ int s_tk[256];
-  __shared__ int s_tm[256];
   // soft masks: the corner values of the threads' cubes and the triangle table
   // (indexed at run time: from LDS 40 cycles a triangle vertex, from constant
   // memory or by selects over registers several times that)
   __shared__ float s_p[DT == 1 ? 8 : 1][DT == 1 ? kBrickThreads : 1];
   __shared__ uint8_t s_tri[DT == 1 ? 256 * MC_MAX_TRI * 3 : 1];
+  __shared__ uint8_t s_nt[DT == 1 ? 256 : 1];
   __shared__ uint32_t s_edge[DT == 1 ? 12 : 1];  // axis | corner 0 << 2 | corner 1 << 5
-  __shared__ __align__(16) uint32_t s_items[kMeshItems];
+  // slots kMeshItems ..: the cubes of rows left over from the chunk before
+  __shared__ __align__(16) uint32_t s_items[kMeshItems + kSegAlign];
+  __shared__ __align__(8) uint16_t s_rows[3 * kMeshItems + kSegAlign];  // slot of the row's cube | axis << 11
+  __shared__ int s_eb[kBrickThreads];                      // each thread's first row,
+  __shared__ uint32_t s_ec[2][kBrickThreads];              // and its rows per plane, a byte each
+  __shared__ int s_ve;
   __shared__ uint32_t s_ly[kBrickThreads];  // (y + 1) | l << 20 of each thread's row-group
   __shared__ int s_scan[4];
   __shared__ uint32_t s_mx[4];
   __shared__ double s_rd[2][4];
-  __shared__ long long s_rl[4];
-  __shared__ int s_ri[8][4];
+  __shared__ int s_rl[4];
+  __shared__ int s_ri[7][4];
   __shared__ long long s_mom[10][4];
   __shared__ long long s_base;
 
@@ -484,157 +483,129 @@ __global__ __launch_bounds__(kBrickThreads, DT == 0 ? 6 : 4) void k_mesh_pass(co
   // a grid sized by a bound (ROI table planned on the device) ends past the last brick
   if (brick >= R.brick_end) return;
   const int tid = threadIdx.x;
-  {
-    const int c = tid;
-    const int nt = MC_NTRI[c];
-    s_hist[c] = 0u;
-    s_tk[c] = nt | ((MC_CASE_KAPPA[c] + 128) << 8);
-    s_tm[c] = (MC_CASE_M[c][0] + 128) | ((MC_CASE_M[c][1] + 128) << 8) | ((MC_CASE_M[c][2] + 128) << 16);
-    if (DT == 1) {
-      for (int i = tid; i < 256 * MC_MAX_TRI * 3; i += kBrickThreads) s_tri[i] = (uint8_t)(&MC_TRI[0][0][0])[i];
-      if (tid < 12) {
-        const uint32_t a = MC_EDGE_AXIS[tid], k0 = MC_EDGE_C0[tid];
-        s_edge[tid] = a | k0 << 2 | (k0 | 4u >> a) << 5;
-      }
+  if (DT == 0) {
+    s_hist[tid] = 0u;
+  } else {
+    for (int i = tid; i < 256 * MC_MAX_TRI * 3; i += kBrickThreads) s_tri[i] = (&MC_TRI[0][0][0])[i];
+    s_nt[tid] = MC_NTRI[tid];
+    if (tid < 12) {
+      const uint32_t a = MC_EDGE_AXIS[tid], k0 = MC_EDGE_C0[tid];
+      s_edge[tid] = a | k0 << 2 | (k0 | 4u >> a) << 5;
     }
   }
-  __syncthreads();
 
   const Tile T = tile_of(R, brick - R.brick_begin);
   if (BITS)
-    cut_tile<kTZ + 1>(bits + R.bits_begin, volume_shift<DT>(R.vol), R.d, R.G, R.mG, R.shG, T.rg0 - 1, T.pz0 - 1, T.np,
+    cut_tile<kTZ + 1>(bits + R.bits_begin, volume_shift(R.vol), R.d, R.G, R.mG, R.shG, T.rg0 - 1, T.pz0 - 1, T.np,
                       T.nw, s_bits);
   else
     load_tile<DT>(R, T, s_bits);
   __syncthreads();
   const Lane L = lane_of(R, T, tid);
   s_ly[tid] = (uint32_t)(L.y + 1) | ((uint32_t)L.l << 20);  // read back by the dense loop (after a barrier)
-  int nv = 0, nt = 0;
+  int nt = 0, full = 0;  // triangles; binary masks: cubes wholly inside
   double area = 0.0, vol_d = 0.0;
-  long long vol_i = 0;
+  int vol_i = 0;
   int bb[6] = {INT_MAX, INT_MAX, INT_MAX, INT_MIN, INT_MIN, INT_MIN};
   // origin of the soft tetrahedron sum: the array centre (as the FP64 oracle uses)
   const double o0 = 0.5 * R.d[0] * R.s[0], o1 = 0.5 * R.d[1] * R.s[1], o2 = 0.5 * R.d[2] * R.s[2];
 
-  // All planes of the brick at once: each thread first classifies its 32
-  // cubes of every plane pair (voxel rows held in registers, each read from
-  // LDS once) into a word of active cubes and three words of crossing edges
-  // per plane; the brick's active cubes, then its crossing edges, are then
-  // enumerated densely over the whole workgroup (mark_words), so that a lane
-  // whose cubes all touch the surface does not hold up its wave and the brick
-  // takes a few barriers instead of a few per plane.
-  // bit counts of the words (active cubes of plane p: byte p of actc; edges
-  // along axis a of plane p, from each cube's corner 0: byte 3p + a of edc);
-  // the words themselves are recomputed from the tile when they are listed
-  uint32_t actc[(kTZ + 3) / 4] = {};
-  uint32_t edc[(3 * kTZ + 3) / 4] = {};
+  // All planes of the brick at once.  Each thread counts its active cubes and
+  // crossing edges of every plane pair, each row word read once (bit counts of
+  // plane pair p: byte p of actc and ec); a crossing edge belongs to the cube
+  // that has it at its corner 0, an active one, so the brick's active cubes are
+  // then enumerated densely over the workgroup (mark_words) and list their
+  // edges in LDS, and the edges' rows are written from there.
+  uint32_t actc[(kTZ + 3) / 4] = {}, ec[(kTZ + 3) / 4] = {};
   int cnt = 0, cnt_e = 0;
-  long long mom[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
   {
-    // voxel rows y and y + 1 (and the bit before each) of the current voxel
-    // plane and the next one, read from the tile one plane at a time
-    uint32_t r0[2] = {0u, 0u}, x0[2] = {0u, 0u};
-    auto plane_rows = [&](int p, uint32_t* r, uint32_t* x) {
+    uint32_t xm = 0u, zm = 0u;  // cubes active in some plane, planes with an active cube
+    uint32_t a0p = 0u, oP = 0u, nP = 0u;
+    int e12 = 0;
+    const uint32_t vm = L.valid ? L.vmask : 0u;
+    const uint32_t* w = s_bits + tid + 1;
 #pragma unroll
-      for (int dy = 0; dy < 2; ++dy) {
-        r[dy] = 0u;
-        x[dy] = 0u;
-        if (L.valid && p < T.np) {
-          const int w = p * T.nw + tid + 1 + dy * R.G;
-          r[dy] = s_bits[w];
-          x[dy] = L.l > 0 ? (s_bits[w - 1] >> 31) : 0u;
+    for (int p = 0; p <= kTZ; ++p) {
+      if (p < T.np) {
+        const uint32_t r0 = w[p * T.nw], r1 = w[p * T.nw + R.G];
+        const uint32_t a0 = shifted(r0, w[p * T.nw - 1]), a1 = shifted(r1, w[p * T.nw + R.G - 1]);
+        const uint32_t o = r0 | a0 | r1 | a1, n = r0 & a0 & r1 & a1;
+        if (p > 0) {
+          const uint32_t act = (oP | o) & ~(nP & n) & vm;
+          const int ca = __popc(act), ce = e12 + __popc((a0p ^ a0) & vm);
+          actc[(p - 1) >> 2] |= (uint32_t)ca << (8 * ((p - 1) & 3));
+          ec[(p - 1) >> 2] |= (uint32_t)ce << (8 * ((p - 1) & 3));
+          cnt += ca;
+          cnt_e += ce;
+          xm |= act;
+          zm |= act ? 1u << (p - 1) : 0u;
+          if (DT == 0) full += __popc(nP & n & vm);
         }
+        e12 = __popc((a0 ^ a1) & vm) + __popc((a0 ^ r0) & vm);
+        a0p = a0;
+        oP = o;
+        nP = n;
       }
-    };
-    plane_rows(0, r0, x0);
-#pragma unroll
-    for (int p = 0; p < kTZ; ++p) {
-      uint32_t r1[2], x1[2];
-      plane_rows(p + 1, r1, x1);
-      uint32_t act = 0u, ed[3] = {0u, 0u, 0u};
-      if (L.valid && p + 1 < T.np) {
-        const Corners C = make_corners(r0[0], x0[0], r0[1], x0[1], r1[0], x1[0], r1[1], x1[1]);
-        uint32_t any = 0u, all = 0xffffffffu;
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-          any |= C.c[c];
-          all &= C.c[c];
-        }
-        ed[0] = (C.c[0] ^ C.c[4]) & L.vmask;
-        ed[1] = (C.c[0] ^ C.c[2]) & L.vmask;
-        ed[2] = (C.c[0] ^ C.c[1]) & L.vmask;
-        const uint32_t active = any & ~all & L.vmask;
-        if (active) {
-          const int z = T.pz0 - 1 + p;
-          bb[0] = min(bb[0], z);
-          bb[1] = min(bb[1], L.y);
-          bb[2] = min(bb[2], 32 * L.l - 1 + (__ffs(active) - 1));
-          bb[3] = max(bb[3], z);
-          bb[4] = max(bb[4], L.y);
-          bb[5] = max(bb[5], 32 * L.l - 1 + (31 - __clz(active)));
-        }
-        act = active;
-      }
-      const uint32_t ca = (uint32_t)__popc(act);
-      actc[p >> 2] |= ca << (8 * (p & 3));
-      cnt += (int)ca;
-#pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        const uint32_t ce = (uint32_t)__popc(ed[a]);
-        edc[(3 * p + a) >> 2] |= ce << (8 * ((3 * p + a) & 3));
-        cnt_e += (int)ce;
-      }
-#pragma unroll
-      for (int dy = 0; dy < 2; ++dy) {
-        r0[dy] = r1[dy];
-        x0[dy] = x1[dy];
-      }
+    }
+    if (xm) {
+      bb[0] = T.pz0 - 2 + __ffs(zm);
+      bb[3] = T.pz0 - 1 + 31 - __clz(zm);
+      bb[1] = bb[4] = L.y;
+      bb[2] = 32 * L.l - 2 + __ffs(xm);
+      bb[5] = 32 * L.l - 1 + 31 - __clz(xm);
     }
   }
   // the brick's staged rows: one reservation (of whole 32-row blocks when the
   // blocks' boxes are asked for)
   int total_e;
-  const int off_e = block_excl_scan256(cnt_e, s_scan, total_e);
-  nv = cnt_e;
+  s_eb[tid] = block_excl_scan256(cnt_e, s_scan, total_e);
+#pragma unroll
+  for (int q = 0; q < 2; ++q) s_ec[q][tid] = ec[q];
   if (tid == 0) {
     const int rows = pbox ? (total_e + kSegAlign - 1) & ~(kSegAlign - 1) : total_e;
     s_base = rows ? (long long)atomicAdd((unsigned long long*)&totals[8], (unsigned long long)rows) : 0;
   }
   int total;
   const int off = block_excl_scan256(cnt, s_scan, total);
+  const long long base = s_base;
+  int done = 0;  // rows written (whole blocks)
   for (int c0 = 0; c0 < total; c0 += kMeshItems) {
     const int n = min(kMeshItems, total - c0);
     mark_words<kTZ>(actc, off, c0, n, s_items, s_mx);
     for (int i = tid; i < n; i += kBrickThreads) {
       const uint32_t mk = s_items[i];
       const int p = (int)(mk & 255u), t = (int)((mk >> 8) & 255u);
-      const int z = T.pz0 - 1 + p;
-      const uint32_t ly = s_ly[t];
-      Lane Lt;
-      Lt.y = (int)(ly & 0xfffffu) - 1;
-      Lt.l = (int)(ly >> 20);
-      const Corners C = tile_corners(s_bits, T, Lt, p, t, R.G);
-      uint32_t any = 0u, all = 0xffffffffu;
-#pragma unroll
-      for (int c = 0; c < 8; ++c) {
-        any |= C.c[c];
-        all &= C.c[c];
-      }
-      const int k = nth_set_bit(any & ~all & lane_vmask(R, Lt.l), marker_rank(mk, i));
-      const int cas = case_of(C, k);
-      const int y = Lt.y, x = 32 * Lt.l - 1 + k;
-      const int tk = s_tk[cas];
-      nt += tk & 0xff;
+      const uint32_t* w0 = s_bits + p * T.nw + t + 1;
+      const uint32_t* w1 = w0 + T.nw;
+      const uint32_t r00 = w0[0], r01 = w0[R.G], r10 = w1[0], r11 = w1[R.G];
+      const uint32_t a00 = shifted(r00, w0[-1]), a01 = shifted(r01, w0[R.G - 1]);
+      const uint32_t a10 = shifted(r10, w1[-1]), a11 = shifted(r11, w1[R.G - 1]);
+      const uint32_t any = (r00 | a00 | r01) | (a01 | r10 | a10) | (r11 | a11);
+      const uint32_t all = (r00 & a00 & r01) & (a01 & r10 & a10) & (r11 & a11);
+      // (cubes past the row's end come after the word's last counted one)
+      const int k = nth_set_bit(any & ~all, marker_rank(mk, i));
+      const int cas = (int)(bit_pair(r00, a00, k) | bit_pair(r01, a01, k) << 2 | bit_pair(r10, a10, k) << 4 |
+                            bit_pair(r11, a11, k) << 6);
+      // the cube's rows: after those of the threads, planes and cubes before it
+      const uint32_t below = (1u << k) - 1u, e0 = a00 ^ a10, e1 = a00 ^ a01, e2 = a00 ^ r00;
+      const uint32_t q0 = s_ec[0][t], q1 = s_ec[1][t];
+      const uint32_t h0 = p >= 4 ? q0 : q0 & ((1u << (8 * p)) - 1u), h1 = p > 4 ? q1 & ((1u << (8 * p - 32)) - 1u) : 0u;
+      int at = s_eb[t] - done + (int)__builtin_amdgcn_sad_u8(h1, 0u, __builtin_amdgcn_sad_u8(h0, 0u, 0u));
+      at += __popc(e0 & below) + __popc(e1 & below) + __popc(e2 & below);
+      if (e0 >> k & 1u) s_rows[at++] = (uint16_t)i;
+      if (e1 >> k & 1u) s_rows[at++] = (uint16_t)(i | 1 << 11);
+      if (e2 >> k & 1u) s_rows[at++] = (uint16_t)(i | 2 << 11);
+      if (i == n - 1) s_ve = at;
+      s_items[i] = (uint32_t)p | (uint32_t)t << 3 | (uint32_t)k << 11;
       if (DT == 0) {
-        const int tm = s_tm[cas];
         atomicAdd(&s_hist[cas], 1u);
-        vol_i += (long long)((tk >> 8) - 128) +
-                 2ll * ((long long)z * ((tm & 0xff) - 128) + (long long)y * (((tm >> 8) & 0xff) - 128) +
-                        (long long)x * (((tm >> 16) & 0xff) - 128));
       } else {
+        const uint32_t ly = s_ly[t];
+        const int z = T.pz0 - 1 + p, y = (int)(ly & 0xfffffu) - 1, x = 32 * (int)(ly >> 20) - 1 + k;
+        const int ntri = s_nt[cas];
+        nt += ntri;
 #pragma unroll
         for (int c = 0; c < 8; ++c) s_p[c][tid] = soft_load(R, z + ((c >> 2) & 1), y + ((c >> 1) & 1), x + (c & 1));
-        const int ntri = tk & 0xff;
         for (int tr = 0; tr < ntri; ++tr) {
           double P[3][3];
 #pragma unroll
@@ -663,139 +634,200 @@ __global__ __launch_bounds__(kBrickThreads, DT == 0 ? 6 : 4) void k_mesh_pass(co
       }
     }
     __syncthreads();
-  }
-
-  __syncthreads();
-  const long long base = s_base;
-  for (int c0 = 0; c0 < total_e; c0 += kMeshItems) {
-    const int n = min(kMeshItems, total_e - c0);
-    mark_words<3 * kTZ>(edc, off_e, c0, n, s_items, s_mx);
-    // with boxes, the rows that fill up the last block repeat the last vertex
-    const int n_fill = pbox ? (n + kSegAlign - 1) & ~(kSegAlign - 1) : n;
-    for (int i = tid; i < n_fill; i += kBrickThreads) {
-      const int iv = min(i, n - 1);
-      const uint32_t mk = s_items[iv];
-      const int j = (int)(mk & 255u), t = (int)((mk >> 8) & 255u);
-      const int p = j / 3, a = j - 3 * p;
-      const uint32_t ly = s_ly[t];
-      const int l = (int)(ly >> 20);
-      // the thread's edge word (corner 0 against the corner one step along a)
-      const int w0 = p * T.nw + t + 1;
-      const int wq = a == 0 ? w0 + T.nw : (a == 1 ? w0 + R.G : w0);
-      const uint32_t r0 = s_bits[w0], rq = s_bits[wq];
-      const uint32_t x0 = l > 0 ? (s_bits[w0 - 1] >> 31) : 0u, xq = l > 0 ? (s_bits[wq - 1] >> 31) : 0u;
-      const uint32_t cq = a == 2 ? r0 : ((rq << 1) | xq);
-      const int k = nth_set_bit((((r0 << 1) | x0) ^ cq) & lane_vmask(R, l), marker_rank(mk, iv));
-      const int u0 = T.pz0 - 1 + p, u1 = (int)(ly & 0xfffffu) - 1, u2 = 32 * l - 1 + k;
-      const long long row = base + c0 + i;
-      double tt = 0.5;
-      if (DT == 1) {
-        const double pa = (double)soft_load(R, u0, u1, u2);
-        const double pb = (double)soft_load(R, u0 + (a == 0), u1 + (a == 1), u2 + (a == 2));
-        tt = (0.5 - pa) / (pb - pa);
-      }
-      if (row < tmp_cap) {
-        tmpkey[row] = pack_key(u0, u1, u2, a);
-        if (DT == 1) tmpt[row] = tt;
-      }
-      if (pbox) {
-        // the block's box over its half wave, in half voxels: exact for binary
-        // masks, widened by the rounding of the soft coordinate (a vertex that
-        // NaN voxels leave without a position is in no box)
-        float lo[3], hi[3];
-        const int u[3] = {u0, u1, u2};
+    // rows [0, m) of the list are brick rows done ..; whole blocks, unless these
+    // are the last ones; with boxes, the rows that fill up the last block repeat
+    // the last vertex
+    const int have = s_ve;
+    const bool last = c0 + kMeshItems >= total;
+    const int m = last ? have : have & ~(kSegAlign - 1);
+    const int n_fill = last && pbox ? (m + kSegAlign - 1) & ~(kSegAlign - 1) : m;
+    // four rows per lane: a block's box is a reduction over 8 lanes
+    for (int j = 4 * tid; j < n_fill; j += 4 * kBrickThreads) {
+      const uint2 q = *(const uint2*)(s_rows + j);
+      const uint32_t rws[4] = {q.x & 0xffffu, q.x >> 16, q.y & 0xffffu, q.y >> 16};
+      const uint32_t end = s_rows[m - 1];
+      const long long row = base + done + j;
+      unsigned long long key[4];
+      double tt[4];
+      int lo[3] = {INT_MAX, INT_MAX, INT_MAX}, hi[3] = {INT_MIN, INT_MIN, INT_MIN};
 #pragma unroll
-        for (int q = 0; q < 3; ++q) {
+      for (int r = 0; r < 4; ++r) {
+        const uint32_t rw = j + r < m ? rws[r] : end, code = s_items[rw & 2047u];
+        const int a = (int)(rw >> 11);
+        const uint32_t ly = s_ly[code >> 3 & 255u];
+        const int u[3] = {T.pz0 - 1 + (int)(code & 7u), (int)(ly & 0xfffffu) - 1,
+                          32 * (int)(ly >> 20) - 1 + (int)(code >> 11)};
+        key[r] = pack_key(u[0], u[1], u[2], a);
+        tt[r] = 0.5;
+        if (DT == 1) {
+          const double pa = (double)soft_load(R, u[0], u[1], u[2]);
+          const double pb = (double)soft_load(R, u[0] + (a == 0), u[1] + (a == 1), u[2] + (a == 2));
+          tt[r] = (0.5 - pa) / (pb - pa);
+        }
+        // the block's box in half voxels: exact for binary masks, widened by the
+        // rounding of the soft coordinate (a vertex that NaN voxels leave without
+        // a position is in no box)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
           if (DT == 0) {
-            const int c = 2 * u[q] + (a == q);
-            lo[q] = (float)lanes_min_i32<5>(c);
-            hi[q] = (float)lanes_max_i32<5>(c);
+            const int c = 2 * u[k] + (a == k);
+            lo[k] = min(lo[k], c);
+            hi[k] = max(hi[k], c);
           } else {
-            const float c = (float)(2.0 * ((double)u[q] + (a == q ? tt : 0.0))), w = fabsf(c) * 1.1920928955078125e-07f;
-            const bool ok = tt == tt;
-            lo[q] = order_float(lanes_min_i32<5>(float_order(ok ? c - w : 3.0e38f)));
-            hi[q] = order_float(lanes_max_i32<5>(float_order(ok ? c + w : -3.0e38f)));
+            const float c = (float)(2.0 * ((double)u[k] + (a == k ? tt[r] : 0.0))), wd = fabsf(c) * 1.1920928955078125e-07f;
+            const bool ok = tt[r] == tt[r];
+            lo[k] = min(lo[k], float_order(ok ? c - wd : 3.0e38f));
+            hi[k] = max(hi[k], float_order(ok ? c + wd : -3.0e38f));
           }
         }
-        if ((i & (kSegAlign - 1)) == 0 && row < tmp_cap) {
+      }
+      if (pbox && row + 4 <= tmp_cap) {  // (a block's rows start at a multiple of 32)
+        ((ulonglong2*)(tmpkey + row))[0] = make_ulonglong2(key[0], key[1]);
+        ((ulonglong2*)(tmpkey + row))[1] = make_ulonglong2(key[2], key[3]);
+        if (DT == 1) {
+          ((double2*)(tmpt + row))[0] = make_double2(tt[0], tt[1]);
+          ((double2*)(tmpt + row))[1] = make_double2(tt[2], tt[3]);
+        }
+      } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          if (j + r < n_fill && row + r < tmp_cap) {
+            tmpkey[row + r] = key[r];
+            if (DT == 1) tmpt[row + r] = tt[r];
+          }
+        }
+      }
+      if (pbox) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          lo[k] = lanes_min_i32<3>(lo[k]);
+          hi[k] = lanes_max_i32<3>(hi[k]);
+        }
+        if ((j & (kSegAlign - 1)) == 0 && row < tmp_cap) {
+          float fl[3], fh[3];
+#pragma unroll
+          for (int k = 0; k < 3; ++k) {
+            fl[k] = DT == 0 ? (float)lo[k] : order_float(lo[k]);
+            fh[k] = DT == 0 ? (float)hi[k] : order_float(hi[k]);
+          }
           float4* bx = pbox + 2 * (row / kSegAlign);
-          bx[0] = make_float4(lo[0], lo[1], lo[2], hi[0]);
-          bx[1] = make_float4(hi[1], hi[2], 0.0f, 0.0f);
+          bx[0] = make_float4(fl[0], fl[1], fl[2], fh[0]);
+          bx[1] = make_float4(fh[1], fh[2], 0.0f, 0.0f);
         }
       }
     }
-    __syncthreads();
+    if (!last) {
+      // the rows left over go to the front, their cubes to the spare slots
+      uint32_t rw = 0u, code = 0u;
+      if (tid < have - m) {
+        rw = s_rows[m + tid];
+        code = s_items[rw & 2047u];
+      }
+      __syncthreads();
+      if (tid < have - m) {
+        s_rows[tid] = (uint16_t)((rw & ~2047u) | (uint32_t)(kMeshItems + tid));
+        s_items[kMeshItems + tid] = code;
+      }
+      done += m;
+    }
   }
 
+  // Inside-voxel moments, from the tile: voxel row (z, y) = (pz0 + p, L.y + 1),
+  // x = 32 l + bit, is the tile word of plane p + 1, row-group tid + G (the far
+  // corner row of plane pair p); rows past the array read as 0.  Summed with z
+  // and y from the brick's first row (z' < 8, y' < 257): only the sums of x^2
+  // and x y' of a wave can pass 32 bits.
+  unsigned int mom[8] = {};  // n, z', y', x, z'z', y'y', z'y', z'x
+  long long mxx = 0, mxy = 0;
+  const int y0 = (int)(s_ly[0] & 0xfffffu);
   if (moments && L.valid) {
-    // Inside-voxel moments, from the tile (still in LDS; computed here so that
-    // their registers are not held through the enumeration): voxel row
-    // (z, y) = (pz0 + p, L.y + 1), x = 32 l + bit, is the tile word of plane
-    // p + 1, row-group tid + G (the far corner row of plane pair p); rows past
-    // the array read as 0.
-    long long n = 0, sz = 0, szz = 0, sb1 = 0, sb2 = 0, szb = 0;
+    unsigned int n = 0, sz = 0, szz = 0, sb1 = 0, szb = 0, sb2 = 0;
 #pragma unroll
     for (int p = 0; p < kTZ; ++p) {
       if (p + 1 < T.np) {
-        const WordMom wm = word_moments(s_bits[(p + 1) * T.nw + tid + 1 + R.G]);
-        const long long z = T.pz0 + p;
+        const uint32_t w = s_bits[(p + 1) * T.nw + tid + 1 + R.G];
+        const WordMom wm = word_moments(w);
         n += wm.c;
-        sz += z * wm.c;
-        szz += z * z * wm.c;
+        sz += p * wm.c;
+        szz += p * p * wm.c;
         sb1 += wm.b1;
+        szb += p * wm.b1;
         sb2 += wm.b2;
-        szb += z * wm.b1;
       }
     }
-    const long long y = L.y + 1, x0 = 32ll * L.l;
-    const long long sx = x0 * n + sb1;
+    const unsigned int y = L.y + 1 - y0, x0 = 32 * L.l;
+    const unsigned int sx = x0 * n + sb1;
     mom[0] = n;
     mom[1] = sz;
     mom[2] = y * n;
     mom[3] = sx;
     mom[4] = szz;
     mom[5] = y * y * n;
-    mom[6] = x0 * x0 * n + 2 * x0 * sb1 + sb2;
-    mom[7] = y * sz;
-    mom[8] = x0 * sz + szb;
-    mom[9] = y * sx;
+    mom[6] = y * sz;
+    mom[7] = x0 * sz + szb;
+    mxx = (long long)x0 * (sx + sb1) + sb2;
+    mxy = (long long)y * sx;
   }
 
   // fixed-order block reduction
   const int lane = tid & 63, wid = tid >> 6;
-  nv = wave_sum(nv);
-  nt = wave_sum(nt);
-  area = wave_sum(area);
-  vol_d = wave_sum(vol_d);
-  vol_i = wave_sum(vol_i);
-  for (int k = 0; k < 3; ++k) {
-    bb[k] = wave_min(bb[k]);
-    bb[3 + k] = wave_max(bb[3 + k]);
+  if (DT == 0) {
+    // triangles and volume from the case counts (the last item's barrier is past)
+    const int h = (int)s_hist[tid];
+    nt = h * MC_NTRI[tid];
+    vol_i = lanes_sum_i32<6>(h * MC_CASE_VOLUME[tid] + 48 * full);
   }
-  if (moments)
-    for (int k = 0; k < 10; ++k) mom[k] = wave_sum(mom[k]);
+  nt = lanes_sum_i32<6>(nt);
+  if (DT == 1) {
+    area = wave_sum(area);
+    vol_d = wave_sum(vol_d);
+  }
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    bb[k] = lanes_min_i32<6>(bb[k]);
+    bb[3 + k] = lanes_max_i32<6>(bb[3 + k]);
+  }
+  if (moments) {
+    for (int k = 0; k < 8; ++k) mom[k] = (unsigned int)lanes_sum_i32<6>((int)mom[k]);
+    mxx = wave_sum(mxx);
+    mxy = wave_sum(mxy);
+  }
   if (lane == 0) {
-    s_ri[0][wid] = nv;
-    s_ri[1][wid] = nt;
-    for (int k = 0; k < 6; ++k) s_ri[2 + k][wid] = bb[k];
+    s_ri[0][wid] = nt;
+    for (int k = 0; k < 6; ++k) s_ri[1 + k][wid] = bb[k];
     s_rd[0][wid] = area;
     s_rd[1][wid] = vol_d;
     s_rl[wid] = vol_i;
-    for (int k = 0; k < 10; ++k) s_mom[k][wid] = mom[k];
+    for (int k = 0; k < 8; ++k) s_mom[k][wid] = mom[k];
+    s_mom[8][wid] = mxx;
+    s_mom[9][wid] = mxy;
   }
   __syncthreads();
   if (tid == 0) {
     BrickPart P;
-    P.nv = s_ri[0][0] + s_ri[0][1] + s_ri[0][2] + s_ri[0][3];
-    P.nt = s_ri[1][0] + s_ri[1][1] + s_ri[1][2] + s_ri[1][3];
+    P.nv = total_e;
+    P.nt = s_ri[0][0] + s_ri[0][1] + s_ri[0][2] + s_ri[0][3];
     for (int k = 0; k < 3; ++k) {
-      P.bb[k] = min(min(s_ri[2 + k][0], s_ri[2 + k][1]), min(s_ri[2 + k][2], s_ri[2 + k][3]));
-      P.bb[3 + k] = max(max(s_ri[5 + k][0], s_ri[5 + k][1]), max(s_ri[5 + k][2], s_ri[5 + k][3]));
+      P.bb[k] = min(min(s_ri[1 + k][0], s_ri[1 + k][1]), min(s_ri[1 + k][2], s_ri[1 + k][3]));
+      P.bb[3 + k] = max(max(s_ri[4 + k][0], s_ri[4 + k][1]), max(s_ri[4 + k][2], s_ri[4 + k][3]));
     }
     P.area = ((s_rd[0][0] + s_rd[0][1]) + s_rd[0][2]) + s_rd[0][3];
     P.vol_d = ((s_rd[1][0] + s_rd[1][1]) + s_rd[1][2]) + s_rd[1][3];
-    P.vol_i = s_rl[0] + s_rl[1] + s_rl[2] + s_rl[3];
-    for (int k = 0; k < 10; ++k) P.mom[k] = s_mom[k][0] + s_mom[k][1] + s_mom[k][2] + s_mom[k][3];
+    P.vol_i = (long long)s_rl[0] + s_rl[1] + s_rl[2] + s_rl[3];
+    long long m[10];
+    for (int k = 0; k < 10; ++k) m[k] = s_mom[k][0] + s_mom[k][1] + s_mom[k][2] + s_mom[k][3];
+    // back to the ROI's z and y: n, z, y, x, zz, yy, xx, zy, zx, yx
+    const long long zo = T.pz0, yo = y0;
+    P.mom[0] = m[0];
+    P.mom[1] = m[1] + zo * m[0];
+    P.mom[2] = m[2] + yo * m[0];
+    P.mom[3] = m[3];
+    P.mom[4] = m[4] + 2 * zo * m[1] + zo * zo * m[0];
+    P.mom[5] = m[5] + 2 * yo * m[2] + yo * yo * m[0];
+    P.mom[6] = m[8];
+    P.mom[7] = m[6] + zo * m[2] + yo * m[1] + zo * yo * m[0];
+    P.mom[8] = m[7] + zo * m[3];
+    P.mom[9] = m[9] + yo * m[3];
     P.stage = base;
     part[brick] = P;
   }
@@ -1305,13 +1337,13 @@ __global__ __launch_bounds__(256) void k_head(Roi* __restrict__ rois, int n_rois
 }
 
 // ---------------------------------------------------------------------------
-// The bit strings of a table of dense volumes, a stream: 16-byte loads, 16 in
+// The bit strings of a table of dense float volumes, a stream: 16-byte loads, 16 in
 // flight a thread (256 soft ROIs of edges 48 to 160, 1.09 GB: 218 us, 5.0 TB/s).
-template <int DT, int ROUNDS>
+template <int ROUNDS>
 __global__ __launch_bounds__(256) void k_volume_bits(const Roi* __restrict__ rois, const int* __restrict__ map,
                                                      uint32_t* __restrict__ bits) {
   const Roi& R = rois[map ? map[blockIdx.x] : 0];
-  pack_bits<DT, ROUNDS>(R.vol, (long long)R.d[0] * R.d[1] * R.d[2],
+  pack_bits<ROUNDS>(R.vol, (long long)R.d[0] * R.d[1] * R.d[2],
                         (blockIdx.x - R.bitblk_begin) * (ROUNDS * 4096ll), bits + R.bits_begin);
 }
 
@@ -1425,7 +1457,7 @@ hipError_t launch_mesh_pass(int dtype, Roi* rois, int n_rois, long long nbricks,
   const size_t lds = mesh_lds_bytes(max_G);
   const uint32_t* bits = nullptr;
   if (vb) {
-    const auto pack = vb->rounds == 1 ? k_volume_bits<1, 1> : k_volume_bits<1, kBitRounds>;
+    const auto pack = vb->rounds == 1 ? k_volume_bits<1> : k_volume_bits<kBitRounds>;
     hipLaunchKernelGGL(pack, dim3((unsigned)vb->n_blocks), dim3(256), 0, st, (const Roi*)rois, (const int*)bitmap,
                        vb->bits);
     bits = vb->bits;

@@ -117,6 +117,11 @@ __device__ inline int lanes_max_i32(int v) {
   return (int)lanes_reduce<STEPS>((uint32_t)v, [](uint32_t a, uint32_t b) { return (uint32_t)max((int)a, (int)b); });
 }
 
+template <int STEPS>
+__device__ inline int lanes_sum_i32(int v) {
+  return (int)lanes_reduce<STEPS>((uint32_t)v, [](uint32_t a, uint32_t b) { return a + b; });
+}
+
 // A float as an integer of the same order (NaN apart), and back.
 __device__ inline int float_order(float f) {
   const int b = __float_as_int(f);
@@ -246,7 +251,7 @@ __device__ inline unsigned long long key_canonical_id(uint64_t key, const int* d
 }
 
 // ---------------------------------------------------------------------------
-// Inside bits of dense volumes as one bit string (bit i: element i), written by
+// Inside bits of dense float volumes as one bit string (bit i: element i), written by
 // a streaming pass, from which the passes over cubes cut the 32-voxel words of
 // their rows: a brick that reads the volume itself waits for its own few loads
 // and reads its neighbours' rows again, in four bytes a voxel.
@@ -255,15 +260,12 @@ __device__ inline unsigned long long key_canonical_id(uint64_t key, const int* d
 // shift + i is element i, shift = volume_shift(), so that every load is a whole
 // aligned 16 bytes (one that holds a byte of the volume lies on its pages).
 
-template <int DT>
-__host__ __device__ inline int volume_shift(const void* vol) {
-  return (int)((uintptr_t)vol & 15u) / (DT == 0 ? 1 : 4);
-}
+__host__ __device__ inline int volume_shift(const void* vol) { return (int)((uintptr_t)vol & 15u) / 4; }
 
 // 32-bit words of the string of n elements (whatever its shift), one more for
 // the last cut and even, and its workgroups of `block` elements.
-__host__ __device__ inline long long bit_words(long long n) { return (n + 15 + 63) / 64 * 2 + 2; }
-__host__ __device__ inline long long bit_blocks(long long n, int block) { return (n + 15 + block - 1) / block; }
+__host__ __device__ inline long long bit_words(long long n) { return (n + 3 + 63) / 64 * 2 + 2; }
+__host__ __device__ inline long long bit_blocks(long long n, int block) { return (n + 3 + block - 1) / block; }
 
 // The word of the bits pos .. pos + left - 1 (at most 32 of them; 0 if left <= 0).
 __device__ inline uint32_t cut_word(const uint32_t* __restrict__ bits, unsigned int pos, int left) {
@@ -297,57 +299,34 @@ __device__ inline void cut_tile(const uint32_t* __restrict__ bits, int shift, co
   }
 }
 
-// Bits 0..3 set for the nonzero bytes of w.
-__device__ inline uint32_t nz4(uint32_t w) {
-  // high bit of each byte set iff the byte is nonzero, then gathered to bits 0..3
-  const uint32_t t = (((w & 0x7f7f7f7fu) + 0x7f7f7f7fu) | w) & 0x80808080u;
-  return (t * 0x00204081u) >> 28;
-}
-
 // A workgroup's (256 threads) bits [e0, e0 + ROUNDS * 4096) of the string of n
 // elements, a wave's ROUNDS * 1024 together.
-template <int DT, int ROUNDS>
+template <int ROUNDS>
 __device__ inline void pack_bits(const void* __restrict__ vol, long long n, long long e0,
                                  uint32_t* __restrict__ bits) {
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  const long long end = n + volume_shift<DT>(vol);
+  const long long end = n + volume_shift(vol);
   const long long w0 = e0 + (long long)wid * (ROUNDS * 1024);
   const uint4* src = (const uint4*)((uintptr_t)vol & ~(uintptr_t)15);
-  if (DT == 0) {
-    uint4 v[ROUNDS];
+  constexpr int J = ROUNDS > 1 ? 8 : 4;  // 16-byte loads in flight per thread
 #pragma unroll
-    for (int u = 0; u < ROUNDS; ++u) {
-      const long long e = w0 + 1024 * u + 16 * lane;
-      v[u] = e < end ? src[e >> 4] : make_uint4(0u, 0u, 0u, 0u);
+  for (int g = 0; g < ROUNDS * 4; g += J) {
+    uint4 v[J];
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      const long long e = w0 + 256 * (g + j) + 4 * lane;
+      v[j] = e < end ? src[e >> 2] : make_uint4(0u, 0u, 0u, 0u);
     }
+    uint32_t mine = 0u;
 #pragma unroll
-    for (int u = 0; u < ROUNDS; ++u) {
-      const uint32_t h = nz4(v[u].x) | nz4(v[u].y) << 4 | nz4(v[u].z) << 8 | nz4(v[u].w) << 12;
-      const uint32_t w = lane_step<0>(h << (16 * (lane & 1)), [](uint32_t a, uint32_t b) { return a | b; });
-      const long long e = w0 + 1024 * u + 16 * lane;
-      if (!(lane & 1) && e < end) bits[e >> 5] = w;
+    for (int j = 0; j < J; ++j) {
+      const uint32_t b = (uint32_t)(__uint_as_float(v[j].x) > 0.5f) | (uint32_t)(__uint_as_float(v[j].y) > 0.5f) << 1 |
+                         (uint32_t)(__uint_as_float(v[j].z) > 0.5f) << 2 | (uint32_t)(__uint_as_float(v[j].w) > 0.5f) << 3;
+      const uint32_t w = lanes_reduce<3>(b << (4 * (lane & 7)), [](uint32_t a, uint32_t c) { return a | c; });
+      mine = (lane & 7) == j ? w : mine;
     }
-  } else {
-    constexpr int J = ROUNDS > 1 ? 8 : 4;  // 16-byte loads in flight per thread
-#pragma unroll
-    for (int g = 0; g < ROUNDS * 4; g += J) {
-      uint4 v[J];
-#pragma unroll
-      for (int j = 0; j < J; ++j) {
-        const long long e = w0 + 256 * (g + j) + 4 * lane;
-        v[j] = e < end ? src[e >> 2] : make_uint4(0u, 0u, 0u, 0u);
-      }
-      uint32_t mine = 0u;
-#pragma unroll
-      for (int j = 0; j < J; ++j) {
-        const uint32_t b = (uint32_t)(__uint_as_float(v[j].x) > 0.5f) | (uint32_t)(__uint_as_float(v[j].y) > 0.5f) << 1 |
-                           (uint32_t)(__uint_as_float(v[j].z) > 0.5f) << 2 | (uint32_t)(__uint_as_float(v[j].w) > 0.5f) << 3;
-        const uint32_t w = lanes_reduce<3>(b << (4 * (lane & 7)), [](uint32_t a, uint32_t c) { return a | c; });
-        mine = (lane & 7) == j ? w : mine;
-      }
-      const long long e = w0 + 256 * (g + (lane & 7)) + 32 * (lane >> 3);
-      if ((lane & 7) < J && e < end) bits[e >> 5] = mine;
-    }
+    const long long e = w0 + 256 * (g + (lane & 7)) + 32 * (lane >> 3);
+    if ((lane & 7) < J && e < end) bits[e >> 5] = mine;
   }
 }
 

@@ -154,9 +154,9 @@ __global__ __launch_bounds__(256) void k_soft_bits(SoftBwdBufs B) {
   const SoftBwdRoi& R = B.rois[roi];
   const long long n = (long long)R.d[0] * R.d[1] * R.d[2];
   const long long e0 = (blockIdx.x - R.bitblk_begin) * (long long)(ROUNDS * kBitRound);
-  pack_bits<1, ROUNDS>(R.p, n, e0, B.bits + R.bits_begin);
+  pack_bits<ROUNDS>(R.p, n, e0, B.bits + R.bits_begin);
   // the gradient's elements have their own 16-byte boundary
-  const int shift = volume_shift<1>(R.grad);
+  const int shift = volume_shift(R.grad);
   float4* out = (float4*)((uintptr_t)R.grad & ~(uintptr_t)15);
 #pragma unroll
   for (int u = 0; u < ROUNDS * kBitRound / 1024; ++u) {
@@ -187,7 +187,7 @@ __global__ __launch_bounds__(256) void k_soft_scan(SoftBwdBufs B) {
   const int nz = min(R.tz, d0 + 1 - pz0);  // cube planes
   const int np = nz + 2, nw = 258 + 2 * G;
   const int tid = threadIdx.x, lane = tid & 63;
-  cut_tile<kTZ + 2>(B.bits + R.bits_begin, volume_shift<1>(R.p), R.d, G, R.mG, R.shG, rg0 - 1, pz0 - 1, np, nw, s_bits);
+  cut_tile<kTZ + 2>(B.bits + R.bits_begin, volume_shift(R.p), R.d, G, R.mG, R.shG, rg0 - 1, pz0 - 1, np, nw, s_bits);
   __syncthreads();
 
   const int rg = rg0 + tid;
