@@ -38,14 +38,6 @@ namespace s3d {
 // ---------------------------------------------------------------------------
 // Voxel bytes to inside bits, four at a time.
 
-// Bits 7..14 set for the nonzero bytes of x (low four) and y.
-__device__ inline uint32_t nz8(uint32_t x, uint32_t y) {
-  // high bit of each byte set iff the byte is nonzero, then gathered by dot products
-  const uint32_t s = (((x & 0x7f7f7f7fu) + 0x7f7f7f7fu) | x) & 0x80808080u;
-  const uint32_t t = (((y & 0x7f7f7f7fu) + 0x7f7f7f7fu) | y) & 0x80808080u;
-  return __builtin_amdgcn_udot4(s, 0x08040201u, __builtin_amdgcn_udot4(t, 0x80402010u, 0u, false), false);
-}
-
 // Active cubes per chunk of a brick's dense enumeration (4 per thread).
 constexpr int kMeshItems = 1024;
 static_assert(kMeshItems == 4 * kBrickThreads, "the slot scan gives each thread 4 slots");

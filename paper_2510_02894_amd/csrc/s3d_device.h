@@ -250,6 +250,14 @@ __device__ inline unsigned long long key_canonical_id(uint64_t key, const int* d
   return 3ull * lin + a;
 }
 
+// Bits 7..14 set for the nonzero bytes of x (low four) and y.
+__device__ inline uint32_t nz8(uint32_t x, uint32_t y) {
+  // high bit of each byte set iff the byte is nonzero, then gathered by dot products
+  const uint32_t s = (((x & 0x7f7f7f7fu) + 0x7f7f7f7fu) | x) & 0x80808080u;
+  const uint32_t t = (((y & 0x7f7f7f7fu) + 0x7f7f7f7fu) | y) & 0x80808080u;
+  return __builtin_amdgcn_udot4(s, 0x08040201u, __builtin_amdgcn_udot4(t, 0x80402010u, 0u, false), false);
+}
+
 // ---------------------------------------------------------------------------
 // Inside bits of dense float volumes as one bit string (bit i: element i), written by
 // a streaming pass, from which the passes over cubes cut the 32-voxel words of
