@@ -391,7 +391,11 @@ __global__ __launch_bounds__(64 * kWaves, 7) void k_block_seed(BlockBufs B) {
   static_assert(kWaves == 4, "a wave per family");
   const long long nsb = staged_superblocks(B);
   const int lane = threadIdx.x & 63, g = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  for (long long A = blockIdx.x; A < nsb; A += gridDim.x) {
+  // neighbouring superblocks one after another: a ROI's first ones raise its
+  // maxima, and most of the others then cannot reach them (4,096 ROIs of 50 M
+  // vertices: 304 us; dealt over the workgroups, all of a ROI at once, 518)
+  const long long share = (nsb + gridDim.x - 1) / gridDim.x, end = min(nsb, (blockIdx.x + 1) * share);
+  for (long long A = blockIdx.x * share; A < end; ++A) {
     const float4 a0 = B.sbox[2 * A], a1 = B.sbox[2 * A + 1];
     const int r = __builtin_amdgcn_readfirstlane(__float_as_int(a1.z));
     const Roi& R = B.rois[r];
