@@ -324,10 +324,6 @@ __device__ inline Lane lane_of(const Roi& R, const Tile& T, int tid) {
   return L;
 }
 
-// The bits one voxel before those of row word r (prev: the word before it;
-// bit 31 of a row's last word lies past the array, so it is 0 before a row).
-__device__ inline uint32_t shifted(uint32_t r, uint32_t prev) { return __builtin_amdgcn_alignbit(r, prev, 31u); }
-
 // Bits k - 1 and k of a row as bits 0 and 1 (a: shifted(r)).
 __device__ inline uint32_t bit_pair(uint32_t r, uint32_t a, int k) {
   return __builtin_amdgcn_alignbit(r >> 31, a, (uint32_t)k) & 3u;

@@ -282,6 +282,10 @@ __device__ inline uint32_t cut_word(const uint32_t* __restrict__ bits, unsigned 
   return left >= 32 ? w : w & ((1u << left) - 1u);
 }
 
+// The bits one voxel before those of row word r (prev: the word before it;
+// bit 31 of a row's last word lies past the array, so it is 0 before a row).
+__device__ inline uint32_t shifted(uint32_t r, uint32_t prev) { return __builtin_amdgcn_alignbit(r, prev, 31u); }
+
 // The words of voxel planes z0 .. z0 + np - 1 (at most MAXP), row-groups rg0 ..
 // rg0 + nw - 1 (row-group = cube row * G + group; 0 outside the array) of a
 // dense volume of dims d into tile[plane * nw + word].  Thread t (of 256) takes

@@ -284,8 +284,8 @@ struct SoftBwdBufs {
   long long cap_cubes, cap_vox;
   unsigned long long* cubes;  // [cap_cubes] min corner (pack_key with axis 0) and ROI
   int* croi;
-  double* cgrad;              // [12 cap_cubes] per cube edge, the gradient's component along it
-  float* egrad;               // [3 cap_cubes] the summed gradient of the edges from its min corner
+  double* cgrad;              // [12][cap_cubes] per cube edge, the gradient's component along it
+  float* egrad;               // [3][cap_cubes] the summed gradient of the edges from its min corner
   unsigned long long* vox;    // [cap_vox]
   int* vroi;
   unsigned int* index;        // per cube of every ROI: its place in the list (active cubes only)

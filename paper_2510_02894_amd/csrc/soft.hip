@@ -24,13 +24,15 @@
 //      evaluates every triangle three times (5,440 instructions an edge);
 //      k_soft_diam then adds the diameters' terms to the ends of their pairs;
 //   3. k_soft_edges sums each crossing edge over its four cubes, in a fixed order,
-//      into (dL/dx_v)_a s_a / (p_b - p_u)^2, three floats per active cube;
+//      into (dL/dx_v)_a s_a / (p_b - p_u)^2, three floats per active cube (sums and
+//      values edge by edge, since neighbouring cubes along a row are neighbours in
+//      the list: with a cube's 12 side by side this pass took 349 us);
 //   4. k_soft_voxels, a thread per listed voxel: the terms of its (at most six)
 //      crossing edges, the edge's value times 0.5 - p_b or -(0.5 - p_u).
 //      Bound: latency of scattered reads, all of a voxel's in flight at once.
 // No float atomics: the result does not depend on scheduling.
-// Measured on a batch of 256 soft ROIs of edges 48 to 160 (us): bits 424, scan 367, cubes 367,
-// edges 348, voxels 210, in all 1,716, against 2,408 of a wave per cube row that
+// Measured on a batch of 256 soft ROIs of edges 48 to 160 (us): bits 424, scan 360, cubes 364,
+// edges 310, voxels 207, in all 1,665, against 2,408 of a wave per cube row that
 // listed the edges (540), a thread per edge (1,064) and a gather over all voxels
 // (804).
 #include <hip/hip_runtime.h>
@@ -207,9 +209,8 @@ __global__ __launch_bounds__(256) void k_soft_scan(SoftBwdBufs B) {
     const uint32_t* w0 = s_bits + p * nw + tid + 1;  // plane z, row y
     const uint32_t* w1 = w0 + nw;                    // plane z + 1
     const uint32_t r00 = w0[0], r01 = w0[G], r10 = w1[0], r11 = w1[G];
-    const uint32_t x00 = l > 0 ? w0[-1] >> 31 : 0u, x01 = l > 0 ? w0[G - 1] >> 31 : 0u;
-    const uint32_t x10 = l > 0 ? w1[-1] >> 31 : 0u, x11 = l > 0 ? w1[G - 1] >> 31 : 0u;
-    const uint32_t a00 = r00 << 1 | x00, a01 = r01 << 1 | x01, a10 = r10 << 1 | x10, a11 = r11 << 1 | x11;
+    const uint32_t a00 = shifted(r00, w0[-1]), a01 = shifted(r01, w0[G - 1]);
+    const uint32_t a10 = shifted(r10, w1[-1]), a11 = shifted(r11, w1[G - 1]);
     act[p] = (a00 | r00 | a01 | r01 | a10 | r10 | a11 | r11) & ~(a00 & r00 & a01 & r01 & a10 & r10 & a11 & r11) & cmask;
     n_e += __popc((a00 ^ a10) & cmask) + __popc((a00 ^ a01) & cmask) + __popc((a00 ^ r00) & cmask);
     // the voxel row (z + 1, y + 1) against its six neighbours
@@ -327,12 +328,12 @@ __global__ __launch_bounds__(kCubeThreads, 4) void k_soft_cubes(SoftBwdBufs B) {
       s_g[e1][tid] += term(P2, P0, d1);
       s_g[e2][tid] += term(P0, P1, d2);
     }
-    double* out = B.cgrad + 12 * i;
+    double* out = B.cgrad + i;
 #pragma unroll
     for (int e = 0; e < 12; ++e) {
       constexpr uint8_t c0[12] = {0, 1, 2, 3, 0, 1, 4, 5, 0, 2, 4, 6};
       const int k0 = c0[e], k1 = k0 | 4 >> (e >> 2);
-      if ((cas >> k0 ^ cas >> k1) & 1) out[e] = s_g[e][tid];
+      if ((cas >> k0 ^ cas >> k1) & 1) out[e * B.cap_cubes] = s_g[e][tid];
     }
   }
 }
@@ -372,7 +373,7 @@ __global__ __launch_bounds__(64) void k_soft_diam(SoftBwdBufs B) {
       // (a saved context of other probabilities may name an edge outside the grid)
       if (u[0] >= -1 && u[0] < R.d[0] && u[1] >= -1 && u[1] < R.d[1] && u[2] >= -1 && u[2] < R.d[2]) {
         const unsigned int idx = B.index[R.cube_begin + cube_index(R.d, u[0], u[1], u[2])];
-        if ((long long)idx < listed_cubes(B)) at = 12ll * idx + 4 * a;
+        if ((long long)idx < listed_cubes(B)) at = 4 * a * B.cap_cubes + idx;
       }
     }
   }
@@ -404,32 +405,34 @@ __global__ __launch_bounds__(256) void k_soft_edges(SoftBwdBufs B) {
     const long long cs[3] = {(long long)(R.d[1] + 1) * (R.d[2] + 1), R.d[2] + 1, 1};
     const unsigned int* index = B.index + R.cube_begin + cube_index(R.d, u0, u1, u2);
     bool cross[3];
-    unsigned int idx[3][3];
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      cross[a] = (f0 > 0.5f) != (fa[a] > 0.5f);
-      // a crossing edge lies inside the grid along its other axes: so do its cubes
-      const long long sb = cs[a == 0 ? 1 : 0], sc = cs[a == 2 ? 1 : 2];
-      if (cross[a]) {
-        idx[a][0] = index[-sc];
-        idx[a][1] = index[-sb];
-        idx[a][2] = index[-sb - sc];
-      }
+    for (int a = 0; a < 3; ++a) cross[a] = (f0 > 0.5f) != (fa[a] > 0.5f);
+    // the cubes one step back along one axis (nb[k]) and along the two others than
+    // k (nb2[k]); a crossing edge lies inside the grid along its other axes, and so
+    // do its cubes
+    unsigned int nb[3], nb2[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const int b = k == 0 ? 1 : 0, c = k == 2 ? 1 : 2;
+      nb[k] = cross[b] || cross[c] ? index[-cs[k]] : ~0u;
+      nb2[k] = cross[k] ? index[-cs[b] - cs[c]] : ~0u;
     }
     double part[3][4];
 #pragma unroll
     for (int a = 0; a < 3; ++a)
       if (cross[a]) {
-        part[a][0] = B.cgrad[12 * i + 4 * a];
+        const unsigned int around[3] = {nb[a == 2 ? 1 : 2], nb[a == 0 ? 1 : 0], nb2[a]};
+        const double* g = B.cgrad + 4 * a * B.cap_cubes;
+        part[a][0] = g[i];
 #pragma unroll
         for (int q = 1; q < 4; ++q)
-          part[a][q] = idx[a][q - 1] < n_cubes ? B.cgrad[12ll * idx[a][q - 1] + 4 * a + q] : 0.0;
+          part[a][q] = around[q - 1] < n_cubes ? g[q * B.cap_cubes + around[q - 1]] : 0.0;
       }
 #pragma unroll
     for (int a = 0; a < 3; ++a)
       if (cross[a]) {
         const double den = (double)fa[a] - (double)f0;  // at least one float ulp at 0.5: the edge straddles it
-        B.egrad[3 * i + a] =
+        B.egrad[a * B.cap_cubes + i] =
             (float)((((part[a][0] + part[a][1]) + part[a][2]) + part[a][3]) * R.s[a] / (den * den));
       }
   }
@@ -473,7 +476,7 @@ __global__ __launch_bounds__(256) void k_soft_voxels(SoftBwdBufs B) {
     for (int j = 0; j < 6; ++j) {
       e[j] = 0.0f;
       const unsigned int c = j & 1 ? here : idx[j];
-      if (cross[j] && c < n_cubes) e[j] = B.egrad[3ll * c + (j >> 1)];
+      if (cross[j] && c < n_cubes) e[j] = B.egrad[(j >> 1) * B.cap_cubes + c];
     }
     double g = 0.0;
 #pragma unroll
