@@ -315,9 +315,10 @@ typedef struct {
   int32_t blocks_per_cu;
   int32_t kernel;
   int32_t prune;  /* kernel 1: 1 (default) prune the 3D pair tiles of large ROIs, 2 always, 0 never */
-  int32_t small_path; /* 1 (default): single-ROI calls of at most 2^22 voxels and 16,384 vertices
-                         (six features, no phase timing) evaluate all pairs exactly in one kernel
-                         after the mesh pass; 0: always the general pipeline.  Results are identical. */
+  int32_t small_path; /* 1 (default): small single-ROI calls (six features, no phase timing; at most
+                         2^16 uint8 or 2^18 float32 voxels where the block-pair pass is the other
+                         way, else 2^22; at most 16,384 vertices) evaluate all pairs exactly in one
+                         kernel after the mesh pass; 0: never.  Results are identical. */
 } shape3d_tuning;
 
 int shape3d_get_tuning(shape3d_tuning* t);

@@ -1095,12 +1095,13 @@ int run_small(Workspace& w, const void* vol, int dtype, const int64_t dims[3], c
 // no phase timing, a ROI small enough that a mesh beyond kSmallMaxV vertices
 // is unlikely (one that has more costs one extra mesh pass), and the
 // tuning's small-path switch on.
-bool small_path(const Batch& Bt, bool moments, int timing) {
+bool small_path(const Batch& Bt, int dtype, bool moments, int timing) {
   if (moments || timing || !g_tune.small_path || Bt.n() != 1) return false;
   const Roi& R = Bt.rois[0];
   // the pair kernels pack two canonical ids, below 3 (d0 + 2) (d1 + 2) (d2 + 2), in 64 bits
   const long long ids = 3ll * (R.d[0] + 2) * (R.d[1] + 2) * (R.d[2] + 2);
-  return (long long)R.d[0] * R.d[1] * R.d[2] <= kSmallMaxVoxels && ids < (1ll << 32);
+  const long long most = !block_path() ? 1ll << 22 : dtype == SHAPE3D_U8 ? kSmallMaxVoxels : kSmallMaxSoftVoxels;
+  return (long long)R.d[0] * R.d[1] * R.d[2] <= most && ids < (1ll << 32);
 }
 
 // out: the six features, or with `moments` the SHAPE3D_N_CLASS Shape-class members.
@@ -1120,7 +1121,7 @@ int shape3d_impl(const void* vol, int dtype, const int64_t dims[3], const double
   RoiResult* hres = host_results(w, Bt);
   float ms[8] = {0};
   bool done = false;
-  if (!raw && small_path(Bt, moments, timing)) {
+  if (!raw && small_path(Bt, dtype, moments, timing)) {
     if ((rc = run_small(w, vol, dtype, dims, spacing, st, hres))) return rc;
     done = hres->status != kSmallOverflow;
   }

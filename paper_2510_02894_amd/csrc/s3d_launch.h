@@ -33,7 +33,11 @@ struct SmallAcc {
   unsigned int pad_;
 };
 constexpr long long kSmallMaxV = 16384;         // largest mesh the small path evaluates
-constexpr long long kSmallMaxVoxels = 1ll << 22; // larger ROIs go straight to the general path
+// Larger ROIs go straight to the block-pair pass.  Whole call on one ellipsoid,
+// small path against block-pair pass (us): uint8 28^3 60 / 75, 40^3 70 / 75, 48^3
+// 82 / 72, 64^3 140 / 75, 100^3 (more than kSmallMaxV vertices) 124 / 83; soft (whose
+// few thick bricks take as long in either) 32^3 87 / 102, 64^3 101 / 106, 80^3 267 / 154.
+constexpr long long kSmallMaxVoxels = 1ll << 16, kSmallMaxSoftVoxels = 1ll << 18;
 constexpr int kSmallOverflow = -100;             // status: more vertices than kSmallMaxV
 
 // mesh.hip
