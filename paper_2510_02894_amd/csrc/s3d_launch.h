@@ -164,8 +164,6 @@ hipError_t launch_set_roi(const Roi& R, Roi* out, hipStream_t st);
 long long scan_tmp_elems(long long n);
 hipError_t launch_scan(const long long* in, long long* out, long long n, long long* total, long long* tmp,
                        hipStream_t st, const unsigned int* n_dev = nullptr);
-hipError_t launch_fill_u32(unsigned int* p, unsigned int v, long long n, hipStream_t st);
-hipError_t launch_fill_i64(long long* p, long long v, long long n, hipStream_t st);
 
 // Tile sizes of the pair pass (chosen by the autotuner; results do not depend on them).
 struct Tuning {

@@ -150,33 +150,4 @@ hipError_t launch_scan(const long long* in, long long* out, long long n, long lo
   return hipGetLastError();
 }
 
-__global__ void k_fill_u32(unsigned int* p, unsigned int v, long long n) {
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x)
-    p[i] = v;
-}
-
-__global__ void k_fill_i64(long long* p, long long v, long long n) {
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x)
-    p[i] = v;
-}
-
-static unsigned fill_grid(long long n) {
-  long long g = (n + 255) / 256;
-  if (g < 1) g = 1;
-  if (g > 4096) g = 4096;
-  return (unsigned)g;
-}
-
-hipError_t launch_fill_u32(unsigned int* p, unsigned int v, long long n, hipStream_t st) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_fill_u32, dim3(fill_grid(n)), dim3(256), 0, st, p, v, n);
-  return hipGetLastError();
-}
-
-hipError_t launch_fill_i64(long long* p, long long v, long long n, hipStream_t st) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_fill_i64, dim3(fill_grid(n)), dim3(256), 0, st, p, v, n);
-  return hipGetLastError();
-}
-
 }  // namespace s3d

@@ -9,9 +9,9 @@ measurement records kept with the repository.
 DIR is a rocprofv3 output directory written with ``--output-format csv``
 (``run_kernel_trace.csv`` for ``--kernel-trace``, ``run_counter_collection.csv``
 for ``--pmc``).  Dispatches are grouped into library calls by the first kernel
-of each call (k_head_clear for the general pipeline, k_small_head for the
-small-mesh path); a call that runs the pruning pass (k_prune_box) is a
-call with pruning, one without it a call that evaluates every pair.  This
+of each call (k_head for the general and the block-pair pipeline, k_small_head
+for the small-mesh path); a call that runs the block-pair pass (k_block_seed)
+is a call with pruning, one without it a call that evaluates every pair.  This
 module reads only the profiler's text output; it runs nothing on the GPU.
 """
 from __future__ import annotations
@@ -27,10 +27,10 @@ import re
 import sys
 from collections import OrderedDict, defaultdict
 
-CALL_HEADS = ("k_head_clear", "k_small_head")
+CALL_HEADS = ("k_head", "k_small_head")
 # call classes
 ALL_PAIRS = "general pipeline, every pair"
-PRUNED = "general pipeline with the pruning pass"
+PRUNED = "block-pair pass"
 SMALL = "single ROI, small-mesh path"
 COPY_BYTES = 256 << 20  # the benchmark's calibration copy (--copy-calibration)
 
@@ -94,7 +94,7 @@ def read_counters(d: str):
 
 
 def _disp_rois(disp):
-    return [w if n.endswith("k_mesh_totals") else 0 for n, _, w in disp]
+    return [w if base_name(n) == "k_mesh_totals" else 0 for n, _, w in disp]
 
 
 def split_calls(names, rois=None):
@@ -117,12 +117,12 @@ def split_calls(names, rois=None):
         bases = {names[i].split("::")[-1].split("<")[0] for i in idx}
         n_rois = max([rois[i] for i in idx if rois and rois[i]] or [1])
         kind = "batch of %d ROIs" % n_rois if n_rois > 1 else "single ROI"
-        out.append(("%s, %s" % (kind, PRUNED if "k_prune_box" in bases else ALL_PAIRS), idx))
+        out.append(("%s, %s" % (kind, PRUNED if "k_block_seed" in bases else ALL_PAIRS), idx))
     return out
 
 
 def _rois(rows):
-    return [r["grid"] // max(r["wg"], 1) if r["name"].endswith("k_mesh_totals") else 0 for r in rows]
+    return [r["grid"] // max(r["wg"], 1) if base_name(r["name"]) == "k_mesh_totals" else 0 for r in rows]
 
 
 def _classes(groups):
