@@ -404,6 +404,12 @@ __global__ __launch_bounds__(64 * kWaves, 7) void k_block_seed(BlockBufs B) {
     const Box ba = box_of(a0, a1);
     const long long blk0 = M.blk0, s0 = blk0 / kSuper;
     const int nblk = M.nblk, ns = (nblk + kSuper - 1) / kSuper;
+    // The scan costs ns^2 boxes; a large ROI's superblocks are small patches
+    // whose neighbours have nearly the same partner, so every second or fourth
+    // seeds (300 x 512 x 512, ns 1,822: seed and eval 45 + 20 us with all, 33 + 21,
+    // 26 + 23, and with every eighth 32 + 53; ROIs of ns about 100 lose: eval of a
+    // batch of 256 soft ROIs 210, 226 and 307 us with all, second, fourth).
+    if (ns > 512 && ((A - s0) & (ns > 1024 ? 3 : 1))) continue;
     // 16 x 16 block pairs later: lane holds block lane % 16 of A
     const int ia = (int)(A - s0) * kSuper + (lane & 15), ic = min(ia, nblk - 1);
     const float4 p0 = B.lbox[2 * (blk0 + ic)], p1 = B.lbox[2 * (blk0 + ic) + 1];
