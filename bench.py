@@ -15,8 +15,7 @@ switched off); roofline of that call's dominant kernel (the MFMA pair pass),
 8 algorithmic flops per vertex pair (3D and in-plane) over its time from HIP
 events recorded around it inside the library, against the peak of the
 contraction's dtype.  `effective` gives the library's default call on the same
-masks, which skips pair tiles that cannot hold the diameter (identical
-results), as V(V-1)/2 per second.  cpu_baseline = the FP64 oracle timed on a
+masks, which skips pairs that cannot hold a diameter (identical results), as V(V-1)/2 per second.  cpu_baseline = the FP64 oracle timed on a
 bounded sample of the same workload.
 
     python bench.py [--gpus 1] [--steps 10] [--warmup 2] [--no-cpu-baseline]
@@ -424,8 +423,8 @@ def main():
         log("%s: %.3f ms per call; phases (ms): %s" % (label, ms, ", ".join("%s %.4f" % kv for kv in avg.items())))
         return f, st, ms, avg, phases
 
-    # the library's default call (exact; the 3D pair tiles that cannot hold
-    # the diameter are skipped), then every vertex pair evaluated
+    # the library's default call (exact; pairs that cannot hold a diameter are
+    # skipped), then every vertex pair evaluated
     S.set_tuning(*tiles_eff)
     f_eff, st_eff, ms_eff, avg_eff, _ = timed("default call")
     S.set_prune(0)
@@ -454,8 +453,8 @@ def main():
     # (dense Gram operands, split terms and padding included): not a roofline
     mfma_occupancy = MFMA_FLOPS_PER_PAIR[kern] * (pairs3 + pairs2) / t_pair / 1e12 / PEAK_TFLOPS[kern]
     effective = {
-        "what": "the library's default call on the same masks: exact pruned 3D pairs (tiles whose bounding-box "
-                "distance bound is below a vertex-pair distance are skipped); identical results",
+        "what": "the library's default call on the same masks: only the pairs of vertex blocks whose "
+                "bounding boxes can hold a diameter are evaluated, exactly; identical results",
         "effective_pairs_per_s": pairs3 / (ms_eff * 1e-3),
         "ms_per_step": ms_eff,
         "phases_ms": avg_eff,

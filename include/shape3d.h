@@ -73,12 +73,14 @@ typedef struct {
   int64_t pair_ids[4][2];  /* canonical ids of the maximising pair: 3D, slice, column, row (-1: none) */
   int64_t pairs_3d;        /* V*(V-1)/2 */
   int64_t pairs_2d;        /* sum over planes of n*(n-1)/2 */
-  int64_t candidates[4];   /* rows re-examined in FP64 per diameter */
-  float ms[8];             /* device time per phase (ms), filled when timing != 0:
-                              0 mesh pass (one read of the volume) and per-ROI totals,
-                              1 vertex rows and pair-pass operands, 2 pruning and plane bucketing,
-                              3 pair maxima (MFMA),
-                              4 exact refinement, 5 finalisation, 6 whole call, 7 reserved */
+  int64_t candidates[4];   /* rows re-examined in FP64 per diameter (0 where block pairs are evaluated in FP64) */
+  float ms[8];             /* device time per phase (ms), filled when timing != 0
+                              (in brackets: where every pair is evaluated, prune = 0):
+                              0 mesh pass [and per-ROI totals],
+                              1 per-ROI totals and block boxes [vertex rows, pair-pass operands],
+                              2 lower bounds and block pairs [plane bucketing],
+                              3 exact maxima of the block pairs [pair maxima (MFMA)],
+                              4 tie-break [exact refinement], 5 finalisation, 6 whole call, 7 reserved */
 } shape3d_stats;
 
 /*
@@ -273,18 +275,17 @@ int shape3d_batched_soft_backward(const float* base, const shape3d_roi* rois, in
  *                  1 = FP32-accurate Gram values from coordinates split into
  *                  two f16 parts on the 32x32x16 f16 matrix cores.  Both are
  *                  followed by the same exact FP64 refinement.
- *   prune:         (kernel 1) skip the 3D pair tiles whose largest possible
- *                  distance, from the bounding boxes of their vertex blocks,
- *                  stays below a vertex-pair distance found by two
- *                  farthest-point sweeps, and the plane buckets whose box
- *                  diagonal stays below the largest in-plane extent of any
- *                  bucket of their family: 1 = in calls whose largest ROI may
- *                  have 16,384 vertices or more (then the 3D pairs of every
- *                  ROI with 1,024 or more), 2 = always (every ROI), 0 = never
- *                  (all pairs).  Exact: the maximising pairs are never
- *                  skipped, and the FP64 refinement rescans its candidate rows
- *                  against all vertices of their segment, so the results equal
- *                  those of prune = 0.
+ *   prune:         (kernel 1) evaluate only the pairs of 32-vertex blocks whose
+ *                  boxes can hold a diameter: a lower bound per family comes
+ *                  from the exact maximum of the farthest block pairs, block
+ *                  pairs whose bound reaches it are listed, and their pairs
+ *                  evaluated in FP64.  1 and 2 = always, 0 = never (all pairs
+ *                  through the Gram kernels).  Exact: a maximising pair is
+ *                  never skipped, so the results equal those of prune = 0.
+ *                  (Where the block lists do not fit a caller's workspace, and
+ *                  in the autotuner's timed runs, 1 and 2 skip pair tiles of the
+ *                  Gram kernels by their boxes instead: 1 in calls whose largest
+ *                  ROI may have 16,384 vertices or more, 2 in all.)
  * The setting is process-wide (all devices); the default is {8, 1024, 0, 1, 1}
  * (the autotuner's choice on one very large ROI; batches of small ROIs gain
  * about 1 % from jchunk 512).
@@ -314,7 +315,7 @@ typedef struct {
   int32_t jchunk_blocks;
   int32_t blocks_per_cu;
   int32_t kernel;
-  int32_t prune;  /* kernel 1: 1 (default) prune the 3D pair tiles of large ROIs, 2 always, 0 never */
+  int32_t prune;  /* kernel 1: 1 (default) or 2: only block pairs that can hold a diameter; 0: all pairs */
   int32_t small_path; /* 1 (default): small single-ROI calls (six features, no phase timing; at most
                          2^16 uint8 or 2^18 float32 voxels where the block-pair pass is the other
                          way, else 2^22; at most 16,384 vertices) evaluate all pairs exactly in one

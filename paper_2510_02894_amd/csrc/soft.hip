@@ -228,8 +228,8 @@ __global__ __launch_bounds__(256) void k_soft_scan(SoftBwdBufs B) {
   if (tid == 0) {
     unsigned long long* ctr = (unsigned long long*)B.counters;
     if (total_e) atomicAdd(&ctr[C_EDGES], (unsigned long long)total_e);
-    // one reservation for both lists (the workgroups' atomics on one address
-    // serialise, about 20 ns each), unless a count could pass 32 bits
+    // one reservation for both lists (one round trip less on the workgroup's
+    // critical path), unless a count could pass 32 bits
     if (B.packed) {
       const unsigned long long both = (unsigned long long)total_v << 32 | (unsigned int)total_c;
       const unsigned long long got = both ? atomicAdd(&ctr[C_BOTH], both) : 0ull;
