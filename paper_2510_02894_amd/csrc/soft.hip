@@ -316,13 +316,14 @@ __global__ __launch_bounds__(kCubeThreads, 4) void k_soft_cubes(SoftBwdBufs B) {
       const D3 P0 = vertex(d0), P1 = vertex(d1), P2 = vertex(d2);
       const D3 n3 = cross3(sub3(P1, P0), sub3(P2, P0));
       const double len = sqrt(n3.x * n3.x + n3.y * n3.y + n3.z * n3.z);
-      const double il = len > 0.0 ? ga * rcp64(len) : 0.0;
+      const bool flat = !(len > 0.0);  // no area, or NaN: the area term is left out
+      const double il = ga * rcp64(len);
       const D3 nh = {n3.x * il, n3.y * il, n3.z * il};
       // the vertex's own edge axis of ga nhat x (c - b) + gv b x c
       auto term = [&](const D3& b, const D3& c, uint32_t ed) {
         const D3 r = cross3(nh, sub3(c, b)), q = cross3(b, c);
         const int ax = (int)(ed & 3u);
-        return axis_of(r, ax) + gv * axis_of(q, ax);
+        return (flat ? 0.0 : axis_of(r, ax)) + gv * axis_of(q, ax);
       };
       s_g[e0][tid] += term(P1, P2, d0);
       s_g[e1][tid] += term(P2, P0, d1);

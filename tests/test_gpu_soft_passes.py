@@ -83,3 +83,21 @@ def test_adjoint_batch_equals_single(S):
         assert np.array_equal(feats[i], f1), SHAPES[i]
         exp = S.soft_backward(t, one, gout[i]).cpu().numpy()
         assert np.array_equal(grad[offs[i]:offs[i] + p.size].reshape(p.shape), exp), SHAPES[i]
+
+
+def test_adjoint_of_nan_voxels(S):
+    """A triangle without a finite normal adds no area term: NaN voxels reach the
+    same gradient entries as in the oracle, and the others are untouched."""
+    import torch
+
+    print("[case] adjoint NaN", flush=True)
+    p = noise((12, 15, 40), 3)
+    p.flat[np.random.default_rng(3).integers(0, p.size, 25)] = np.nan
+    t = torch.from_numpy(p).cuda()
+    gout = GOUT * (1, 1, 0, 0, 0, 0)
+    _, saved = S.soft_forward(t, SP)
+    got = S.soft_backward(t, saved, gout).cpu().numpy().astype(np.float64)
+    exp = O.soft_grad(p, SP, gout)
+    np.testing.assert_array_equal(np.isnan(got), np.isnan(exp))
+    ok = ~np.isnan(exp)
+    np.testing.assert_allclose(got[ok], exp[ok], rtol=2e-6, atol=2e-6 * np.abs(exp[ok]).max())
