@@ -32,7 +32,10 @@
  * the null stream).  The caller owns every buffer it passes.  The library
  * owns a workspace per device that grows on demand and is kept between calls
  * (shape3d_release frees it).  Calls are serialised by an internal lock;
- * device buffers given to a call must stay valid until it returns.
+ * device buffers given to a call must stay valid until it returns (of a call
+ * whose results stay on the device: until its work on the stream is done).
+ * A call that uses the library's workspace runs after the work that earlier
+ * calls have left on it, whichever stream or thread they came from.
  *
  * Every function returns a status.  On a failure (negative status) the
  * outputs are left untouched and shape3d_last_error() describes the cause.

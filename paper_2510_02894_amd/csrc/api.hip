@@ -106,6 +106,11 @@ struct Workspace {
   size_t host_cap = 0;
   hipEvent_t ev[8] = {};
   bool events = false;
+  // work that a returned call has left on the buffers (results that stay on the
+  // device): `used` is recorded behind it, and every later call waits for it on
+  // its own stream before it touches a buffer
+  hipEvent_t used = nullptr;
+  bool busy = false;
   hipStream_t graph_stream = nullptr;  // graphs are recorded and replayed here (the caller's
                                        // stream may be the legacy null stream, which cannot record)
   long long rows0_cap = 0;   // layout-0 rows the vertex buffers were sized for
@@ -157,7 +162,14 @@ bool valid_tuning(const Tuning& t) {
          (t.small_path == 0 || t.small_path == 1);
 }
 
+// Waits on the host for work that a returned call left on the workspace.
+void finish_use(Workspace& w) {
+  if (w.busy) (void)hipEventSynchronize(w.used);
+  w.busy = false;
+}
+
 void drop_graphs(Workspace& w) {
+  if (!w.graphs.empty()) finish_use(w);  // a replay may still run
   for (auto& kv : w.graphs) {
     if (kv.second.exec) (void)hipGraphExecDestroy(kv.second.exec);
     if (kv.second.host_res) (void)hipHostFree(kv.second.host_res);
@@ -207,7 +219,9 @@ int device_cu_count(int dev, int* cu) {
   return SHAPE3D_OK;
 }
 
-int get_workspace(Workspace** out) {
+// The current device's workspace, for work on stream st: that work runs after
+// whatever an earlier call has left on it, on whichever stream that was.
+int get_workspace(Workspace** out, hipStream_t st) {
   int n = 0;
   if (hipGetDeviceCount(&n) != hipSuccess || n <= 0) {
     (void)hipGetLastError();
@@ -225,11 +239,28 @@ int get_workspace(Workspace** out) {
       return rc;
     }
     for (int i = 0; i < 8; ++i) HIPCK(hipEventCreate(&w->ev[i]));
+    HIPCK(hipEventCreateWithFlags(&w->used, hipEventDisableTiming));
     w->events = true;
     HIPCK(hipStreamCreateWithFlags(&w->graph_stream, hipStreamNonBlocking));
     it = g_ws.emplace(dev, w).first;
   }
   *out = it->second;
+  if (it->second->busy) HIPCK(hipStreamWaitEvent(st, it->second->used, 0));
+  return SHAPE3D_OK;
+}
+
+// The call has left work on the workspace behind it on st.
+int leave_use(Workspace& w, hipStream_t st) {
+  HIPCK(hipEventRecord(w.used, st));
+  w.busy = true;
+  return SHAPE3D_OK;
+}
+
+// Waits for st, on which the call's work runs: nothing is left on the workspace
+// (what an earlier call left there was waited for on st).
+int sync_use(Workspace& w, hipStream_t st) {
+  HIPCK(hipStreamSynchronize(st));
+  w.busy = false;
   return SHAPE3D_OK;
 }
 
@@ -726,7 +757,7 @@ int run_eager(Workspace& w, const Batch& Bt, int dtype, hipStream_t st, RoiResul
     if ((rc = launch_head(P, Bt, dtype, tcap, st))) return rc;
     if (timing) HIPCK(hipEventRecord(w.ev[1], st));
     HIPCK(hipMemcpyAsync(th, P.p[W_TOTALS], sizeof(long long) * 9, hipMemcpyDeviceToHost, st));
-    HIPCK(hipStreamSynchronize(st));
+    if ((rc = sync_use(w, st))) return rc;
     if (th[8] <= tcap || pass > 0) break;
     // more vertices than the staging list held: size it and run the mesh pass again
     if ((rc = ensure_staging(w, dtype, th[8], &tcap))) return rc;
@@ -741,7 +772,7 @@ int run_eager(Workspace& w, const Batch& Bt, int dtype, hipStream_t st, RoiResul
   if ((rc = launch_tail(P, Bt, dtype, S, tcap, w.cu_count, st, timing ? &w.ev[2] : nullptr, th[1]))) return rc;
   if (host_res) HIPCK(hipMemcpyAsync(host_res, P.p[W_RES], sizeof(RoiResult) * Bt.n(), hipMemcpyDeviceToHost, st));
   if (timing) HIPCK(hipEventRecord(w.ev[7], st));
-  HIPCK(hipStreamSynchronize(st));
+  if ((rc = sync_use(w, st))) return rc;
   if (timing && phase_ms) {
     // 0 mesh count + totals, 1 emit, 2 buckets + work list, 3 MFMA pair maxima, 4 refine,
     // 5 finalise + read-back, 6 whole call (including the row-count read-back)
@@ -920,7 +951,7 @@ int run_blocks(Workspace& w, const Batch& Bt, int dtype, hipStream_t st, RoiResu
     if ((rc = launch_block_list(P, block_ptrs(w), Z, Bt, dtype, st))) return rc;
     if (!host_res) {
       HIPCK(hipMemcpyAsync(th, P.p[W_TOTALS], sizeof(long long) * 9, hipMemcpyDeviceToHost, st));
-      HIPCK(hipStreamSynchronize(st));
+      if ((rc = sync_use(w, st))) return rc;
       if (th[8] > Z.rows) {
         if (pass > 0) return fail(SHAPE3D_EINTERNAL, "the mesh pass's staging list overflowed twice");
         if ((rc = ensure_block_bufs(w, Bt, dtype, th[8], 0, Z))) return rc;
@@ -937,7 +968,7 @@ int run_blocks(Workspace& w, const Batch& Bt, int dtype, hipStream_t st, RoiResu
     if (!direct)
       HIPCK(hipMemcpyAsync(host_res, P.p[W_RES], sizeof(RoiResult) * Bt.n(), hipMemcpyDeviceToHost, st));
     if (timing) HIPCK(hipEventRecord(w.ev[7], st));
-    HIPCK(hipStreamSynchronize(st));
+    if ((rc = sync_use(w, st))) return rc;
     bool short_rows = false, short_list = false;
     for (int r = 0; r < Bt.n(); ++r) {
       short_rows |= host_res[r].status == SHAPE3D_ECAPACITY;
@@ -946,7 +977,7 @@ int run_blocks(Workspace& w, const Batch& Bt, int dtype, hipStream_t st, RoiResu
     if (!short_rows && !short_list) break;
     // once more with lists that are long enough (or, past kMaxList, without one)
     HIPCK(hipMemcpyAsync(th, P.p[W_TOTALS], sizeof(long long) * 11, hipMemcpyDeviceToHost, st));
-    HIPCK(hipStreamSynchronize(st));
+    if ((rc = sync_use(w, st))) return rc;
     if (pass > 2 || (!short_list && th[8] <= Z.rows)) break;
     const long long list = short_list ? th[10] + th[10] / 8 : 0;
     again |= list > kMaxList;
@@ -1087,7 +1118,7 @@ int run_small(Workspace& w, const void* vol, int dtype, const int64_t dims[3], c
                            dtype == SHAPE3D_F32 ? P.as<const double>(W_TMPT) : nullptr,
                            P.as<const long long>(W_TOTALS), vmax, acc, groups, P.as<RoiResult>(W_RES), st));
   HIPCK(hipMemcpyAsync(hres, P.p[W_RES], sizeof(RoiResult), hipMemcpyDeviceToHost, st));
-  HIPCK(hipStreamSynchronize(st));
+  if ((rc = sync_use(w, st))) return rc;
   return SHAPE3D_OK;
 }
 
@@ -1111,7 +1142,7 @@ int shape3d_impl(const void* vol, int dtype, const int64_t dims[3], const double
   if (rc) return rc;
   if (!out) return fail(SHAPE3D_EINVAL, "null out");
   Workspace* wp = nullptr;
-  if ((rc = get_workspace(&wp))) return rc;
+  if ((rc = get_workspace(&wp, st))) return rc;
   Workspace& w = *wp;
   Batch Bt;
   Bt.moments = moments;
@@ -1217,6 +1248,7 @@ int capture_graph(Workspace& w, const Batch& Bt, int dtype, hipStream_t st, Grap
 }
 
 void erase_graph(Workspace& w, std::map<std::string, GraphRec>::iterator it) {
+  finish_use(w);  // a replay may still run
   if (it->second.exec) (void)hipGraphExecDestroy(it->second.exec);
   if (it->second.host_res) (void)hipHostFree(it->second.host_res);
   w.graphs.erase(it);
@@ -1267,7 +1299,7 @@ int batched_impl(const void* base, int dtype, const shape3d_roi* rois, int64_t n
   int rc = make_batch(base, dtype, rois, n_rois, Bt);
   if (rc) return rc;
   Workspace* wp = nullptr;
-  if ((rc = get_workspace(&wp))) return rc;
+  if ((rc = get_workspace(&wp, st))) return rc;
   Workspace& w = *wp;
   if ((rc = ensure_layout_bufs(w, Bt, dtype))) return rc;
   const bool use_graph = (flags & SHAPE3D_BATCH_GRAPH) != 0;
@@ -1288,7 +1320,7 @@ int batched_impl(const void* base, int dtype, const shape3d_roi* rois, int64_t n
       HIPCK(hipStreamWaitEvent(gs, w.ev[0], 0));
       HIPCK(hipMemcpyAsync(w.buf[W_ROIS].p, h + 4096, sizeof(Roi) * Bt.n(), hipMemcpyHostToDevice, gs));
       HIPCK(hipGraphLaunch(it->second.exec, gs));
-      HIPCK(hipStreamSynchronize(gs));
+      if ((rc = sync_use(w, gs))) return rc;
       hres = it->second.host_res;
       done = true;
       for (int64_t r = 0; r < n_rois; ++r)
@@ -1305,7 +1337,7 @@ int batched_impl(const void* base, int dtype, const shape3d_roi* rois, int64_t n
     if (use_graph) {
       graph_slot(w, sig);
       GraphRec rec;
-      HIPCK(hipStreamSynchronize(st));
+      if ((rc = sync_use(w, st))) return rc;
       rc = capture_graph(w, Bt, dtype, w.graph_stream, rec, counts);
       if (rc) {
         if (rec.exec) (void)hipGraphExecDestroy(rec.exec);
@@ -1357,7 +1389,7 @@ int batched_dev_impl(const void* base, int dtype, const shape3d_roi_ex* rois, in
     return run_fixed(Bt, nullptr, dtype, &dt, ws, ws_bytes, cu, out, status, st);
   }
   Workspace* wp = nullptr;
-  if ((rc = get_workspace(&wp))) return rc;
+  if ((rc = get_workspace(&wp, st))) return rc;
   Workspace& w = *wp;
   if ((rc = ensure_layout_bufs(w, Bt, dtype))) return rc;
   const bool use_graph = (flags & SHAPE3D_BATCH_GRAPH) != 0;
@@ -1374,8 +1406,8 @@ int batched_dev_impl(const void* base, int dtype, const shape3d_roi_ex* rois, in
       HIPCK(hipEventRecord(w.ev[0], st));  // the caller's earlier work (the table, the masks) first
       HIPCK(hipStreamWaitEvent(gs, w.ev[0], 0));
       HIPCK(hipGraphLaunch(it->second.exec, gs));
-      HIPCK(hipEventRecord(w.ev[1], gs));  // and the caller's later work after the results
-      HIPCK(hipStreamWaitEvent(st, w.ev[1], 0));
+      if ((rc = leave_use(w, gs))) return rc;  // and the caller's later work after the results
+      HIPCK(hipStreamWaitEvent(st, w.used, 0));
       it->second.stamp = ++w.stamp;
       g_err.clear();
       return SHAPE3D_OK;
@@ -1385,10 +1417,11 @@ int batched_dev_impl(const void* base, int dtype, const shape3d_roi_ex* rois, in
                     : run_eager(w, Bt, dtype, st, nullptr, 0, nullptr, &dt);
   if (rc) return rc;
   HIPCK(launch_results_out(w.ptrs().as<const RoiResult>(W_RES), Bt.n(), out, status, Bt.nf(), st));
+  if ((rc = leave_use(w, st))) return rc;
   if (use_graph) {
     graph_slot(w, sig);
     GraphRec rec;
-    HIPCK(hipStreamSynchronize(st));
+    if ((rc = sync_use(w, st))) return rc;
     rc = capture_graph(w, Bt, dtype, w.graph_stream, rec, false, &dt, out, status);
     if (rc) {
       if (rec.exec) (void)hipGraphExecDestroy(rec.exec);
@@ -1451,7 +1484,7 @@ int soft_backward_impl(const float* base, const shape3d_roi* rois, int64_t n_roi
                        const double* grad_out, float* grad_base, hipStream_t st) {
   int rc;
   Workspace* wp = nullptr;
-  if ((rc = get_workspace(&wp))) return rc;
+  if ((rc = get_workspace(&wp, st))) return rc;
   Workspace& w = *wp;
   std::vector<SoftBwdRoi> table((size_t)n_rois);
   const int bit_rounds = n_rois == 1 && rois[0].dims[0] * rois[0].dims[1] * rois[0].dims[2] < kBitManyVoxels ? 1 : kBitRounds;
@@ -1560,7 +1593,7 @@ int soft_backward_impl(const float* base, const shape3d_roi* rois, int64_t n_roi
   HIPCK(launch_soft_backward(B, st));
   long long* used = (long long*)h;
   HIPCK(hipMemcpyAsync(used, w.soft_ctr.p, sizeof(long long), hipMemcpyDeviceToHost, st));
-  HIPCK(hipStreamSynchronize(st));
+  if ((rc = sync_use(w, st))) return rc;
   if (*used != cap)
     return fail(SHAPE3D_EINVAL, "the probabilities differ from those of the forward pass (crossing edges " +
                                     std::to_string(*used) + ", saved " + std::to_string(cap) + "); grad is undefined");
@@ -1610,7 +1643,7 @@ int autotune_impl(const void* base, int dtype, const shape3d_roi* rois, int64_t 
   if (rc) return rc;
   if (reps < 1 || reps > 100) return fail(SHAPE3D_EINVAL, "reps must be in [1, 100]");
   Workspace* wp = nullptr;
-  if ((rc = get_workspace(&wp))) return rc;
+  if ((rc = get_workspace(&wp, st))) return rc;
   Workspace& w = *wp;
   if ((rc = ensure_layout_bufs(w, Bt, dtype))) return rc;
   const Tuning saved = g_tune;
@@ -1788,7 +1821,7 @@ int host_stream_impl(const void* const* vols, int dtype, const int64_t* dims, co
     max_bytes = std::max(max_bytes, bytes[i]);
   }
   Workspace* wp = nullptr;
-  if ((rc = get_workspace(&wp))) return rc;
+  if ((rc = get_workspace(&wp, st))) return rc;
   Workspace& w = *wp;
   if ((rc = host_stream_buffers(w, max_bytes, any_pageable))) return rc;
   StreamSync S;
@@ -1896,7 +1929,7 @@ int shape3d_vertices(const void* vol, int dtype, const int64_t dims[3], const do
   if (!n_out || (!ids && cap > 0)) return fail(SHAPE3D_EINVAL, "null output");
   hipStream_t st = (hipStream_t)stream;
   Workspace* wp = nullptr;
-  if ((rc = get_workspace(&wp))) return rc;
+  if ((rc = get_workspace(&wp, st))) return rc;
   Workspace& w = *wp;
   Batch Bt;
   batch_add(Bt, vol, dims, spacing);
@@ -1912,7 +1945,7 @@ int shape3d_vertices(const void* vol, int dtype, const int64_t dims[3], const do
     if ((rc = launch_head(P, Bt, dtype, tcap, st))) return rc;
     HIPCK(hipMemcpyAsync(th, P.p[W_TOTALS], sizeof(long long) * 9, hipMemcpyDeviceToHost, st));
     HIPCK(hipMemcpyAsync(mh, P.p[W_META], sizeof(RoiMeta), hipMemcpyDeviceToHost, st));
-    HIPCK(hipStreamSynchronize(st));
+    if ((rc = sync_use(w, st))) return rc;
     if (th[8] <= tcap || pass > 0) break;
     if ((rc = ensure_staging(w, dtype, th[8], &tcap))) return rc;
     P = w.ptrs();
@@ -1930,7 +1963,7 @@ int shape3d_vertices(const void* vol, int dtype, const int64_t dims[3], const do
   HIPCK(launch_export_vertices(P.as<const unsigned long long>(W_KEY),
                                dtype == SHAPE3D_F32 ? P.as<const double>(W_TSOFT) : nullptr,
                                P.as<const RoiMeta>(W_META), P.as<const Roi>(W_ROIS), (long long*)ids, pos, V, st));
-  HIPCK(hipStreamSynchronize(st));
+  if ((rc = sync_use(w, st))) return rc;
   g_err.clear();
   return SHAPE3D_OK;
 }
@@ -2141,6 +2174,7 @@ int shape3d_release(void) {
     }
     for (int i = 0; i < 8; ++i)
       if (w->events) (void)hipEventDestroy(w->ev[i]);
+    if (w->used) (void)hipEventDestroy(w->used);
     (void)hipSetDevice(cur);
     delete w;
   }
