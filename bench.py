@@ -390,8 +390,8 @@ def main():
     vols = [torch.from_numpy(mask).to(dev) for _ in range(max(1, args.copies))]
     torch.cuda.synchronize()
 
-    # pair-pass tiles: tuned separately for the default call (pruned 3D
-    # pairs) and for the call that evaluates every pair
+    # pair-pass tiles of the call that evaluates every pair (the default call
+    # takes the block-pair pass, which has none: its setting stays)
     prune_default = S.get_prune()
     table1 = S.roi_table([0], [mask.shape], [spacing])
     tiles = tiles_eff = S.get_tuning()

@@ -285,10 +285,10 @@ int shape3d_batched_soft_backward(const float* base, const shape3d_roi* rois, in
  *                  evaluated in FP64.  1 and 2 = always, 0 = never (all pairs
  *                  through the Gram kernels).  Exact: a maximising pair is
  *                  never skipped, so the results equal those of prune = 0.
- *                  (Where the block lists do not fit a caller's workspace, and
- *                  in the autotuner's timed runs, 1 and 2 skip pair tiles of the
- *                  Gram kernels by their boxes instead: 1 in calls whose largest
- *                  ROI may have 16,384 vertices or more, 2 in all.)
+ *                  (Where the block lists do not fit a caller's workspace, 1
+ *                  and 2 skip pair tiles of the Gram kernels by their boxes
+ *                  instead: 1 in calls whose largest ROI may have 16,384
+ *                  vertices or more, 2 in all.)
  * The setting is process-wide (all devices); the default is {8, 1024, 0, 1, 1}
  * (the autotuner's choice on one very large ROI; batches of small ROIs gain
  * about 1 % from jchunk 512).
@@ -297,20 +297,24 @@ int shape3d_batched_soft_backward(const float* base, const shape3d_roi* rois, in
  * (HOST struct).  Setting drops the graphs recorded by shape3d_batched.
  * Neither needs a device.  SHAPE3D_EINVAL for unsupported values.
  *
- * shape3d_autotune -- runs the batch (as shape3d_batched, eagerly) once per
- * candidate setting (kernel 0 with itile 2, 4, 8 and kernel 1 with itile 4, 8,
- * each with the four jchunk values; `reps` timed runs each, 1..100), keeps
- * the tiling with the shortest pair-pass time (HIP events) and makes it the
- * current setting.  Returns SHAPE3D_EINTERNAL if a candidate changes any
- * result.
+ * shape3d_autotune -- with prune = 0, runs the batch (as shape3d_batched,
+ * eagerly) once per candidate setting (kernel 0 with itile 2, 4, 8 and kernel 1
+ * with itile 4, 8, each with the five jchunk values; `reps` timed runs each,
+ * 1..100), keeps the tiling with the shortest pair-pass time (HIP events) and
+ * makes it the current setting.  With prune 1 or 2 the block-pair pass, which
+ * has no tiles, is the way of every call: it is timed as a whole, and the
+ * setting is kernel 1 with the current tiles (8 x 1024 if kernel 0 was set).
+ * Returns SHAPE3D_EINTERNAL if a candidate changes any result.
  *   cache_path: HOST path of a text file or NULL.  Lines are
  *               "<class> <kernel> <itile> <jchunk> <blocks_per_cu> <ms>", the class
- *               being the dtype and the rounded log2 of the ROI count, of
- *               the total and of the largest vertex count.  A line for the
+ *               being the dtype, the rounded log2 of the ROI count, of the
+ *               total and of the largest vertex count, and ":b" with prune 1
+ *               or 2 (then lines of kernel 0 do not count).  A line for the
  *               batch's class is used without timing; otherwise the choice is
  *               appended.
- *   best:       HOST; receives the chosen tiles.  best_ms: HOST; its pair-pass
- *               time (from the cache on a hit).
+ *   best:       HOST; receives the chosen setting.  best_ms: HOST; its pair-pass
+ *               time, with prune 1 or 2 that of the whole call (from the cache
+ *               on a hit).
  * Synchronous on `stream`.
  */
 typedef struct {

@@ -147,12 +147,12 @@ void* g_scratch[kMaxScratchDevices] = {};
 // Tile sizes of the pair pass for every device (results do not depend on them).
 Tuning g_tune = {8, 1024, 0, 1, 1, 1};
 
-// Vertex count from which a ROI's 3D pairs are pruned: kPruneMinV for prune = 1,
-// every ROI with pairs for prune = 2.
 // Whether calls take the block-pair pass (every pair is visited with prune = 0
 // or the FP32 pair kernel).
 bool block_path() { return g_tune.kernel == 1 && g_tune.prune != 0; }
 
+// Vertex count from which a ROI's 3D pairs are pruned in the Gram pipeline:
+// kPruneMinV for prune = 1, every ROI with pairs for prune = 2.
 int prune_min_v() { return g_tune.prune == 2 ? 2 : kPruneMinV; }
 
 bool valid_tuning(const Tuning& t) {
@@ -1617,7 +1617,8 @@ std::string tuning_key(int dtype, int64_t n_rois, const RoiResult* res) {
 }
 
 // Looks `key` up in a tuning cache file (lines "key kernel itile jchunk blocks_per_cu ms").
-bool tuning_cache_find(const char* path, const std::string& key, Tuning& t, double& ms) {
+// kernel1: only lines of that kernel count.
+bool tuning_cache_find(const char* path, const std::string& key, bool kernel1, Tuning& t, double& ms) {
   FILE* f = fopen(path, "r");
   if (!f) return false;
   char line[256], k[128];
@@ -1626,7 +1627,7 @@ bool tuning_cache_find(const char* path, const std::string& key, Tuning& t, doub
     Tuning c = g_tune;  // the cache holds the tiles; pruning and the small path stay as set
     double m;
     if (sscanf(line, "%127s %d %d %d %d %lf", k, &c.kernel, &c.itile, &c.jchunk, &c.blocks_per_cu, &m) == 6 &&
-        key == k && valid_tuning(c)) {
+        key == k && valid_tuning(c) && (c.kernel == 1 || !kernel1)) {
       t = c;  // the last entry for a key wins
       ms = m;
       found = true;
@@ -1647,46 +1648,63 @@ int autotune_impl(const void* base, int dtype, const shape3d_roi* rois, int64_t 
   Workspace& w = *wp;
   if ((rc = ensure_layout_bufs(w, Bt, dtype))) return rc;
   const Tuning saved = g_tune;
-  // reference run with the current tiles: vertex counts (for the cache key) and results
-  std::vector<RoiResult> ref((size_t)n_rois);
+  // With pruning on, calls of kernel 1 take the block-pair pass, which has no
+  // tiles, and no other setting is faster (the FP32 kernel visits every pair):
+  // the choice is kernel 1, timed as a whole call, so that tuning never takes
+  // later calls off that pass.  Its cache lines have a class of their own, since
+  // those of the tiles hold pair-pass times and may name kernel 0.
+  const bool blocks = saved.prune != 0;
+  std::vector<Tuning> cand;
+  if (blocks) {
+    const bool tiles = saved.kernel == 1;
+    cand.push_back(Tuning{tiles ? saved.itile : 8, tiles ? saved.jchunk : 1024, 0, 1, saved.prune, saved.small_path});
+  } else {
+    static const int kCand[5][2] = {{0, 2}, {0, 4}, {0, 8}, {1, 4}, {1, 8}};  // (kernel, itile)
+    for (const auto& kc : kCand)
+      for (int jc : {64, 128, 256, 512, 1024})
+        cand.push_back(Tuning{kc[1], jc, 0, kc[0], saved.prune, saved.small_path});
+  }
   RoiResult* hres = host_results(w, Bt);
   float ms[8] = {0};
-  if ((rc = run_eager(w, Bt, dtype, st, hres, 1, ms))) return rc;
+  auto run = [&]() {
+    return block_path() ? run_blocks(w, Bt, dtype, st, hres, false, 1, ms) : run_eager(w, Bt, dtype, st, hres, 1, ms);
+  };
+  // reference run with the current setting: vertex counts (for the cache key) and results
+  std::vector<RoiResult> ref((size_t)n_rois);
+  if ((rc = run())) return rc;
   for (int64_t r = 0; r < n_rois; ++r)
     if (hres[r].status < 0) return fail(hres[r].status, "an internal capacity was exceeded");
   std::copy(hres, hres + n_rois, ref.begin());
-  const std::string key = tuning_key(dtype, n_rois, ref.data());
-  if (cache_path && tuning_cache_find(cache_path, key, best, best_ms)) {
+  const std::string key = tuning_key(dtype, n_rois, ref.data()) + (blocks ? ":b" : "");
+  if (cache_path && tuning_cache_find(cache_path, key, blocks, best, best_ms)) {
     g_tune = best;
     for (auto& kv : g_ws) drop_graphs(*kv.second);
     return SHAPE3D_OK;
   }
   best_ms = 1e300;
   best = saved;
-  static const int kCand[5][2] = {{0, 2}, {0, 4}, {0, 8}, {1, 4}, {1, 8}};  // (kernel, itile)
-  for (const auto& kc : kCand)
-    for (int jc : {64, 128, 256, 512, 1024}) {
-      g_tune = Tuning{kc[1], jc, 0, kc[0], saved.prune, saved.small_path};
-      double t = 1e300;
-      for (int k = 0; k < reps; ++k) {
-        if ((rc = run_eager(w, Bt, dtype, st, hres, 1, ms))) {
-          g_tune = saved;
-          return rc;
-        }
-        t = std::min(t, (double)ms[3]);
+  for (const Tuning& c : cand) {
+    g_tune = c;
+    double t = 1e300;
+    for (int k = 0; k < reps; ++k) {
+      if ((rc = run())) {
+        g_tune = saved;
+        return rc;
       }
-      // the tiles only change the work order: every result must be identical
-      for (int64_t r = 0; r < n_rois; ++r)
-        if (memcmp(hres[r].out, ref[(size_t)r].out, sizeof(ref[0].out)) != 0 ||
-            memcmp(hres[r].ids, ref[(size_t)r].ids, sizeof(ref[0].ids)) != 0 || hres[r].status != ref[(size_t)r].status) {
-          g_tune = saved;
-          return fail(SHAPE3D_EINTERNAL, "pair-pass tiles changed a result");
-        }
-      if (t < best_ms) {
-        best_ms = t;
-        best = g_tune;
-      }
+      t = std::min(t, (double)ms[blocks ? 6 : 3]);
     }
+    // the setting only changes the order of the work: every result must be identical
+    for (int64_t r = 0; r < n_rois; ++r)
+      if (memcmp(hres[r].out, ref[(size_t)r].out, sizeof(ref[0].out)) != 0 ||
+          memcmp(hres[r].ids, ref[(size_t)r].ids, sizeof(ref[0].ids)) != 0 || hres[r].status != ref[(size_t)r].status) {
+        g_tune = saved;
+        return fail(SHAPE3D_EINTERNAL, "pair-pass tiles changed a result");
+      }
+    if (t < best_ms) {
+      best_ms = t;
+      best = g_tune;
+    }
+  }
   g_tune = best;
   for (auto& kv : g_ws) drop_graphs(*kv.second);
   if (cache_path) {

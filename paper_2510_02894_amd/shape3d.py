@@ -782,7 +782,8 @@ def set_small_path(on: bool):
 
 def autotune(base, table, reps: int = 2, cache_path=None):
     """Choose the pair-pass setting for this batch (see shape3d_autotune):
-    returns ((itile, jchunk, blocks_per_cu, kernel), pair-pass ms)."""
+    returns ((itile, jchunk, blocks_per_cu, kernel), its time in ms: of the pair
+    pass with prune 0, else of the whole call)."""
     import torch
 
     lib = load()
