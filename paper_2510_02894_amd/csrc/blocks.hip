@@ -209,10 +209,18 @@ __device__ inline double staged_max(const PairStage* S, int n_a, int n_b, int sh
   return wave_max_f64(i < n_a ? m : -1.0);
 }
 
+// Whether a parameter is a number, by its bits (this file is compiled for
+// operands that are: its maxima would drop or keep a NaN as the instruction
+// happens to treat one).
+__device__ inline bool is_number(double t) {
+  return ((unsigned long long)__double_as_longlong(t) & 0x7fffffffffffffffull) <= 0x7ff0000000000000ull;
+}
+
 // Stages the vertices of a block pair that can take part in a pair at or above
 // thr for a family in `mask`: those whose bound to the other block's box reaches
-// it (of the 1,024 pairs of a listed block pair a few dozen are left).  n_a, n_b:
-// their numbers; false if there is no pair.
+// it (of the 1,024 pairs of a listed block pair a few dozen are left).  A vertex
+// that NaN voxels leave without a position takes part in none.  n_a, n_b: their
+// numbers; false if there is no pair.
 __device__ inline bool stage_rows(const PairLoad& K, const Roi& R, const Metric& met, unsigned int mask,
                                   const float* thr, int lane, PairStage* S, bool keys, int& n_a, int& n_b) {
   const VRow V = vertex_row(K.k, K.t, R.s);
@@ -236,6 +244,7 @@ __device__ inline bool stage_rows(const PairLoad& K, const Roi& R, const Metric&
     far_bounds(v, box_of(K.b0, K.b1), met, f);
 #pragma unroll
     for (int g = 0; g < 4; ++g) take |= (mask >> g & 1u) && f[g] >= thr[g];
+    take &= is_number(K.t);
   }
   const unsigned long long em = __ballot(take);
   const unsigned int mb = (unsigned int)em, ma = (unsigned int)(em >> 32);
