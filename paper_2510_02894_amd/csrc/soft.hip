@@ -316,7 +316,8 @@ __global__ __launch_bounds__(kCubeThreads, 4) void k_soft_cubes(SoftBwdBufs B) {
       const D3 P0 = vertex(d0), P1 = vertex(d1), P2 = vertex(d2);
       const D3 n3 = cross3(sub3(P1, P0), sub3(P2, P0));
       const double len = sqrt(n3.x * n3.x + n3.y * n3.y + n3.z * n3.z);
-      const bool flat = !(len > 0.0);  // no area, or NaN: the area term is left out
+      // no area, or one out of range, or NaN: the area term is left out
+      const bool flat = !(len > 0.0 && len < __builtin_huge_val());
       const double il = ga * rcp64(len);
       const D3 nh = {n3.x * il, n3.y * il, n3.z * il};
       // the vertex's own edge axis of ga nhat x (c - b) + gv b x c

@@ -69,3 +69,23 @@ def test_masks_that_are_not_finite(S, name, m):
         assert rc == ref["status"] and st["V"] == ref["V"] and st["T"] == ref["T"]
         np.testing.assert_array_equal(st["pair_ids"], ref["pair_ids"])
         np.testing.assert_array_equal(f[2:][has], ref["features"][2:][has])
+
+
+@pytest.mark.parametrize("scale", [1e-90, 1e78, 1e80])
+def test_adjoint_where_a_normal_leaves_the_range(S, scale):
+    """The squares of the triangles' normals are 0 or infinite: no area term,
+    as the oracle's division by that length gives."""
+    import torch
+
+    p = np.full((4, 5, 6), 0.2, np.float32)
+    p[1:3, 1:4, 2:4] = 0.8
+    sp = (scale, 2 * scale, scale)
+    g = np.array([0.0, 1.0, 0.0, 0.0, 0.0, 0.0])
+    say("adjoint, spacing %g" % scale)
+    t = torch.from_numpy(p).cuda()
+    _, saved = S.soft_forward(t, sp)
+    got = S.soft_backward(t, saved, g).cpu().numpy()
+    with np.errstate(all="ignore"):
+        exp = O.soft_grad(p, sp, g)
+    assert np.all(exp == 0.0)
+    np.testing.assert_array_equal(got, exp)
