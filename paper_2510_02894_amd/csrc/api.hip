@@ -332,8 +332,8 @@ struct Batch {
   int max_G = 1;
   bool planned = false;
   long long max_d[3] = {0, 0, 0};  // every ROI's dims are at most these
-  // the bit pass over dense ROIs without labels (host tables): elements per workgroup / kBitRound, its
-  // workgroups and 32-bit words; bits = false: a ROI is not of that kind
+  // the bit pass over dense ROIs of aligned floats without labels (host tables): elements per workgroup /
+  // kBitRound, its workgroups and 32-bit words; bits = false: a ROI is not of that kind
   int bit_rounds = kBitRounds;
   long long bit_blks = 0, bit_words = 0;
   bool bits = true;
@@ -352,7 +352,8 @@ void batch_add(Batch& B, const void* vol, const int64_t dims[3], const double sp
   R.brick_end = B.nbricks + nb;
   roi_set_buckets(R, B.n_buckets);
   const long long vox = d[0] * d[1] * d[2];
-  B.bits = B.bits && vox < (1ll << 31) && label == 0 && R.stride1 == d[2] && R.stride0 == d[1] * d[2];
+  B.bits = B.bits && vox < (1ll << 31) && label == 0 && R.stride1 == d[2] && R.stride0 == d[1] * d[2] &&
+           !odd_floats(vol);
   R.bits_begin = B.bit_words;
   R.bitblk_begin = B.bit_blks;
   B.bit_words += bit_words(vox);

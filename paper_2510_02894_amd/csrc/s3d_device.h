@@ -266,9 +266,13 @@ __device__ inline uint32_t nz8(uint32_t x, uint32_t y) {
 
 // The string starts at the 16-byte boundary at or before the volume: bit
 // shift + i is element i, shift = volume_shift(), so that every load is a whole
-// aligned 16 bytes (one that holds a byte of the volume lies on its pages).
+// aligned 16 bytes (one that holds a byte of the volume lies on its pages).  Floats
+// that are not aligned themselves are read one by one, with no shift.
 
-__host__ __device__ inline int volume_shift(const void* vol) { return (int)((uintptr_t)vol & 15u) / 4; }
+__host__ __device__ inline bool odd_floats(const void* vol) { return ((uintptr_t)vol & 3u) != 0; }
+__host__ __device__ inline int volume_shift(const void* vol) {
+  return odd_floats(vol) ? 0 : (int)((uintptr_t)vol & 15u) / 4;
+}
 
 // 32-bit words of the string of n elements (whatever its shift), one more for
 // the last cut and even, and its workgroups of `block` elements.
@@ -316,6 +320,15 @@ __device__ inline void cut_tile(const uint32_t* __restrict__ bits, int shift, co
 template <int ROUNDS>
 __device__ inline void pack_bits(const void* __restrict__ vol, long long n, long long e0,
                                  uint32_t* __restrict__ bits) {
+  if (odd_floats(vol)) {
+    const float* f = (const float*)vol;
+    for (long long w = e0 / 32 + threadIdx.x; w < e0 / 32 + ROUNDS * 128 && 32 * w < n; w += 256) {
+      uint32_t b = 0u;
+      for (int k = 0; k < 32 && 32 * w + k < n; ++k) b |= (uint32_t)(f[32 * w + k] > 0.5f) << k;
+      bits[w] = b;
+    }
+    return;
+  }
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   const long long end = n + volume_shift(vol);
   const long long w0 = e0 + (long long)wid * (ROUNDS * 1024);

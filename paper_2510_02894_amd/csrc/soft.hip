@@ -157,6 +157,11 @@ __global__ __launch_bounds__(256) void k_soft_bits(SoftBwdBufs B) {
   const long long n = (long long)R.d[0] * R.d[1] * R.d[2];
   const long long e0 = (blockIdx.x - R.bitblk_begin) * (long long)(ROUNDS * kBitRound);
   pack_bits<ROUNDS>(R.p, n, e0, B.bits + R.bits_begin);
+  if (odd_floats(R.grad)) {
+    const long long e1 = min(n, e0 + ROUNDS * kBitRound);
+    for (long long e = e0 + threadIdx.x; e < e1; e += 256) R.grad[e] = 0.0f;
+    return;
+  }
   // the gradient's elements have their own 16-byte boundary
   const int shift = volume_shift(R.grad);
   float4* out = (float4*)((uintptr_t)R.grad & ~(uintptr_t)15);
