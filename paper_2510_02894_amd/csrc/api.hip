@@ -814,8 +814,11 @@ BlockSizes block_sizes(long long rows, int n_rois) {
   return Z;
 }
 
-// Staged rows that hold any mesh of `v` vertices: each brick's are padded to whole blocks.
-long long staged_rows(const Batch& Bt, long long v) { return v + (long long)(kSegAlign - 1) * Bt.nbricks; }
+// Staged rows that hold any mesh of `v` vertices: a brick's are padded to whole
+// blocks, and at most v bricks have any.
+long long staged_rows(const Batch& Bt, long long v) {
+  return v + (long long)(kSegAlign - 1) * std::min(Bt.nbricks, v);
+}
 
 // Most block pairs the library's list grows to (1 GiB).
 constexpr long long kMaxList = 1ll << 26;
@@ -824,7 +827,7 @@ constexpr long long kMaxList = 1ll << 26;
 // and (up to kMaxList) `list` block pairs.
 int ensure_block_bufs(Workspace& w, const Batch& Bt, int dtype, long long rows, long long list, BlockSizes& Z) {
   long long cap = 0;
-  int rc = ensure_staging(w, dtype, rows, &cap);
+  int rc = ensure_staging(w, dtype, std::min(rows, kMaxRows), &cap);
   if (rc) return rc;
   if (cap > kMaxRows) cap = kMaxRows;
   Z = block_sizes(cap, Bt.n());
@@ -925,8 +928,14 @@ int launch_block_tail(const Ptrs& P, const BlockPtrs& Q, const BlockSizes& Z, co
   return SHAPE3D_OK;
 }
 
-// A first guess of a batch's staged rows.
-long long block_guess(const Batch& Bt) { return staged_rows(Bt, staging_guess(Bt)); }
+// A first guess of a batch's staged rows: of its vertices (bricks that have any
+// hold hundreds, and the brick count of a table planned on the device is only a
+// bound, of ROIs as large as the largest: 31 rows for each would be several times
+// the bricks' records).
+long long block_guess(const Batch& Bt) {
+  const long long v = staging_guess(Bt);
+  return v + (long long)(kSegAlign - 1) * std::min(Bt.nbricks, v / 64);
+}
 
 // One run of a batch on the library workspace.  host_res (pinned) receives the
 // results; with host_res null they are left in W_RES (the staged row count is
