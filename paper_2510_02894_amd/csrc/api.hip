@@ -74,7 +74,7 @@ enum WsId {
 };
 
 // Buffers of the block-pair pass, beside the layout buffers and the staging list.
-enum BlockId { B_PBOX, B_LPHYS, B_LBOX, B_SBROI, B_SBOX, B_LIST, B_NUM };
+enum BlockId { B_PBOX, B_LPHYS, B_LBOX, B_SBROI, B_SBOX, B_PRAD, B_SRAD, B_LIST, B_NUM };
 
 struct Ptrs {
   void* p[W_NUM] = {};
@@ -810,6 +810,8 @@ BlockSizes block_sizes(long long rows, int n_rois) {
   Z.bytes[B_LBOX] = sizeof(float4) * 2 * (size_t)Z.lblk;
   Z.bytes[B_SBROI] = sizeof(int) * (size_t)(Z.lblk / kSuper);
   Z.bytes[B_SBOX] = sizeof(float4) * 2 * (size_t)(Z.lblk / kSuper);
+  Z.bytes[B_PRAD] = sizeof(float4) * (size_t)nblk;
+  Z.bytes[B_SRAD] = sizeof(float4) * (size_t)(Z.lblk / kSuper);
   Z.bytes[B_LIST] = sizeof(int4) * (size_t)Z.list;
   return Z;
 }
@@ -916,6 +918,8 @@ int launch_block_tail(const Ptrs& P, const BlockPtrs& Q, const BlockSizes& Z, co
   B.lbox = Q.as<float4>(B_LBOX);
   B.sbroi = Q.as<const int>(B_SBROI);
   B.sbox = Q.as<float4>(B_SBOX);
+  B.prad = Q.as<float4>(B_PRAD);
+  B.srad = Q.as<float4>(B_SRAD);
   B.list = Q.as<int4>(B_LIST);
   B.list_n = (unsigned long long*)P.as<long long>(W_TOTALS) + 10;
   B.list_cap = Z.list;

@@ -10,14 +10,14 @@
 // them.  For the planes of axis k the bound drops axis k (the pair shares that
 // coordinate) and two blocks whose extents along k do not meet hold no pair.
 //
-//   1. k_block_boxes: the blocks' boxes in ROI order, and the box of every 16
-//      blocks (a superblock);
+//   1. k_block_boxes: the blocks' boxes in ROI order, their largest distances from
+//      the ROI's centre, and both of every 16 blocks (a superblock);
 //   2. k_block_seed: each superblock finds, per family, the superblock whose
 //      bound is largest, in that pair of superblocks the pair of blocks whose
 //      bound is largest, and that pair of blocks' exact maximum: a lower bound
 //      L of the family's diameter, 0.95 to 1.00 of it on unions of ellipsoids;
 //   3. k_block_pairs: superblock pairs, then block pairs, whose bound reaches
-//      L go to a list;
+//      L go to a list (superblocks by both bounds below, blocks by their boxes);
 //   4. k_block_eval: the exact maximum over each listed block pair's 1,024
 //      pairs, in FP64 with the oracle's operations and order;
 //   5. k_block_ties: among the pairs at the maximum, the smallest id pair.
@@ -99,6 +99,48 @@ __device__ inline void far_bounds(const Box& a, const Box& b, const Metric& m, f
   f[3] = meet[2] ? (q[0] + q[1] + p[2]) * kBoundUp : -1.0f;
 }
 
+// A second bound, from the distances |p| of a block's vertices from the centre of
+// the ROI's box: |p - q|^2 = 2 |p|^2 + 2 |q|^2 - |p + q|^2, and |p + q| is at least
+// the gap between one block's box and the other's mirror image.  Where the far
+// pairs of a shape lie opposite each other, as on everything round, it follows the
+// surface, and the boxes' corners stick out of it: a ball of radius 200 lists
+// 43,000 block pairs where boxes alone list 16.5 M (the call 180 us and 7,800), 300
+// balls of radii 5 to 40 take 630 us and 4,600, and of 4,096 unions of ellipsoids
+// k_block_eval takes 440 us and 710.
+struct Mirror {
+  float o2[3];  // twice the centre (half voxels)
+  float w[3];   // what the soft coordinates' rounding may add to a gap
+};
+
+__device__ inline Mirror mirror_of(const RoiMeta& M, const Roi& R, bool soft) {
+  Mirror c;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    c.o2[k] = (float)(2 * (M.bb[k] + M.bb[3 + k] + 1));
+    c.w[k] = soft ? 9.5367431640625e-07f * (float)(4 * (R.d[k] + 2)) : 0.0f;
+  }
+  return c;
+}
+
+constexpr float kBoundDown = 1.0f - 3.814697265625e-06f;
+
+// ra, rb: the largest |p|^2 of the blocks' vertices, over all axes and without axis 0, 1, 2.
+__device__ inline void mirror_bounds(const Box& a, const Box& b, const float* ra, const float* rb, const Metric& m,
+                                     const Mirror& c, float* f) {
+  float q[3];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const float lo = a.lo[k] - c.o2[k] + b.lo[k], hi = a.hi[k] - c.o2[k] + b.hi[k];
+    const float g = fmaxf(fmaxf(lo, -hi) - c.w[k], 0.0f) * m.hs[k], s = m.slack * m.hs[k];
+    q[k] = g * g;
+    f[k + 1] = s * s;
+  }
+  f[0] = 2.0f * (ra[0] + rb[0]) * kBoundUp - (q[0] + q[1] + q[2]) * kBoundDown;
+  f[1] = (2.0f * (ra[1] + rb[1]) + f[1]) * kBoundUp - (q[1] + q[2]) * kBoundDown;
+  f[2] = (2.0f * (ra[2] + rb[2]) + f[2]) * kBoundUp - (q[0] + q[2]) * kBoundDown;
+  f[3] = (2.0f * (ra[3] + rb[3]) + f[3]) * kBoundUp - (q[0] + q[1]) * kBoundDown;
+}
+
 // The bound of family g alone (g the same for the whole wave).
 __device__ inline float far_bound(const Box& a, const Box& b, const Metric& m, int g) {
   float sum = 0.0f;
@@ -140,6 +182,13 @@ __device__ inline bool raise_max(GroupRes* g, double v, unsigned long long seen)
   if (b < seen) return false;
   const unsigned long long now = seen_bits(g);
   return b > now ? b >= atomicMax(&g->best_bits, b) : b == now;
+}
+
+// Whether a parameter is a number, by its bits (this file is compiled for
+// operands that are: its maxima would drop or keep a NaN as the instruction
+// happens to treat one).
+__device__ inline bool is_number(double t) {
+  return ((unsigned long long)__double_as_longlong(t) & 0x7fffffffffffffffull) <= 0x7ff0000000000000ull;
 }
 
 // A staged vertex: position and the plane keys of its three axes.
@@ -207,13 +256,6 @@ __device__ inline double staged_max(const PairStage* S, int n_a, int n_b, int sh
     m = fmax(m, G == 0 || A.pk[G ? G - 1 : 0] == S->row[c].pk[G ? G - 1 : 0] ? d : -1.0);
   }
   return wave_max_f64(i < n_a ? m : -1.0);
-}
-
-// Whether a parameter is a number, by its bits (this file is compiled for
-// operands that are: its maxima would drop or keep a NaN as the instruction
-// happens to treat one).
-__device__ inline bool is_number(double t) {
-  return ((unsigned long long)__double_as_longlong(t) & 0x7fffffffffffffffull) <= 0x7ff0000000000000ull;
 }
 
 // Stages the vertices of a block pair that can take part in a pair at or above
@@ -352,41 +394,105 @@ __device__ inline long long staged_superblocks(const BlockBufs& B) {
 
 }  // namespace
 
-// The boxes of the ROIs' blocks in ROI order (a ROI's blocks are consecutive
-// and start on a superblock) and of the superblocks: a thread per block, 16
-// neighbouring lanes per superblock.
-__global__ __launch_bounds__(256) void k_block_boxes(BlockBufs B) {
+// The boxes and distances from the centre of the ROIs' blocks in ROI order (a
+// ROI's blocks are consecutive and start on a superblock), and those of the
+// superblocks: eight lanes per block, four vertices each, two superblocks per
+// workgroup.  Bound: one read of the staged keys (50 M vertices: 132 us, 3.9 TB/s;
+// 23 us for the boxes alone), a chain of three loads where there are few.
+constexpr int kBoxBlocks = 32;
+
+__global__ __launch_bounds__(8 * kBoxBlocks) void k_block_boxes(BlockBufs B) {
+  __shared__ float s_v[kBoxBlocks][10];  // lo, hi, and the largest |p|^2
   const long long n = staged_superblocks(B) * kSuper;
-  const int lane = threadIdx.x & 63;
-  for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < n; i += 256ll * gridDim.x) {
-    const int ph = B.lphys[i];
-    float lo[3] = {3.0e38f, 3.0e38f, 3.0e38f}, hi[3] = {-3.0e38f, -3.0e38f, -3.0e38f};
+  const int tid = threadIdx.x, j = tid >> 3, lane = tid & 7;
+  for (long long i0 = (long long)blockIdx.x * kBoxBlocks; i0 < n; i0 += (long long)kBoxBlocks * gridDim.x) {
+    const long long i = i0 + j;
+    const int ph = i < n ? B.lphys[i] : -1;
+    const int r = i < n ? B.sbroi[i / kSuper] : 0;
+    float rr[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    float4 a = make_float4(3.0e38f, 3.0e38f, 3.0e38f, -3.0e38f), b = make_float4(-3.0e38f, -3.0e38f, 0.0f, 0.0f);
     if (ph >= 0) {
-      const float4 a = B.pbox[2 * (long long)ph], b = B.pbox[2 * (long long)ph + 1];
-      B.lbox[2 * i] = a;
-      B.lbox[2 * i + 1] = make_float4(b.x, b.y, __int_as_float(ph), 0.0f);
-      lo[0] = a.x;
-      lo[1] = a.y;
-      lo[2] = a.z;
-      hi[0] = a.w;
-      hi[1] = b.x;
-      hi[2] = b.y;
-    }
-#pragma unroll
-    for (int m = 1; m < kSuper; m <<= 1)
+      a = B.pbox[2 * (long long)ph];
+      b = B.pbox[2 * (long long)ph + 1];
+      const RoiMeta& M = B.meta[r];
+      const bool soft = B.t != nullptr;
+      const long long row = 32ll * ph + 4 * lane;
+      const ulonglong2 ka = *(const ulonglong2*)(B.key + row), kb = *(const ulonglong2*)(B.key + row + 2);
+      const unsigned long long key[4] = {ka.x, ka.y, kb.x, kb.y};
+      double t[4] = {0.5, 0.5, 0.5, 0.5};
+      if (soft) {
+        const double2 ta = *(const double2*)(B.t + row), tb = *(const double2*)(B.t + row + 2);
+        t[0] = ta.x;
+        t[1] = ta.y;
+        t[2] = tb.x;
+        t[3] = tb.y;
+      }
+      float o[3], hs[3];
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
-        lo[k] = fminf(lo[k], __shfl_xor(lo[k], m, 64));
-        hi[k] = fmaxf(hi[k], __shfl_xor(hi[k], m, 64));
+        o[k] = (float)(M.bb[k] + M.bb[3 + k] + 1);
+        hs[k] = M.hs[k];
       }
-    if ((lane & (kSuper - 1)) == 0) {
-      const long long s = i / kSuper;
-      B.sbox[2 * s] = make_float4(lo[0], lo[1], lo[2], hi[0]);
-      const int r = B.sbroi[s];
-      const RoiMeta& M = B.meta[r];
-      const int left = (M.nblk + kSuper - 1) / kSuper - (int)(s - M.blk0 / kSuper);
-      B.sbox[2 * s + 1] = make_float4(hi[1], hi[2], __int_as_float(r), __int_as_float(left));
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        float q[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          const int u = (int)(key[v] >> (40 - 20 * k) & 0xFFFFFull) - 1;
+          const bool along = (int)(key[v] >> 60 & 3ull) == k;
+          float c = (float)(2 * u + (along ? 1 : 0)), w = 0.0f;
+          if (soft) {
+            c = along ? (float)(2 * u) + 2.0f * (float)t[v] : c;
+            w = fabsf(c) * 2.384185791015625e-07f + 2.384185791015625e-07f;
+          }
+          const float x = (fabsf(c - o[k]) + w) * hs[k];
+          q[k] = x * x;
+        }
+        if (is_number(t[v])) {
+          rr[0] = fmaxf(rr[0], q[0] + q[1] + q[2]);
+          rr[1] = fmaxf(rr[1], q[1] + q[2]);
+          rr[2] = fmaxf(rr[2], q[0] + q[2]);
+          rr[3] = fmaxf(rr[3], q[0] + q[1]);
+        }
+      }
     }
+#pragma unroll
+    for (int f = 0; f < 4; ++f)
+      rr[f] = __uint_as_float(
+          lanes_reduce<3>(__float_as_uint(rr[f]), [](uint32_t x, uint32_t y) { return x > y ? x : y; }));
+    if (lane == 0) {
+      if (ph >= 0) {
+        B.lbox[2 * i] = a;
+        B.lbox[2 * i + 1] = make_float4(b.x, b.y, __int_as_float(ph), 0.0f);
+        B.prad[ph] = make_float4(rr[0], rr[1], rr[2], rr[3]);
+      }
+      const float v[10] = {a.x, a.y, a.z, a.w, b.x, b.y, rr[0], rr[1], rr[2], rr[3]};
+#pragma unroll
+      for (int k = 0; k < 10; ++k) s_v[j][k] = v[k];
+    }
+    __syncthreads();
+    const long long sb = i0 / kSuper + tid / kSuper;
+    if (tid < kBoxBlocks && sb * kSuper < n) {
+      float v[10];
+#pragma unroll
+      for (int k = 0; k < 10; ++k) {
+        v[k] = s_v[tid][k];
+#pragma unroll
+        for (int m = 1; m < kSuper; m <<= 1) {
+          const float x = __shfl_xor(v[k], m, 64);
+          v[k] = k < 3 ? fminf(v[k], x) : fmaxf(v[k], x);
+        }
+      }
+      if ((tid & (kSuper - 1)) == 0) {
+        const int r = B.sbroi[sb];
+        const RoiMeta& M = B.meta[r];
+        const int left = (M.nblk + kSuper - 1) / kSuper - (int)(sb - M.blk0 / kSuper);
+        B.sbox[2 * sb] = make_float4(v[0], v[1], v[2], v[3]);
+        B.sbox[2 * sb + 1] = make_float4(v[4], v[5], __int_as_float(r), __int_as_float(left));
+        B.srad[sb] = make_float4(v[6], v[7], v[8], v[9]);
+      }
+    }
+    __syncthreads();
   }
 }
 
@@ -543,7 +649,8 @@ __device__ inline void enumerate_pairs(const BlockBufs& B, long long A, int spli
   auto read_seen = [&]() {
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
-      tb[g] = seen_bits(&G[g]);
+      // (nothing raises them while the list is made: from the caches)
+      tb[g] = MODE == kModeList ? G[g].best_bits : seen_bits(&G[g]);
       thr[g] = bits_bound(tb[g], m.ex);
     }
   };
@@ -570,6 +677,15 @@ __device__ inline void enumerate_pairs(const BlockBufs& B, long long A, int spli
       far_bounds(ba, box_of(b0, b1), m, f);
 #pragma unroll
       for (int g = 0; g < 4; ++g) um |= (unsigned int)(f[g] >= thr[g]) << g;
+      if (um) {
+        const float4 ra4 = B.srad[A], rb4 = B.srad[A + j];
+        const float ra[4] = {ra4.x, ra4.y, ra4.z, ra4.w}, rb[4] = {rb4.x, rb4.y, rb4.z, rb4.w};
+        int rr = r;
+        asm volatile("" : "+s"(rr));  // (keeps the constants out of the registers of the loop)
+        mirror_bounds(ba, box_of(b0, b1), ra, rb, m, mirror_of(B.meta[rr], B.rois[rr], B.t != nullptr), f);
+#pragma unroll
+        for (int g = 0; g < 4; ++g) um &= ~((unsigned int)(f[g] < thr[g]) << g);
+      }
     }
     unsigned int todo = (unsigned int)(__ballot(um != 0u) & ((1ull << kPartners) - 1ull));
     int src = todo ? __ffs((int)todo) - 1 : 0;
@@ -608,6 +724,15 @@ __device__ inline void enumerate_pairs(const BlockBufs& B, long long A, int spli
             ff[q] = fmaxf(ff[q], f[g]);
           }
         if (i >= nblk || jj >= nblk || jj < i) pm[q] = 0u;
+        if (MODE != kModeList && pm[q]) {  // (k_block_eval sees to the list's)
+          const float4 ra4 = B.prad[pha[q]], rb4 = B.prad[phb];
+          const float ra[4] = {ra4.x, ra4.y, ra4.z, ra4.w}, rb[4] = {rb4.x, rb4.y, rb4.z, rb4.w};
+          float h[4];
+          mirror_bounds(pa[q], pb, ra, rb, m, mirror_of(M, R, B.t != nullptr), h);
+#pragma unroll
+          for (int g = 0; g < 4; ++g)
+            if (h[g] < thr[g]) pm[q] &= ~(1u << g);
+        }
       }
       unsigned long long em[4];
       int k = 0;
@@ -664,56 +789,99 @@ __global__ __launch_bounds__(64 * kWaves, 4) void k_block_pairs(BlockBufs B, int
   if (n_buf) append_pairs(B, lane, buf, n_buf);
 }
 
+// The families in which a listed block pair can hold a maximum by its boxes' and
+// by its mirror bounds, a lane per entry.  The maxima may be old ones, from a
+// cache (all waves of a large ROI would meet on one line of the L2).
+__device__ inline unsigned int entry_families(const BlockBufs& B, const int4& E) {
+  unsigned int mask = (unsigned int)E.w & 15u;
+  const RoiMeta& M = B.meta[E.z];
+  const bool soft = B.t != nullptr;
+  const float4 a0 = B.pbox[2 * (long long)E.x], a1 = B.pbox[2 * (long long)E.x + 1], ra4 = B.prad[E.x];
+  const float4 b0 = B.pbox[2 * (long long)E.y], b1 = B.pbox[2 * (long long)E.y + 1], rb4 = B.prad[E.y];
+  const float ra[4] = {ra4.x, ra4.y, ra4.z, ra4.w}, rb[4] = {rb4.x, rb4.y, rb4.z, rb4.w};
+  float f[4];
+  mirror_bounds(box_of(a0, a1), box_of(b0, b1), ra, rb, metric_of(M, soft), mirror_of(M, B.rois[E.z], soft), f);
+#pragma unroll
+  for (int g = 0; g < 4; ++g)
+    if (fminf(f[g], entry_bound(E.w)) < bits_bound(B.gres[4ll * E.z + g].best_bits, M.ex)) mask &= ~(1u << g);
+  return mask;
+}
+
 // The exact maxima of the listed block pairs, a wave each.  An entry keeps the
 // families whose maximum it may hold (its own is not below the one seen), and
 // its own maximum as the new bound (none if it keeps several).
-// A wave takes up to 8 neighbouring entries at a time: it reads the maxima seen
-// so far once for those of one ROI (the waves of a large ROI all read the same
-// line), and loads the next pair's vertices while it evaluates one.
+// A wave takes 16 entries of a long list at a time, four runs of four neighbours,
+// the runs dealt to the waves in turn (entries that take long are neighbours),
+// and drops those that their bounds rule out, a lane each; of a short one, where a
+// wave has one to four in all, its neighbours.  It reads the maxima seen so far
+// once for those of one ROI (the waves of a large ROI all read the same line),
+// and loads the next pair's vertices while it evaluates one.
 __global__ __launch_bounds__(64 * kWaves, 7) void k_block_eval(BlockBufs B) {
   __shared__ PairStage s_pair[kWaves];
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   const long long n = listed_pairs(B);
   const long long nwaves = (long long)gridDim.x * kWaves;
-  const int take = (int)max(1ll, min(8ll, n / nwaves));
-  for (long long e0 = ((long long)blockIdx.x * kWaves + wid) * take; e0 < n; e0 += nwaves * take) {
-    const int cnt = (int)min((long long)take, n - e0);
+  const long long wave = (long long)blockIdx.x * kWaves + wid;
+  const bool many = n >= 4 * nwaves;
+  const int run = (int)max(1ll, min(4ll, (n + nwaves - 1) / nwaves)), runs = many ? 4 : 1;
+  for (long long it = 0; (runs * it * nwaves + wave) * run < n; ++it) {
+    const long long e = ((runs * it + (lane >> 2)) * nwaves + wave) * run + (lane & 3);
+    const bool mine = lane < 4 * runs && (lane & 3) < run && e < n;
     int4 E = make_int4(0, 0, 0, 0);
-    if (lane < cnt) E = B.list[e0 + lane];
-    PairLoad K = load_pair(B, __builtin_amdgcn_readlane(E.x, 0), __builtin_amdgcn_readlane(E.y, 0), lane);
-    int r = -1, word = 0;
-    unsigned long long sbits = 0ull;
-    float seen = 0.0f, thr[4];
-    Metric met;
-    for (int k = 0; k < cnt; ++k) {
-      const int rk = __builtin_amdgcn_readlane(E.z, k), w = __builtin_amdgcn_readlane(E.w, k);
-      const PairLoad K0 = K;
-      if (k + 1 < cnt)
-        K = load_pair(B, __builtin_amdgcn_readlane(E.x, k + 1), __builtin_amdgcn_readlane(E.y, k + 1), lane);
-      GroupRes* G = B.gres + 4ll * rk;
-      if (rk != r) {
-        r = rk;
-        met = metric_of(B.meta[r], B.t != nullptr);
-        sbits = seen_bits(&G[lane & 3]);  // lane g < 4 sees to family g
-        seen = bits_bound(sbits, met.ex);
-#pragma unroll
-        for (int g = 0; g < 4; ++g) thr[g] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(seen), g));
-      }
-      const bool on = lane < 4 && ((unsigned int)w >> (lane & 3) & 1u) && !(entry_bound(w) < seen);
-      const unsigned int mask = (unsigned int)(__ballot(on) & 15ull);
-      if (!mask) continue;
-      double mx[4];
-      pair_max(K0, B.rois[r], met, mask, thr, lane, &s_pair[wid], mx);
-      const double v = (lane & 2) ? ((lane & 1) ? mx[3] : mx[2]) : ((lane & 1) ? mx[1] : mx[0]);
-      bool hold = false;
-      if (on && v > 0.0) hold = raise_max(&G[lane], v, sbits);
-      const unsigned int keep = (unsigned int)(__ballot(hold) & 15ull);
-      if (!keep) continue;
-      int wk = entry_word(3.0e38f, keep);
-      if (!(keep & (keep - 1u))) wk = entry_word((float)ldexp(__shfl(v, __ffs((int)keep) - 1, 64), -2 * met.ex), keep);
-      if (lane == k) word = wk;
+    unsigned int left = 0u;
+    if (mine) {
+      E = B.list[e];
+      left = many ? entry_families(B, E) : (unsigned int)E.w & 15u;
     }
-    if (lane < cnt) B.list[e0 + lane].w = word;
+    unsigned int todo = (unsigned int)__ballot(left != 0u);
+    int r = -1, word = 0;
+    if (todo) {
+      int k = __ffs((int)todo) - 1;
+      PairLoad K = load_pair(B, __builtin_amdgcn_readlane(E.x, k), __builtin_amdgcn_readlane(E.y, k), lane);
+      unsigned long long sbits = 0ull;
+      float seen = 0.0f, thr[4];
+      Metric met;
+      while (true) {
+        const int at = k;
+        const int rk = __builtin_amdgcn_readlane(E.z, at), w = __builtin_amdgcn_readlane(E.w, at);
+        const unsigned int fam = (unsigned int)__builtin_amdgcn_readlane((int)left, at);
+        const PairLoad K0 = K;
+        todo &= todo - 1u;
+        if (todo) {
+          k = __ffs((int)todo) - 1;
+          K = load_pair(B, __builtin_amdgcn_readlane(E.x, k), __builtin_amdgcn_readlane(E.y, k), lane);
+        }
+        GroupRes* G = B.gres + 4ll * rk;
+        if (rk != r) {
+          r = rk;
+          met = metric_of(B.meta[r], B.t != nullptr);
+          // lane g < 4 sees to family g; where all entries are taken at once, the maxima as
+          // they were before (12,000 waves that read one line past the caches wait 20 us)
+          sbits = many ? seen_bits(&G[lane & 3]) : G[lane & 3].best_bits;
+          seen = bits_bound(sbits, met.ex);
+#pragma unroll
+          for (int g = 0; g < 4; ++g) thr[g] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(seen), g));
+        }
+        const bool on = lane < 4 && (fam >> (lane & 3) & 1u) && !(entry_bound(w) < seen);
+        const unsigned int mask = (unsigned int)(__ballot(on) & 15ull);
+        if (mask) {
+          double mx[4];
+          pair_max(K0, B.rois[r], met, mask, thr, lane, &s_pair[wid], mx);
+          const double v = (lane & 2) ? ((lane & 1) ? mx[3] : mx[2]) : ((lane & 1) ? mx[1] : mx[0]);
+          bool hold = false;
+          if (on && v > 0.0) hold = raise_max(&G[lane], v, sbits);
+          const unsigned int keep = (unsigned int)(__ballot(hold) & 15ull);
+          if (keep) {
+            int wk = entry_word(3.0e38f, keep);
+            if (!(keep & (keep - 1u)))
+              wk = entry_word((float)ldexp(__shfl(v, __ffs((int)keep) - 1, 64), -2 * met.ex), keep);
+            if (lane == at) word = wk;
+          }
+        }
+        if (!todo) break;
+      }
+    }
+    if (mine) B.list[e].w = word;
   }
 }
 
@@ -771,7 +939,7 @@ hipError_t launch_blocks(const BlockBufs& B, bool again, hipStream_t st, hipEven
   const long long nsb = B.lblk_cap / kSuper;
   // a few ROIs may have thousands of superblocks each, many have tens
   const int nsplit = B.n_rois <= 16 ? 16 : 2, nsplit_again = B.n_rois <= 16 ? 128 : 16;
-  hipLaunchKernelGGL(k_block_boxes, grid((B.lblk_cap + 255) / 256, 8), dim3(256), 0, st, B);
+  hipLaunchKernelGGL(k_block_boxes, grid((B.lblk_cap + kBoxBlocks - 1) / kBoxBlocks, 16), dim3(8 * kBoxBlocks), 0, st, B);
   if (ev && (e = hipEventRecord(ev[0], st))) return e;
   hipLaunchKernelGGL(k_block_seed, grid(nsb, 16), dim3(64 * kWaves), 0, st, B);
   hipLaunchKernelGGL(k_block_pairs, grid((nsb * nsplit + kWaves - 1) / kWaves, 16), dim3(64 * kWaves), 0, st, B,

@@ -117,7 +117,10 @@ struct BlockBufs {
   long long lblk_cap;
   float4* lbox;        // [2 * lblk_cap] boxes in ROI order, then the staged block's index
   const int* sbroi;    // [lblk_cap / kSuper] ROI of each superblock
-  float4* sbox;        // [2 * lblk_cap / kSuper] superblock boxes, then the ROI
+  float4* sbox;        // [2 * lblk_cap / kSuper] superblock boxes, then the ROI and its superblocks from here on
+  float4* prad;        // [rows_cap / 32] largest squared distance of a staged block's vertices from the centre of the ROI's
+                       // box: over all axes, and without axis 0, 1, 2 (units of 2^(2 RoiMeta::ex))
+  float4* srad;        // [lblk_cap / kSuper] the same of the superblocks
   int4* list;          // [list_cap] block pairs: staged blocks, ROI, bound and families
   unsigned long long* list_n;
   long long list_cap;
