@@ -28,6 +28,7 @@
 #include <algorithm>
 #include <cstring>
 
+#include "../../include/shape3d.h"
 #define MC_TABLE_QUAL __constant__ const
 #include "mc_table.h"
 #include "s3d_device.h"
@@ -407,6 +408,16 @@ __global__ __launch_bounds__(256) void k_small_head(Roi R, Roi* __restrict__ roi
 }
 
 // ---------------------------------------------------------------------------
+// What the mesh pass sums in 32 bits: a wave's moments (64 threads of 32 voxels in
+// kTZ planes; z' < kTZ, y' <= kBrickThreads, x <= SHAPE3D_MAX_DIM2), a brick's
+// volume, and the row and group that share a word.
+static_assert(64ll * 32 * (kTZ * (kTZ - 1) / 2) * SHAPE3D_MAX_DIM2 < (1ll << 32), "sum of z' x of a wave");
+static_assert(64ll * 32 * kTZ * SHAPE3D_MAX_DIM2 < (1ll << 32), "sum of x of a wave");
+static_assert(64ll * 32 * kTZ * kBrickThreads * kBrickThreads < (1ll << 32), "sum of y' y' of a wave");
+static_assert(64ll * 32 * (kTZ * (kTZ - 1) / 2) * kBrickThreads < (1ll << 32), "sum of z' y' of a wave");
+static_assert(48ll * 32 * kTZ * kBrickThreads < (1ll << 31), "volume of a brick in 1/48 voxels");
+static_assert(SHAPE3D_MAX_DIM < (1 << 20) && (SHAPE3D_MAX_DIM2 + 1) / 32 < (1 << 11), "row | group << 20");
+
 // The mesh pass: one read of the volume per brick gives its vertex and
 // triangle counts, area, volume, bounding box and moments, and writes the
 // canonical keys of its vertices (and soft masks' interpolation parameters)
@@ -1424,6 +1435,8 @@ __global__ void k_set_roi(Roi R, Roi* __restrict__ out) {
 // ---------------------------------------------------------------------------
 // Launchers.
 
+// (rows of SHAPE3D_MAX_DIM2 voxels: 46 KB beside the soft pass's 28 KB of static
+// LDS, of the 160 KB of a CU)
 size_t mesh_lds_bytes(int max_G) { return sizeof(uint32_t) * (size_t)(kTZ + 1) * (kBrickThreads + 1 + max_G); }
 
 hipError_t launch_mesh_pass(int dtype, Roi* rois, int n_rois, long long nbricks, int max_G,
