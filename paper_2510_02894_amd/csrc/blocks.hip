@@ -521,9 +521,11 @@ __global__ __launch_bounds__(64 * kWaves, 7) void k_block_seed(BlockBufs B) {
     const int nblk = M.nblk, ns = (nblk + kSuper - 1) / kSuper;
     // The scan costs ns^2 boxes; a large ROI's superblocks are small patches
     // whose neighbours have nearly the same partner, so every second or fourth
-    // seeds (300 x 512 x 512, ns 1,822: seed and eval 45 + 20 us with all, 33 + 21,
-    // 26 + 23, and with every eighth 32 + 53; ROIs of ns about 100 lose: eval of a
-    // batch of 256 soft ROIs 210, 226 and 307 us with all, second, fourth).
+    // seeds.  Seed, pairs and eval together (us) with all, every second, fourth and
+    // eighth, on unions of twelve ellipsoids: ns 375 32, 28, 28, 27; 490 47, 43, 44,
+    // 44; 675 56, 53, 51, 61; 895 95, 91, 103, 108; 1,140 87, 79, 71, 70; 1,520 84, 75,
+    // 80, 127; 2,190 108, 100, 91, 91; 3,420 172, 149, 144, 147.  ROIs of ns about 100
+    // lose (eval of a batch of 256 soft ROIs 210, 226, 307), so all seed up to 512.
     if (ns > 512 && ((A - s0) & (ns > 1024 ? 3 : 1))) continue;
     // 16 x 16 block pairs later: lane holds block lane % 16 of A
     const int ia = (int)(A - s0) * kSuper + (lane & 15), ic = min(ia, nblk - 1);
