@@ -101,8 +101,8 @@ __device__ inline uint32_t differs(const uint4& w, uint32_t l) {
 }
 
 // One read of the map in 16-byte chunks, addressed from the 16-byte aligned
-// address at or below lab (an aligned chunk with a byte of the map lies on its
-// pages; bytes outside the map are masked), kAhead of them in flight per thread.
+// address at or below lab (of the chunks at its ends only the map's own bytes),
+// kAhead of them in flight per thread.
 // A chunk is taken row by row (one row, two at a row's end) and label by label:
 // its first label left, all voxels of that label at once as a 16-bit mask.  Each
 // thread keeps the box of its current label in registers and folds it into the
@@ -138,7 +138,19 @@ __global__ __launch_bounds__(kLabelThreads) void k_label_boxes(const unsigned ch
 #pragma unroll
     for (int u = 0; u < kAhead; ++u) {
       const long long c = c0 + u * kLabelThreads;
-      ahead[u] = c < end ? *(const uint4*)(p0 + c * 16) : make_uint4(0u, 0u, 0u, 0u);
+      const long long j0 = c * 16 - mis;
+      ahead[u] = c < end && j0 >= 0 && j0 + 16 <= n ? *(const uint4*)(p0 + c * 16) : make_uint4(0u, 0u, 0u, 0u);
+    }
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      const long long c = c0 + u * kLabelThreads, j0 = c * 16 - mis;
+      if (c < end && (j0 < 0 || j0 + 16 > n)) {
+        uint32_t w[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int k = 0; k < 16; ++k)
+          if (j0 + k >= 0 && j0 + k < n) w[k >> 2] |= (uint32_t)p0[c * 16 + k] << (8 * (k & 3));
+        ahead[u] = make_uint4(w[0], w[1], w[2], w[3]);
+      }
     }
 #pragma unroll
     for (int u = 0; u < kAhead; ++u) {

@@ -265,9 +265,9 @@ __device__ inline uint32_t nz8(uint32_t x, uint32_t y) {
 // and reads its neighbours' rows again, in four bytes a voxel.
 
 // The string starts at the 16-byte boundary at or before the volume: bit
-// shift + i is element i, shift = volume_shift(), so that every load is a whole
-// aligned 16 bytes (one that holds a byte of the volume lies on its pages).  Floats
-// that are not aligned themselves are read one by one, with no shift.
+// shift + i is element i, shift = volume_shift(), so that the loads are whole
+// aligned 16 bytes, but for the elements before the first and after the last of
+// those.  Floats that are not aligned themselves are read one by one, with no shift.
 
 __host__ __device__ inline bool odd_floats(const void* vol) { return ((uintptr_t)vol & 3u) != 0; }
 __host__ __device__ inline int volume_shift(const void* vol) {
@@ -330,7 +330,8 @@ __device__ inline void pack_bits(const void* __restrict__ vol, long long n, long
     return;
   }
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  const long long end = n + volume_shift(vol);
+  const int shift = volume_shift(vol);
+  const long long end = n + shift;
   const long long w0 = e0 + (long long)wid * (ROUNDS * 1024);
   const uint4* src = (const uint4*)((uintptr_t)vol & ~(uintptr_t)15);
   constexpr int J = ROUNDS > 1 ? 8 : 4;  // 16-byte loads in flight per thread
@@ -340,7 +341,19 @@ __device__ inline void pack_bits(const void* __restrict__ vol, long long n, long
 #pragma unroll
     for (int j = 0; j < J; ++j) {
       const long long e = w0 + 256 * (g + j) + 4 * lane;
-      v[j] = e < end ? src[e >> 2] : make_uint4(0u, 0u, 0u, 0u);
+      v[j] = e >= shift && e + 4 <= end ? src[e >> 2] : make_uint4(0u, 0u, 0u, 0u);
+    }
+    // the volume's ends: the elements of a 16-byte word that is not all its own
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      const long long e = w0 + 256 * (g + j) + 4 * lane;
+      if (e < end && (e < shift || e + 4 > end)) {
+        const uint32_t* w = (const uint32_t*)(src + (e >> 2));
+        v[j].x = e >= shift ? w[0] : 0u;
+        v[j].y = e + 1 >= shift && e + 1 < end ? w[1] : 0u;
+        v[j].z = e + 2 >= shift && e + 2 < end ? w[2] : 0u;
+        v[j].w = e + 3 >= shift && e + 3 < end ? w[3] : 0u;
+      }
     }
     uint32_t mine = 0u;
 #pragma unroll
