@@ -966,13 +966,13 @@ int run_blocks(Workspace& w, const Batch& Bt, int dtype, hipStream_t st, RoiResu
     if (!host_res) {
       HIPCK(hipMemcpyAsync(th, P.p[W_TOTALS], sizeof(long long) * 9, hipMemcpyDeviceToHost, st));
       if ((rc = sync_use(w, st))) return rc;
+      Layout L;  // the limit of the general pipeline's row indices holds for either path
+      if ((rc = ws_layout(Bt, dtype, g_tune, th[0], L))) return rc;
       if (th[8] > Z.rows) {
         if (pass > 0) return fail(SHAPE3D_EINTERNAL, "the mesh pass's staging list overflowed twice");
         if ((rc = ensure_block_bufs(w, Bt, dtype, th[8], 0, Z))) return rc;
         continue;
       }
-      Layout L;  // the limit of the general pipeline's row indices holds for either path
-      if ((rc = ws_layout(Bt, dtype, g_tune, th[0], L))) return rc;
       w.last_rows0 = th[0];
     }
     if ((rc = launch_block_tail(P, block_ptrs(w), Z, Bt, dtype, kMaxRows, counts, again, w.cu_count,
@@ -993,6 +993,8 @@ int run_blocks(Workspace& w, const Batch& Bt, int dtype, hipStream_t st, RoiResu
     HIPCK(hipMemcpyAsync(th, P.p[W_TOTALS], sizeof(long long) * 11, hipMemcpyDeviceToHost, st));
     if ((rc = sync_use(w, st))) return rc;
     if (pass > 2 || (!short_list && th[8] <= Z.rows)) break;
+    Layout L;  // a mesh beyond the limit below is refused now, not after the pass
+    if ((rc = ws_layout(Bt, dtype, g_tune, th[0], L))) return rc;
     const long long list = short_list ? th[10] + th[10] / 8 : 0;
     again |= list > kMaxList;
     if ((rc = ensure_block_bufs(w, Bt, dtype, th[8], list, Z))) return rc;
