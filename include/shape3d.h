@@ -15,7 +15,9 @@
  *   - dtype SHAPE3D_U8: uint8 mask, voxel inside iff value != 0, mesh
  *     vertices at edge midpoints; dtype SHAPE3D_F32: float32 probabilities,
  *     inside iff p > 0.5, vertices linearly interpolated at the 0.5 level;
- *   - voxels outside the array count as outside (one-voxel zero pad);
+ *   - voxels outside the array count as outside (one-voxel zero pad); no byte
+ *     outside the array is used.  A uint8 row is read in aligned 4-byte words,
+ *     whose other bytes may lie beside the array (on its pages);
  *   - features, in order: MeshVolume (mm^3, absolute value of the signed
  *     tetrahedron sum), SurfaceArea (mm^2), Maximum3DDiameter,
  *     Maximum2DDiameterSlice (vertex pairs on a common plane of axis 0),

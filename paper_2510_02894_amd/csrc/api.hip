@@ -2,12 +2,15 @@
 // workspace, and the launch sequence of a call.
 //
 // Every call processes a batch of ROIs (a single ROI is a batch of one), all
-// on the caller's stream:
-//   mesh count -> per-ROI totals (vertex offsets, area, volume, centre)
-//   -> read back the total vertex rows (sizes the vertex buffers)
-//   -> capacity check -> emission -> plane buckets and work list
-//   -> MFMA pair maxima -> exact FP64 refinement -> finalisation
-//   -> read back the per-ROI results.
+// on the caller's stream.  By default (run_blocks):
+//   head -> [bit strings of soft masks ->] mesh pass into the staging list
+//   -> per-ROI totals and block list -> boxes -> seeds -> block pairs
+//   -> their exact maxima -> ties -> results, read back once;
+// a small single ROI (run_small): head -> mesh pass -> all pairs' maxima -> ties
+// and result; where every pair is visited (run_eager):
+//   head -> mesh pass -> totals -> read back the vertex rows -> capacity check
+//   -> vertex rows -> plane buckets and work list -> MFMA pair maxima
+//   -> exact FP64 refinement -> results.
 // The batched entry point can record everything after the ROI table upload as
 // a hipGraph and replay it for later calls with the same layout; the capacity
 // check turns a replay on larger meshes into SHAPE3D_ECAPACITY for the graph
@@ -1103,7 +1106,7 @@ void fill_stats(shape3d_stats* stats, const RoiResult& R, const float* ms) {
 }
 
 // The small-mesh path of one ROI: the ROI record, the mesh pass into the
-// staging list and the exact all-pairs kernel (three launches), then the
+// staging list and the exact all-pairs kernels (four launches), then the
 // result read back.  hres->status is kSmallOverflow when the mesh has more
 // than kSmallMaxV vertices (the general path must run instead).
 int run_small(Workspace& w, const void* vol, int dtype, const int64_t dims[3], const double spacing[3], hipStream_t st,

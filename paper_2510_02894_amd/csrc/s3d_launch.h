@@ -174,7 +174,7 @@ struct Tuning {
   int jchunk;         // 16-row column blocks per work item: 64, 128, 256 or 512
   int blocks_per_cu;  // persistent workgroups per CU (0: as many as fit)
   int kernel;         // 0: FP32 16x16x4 MFMA; 1: split-f16 32x32x16 MFMA
-  int prune;          // 1: skip 3D pair tiles that cannot reach the diameter (kernel 1); 0: all pairs
+  int prune;          // 1, 2: only block pairs that can reach a diameter (kernel 1); 0: all pairs
   int small_path;     // 1: small single ROIs take the exact all-pairs kernel after the mesh pass
 };
 

@@ -742,7 +742,8 @@ def get_tuning():
 
 
 def get_prune() -> int:
-    """3D pruning mode: 0 never, 1 for large ROIs (default), 2 always."""
+    """Pruning mode: 0 every pair is visited, 1 (default) or 2 only block pairs
+    that can hold a diameter (see shape3d_set_tuning)."""
     t = Tuning()
     _check(load().shape3d_get_tuning(ctypes.byref(t)))
     return int(t.prune)
@@ -758,7 +759,8 @@ def set_tuning(itile_blocks: int, jchunk_blocks: int, blocks_per_cu: int = 0, ke
 
 
 def set_prune(mode: int):
-    """3D pruning mode: 0 never, 1 for large ROIs (default), 2 always."""
+    """Pruning mode: 0 every pair is visited, 1 (default) or 2 only block pairs
+    that can hold a diameter (see shape3d_set_tuning)."""
     t = Tuning()
     _check(load().shape3d_get_tuning(ctypes.byref(t)))
     t.prune = int(mode)
